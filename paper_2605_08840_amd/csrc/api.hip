@@ -42,13 +42,8 @@ int resolve(const restkv_params* p, Prob* o) {
 
 ScoreWs score_ws(const Prob& pb) {
   ScoreWs w;
-  // enough key splits to give every CU work, each at least one 64-key tile
-  int S = (pb.L + 1023) / 1024;
-  if (S < 1) S = 1;
-  if (S > 64) S = 64;
-  w.S_simple = S;
   w.S_max = 64;
-  S = w.S_max;
+  const int S = w.S_max;
   w.ldv = (pb.P + 3) / 4 * 4;
   const size_t rows = (size_t)pb.Hq * pb.W;
   size_t off = 0;
@@ -112,6 +107,20 @@ FuseWs fuse_ws(const Prob& pb) {
   w.sidx = take(rows * w.nchunks * w.caps * 4);
   w.bytes = off;
   return w;
+}
+
+// compute units of the current device (queried once)
+int n_cu() {
+  static int n = 0;
+  if (n == 0) {
+    int dev = 0, v = 0;
+    if (hipGetDevice(&dev) == hipSuccess &&
+        hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && v > 0)
+      n = v;
+    else
+      n = 256;
+  }
+  return n;
 }
 
 static bool g_force_fp32 = false;   // see restkv_debug_force_fp32

@@ -29,7 +29,6 @@ int resolve(const restkv_params* p, Prob* out);
 // ---- scratch layout ---------------------------------------------------------
 // All offsets are in bytes from the 256-byte aligned workspace base.
 struct ScoreWs {
-  int S_simple;          // key splits of the attention pass, FP32 path
   int S_max;             // capacity of the split dimension
   int ldv;               // row stride of vv (P rounded up to 4)
   size_t part_m, part_mx, part_n, part_ref, part_l, part_z;   // [Hq*W*S] , part_z [Hq*W*S*d] f32
@@ -62,6 +61,8 @@ struct FuseWs {
 ScoreWs score_ws(const Prob& pb);
 SmoothWs smooth_ws(const Prob& pb);
 FuseWs fuse_ws(const Prob& pb);
+
+int n_cu();   // compute units of the current device
 
 inline size_t align_up(size_t x, size_t a = 256) { return (x + a - 1) / a * a; }
 

@@ -1220,20 +1220,6 @@ __global__ __launch_bounds__(512) void k_score_pipe(Prob pb, const uint16_t* __r
   }
 }
 
-// compute units of the current device (queried once)
-int n_cu() {
-  static int n = 0;
-  if (n == 0) {
-    int dev = 0, v = 0;
-    if (hipGetDevice(&dev) == hipSuccess &&
-        hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && v > 0)
-      n = v;
-    else
-      n = 256;
-  }
-  return n;
-}
-
 // geometry of the score pass: padded group size, row blocks, tiles per workgroup, key chunks
 struct ScoreGeom { int gp, gy, tpp, chunks; };
 ScoreGeom score_geom(const Prob& pb) {

@@ -1,0 +1,49 @@
+"""GPU parity at the edges of the kernels' tiles and at the sizes where a launch rule changes side,
+against the oracle with the tolerances of gpu_util.py."""
+import numpy as np
+import pytest
+import torch
+
+import workloads
+from gpu_util import assert_score_close, oracle_score, params_for
+from test_gpu_parity import _score_against_oracle_then_every_stage_exactly, rk  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("Hq,Hkv,d,L,W,B", [
+    (2, 1, 64, 33, 1, 20),          # 32 keys of prefix: one block exactly, one query row
+    (4, 2, 64, 32 + 65, 32, 40),    # 64 query rows per KV head: the last size with two wavefronts; prefix one past two blocks
+    (6, 2, 64, 500, 22, 60),        # 66 query rows: four wavefronts, two of them nearly empty
+    (8, 1, 128, 1031, 33, 90),      # window one past a 32-row block, prefix of 998
+    (3, 3, 128, 32 * 171, 5, 90),   # 3 heads x 171 key blocks: just above the size up to which a score workgroup is one wavefront
+    (40, 1, 64, 700, 12, 50),       # more heads per group than the bf16 path takes
+])
+def test_fp32_kernels_block_edges(rk, oracle_mod, Hq, Hkv, d, L, W, B):  # noqa: F811
+    w = workloads.small_case(Hq=Hq, Hkv=Hkv, d=d, L=L, W=W, B=B, dtype="f32", D=2 * d, structure="sinks", seed=57)
+    _score_against_oracle_then_every_stage_exactly(rk, oracle_mod, w, "fp32 block edges")
+
+
+@pytest.mark.parametrize("dtype,pad", [("f32", 1), ("f32", 4), ("bf16", 3), ("bf16", 4)])
+def test_fp32_kernels_row_alignment(rk, oracle_mod, dtype, pad):  # noqa: F811
+    """Rows that start on no 4-element boundary (element-wise loads) and on one (4-element loads);
+    bf16 rows that are not 16-byte aligned take the same kernels."""
+    w = workloads.small_case(Hq=4, Hkv=2, d=64, L=210, W=9, B=40, dtype=dtype, D=96, seed=58)
+    q, k, v = workloads.make_qkv(w)
+    wo = workloads.make_wo(w)
+    st = w.head_dim + pad
+    kp, vp = (torch.zeros((w.n_kv_heads, w.seq_len, st), dtype=k.dtype, device="cuda") for _ in range(2))
+    kp[..., :w.head_dim] = k.cuda()
+    vp[..., :w.head_dim] = v.cuda()
+    p = params_for(rk, w, kv_stride_t=st, kv_stride_h=w.seq_len * st)
+    gram = torch.empty((w.n_q_heads, w.head_dim, w.head_dim), dtype=torch.float32, device="cuda")
+    rk.restkv_prepare_wo(p, wo.cuda(), gram)
+    buf = rk.alloc_layer_buffers(p, k.dtype, "cuda")
+    rk.restkv_score(p, q.cuda(), kp, vp, gram, buf.score, buf.workspace)
+    torch.cuda.synchronize()
+    got = buf.score.cpu().numpy()
+    ref = oracle_score(oracle_mod, w, q, k, v, wo)
+    for g in range(w.n_kv_heads):
+        Ig, tol = ref[g]
+        assert np.isfinite(got[g]).all()
+        assert_score_close(got[g], Ig, tol, f"row alignment head {g}")
