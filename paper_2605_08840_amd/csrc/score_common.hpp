@@ -40,10 +40,10 @@ inline ScorePtrs score_ptrs(char* ws, const ScoreWs& lay) {
 // bf16 weight is exact).
 // The merge keeps out the excluded key that is the overall maximum (if any) and folds every
 // other excluded key back in.  With a key kept out ("champion", weight A* = 1/l):
-//   l = 1 + l_rest, z = (v* + z_rest)/l, u = z M_h, zz = u.z, and the champion's indicator
-//   in its leave-one-out form I* = A* ||(z_rest/l_rest - v*) W_O||  (Eq. ori with Eq. relation;
-//   equals Eq. rec_ei).  Without one, l and z are the plain softmax sums relative to the maximum.
-constexpr int CMB_RQ = 4;    // query rows of one head per workgroup of the merge kernel
+//   l = 1 + l_rest, z = (v* + z_rest)/l, u = z M_h, zz = u.z, and, if A* > 1/2, the champion's
+//   indicator in its leave-one-out form I* = A* ||(z_rest/l_rest - v*) W_O||  (Eq. ori with
+//   Eq. relation; equals Eq. rec_ei).  Without one, l and z are the plain softmax sums relative to
+//   the maximum.
 
 // Statistics of a caller's own attention kernel as ONE split of the attention pass: the log-sum-exp
 // of a row (natural log) is both the reference and the "largest logit", the sum of weights is 1, no
@@ -60,216 +60,336 @@ __global__ __launch_bounds__(256) void k_stats_fill(int rows, const float* __res
   part_m[r] = m2; part_ref[r] = m2; part_mx[r] = 0.f; part_n[r] = -1; part_l[r] = 1.f;
 }
 
-// Merge of the key splits and the per-row quantities of the score pass.
-// grid (ceil(W / CMB_RQ), Hq), CMB_RQ * D threads.  For the merge a thread is (row r of the
-// group, column c); the per-split scalars of a row are fetched by one thread each and shared
-// through LDS.  For u = z M_h (and y = x M_h) a thread is (part p = r of the Gram matrix's rows,
-// column c): it holds its D / CMB_RQ Gram entries in registers (loaded first, their latency
-// hides behind the merge; every entry is needed by exactly one thread, so the matrix never
-// touches LDS) and works on all CMB_RQ rows at once, whose z and x it reads as LDS broadcasts;
-// the partial sums of the parts meet in LDS.
-template <typename T, int D>
-__global__ __launch_bounds__(CMB_RQ * D, 4) void k_attn_combine(Prob pb, const T* __restrict__ v, int S,
-                                                             const float* __restrict__ gram,
-                                                             const float* __restrict__ part_m,
-                                                             const float* __restrict__ part_mx,
-                                                             const int* __restrict__ part_n,
-                                                             const float* __restrict__ part_ref,
-                                                             const float* __restrict__ part_l,
-                                                             const float* __restrict__ part_z,
-                                                             float* __restrict__ rs_m, float* __restrict__ rs_l,
-                                                             float* __restrict__ rs_zz, int* __restrict__ rs_nstar,
-                                                             float* __restrict__ rs_istar,
-                                                             float* __restrict__ rs_u,
-                                                             const T* __restrict__ q, uint16_t* __restrict__ op,
-                                                             int log2gp, int nwb, int ngrp) {
-  constexpr int NWV = D / 64, SMAX = 64;     // wavefronts per row; capacity of the split dimension
-  constexpr int AP = D / CMB_RQ;             // Gram rows per thread
-  static_assert(CMB_RQ == 4, "z and x of the group's rows travel as one float4 each");
-  __shared__ __attribute__((aligned(16))) float zx[D][2 * CMB_RQ];     // [a][z of the rows | x of the rows]
-  __shared__ float up[CMB_RQ][2][CMB_RQ][D];                           // [part][u | y][row][c]
-  __shared__ float red[CMB_RQ][NWV][2];
-  __shared__ float s_m[CMB_RQ][2], s_mx[CMB_RQ][SMAX], s_l[CMB_RQ][SMAX];
-  __shared__ int s_n[CMB_RQ][SMAX + 1];      // [SMAX]: the split that holds the champion, or -1
-  __shared__ float s_w[CMB_RQ][SMAX];
-  const int h = blockIdx.y, g = h / pb.G;
-  const int r = threadIdx.x / D, c = threadIdx.x % D;
+// Merge of the key splits and the per-row quantities of the score pass, RQ query rows of one head
+// per workgroup of 4 D threads.
+//   * One wavefront per row brings in the row's per-split scalars (a lane each, S <= 64) and leaves
+//     the splits' factors, the list of kept-out keys that join the sums, and the row's scalars.
+//   * The sums over the splits: a thread owns four columns of a row; 16 / RQ threads share a row's
+//     columns and take every (16 / RQ)-th split, so that few rows still mean many loads in flight.
+//   * u = z M_h (and y = x M_h where a row has a champion) is a 16-row product on
+//     v_mfma_f32_16x16x4_f32: a wavefront owns 16 columns, its Gram entries stay in registers
+//     (loaded first, every entry needed by exactly one lane), z and x are LDS operands.
+// Bound by latency (three dependent round trips to memory) until the rows fill the chip, then by the
+// partial sums, Gram matrices and operands it moves.  Against a kernel of four rows per workgroup
+// with u on the vector ALU and value rows fetched for every split: 65536 rows x 1 split (32 layers of
+// 2112 tokens folded) 207 -> 66 us, 2048 rows x 17 splits 15.8 -> 13.2 us, 1024 rows (window 32) 13.1
+// -> 10.8 us, 4096 rows x 32 splits 24.6 -> 14.7 us, 2048 rows x 32 splits 19.5 -> 17.5 us.
+// Workgroups of one KV head follow each other on one XCD (ids 8 apart): its L2 holds their Gram matrices
+// and completes the cache lines that the heads of a group write in pieces.
+// grid (Hq * ceil(W / RQ)), 4 D threads.
+typedef float f32x4_t __attribute__((ext_vector_type(4)));
+
+// reductions over groups of `w` lanes (a power of two)
+__device__ __forceinline__ float group_sum(float x, int w) {
+  for (int sh = w >> 1; sh >= 1; sh >>= 1) x += __shfl_xor(x, sh, 64);
+  return x;
+}
+__device__ __forceinline__ float group_max(float x, int w) {
+  for (int sh = w >> 1; sh >= 1; sh >>= 1) x = fmaxf(x, __shfl_xor(x, sh, 64));
+  return x;
+}
+// sum over each row of 16 lanes (rotations, no LDS traffic)
+__device__ __forceinline__ float row16_sum(float x) {
+#define RK_ROR(n) x += __uint_as_float(__builtin_amdgcn_update_dpp(0u, __float_as_uint(x), 0x120 + (n), 0xF, 0xF, false))
+  RK_ROR(8); RK_ROR(4); RK_ROR(2); RK_ROR(1);
+#undef RK_ROR
+  return x;
+}
+// four consecutive elements of a row, whatever its alignment
+__device__ __forceinline__ f32x4_t quad_of(const float* p) {
+  f32x4_t x;
+  __builtin_memcpy(&x, p, 16);
+  return x;
+}
+__device__ __forceinline__ f32x4_t quad_of(const bf16_t* p) {
+  uint2 u;
+  __builtin_memcpy(&u, p, 8);
+  return f32x4_t{__uint_as_float(u.x << 16), __uint_as_float(u.x & 0xFFFF0000u), __uint_as_float(u.y << 16),
+                 __uint_as_float(u.y & 0xFFFF0000u)};
+}
+
+// splits that the LDS lists of a workgroup hold (many rows come with few splits)
+constexpr int combine_max_splits(int rq) { return rq >= 64 ? 8 : (rq >= 32 ? 16 : 64); }
+
+template <typename T, int D, int RQ>
+__global__ __launch_bounds__(4 * D, 4) void k_attn_combine(Prob pb, const T* __restrict__ v, int S,
+                                                           const float* __restrict__ gram, ScorePtrs o,
+                                                           const float* __restrict__ part_z, const T* __restrict__ q,
+                                                           int use_op, int log2gp, int nwb) {
+  constexpr int SMAX = combine_max_splits(RQ), NT = 4 * D, NWV = D / 16, CQ = D / 4, ZST = D + 4;
+  constexpr int NP = RQ < 16 ? 16 / RQ : 1;              // threads that share a row's columns
+  constexpr int MB = RQ < 16 ? 1 : RQ / 16;              // rows per thread, 16-row blocks of the product
+  constexpr int SB = MB >= 4 ? 2 : (RQ <= 8 ? 8 : 4);    // splits in flight per row
+  constexpr int JB = MB >= 2 ? 4 : 8;   // joining keys in flight per row
+  __shared__ __attribute__((aligned(16))) float zs[RQ][ZST];             // z of the rows
+  __shared__ __attribute__((aligned(16))) float xs[RQ * NP][ZST];        // partial sums of the splits, then x, then u
+  __shared__ float red[NWV][RQ][2];
+  __shared__ float s_w[RQ][SMAX], s_jw[RQ][SMAX];
+  __shared__ int s_jn[RQ][SMAX];
+  __shared__ float s_fr[RQ], s_lrest[RQ];
+  __shared__ int s_nj[RQ], s_nstar[RQ];
+  const int tid = threadIdx.x, l = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int npg = (pb.W + RQ - 1) / RQ;
+  const int per = pb.G * npg, id = blockIdx.x, full = (pb.Hkv & ~7) * per;      // workgroups per KV head
+  const int g = id < full ? (id / (8 * per)) * 8 + (id & 7) : id / per;
+  const int wg = id < full ? (id >> 3) % per : id % per;
+  const int h = g * pb.G + wg / npg, i0 = wg % npg * RQ;
   const T* vg = v + (int64_t)g * pb.kv_sh;
-  float mreg[AP];
+  const int SW = S <= 1 ? 1 : 1 << (32 - __builtin_clz((unsigned)(S - 1)));      // lanes per row
+  const int sub = l & (SW - 1);
+  const unsigned long long mine = SW >= 64 ? ~0ull : ((1ull << SW) - 1ull) << (l & ~(SW - 1));
+  // what the workgroup needs from memory is asked for in the order in which it will be waited for:
+  // the scalars, the first splits' sums, the Gram entries
+  float pm, pmx, pref, pl;
+  int pn;
+  auto fetch_scalars = [&](int r) {
+    const int64_t po = (int64_t)(h * pb.W + min(i0 + r, pb.W - 1)) * S + min(sub, S - 1);
+    pm = o.part_m[po]; pmx = o.part_mx[po]; pn = o.part_n[po]; pref = o.part_ref[po]; pl = o.part_l[po];
+  };
+  fetch_scalars(min(tid / SW, RQ - 1));
+  const int c4 = 4 * (tid % CQ), rz = (tid / CQ) % (RQ / MB), part = tid / (CQ * (RQ / MB));
+  const float* pz[MB];
+  f32x4_t t[MB][SB];
+#pragma unroll
+  for (int m = 0; m < MB; ++m) pz[m] = part_z + (int64_t)(h * pb.W + min(i0 + rz + 16 * m, pb.W - 1)) * S * D + c4;
+  auto fetch_splits = [&](int m, int s) {
+#pragma unroll
+    for (int k = 0; k < SB; ++k) t[m][k] = quad_of(pz[m] + (int64_t)min(s + k * NP, S - 1) * D);
+  };
+#pragma unroll
+  for (int m = 0; m < MB; ++m) fetch_splits(m, part);
+  // Gram entries of this lane: column 16 wv + l % 16, the K index of step 4 a + e being 16 a + 4 (l / 16) + e;
+  // read along the row of the same number (M is symmetric), four at a time
+  f32x4_t mreg[D / 16];
   if (gram) {
-    const float* Mh = gram + (int64_t)h * D * D + (int64_t)(r * AP) * D + c;
+    const float* Mh = gram + ((int64_t)h * D + 16 * wv + (l & 15)) * D + 4 * (l >> 4);
 #pragma unroll
-    for (int j = 0; j < AP; ++j) mreg[j] = Mh[j * D];
+    for (int a = 0; a < D / 16; ++a) mreg[a] = *(const f32x4_t*)(Mh + 16 * a);
   }
-  // A workgroup walks ngrp groups of CMB_RQ rows with the one set of Gram registers.
-  for (int grp = 0; grp < ngrp; ++grp) {
-  const int i = (blockIdx.x * ngrp + grp) * CMB_RQ + r;
-  if ((blockIdx.x * ngrp + grp) * CMB_RQ >= pb.W) break;      // workgroup-uniform
-  const bool live = i < pb.W;
-  const int row = h * pb.W + (live ? i : 0);
-  const int64_t o = (int64_t)row * S;
-  // Per-split scalars: thread c < S of the row's first wavefront owns split c (S <= 64).
-  float pm = -INFINITY, pmx = 0.f, pref = 0.f, pl = 0.f;
-  int pn = -1;
-  if (c < S) {
-    pm = part_m[o + c];
-    pmx = part_mx[o + c];
-    pn = part_n[o + c];
-    pref = part_ref[o + c];
-    pl = part_l[o + c];
-  }
-  T qv = T();                    // needed at the very end: its latency hides behind everything else
-  if (op) qv = q[(int64_t)h * pb.q_sh + (int64_t)(live ? i : 0) * pb.q_st + c];
-  if (c < 64) {
-    float M0 = pm;
-#pragma unroll
-    for (int sh = 32; sh >= 1; sh >>= 1) M0 = fmaxf(M0, __shfl_xor(M0, sh, 64));
+  for (int r = tid / SW; r < RQ; r += NT / SW) {
+    const int row = h * pb.W + min(i0 + r, pb.W - 1);
+    if (r >= NT / SW) fetch_scalars(r);
+    if (sub >= S) { pm = -INFINITY; pn = -1; }
+    const float M0 = group_max(pm, SW);
     // split whose kept-out key is the overall maximum: the earliest one (= lowest key)
-    const unsigned long long cand = __ballot(pn >= 0 && pmx == M0);
-    const int ss = cand ? __builtin_ctzll(cand) : -1;
+    const unsigned long long cand = __ballot(pn >= 0 && pmx == M0) & mine;
+    const int sl = cand ? __builtin_ctzll(cand) : -1;      // its lane
     // a split adds to the merged sums if it saw a key and its own sums are not empty; its
     // kept-out key joins them unless it is the overall maximum
     const bool has = pm != -INFINITY && pl > 0.f;
-    const bool joins = pm != -INFINITY && pn >= 0 && c != ss;
+    const bool joins = pm != -INFINITY && pn >= 0 && l != sl;
     // The merged sums are relative to R, the largest logit that is part of them (reference of a
     // split, logit of a joining key), NOT to the overall maximum M0: a kept-out key may be any
     // distance above the rest without the rest's sums underflowing.
     float R = has ? pref : -INFINITY;
     if (joins) R = fmaxf(R, pmx);
-#pragma unroll
-    for (int sh = 32; sh >= 1; sh >>= 1) R = fmaxf(R, __shfl_xor(R, sh, 64));
-    s_w[r][c] = has ? exp2f(pref - R) : 0.f;
-    s_l[r][c] = has ? pl : 0.f;                    // an empty split's sums may hold anything
-    s_mx[r][c] = joins ? exp2f(pmx - R) : 0.f;
-    s_n[r][c] = pn;
-    if (c == 0) { s_m[r][0] = M0; s_m[r][1] = R == -INFINITY ? 0.f : exp2f(R - M0); s_n[r][SMAX] = ss; }
+    R = group_max(R, SW);
+    const float w = has ? exp2f(pref - R) : 0.f;
+    const float wj = joins ? exp2f(pmx - R) : 0.f;
+    const float lrest = group_sum((has ? w * pl : 0.f) + wj, SW);    // (an empty split's sums may hold anything)
+    const unsigned long long jm = __ballot(wj != 0.f) & mine;
+    if (wj != 0.f) {
+      const int e = __popcll(jm & ((1ull << l) - 1ull));
+      s_jw[r][e] = wj;
+      s_jn[r][e] = pn;
+    }
+    s_w[r][sub] = w;
+    const int nst = __shfl(pn, sl < 0 ? l : sl, 64);
+    if (sub == 0) {
+      s_fr[r] = R == -INFINITY ? 0.f : exp2f(R - M0);
+      s_lrest[r] = lrest;
+      s_nj[r] = __popcll(jm);
+      s_nstar[r] = sl >= 0 ? nst : -1;
+      if (i0 + r < pb.W) o.rs_m[row] = M0;
+    }
   }
   __syncthreads();
-  const float M = s_m[r][0];
-  const int sstar = s_n[r][SMAX];
-  const int nstar = sstar >= 0 ? s_n[r][sstar] : -1;
-
-  float lrest = 0.f, zr = 0.f;
-  const float* pz = part_z + o * D + c;
-  for (int s = 0; s < S; s += 8) {           // sixteen independent loads in flight
-    float t[8], tv[8], wk[8], wv[8];
+  // The key that the score pass is to evaluate in its leave-one-out form: the kept-out key if it ended
+  // with more than half of the mass (1 / l > 1/2); a smaller share is well conditioned in Eq. rec_ei.
+  auto loo = [&](int r) { return pb.ind == 0 && s_lrest[r] * s_fr[r] < 1.f ? s_nstar[r] : -1; };
+  const bool champ = __ballot(loo(l & (RQ - 1)) >= 0) != 0ull;
 #pragma unroll
-    for (int k = 0; k < 8; ++k) {
-      const int sk = min(s + k, S - 1);
-      const bool in = s + k < S;
-      wk[k] = in ? s_w[r][sk] : 0.f;
-      wv[k] = in ? s_mx[r][sk] : 0.f;
-      t[k] = pz[(int64_t)sk * D];
-      // value row of the kept-out key, fetched unconditionally (row 0 when there is none)
-      tv[k] = to_float(vg[(int64_t)(wv[k] != 0.f ? s_n[r][sk] : 0) * pb.kv_st + c]);
+  for (int m = 0; m < MB; ++m) {
+    const int r = rz + 16 * m;
+    // value rows of the kept-out keys: the overall maximum's, and those that join, the first JB of them
+    // (kept as they are stored until they are used)
+    const int nj = s_nj[r], nstar = s_nstar[r];
+    T tj[JB][4];
+    auto fetch_joins = [&](int j) {
+#pragma unroll
+      for (int k = 0; k < JB; ++k)
+        __builtin_memcpy(&tj[k][0], vg + (int64_t)s_jn[r][min(j + k * NP, nj - 1)] * pb.kv_st + c4, 4 * sizeof(T));
+    };
+    const f32x4_t vs = quad_of(vg + (int64_t)max(nstar, 0) * pb.kv_st + c4);
+    if (part < nj) fetch_joins(part);
+    f32x4_t z = {0.f, 0.f, 0.f, 0.f};
+    for (int s = part; s < S; s += SB * NP) {
+      if (s != part) fetch_splits(m, s);
+#pragma unroll
+      for (int k = 0; k < SB; ++k) {
+        const float wk = s + k * NP < S ? s_w[r][s + k * NP] : 0.f;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) z[e] = fmaf(wk, wk != 0.f ? t[m][k][e] : 0.f, z[e]);
+      }
     }
+    for (int j = part; j < nj; j += JB * NP) {
+      if (j != part) fetch_joins(j);
 #pragma unroll
-    for (int k = 0; k < 8; ++k) {
-      zr = fmaf(wk[k], wk[k] != 0.f ? t[k] : 0.f, zr);
-      lrest = fmaf(wk[k], s + k < S ? s_l[r][min(s + k, S - 1)] : 0.f, lrest);
-      zr = fmaf(wv[k], tv[k], zr);
-      lrest += wv[k];
+      for (int k = 0; k < JB; ++k) {
+        const float wk = j + k * NP < nj ? s_jw[r][j + k * NP] : 0.f;
+        const f32x4_t x = quad_of(&tj[k][0]);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) z[e] = fmaf(wk, x[e], z[e]);
+      }
+    }
+    if constexpr (NP > 1) {
+      *(f32x4_t*)&xs[part * RQ + r][c4] = z;
+      __syncthreads();
+    }
+    if (part == 0) {
+#pragma unroll
+      for (int k = 1; k < NP; ++k) z += *(const f32x4_t*)&xs[k * RQ + r][c4];
+      // rest -> units of the overall maximum (0 when the rest is below FP32 range next to the kept-out key)
+      const float fr = s_fr[r], lrest = s_lrest[r];
+      f32x4_t zz, x = {0.f, 0.f, 0.f, 0.f};
+      if (nstar >= 0) {
+        const float l_ = 1.f + lrest * fr;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          zz[e] = (vs[e] + z[e] * fr) / l_;
+          x[e] = lrest > 0.f ? z[e] / lrest - vs[e] : 0.f;     // z_without_champion - v_champion
+        }
+      } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) zz[e] = z[e] / lrest;
+      }
+      *(f32x4_t*)&zs[r][c4] = zz;
+      if (champ) *(f32x4_t*)&xs[r][c4] = x;                    // (its own partial sum, or nothing, was there)
     }
   }
-  // rest -> units of the overall maximum (0 when the rest is below FP32 range next to the kept-out key)
-  const float fr = s_m[r][1];
-  float l, z, x;
-  if (nstar >= 0) {
-    const float vstar = to_float(vg[(int64_t)nstar * pb.kv_st + c]);
-    l = 1.f + lrest * fr;
-    z = (vstar + zr * fr) / l;
-    x = lrest > 0.f ? zr / lrest - vstar : 0.f;   // z_without_champion - v_champion
-  } else {
-    l = lrest * fr;
-    z = zr / lrest;
-    x = 0.f;
-  }
-  float u = z, y = x;
+  __syncthreads();
+  // u and y: register j of a lane is row 16 m + 4 (l / 16) + j, column 16 wv + l % 16
+  const int c = 16 * wv + (l & 15), kq = l >> 4;
+  f32x4_t u[MB], y[MB];
+#pragma unroll
+  for (int m = 0; m < MB; ++m) { u[m] = f32x4_t{0.f, 0.f, 0.f, 0.f}; y[m] = u[m]; }
   if (pb.ind != 0) {
     // attention-weight and value-norm indicators: no output term (u = 0, zz = 0), no key is
     // evaluated by the leave-one-out form; the score pass then sees sqrt(vv) with vv = 1 or ||v||^2
-    u = 0.f; y = 0.f;
   } else if (gram) {
-    zx[c][r] = z;
-    zx[c][CMB_RQ + r] = x;
-    __syncthreads();
-    float ua[CMB_RQ], ya[CMB_RQ];
+    auto product = [&](const float (*x)[ZST], f32x4_t (&acc)[MB]) {
 #pragma unroll
-    for (int k = 0; k < CMB_RQ; ++k) { ua[k] = 0.f; ya[k] = 0.f; }
+      for (int a = 0; a < D / 16; ++a) {
+        f32x4_t xa[MB];
 #pragma unroll
-    for (int j = 0; j < AP; ++j) {
-      const float4 z4 = *(const float4*)&zx[r * AP + j][0];
-      const float4 x4 = *(const float4*)&zx[r * AP + j][CMB_RQ];
-      ua[0] = fmaf(z4.x, mreg[j], ua[0]); ua[1] = fmaf(z4.y, mreg[j], ua[1]);
-      ua[2] = fmaf(z4.z, mreg[j], ua[2]); ua[3] = fmaf(z4.w, mreg[j], ua[3]);
-      ya[0] = fmaf(x4.x, mreg[j], ya[0]); ya[1] = fmaf(x4.y, mreg[j], ya[1]);
-      ya[2] = fmaf(x4.z, mreg[j], ya[2]); ya[3] = fmaf(x4.w, mreg[j], ya[3]);
-    }
+        for (int m = 0; m < MB; ++m) xa[m] = *(const f32x4_t*)&x[(16 * m + (l & 15)) & (RQ - 1)][16 * a + 4 * kq];
 #pragma unroll
-    for (int k = 0; k < CMB_RQ; ++k) { up[r][0][k][c] = ua[k]; up[r][1][k][c] = ya[k]; }
-    __syncthreads();
-    u = (up[0][0][r][c] + up[1][0][r][c]) + (up[2][0][r][c] + up[3][0][r][c]);
-    y = (up[0][1][r][c] + up[1][1][r][c]) + (up[2][1][r][c] + up[3][1][r][c]);
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+          for (int m = 0; m < MB; ++m) acc[m] = __builtin_amdgcn_mfma_f32_16x16x4f32(xa[m][e], mreg[a][e], acc[m], 0, 0, 0);
+      }
+      // wait states between the last MFMA and the first read of its result, spelled out because a
+      // branch lies in between (the compiler inserts too few on one of the merging paths)
+#pragma unroll
+      for (int m = 0; m < MB; ++m) asm volatile("s_nop 15" : "+v"(acc[m]));
+    };
+    product(zs, u);
+    if (champ) product(xs, y);                   // workgroup-uniform
+  } else {
+#pragma unroll
+    for (int m = 0; m < MB; ++m)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const int r = (16 * m + 4 * kq + j) & (RQ - 1);
+        u[m][j] = zs[r][c];
+        if (champ) y[m][j] = xs[r][c];
+      }
   }
-  // zz = u.z and |x|_M^2 = y.x of the row: wavefront sums, then across the row's wavefronts
-  float s0 = u * z, s1 = y * x;
+  // zz = u.z and |x|_M^2 = y.x of the rows: sums over 16 lanes, then across the wavefronts
 #pragma unroll
-  for (int sh = 32; sh >= 1; sh >>= 1) { s0 += __shfl_xor(s0, sh, 64); s1 += __shfl_xor(s1, sh, 64); }
-  if ((c & 63) == 0) { red[r][c >> 6][0] = s0; red[r][c >> 6][1] = s1; }
+  for (int m = 0; m < MB; ++m)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int r = 16 * m + 4 * kq + j, rc = r & (RQ - 1);
+      float s0 = u[m][j] * zs[rc][c], s1 = 0.f;
+      s0 = row16_sum(s0);
+      if (champ) {
+        s1 = row16_sum(y[m][j] * xs[rc][c]);
+      }
+      if (r < RQ && (l & 15) == 0) { red[wv][r][0] = s0; red[wv][r][1] = s1; }
+    }
+  if (champ) __syncthreads();                    // (x has been read; u takes its place)
+#pragma unroll
+  for (int m = 0; m < MB; ++m)
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      if (16 * m + 4 * kq + j < RQ) xs[16 * m + 4 * kq + j][c] = u[m][j];
   __syncthreads();
-  if (live) {
-  float zz = 0.f, qx = 0.f;
+  for (int r = tid; r < RQ; r += NT) {
+    if (i0 + r >= pb.W) break;
+    const int row = h * pb.W + i0 + r;
+    float zz = 0.f, qx = 0.f;
 #pragma unroll
-  for (int wv = 0; wv < NWV; ++wv) { zz += red[r][wv][0]; qx += red[r][wv][1]; }
-  rs_u[(int64_t)row * D + c] = u;
-  if (op) {
+    for (int k = 0; k < NWV; ++k) { zz += red[k][r][0]; qx += red[k][r][1]; }
+    const float lr = s_lrest[r] * s_fr[r], l_ = s_nstar[r] >= 0 ? 1.f + lr : lr;
+    o.rs_l[row] = l_;
+    o.rs_zz[row] = zz;
+    o.rs_nstar[row] = loo(r);
+    o.rs_istar[row] = sqrtf(fmaxf(qx, 0.f)) / l_;       // A* ||(z_rest - v*) W_O||,  A* = 1/l
+  }
+  if (use_op) {
     // q, and u split into bf16 high and low parts, in the order the score pass feeds them to the
     // matrix cores: [which][32-row block][d/16][lane half][local row][8], local row =
     // position * Gp + head, so that a wavefront fetches each operand register as one 1 KiB run
-    const int head = h - g * pb.G;
-    const int log2iw = 5 - log2gp;
-    const int wb = i >> log2iw, m_ = ((i & ((1 << log2iw) - 1)) << log2gp) + head;
-    const int64_t nb = (int64_t)pb.Hkv * nwb;
-    const int64_t inner = ((((int64_t)(g * nwb + wb) * (D / 16) + (c >> 4)) * 2 + ((c >> 3) & 1)) * 32 + m_) * 8 + (c & 7);
-    const int64_t plane = nb * (D / 16) * 2 * 32 * 8;
-    const uint32_t ub = __float_as_uint(u);
-    uint32_t hi = ub + 0x7FFFu + ((ub >> 16) & 1u);          // round to nearest even (u is finite)
-    hi &= 0xFFFF0000u;
-    const uint32_t lb = __float_as_uint(u - __uint_as_float(hi));
-    const uint32_t lo = (lb + 0x7FFFu + ((lb >> 16) & 1u)) >> 16;
-    uint16_t qb;
-    __builtin_memcpy(&qb, &qv, 2);
-    op[inner] = qb;
-    op[plane + inner] = (uint16_t)(hi >> 16);
-    op[2 * plane + inner] = (uint16_t)lo;
-  }
-  if (c == 0) {
-    rs_m[row] = M;
-    rs_l[row] = l;
-    rs_zz[row] = zz;
-    rs_nstar[row] = pb.ind != 0 ? -1 : nstar;
-    rs_istar[row] = sqrtf(fmaxf(qx, 0.f)) / l;      // A* ||(z_rest - v*) W_O||,  A* = 1/l
-  }
-  }
-  __syncthreads();                           // the next group reuses the LDS scalars and sums
+    const int head = h - g * pb.G, log2iw = 5 - log2gp;
+    const int64_t plane = (int64_t)pb.Hkv * nwb * (D / 16) * 2 * 32 * 8;
+    for (int x = tid; x < RQ * (D / 8); x += NT) {
+      const int r = x / (D / 8), c8 = x % (D / 8), i = i0 + r;
+      if (i >= pb.W) continue;
+      const int wb = i >> log2iw, m_ = ((i & ((1 << log2iw) - 1)) << log2gp) + head;
+      const int64_t at = ((((int64_t)(g * nwb + wb) * (D / 16) + (c8 >> 1)) * 2 + (c8 & 1)) * 32 + m_) * 8;
+      uint32_t hi[4], lo[4];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const float ue = xs[r][8 * c8 + e];
+        const uint32_t ub = __float_as_uint(ue);
+        const uint32_t hb = (ub + 0x7FFFu + ((ub >> 16) & 1u)) & 0xFFFF0000u;      // round to nearest even (u is finite)
+        const uint32_t lb = __float_as_uint(ue - __uint_as_float(hb));
+        const uint32_t lw = (lb + 0x7FFFu + ((lb >> 16) & 1u)) >> 16;
+        hi[e >> 1] = e & 1 ? (hi[e >> 1] | hb) : (hb >> 16);
+        lo[e >> 1] = e & 1 ? (lo[e >> 1] | (lw << 16)) : lw;
+      }
+      *(uint4*)(o.op + at) = *(const uint4*)(q + (int64_t)h * pb.q_sh + (int64_t)i * pb.q_st + 8 * c8);   // (16-byte rows: checked on the host)
+      *(uint4*)(o.op + plane + at) = make_uint4(hi[0], hi[1], hi[2], hi[3]);
+      *(uint4*)(o.op + 2 * plane + at) = make_uint4(lo[0], lo[1], lo[2], lo[3]);
+    }
+  } else {
+    for (int x = tid; x < RQ * (D / 4); x += NT) {
+      const int r = x / (D / 4), cc = 4 * (x % (D / 4));
+      if (i0 + r < pb.W) *(f32x4_t*)(o.rs_u + ((int64_t)h * pb.W + i0 + r) * D + cc) = *(const f32x4_t*)&xs[r][cc];
+    }
   }
 }
 
-// launch configuration of k_attn_combine
-// groups of CMB_RQ rows per workgroup: one when that already gives plenty of workgroups, more
-// (fewer re-reads of the Gram matrix) when there are very many heads
-inline int combine_groups(const Prob& pb) {
-  const int64_t wgs = (int64_t)pb.Hq * ((pb.W + CMB_RQ - 1) / CMB_RQ);
-  int ngrp = (int)(wgs / 2048);
-  if (ngrp < 1) ngrp = 1;
-  const int all = (pb.W + CMB_RQ - 1) / CMB_RQ;
-  return ngrp < all ? ngrp : all;
+// use_op: leave the score pass's operands (bf16 path) instead of u in FP32.
+template <typename T, int D, int RQ>
+inline void launch_combine_rows(const Prob& pb, const T* v, int S, const float* gram, const ScorePtrs& w, const float* part_z,
+                                const T* q, int use_op, int log2gp, int nwb, hipStream_t st) {
+  RK_LAUNCH(ST_COMBINE, st, (k_attn_combine<T, D, RQ>), dim3(pb.Hq * ((pb.W + RQ - 1) / RQ)), dim3(4 * D), 0, st, pb, v, S, gram,
+            w, part_z, q, use_op, log2gp, nwb);
 }
-inline dim3 combine_grid(const Prob& pb) {
-  const int per = CMB_RQ * combine_groups(pb);
-  return dim3((pb.W + per - 1) / per, pb.Hq);
+template <typename T, int D>
+inline void launch_combine(const Prob& pb, const T* v, int S, const float* gram, const ScorePtrs& w, const float* part_z,
+                           const T* q, int use_op, int log2gp, int nwb, hipStream_t st) {
+  // As many rows per workgroup (one chain of round trips, one read of the Gram matrix) as still leave
+  // a workgroup for every compute unit; where eight rows do not leave two, four rows whose splits are
+  // shared by four threads (1024 rows: 10.8 us against 14.1 with eight; one split has nothing to share).
+  auto fills = [&](int rq) { return S <= combine_max_splits(rq) && pb.W > rq / 2 && (int64_t)pb.Hq * ((pb.W + rq - 1) / rq) >= n_cu(); };
+  if (fills(64)) launch_combine_rows<T, D, 64>(pb, v, S, gram, w, part_z, q, use_op, log2gp, nwb, st);
+  else if (fills(32)) launch_combine_rows<T, D, 32>(pb, v, S, gram, w, part_z, q, use_op, log2gp, nwb, st);
+  else if (fills(16)) launch_combine_rows<T, D, 16>(pb, v, S, gram, w, part_z, q, use_op, log2gp, nwb, st);
+  else if (S > 1 && (int64_t)pb.Hq * ((pb.W + 7) / 8) < 2 * n_cu()) launch_combine_rows<T, D, 4>(pb, v, S, gram, w, part_z, q, use_op, log2gp, nwb, st);
+  else launch_combine_rows<T, D, 8>(pb, v, S, gram, w, part_z, q, use_op, log2gp, nwb, st);
 }
-template <int D>
-inline dim3 combine_block() { return dim3(CMB_RQ * D); }
 
 }  // namespace restkv

@@ -1256,6 +1256,7 @@ int run_mfma(const Prob& pb, const void* q, const void* k, const void* v, const 
   if (S < 1) S = 1;
   int kps = (pb.L + S - 1) / S;
   kps = (kps + TN - 1) / TN * TN;
+  S = (pb.L + kps - 1) / kps;                      // (whole tiles: the last splits may have nothing left)
   const float* part_z = w.part_z;
   if (pb.ext_lse) {
     // the caller's attention output and log-sum-exp stand in for the attention pass: one "split"
@@ -1269,9 +1270,7 @@ int run_mfma(const Prob& pb, const void* q, const void* k, const void* v, const 
               log2iw, w);
   }
   if (pb.ind != 0) gram = nullptr;                 // the attention-weight and value-norm indicators have no projection
-  RK_LAUNCH(ST_COMBINE, st, (k_attn_combine<bf16_t, D>), combine_grid(pb), combine_block<D>(), 0, st, pb,
-            (const bf16_t*)v, S, gram, w.part_m, w.part_mx, w.part_n, w.part_ref, w.part_l, part_z, w.rs_m,
-            w.rs_l, w.rs_zz, w.rs_nstar, w.rs_istar, w.rs_u, (const bf16_t*)q, w.op, ilog2(gp), lay.nwb, combine_groups(pb));
+  launch_combine<bf16_t, D>(pb, (const bf16_t*)v, S, gram, w, part_z, (const bf16_t*)q, 1, ilog2(gp), lay.nwb, st);
   if (gram) {
     constexpr int HPW = D == 128 ? 4 : 8;
     const int NTv = (pb.P + TN - 1) / TN;

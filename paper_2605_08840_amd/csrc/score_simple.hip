@@ -514,9 +514,7 @@ int run(const Prob& pb, const void* q, const void* k, const void* v, const float
     else
       RK_LAUNCH(ST_ATTN, st, (k_attn_f32<T, D, 2, VEC>), dim3(S, gy, pb.Hkv), dim3(128), 0, st, pb, qq, kk, vp, S, kps, w);
   }
-  RK_LAUNCH(ST_COMBINE, st, (k_attn_combine<T, D>), combine_grid(pb), combine_block<D>(), 0, st, pb, vp, S, gram,
-            w.part_m, w.part_mx, w.part_n, w.part_ref, w.part_l, part_z, w.rs_m, w.rs_l, w.rs_zz, w.rs_nstar,
-            w.rs_istar, w.rs_u, (const T*)nullptr, (uint16_t*)nullptr, 0, 0, combine_groups(pb));
+  launch_combine<T, D>(pb, vp, S, gram, w, part_z, (const T*)nullptr, 0, 0, 0, st);
   const int nb = (pb.P + KB - 1) / KB;               // blocks of keys
   if (gram) {
     int chunks = (2 * cu + pb.Hq - 1) / pb.Hq;

@@ -47,3 +47,19 @@ def test_fp32_kernels_row_alignment(rk, oracle_mod, dtype, pad):  # noqa: F811
         Ig, tol = ref[g]
         assert np.isfinite(got[g]).all()
         assert_score_close(got[g], Ig, tol, f"row alignment head {g}")
+
+
+@pytest.mark.parametrize("Hq,Hkv,d,W,dtype", [
+    (256, 256, 64, 33, "bf16"),     # 64 rows per workgroup of the merge, second half nearly empty
+    (256, 64, 128, 64, "bf16"),     # 64 rows, groups of 4
+    (256, 256, 64, 32, "f32"),      # 32 rows
+    (256, 128, 64, 17, "bf16"),     # 32 rows, 15 of them absent
+    (64, 16, 128, 63, "bf16"),      # 16 rows, one of them absent
+    (64, 8, 64, 60, "f32"),         # 16 rows
+    (64, 16, 64, 57, "bf16"),       # 8 rows
+    (12, 4, 128, 5, "bf16"),        # 4 rows
+])
+def test_merge_row_blocks(rk, oracle_mod, Hq, Hkv, d, W, dtype):  # noqa: F811
+    """Every number of rows per workgroup of the merge kernel, with keys that hold most of a row's attention."""
+    w = workloads.small_case(Hq=Hq, Hkv=Hkv, d=d, L=W + 135, W=W, B=W + 30, dtype=dtype, D=2 * d, structure="sinks", seed=59)
+    _score_against_oracle_then_every_stage_exactly(rk, oracle_mod, w, "merge row blocks")
