@@ -61,8 +61,7 @@ extern "C" {
  *                                                     query to the oldest (oldest weighs alpha)
  *   spatial pooling:           RESTKV_POOL_MAX        maximum over the window instead of the mean
  * "No temporal smoothing" is ema_alpha = 1, "no spatial smoothing" base_window = 1 with
- * adaptive = 0, fixed average pooling adaptive = 0.  restkv_score_smooth runs the two separate
- * calls for any variant other than 0.
+ * adaptive = 0, fixed average pooling adaptive = 0.
  */
 #define RESTKV_IND_RECONSTRUCTION 0
 #define RESTKV_IND_ATTENTION      1
@@ -179,15 +178,8 @@ int restkv_smooth(const restkv_params* p, const float* score, float* ema, float*
                   restkv_stream_t stream);
 
 /*
- * restkv_score followed by restkv_smooth as ONE call, with the same outputs (score
- * included).  Where the shape allows it (bf16 inputs on the matrix-core path, G padded
- * to a power of two in {4, 8}, G * W <= 256, adaptive window on, P >= 32768) the score
- * pass itself accumulates the EMA (as the weighted sum that the recursion of Sec. 3.3
- * unrolls to) and the per-query top-B statistics of the adaptive window, from brackets
- * that a short pass over 8192 sampled keys provides, so that the raw score is written
- * once and not read again; otherwise the two calls run one after the other.  A query
- * whose bracket fails is redone exactly from `score`.  Workspace as reported by
- * restkv_workspace_bytes (it covers this call).
+ * restkv_score followed by restkv_smooth as ONE call, with the same outputs (score included).
+ * Workspace as reported by restkv_workspace_bytes.
  */
 int restkv_score_smooth(const restkv_params* p, const void* q, const void* k, const void* v,
                         const float* gram, float* score, float* ema, float* final_score,

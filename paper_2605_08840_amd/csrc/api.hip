@@ -90,25 +90,6 @@ SmoothWs smooth_ws(const Prob& pb) {
   return w;
 }
 
-FuseWs fuse_ws(const Prob& pb) {
-  FuseWs w;
-  w.ns = 8192;
-  w.nchunks = pb.G <= 32 ? score_pass_chunks(pb) : 1;
-  // a row's candidates (at most 4096 are usable) cluster in a few chunks: room for half of them
-  // in every chunk, for all of them when there are only a few chunks
-  const int caps = w.nchunks < 8 ? 4096 : 2048;
-  w.caps = caps;
-  const size_t rows = (size_t)pb.Hkv * pb.W;
-  size_t off = 0;
-  auto take = [&](size_t bytes) { size_t o = off; off = align_up(off + bytes); return o; };
-  w.smp = take(rows * w.ns * 4);
-  w.scnt = take(rows * w.nchunks * 4);
-  w.sval = take(rows * w.nchunks * w.caps * 4);
-  w.sidx = take(rows * w.nchunks * w.caps * 4);
-  w.bytes = off;
-  return w;
-}
-
 // compute units of the current device (queried once)
 int n_cu() {
   static int n = 0;
@@ -142,9 +123,6 @@ size_t restkv_workspace_bytes(const restkv_params* p) {
   size_t n = score_ws(pb).bytes;
   if (smooth_ws(pb).bytes > n) n = smooth_ws(pb).bytes;
   if (select_ws_bytes(pb) > n) n = select_ws_bytes(pb);
-  // the fused call keeps the score scratch, the smoothing scratch and its own side by side
-  const size_t f = align_up(score_ws(pb).bytes) + align_up(smooth_ws(pb).bytes) + fuse_ws(pb).bytes;
-  if (f > n) n = f;
   return n;
 }
 
@@ -225,35 +203,18 @@ int restkv_score_smooth(const restkv_params* p, const void* q, const void* k, co
   int rc = resolve(p, &pb);
   if (rc) return rc;
   if (!q || !k || !v || !score || !final_score) return RESTKV_EINVAL;
-  const ScoreWs ls = score_ws(pb);
-  const SmoothWs lm = smooth_ws(pb);
-  hipStream_t st = (hipStream_t)stream;
-  if (g_force_fp32 || p->variant != 0 || !fused_eligible(pb, q, k, v)) {
-    // same result from the two separate calls (they use the workspace one after the other);
-    // both sizes are checked first so that nothing is enqueued when the second call would fail
-    rc = check_ws(workspace, workspace_bytes, ls.bytes > lm.bytes ? ls.bytes : lm.bytes);
-    if (rc) return rc;
-    rc = restkv_score(p, q, k, v, gram, score, workspace, workspace_bytes, stream);
-    if (rc) return rc;
-    return restkv_smooth(p, score, ema, final_score, aws_info, aws_d, workspace, workspace_bytes, stream);
-  }
-  const FuseWs lf = fuse_ws(pb);
-  const size_t o_sm = align_up(ls.bytes), o_fu = o_sm + align_up(lm.bytes);
-  rc = check_ws(workspace, workspace_bytes, o_fu + lf.bytes);
+  // Both sizes are checked first so that nothing is enqueued when the second call would fail.  The two
+  // use the workspace one after the other.
+  const size_t a = score_ws(pb).bytes, b = smooth_ws(pb).bytes;
+  rc = check_ws(workspace, workspace_bytes, a > b ? a : b);
   if (rc) return rc;
-  char* ws = (char*)workspace;
-  char* wm = ws + o_sm;
-  char* wf = ws + o_fu;
-  FusedPtrs fp;
-  fp.smp = (float*)(wf + lf.smp); fp.ns = lf.ns;
-  fp.thr = (float2*)(wm + lm.thr); fp.cnt_hi = (uint32_t*)(wm + lm.cnt_hi);
-  fp.sum_hi = (unsigned long long*)(wm + lm.sum_hi);
-  fp.scnt = (uint32_t*)(wf + lf.scnt); fp.sval = (float*)(wf + lf.sval); fp.sidx = (int*)(wf + lf.sidx);
-  fp.caps = lf.caps;
-  fp.ema = ema ? ema : (float*)(wm + lm.ema);
-  rc = launch_score_fused(pb, q, k, v, gram, score, ws, ls, fp, st);
+  // A score pass that accumulated the smoothing itself (temporal sums and top-B statistics against
+  // brackets from a sampled pass, prefixes from 32k on) was slower at every size it took: 32/8 heads
+  // of 128, window 64: 269 against 213 us at 32k tokens, 407 against 347 at 64k, 697 against 645 at
+  // 128k; 64/8 heads at 128k 789 against 730.  Its vector work costs more than the read it saves.
+  rc = restkv_score(p, q, k, v, gram, score, workspace, workspace_bytes, stream);
   if (rc) return rc;
-  return launch_smooth_fused_tail(pb, score, fp.ema, final_score, aws_info, aws_d, wm, lm, fp, lf.nchunks, st);
+  return restkv_smooth(p, score, ema, final_score, aws_info, aws_d, workspace, workspace_bytes, stream);
 }
 
 static int select_impl(const restkv_params* p, const float* final_score, const int32_t* head_budget,

@@ -737,37 +737,12 @@ __global__ __launch_bounds__(512) void k_attn_pipe(Prob pb, const uint16_t* __re
 // t-1 (last read before E_2t) and the vv slot of tile t-2 (last read before E_2t-1); each
 // wavefront waits for its own share of tile t+1 before its mid-step barrier, which for both
 // halves precedes E_2t+2, the first barrier after which tile t+1 is read.
-// MODE 0: the pass as described.
-// MODE 1: sample pass.  The "tiles" are made of fa.ns sampled prefix keys (runs of 16 consecutive
-//         keys, evenly spread); their scores go to fa.smp [Hkv*W, fa.ns] instead of `score`.
-// MODE 2: fused pass (needs Gp >= 4, one row block).  Besides writing `score`, the vector
-//         half-step feeds the temporal and the spatial smoothing so that nothing has to read the
-//         raw score again:
-//   * EMA over the window queries as a weighted sum (weights of Sec. 3.3 unrolled): partial sums
-//     per wavefront meet in LDS, one wavefront writes fa.ema for the tile two steps later;
-//   * per (head, query) row and lane: count and position sum of the scores above the row's
-//     bracket fa.thr (registers, reduced once at the end into fa.cnt_hi / fa.sum_hi);
-//   * scores inside the bracket go, with their position and row, to a compact LDS list of the
-//     wavefront (places from a prefix sum over the lanes' counts); every 32 tiles, and when the
-//     list would overflow, the wavefront flushes it into the slices fa.sval / fa.sidx
-//     [row, key chunk = blockIdx.x, fa.caps] that only it writes (ranks by wave ballots, no
-//     atomics, deterministic); the slice fill counts go to fa.scnt at the end.
-struct FuseArgs {
-  float* smp; int ns; int ns_tiles; double step;
-  const float2* thr; uint32_t* cnt_hi; unsigned long long* sum_hi;
-  uint32_t* scnt; float* sval; int* sidx; int caps;
-  float* ema; float alpha;
-};
-constexpr int FUSE_CAPL = 512;       // candidate list entries per wavefront (a tile adds at most 512)
-
-template <int D, int GP, int MODE>
+template <int D, int GP>
 __global__ __launch_bounds__(512) void k_score_pipe(Prob pb, const uint16_t* __restrict__ q,
                                                     const uint16_t* __restrict__ k,
                                                     const uint16_t* __restrict__ v, ScorePtrs o, int ldv,
-                                                    float* __restrict__ score, int tiles_per_wg, int nwb,
-                                                    FuseArgs fa) {
+                                                    float* __restrict__ score, int tiles_per_wg, int nwb) {
   constexpr int NW = 8, KS = D / 16, LG = ilog2(GP), IW = 32 / GP;
-  static_assert(MODE != 2 || GP == 4 || GP == 8, "the fused pass keeps at most four rows per lane and needs LDS for its lists");
   constexpr int GV = GP < 4 ? 4 : GP;               // vv rows per ring slot (whole 1 KiB copies)
   constexpr int NVB = GV / 4;                       // 1 KiB copies per vv tile
   constexpr int ND = GP <= 4 ? GP : GP / 2;         // distinct heads among a lane's 16 registers
@@ -777,12 +752,6 @@ __global__ __launch_bounds__(512) void k_score_pipe(Prob pb, const uint16_t* __r
   __shared__ __attribute__((aligned(1024))) uint16_t Vs[3][TN * D];
   __shared__ __attribute__((aligned(1024))) float vvs[4][GV][TN];
   __shared__ __attribute__((aligned(16))) float rowc[NW][4][32];   // per local row: accumulator start values, champion key and score
-  constexpr int FL = MODE == 2 ? FUSE_CAPL : 1;
-  __shared__ float fval[NW][FL];                    // MODE 2: candidate list of each wavefront, value ...
-  __shared__ uint32_t fpos[NW][FL];                 // ... and position | row slot << 29 | lane half << 31
-  __shared__ __attribute__((aligned(16))) uint32_t fcnt[NW][8];   // MODE 2: slice fill count of each wavefront's rows
-  __shared__ __attribute__((aligned(16))) float frow[NW][3][8];   // MODE 2: per row (slot + 4 half): bracket lo, hi, EMA weight
-  __shared__ float epart[2][NW][TN];                // MODE 2: EMA partial sums of two tiles
 
   const int g = blockIdx.z;
   const int l = threadIdx.x & 63, wv = threadIdx.x >> 6, rr = l & 31, hf = l >> 5;
@@ -791,13 +760,10 @@ __global__ __launch_bounds__(512) void k_score_pipe(Prob pb, const uint16_t* __r
   const uint16_t* kg = k + (int64_t)g * pb.kv_sh;
   const uint16_t* vg = v + (int64_t)g * pb.kv_sh;
 
-  const int NT = MODE == 1 ? fa.ns_tiles : (pb.P + TN - 1) / TN;
+  const int NT = (pb.P + TN - 1) / TN;
   const int t0 = blockIdx.x * tiles_per_wg;
   const int t1 = min(NT, t0 + tiles_per_wg);
   if (t0 >= t1) return;
-  // MODE 1: sample j (tile j / 64, row j % 64) is key start(j / 16) + j % 16, the starts evenly
-  // spread over the prefix and multiples of 4 (a vv copy moves 4 keys)
-  auto key_of = [&](int j) { return min((int)((double)(j >> 4) * fa.step) & ~3, pb.P - 16) + (j & 15); };
 
   // vv copy of this wavefront: block wv % NVB (duplicates write identical bytes)
   const int vb = wvs % NVB;
@@ -811,11 +777,7 @@ __global__ __launch_bounds__(512) void k_score_pipe(Prob pb, const uint16_t* __r
   auto issue_tile = [&](int t) {
     const int tt = min(t, t1 - 1);                  // past the end: harmless repeat into a free slot
     const int kb = tt * TN;
-    if constexpr (MODE == 1) {
-      Ring::template issue_rows<NW>(kg, pitch, [&](int r) { return key_of(kb + r); }, Ks[t % 3], wv, l);
-      Ring::template issue_rows<NW>(vg, pitch, [&](int r) { return key_of(kb + r); }, Vs[t % 3], wv, l);
-      dma_1k(vv_g, (vv_row + (uint32_t)key_of(kb + 4 * (l & 15))) * 4u, &vvs[t & 3][4 * vb][0]);
-    } else if (kb + TN <= pb.L && kb + TN <= ldv) {   // whole tile, no clamp anywhere
+    if (kb + TN <= pb.L && kb + TN <= ldv) {   // whole tile, no clamp anywhere
       const uint64_t tb = (uint64_t)kb * pitch;
       const uint32_t slot = (uint32_t)(t % 3) * (TN * D * 2);
       Ring::template issue_whole<NW>((const char*)kg + tb, kvoff, ks_base + slot, wvs);
@@ -845,9 +807,10 @@ __global__ __launch_bounds__(512) void k_score_pipe(Prob pb, const uint16_t* __r
     const int row = h * pb.W + (valid ? i : 0);
     // operand-ordered copies left by the merge kernel: one 1 KiB run per wavefront and register
     const int64_t plane = (int64_t)pb.Hkv * nwb * (KS * 2 * 32 * 8);
-    const uint16_t* ob = o.op + (((int64_t)(g * nwb + wb) * KS * 2 + hf) * 32 + rr) * 8;
-    // (loaded whether the row exists or not, then masked: the buffer holds every padded row,
-    // and unconditional loads are all in flight together)
+    // (loaded whether the row exists or not, then masked: the buffer holds every padded row of the
+    // nwb blocks, a wavefront without a block reads the last one, and unconditional loads are all in
+    // flight together)
+    const uint16_t* ob = o.op + (((int64_t)(g * nwb + min(wb, nwb - 1)) * KS * 2 + hf) * 32 + rr) * 8;
     const uint4 zero4 = make_uint4(0, 0, 0, 0);
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) {
@@ -884,65 +847,6 @@ __global__ __launch_bounds__(512) void k_score_pipe(Prob pb, const uint16_t* __r
   char* sbase = (char*)(score + (int64_t)g * pb.W * pb.ld);
   const uint32_t ld4 = (uint32_t)pb.ld * 4u;
   const uint32_t voff0 = (uint32_t)i0 * ld4 + (uint32_t)rr * 4u;   // 32-bit: checked on the host
-  // MODE 2: running statistics of this lane's output rows; brackets and EMA weights of the
-  // wavefront's rows sit in LDS (frow)
-  uint32_t hc[NOUT], hsm[NOUT];
-  uint32_t wcount = 0;                               // entries in this wavefront's list (wave-uniform)
-  if constexpr (MODE == 2) {
-#pragma unroll
-    for (int a = 0; a < NOUT; ++a) { hc[a] = 0; hsm[a] = 0; }
-    if (l < 8) {                                     // row l & 3 of lane half l >> 2
-      const int i = wb * IW + out_pos0(l & 3) + (l >> 2) * HS;
-      const bool ok = (l & 3) < NOUT && i < pb.W;
-      const float2 th = ok ? fa.thr[g * pb.W + i] : make_float2(INFINITY, INFINITY);
-      frow[wv][0][l] = th.x;
-      frow[wv][1][l] = th.y;
-      // e_W-1 = sum_i w_i I_i with w_0 = (1-alpha)^(W-1), w_i = alpha (1-alpha)^(W-1-i)
-      frow[wv][2][l] = ok ? (i == 0 ? 1.f : fa.alpha) * powf(1.f - fa.alpha, (float)(pb.W - 1 - i)) : 0.f;
-      fcnt[wv][l] = 0;
-    }
-  }
-  const unsigned long long lanes_below = (1ull << l) - 1ull;
-  // MODE 2: list -> slices, 64 entries at a time; the entries of one row (tag = slot + 4 * lane
-  // half in the top bits of the position word) are ranked with a ballot.  Only this wavefront
-  // touches its list, its counts and its rows' slices.
-  auto flush = [&]() {
-    if constexpr (MODE == 2) {
-      uint32_t cn[8];                          // fill counts of the wavefront's 8 rows (wave-uniform)
-      {
-        const uint4 c0 = *(const uint4*)&fcnt[wv][0], c1 = *(const uint4*)&fcnt[wv][4];
-        cn[0] = c0.x; cn[1] = c0.y; cn[2] = c0.z; cn[3] = c0.w;
-        cn[4] = c1.x; cn[5] = c1.y; cn[6] = c1.z; cn[7] = c1.w;
-      }
-      const int caps = fa.caps;
-      float* const sval = fa.sval;
-      int* const sidx = fa.sidx;
-      for (uint32_t c0 = 0; c0 < wcount; c0 += 64) {
-        const bool have = c0 + (uint32_t)l < wcount;
-        const uint32_t pe = have ? fpos[wv][c0 + l] : 0u;
-        const float ve = have ? fval[wv][c0 + l] : 0.f;
-        const int tag = have ? (int)(pe >> 29) : -1;          // slot | half << 2
-        uint32_t ps = 0;
-#pragma unroll
-        for (int r8 = 0; r8 < 8; ++r8) {
-          const unsigned long long mk = __ballot(tag == r8);
-          if (tag == r8) ps = cn[r8] + (uint32_t)__popcll(mk & lanes_below);
-          cn[r8] += (uint32_t)__popcll(mk);
-        }
-        if (have && ps < (uint32_t)caps) {
-          const int i = wb * IW + 2 * (tag & 3) + (tag >> 2) * HS;     // out_pos0(a) = 2 a for Gp >= 4
-          const int64_t so = ((int64_t)(g * pb.W + i) * gridDim.x + blockIdx.x) * caps + ps;
-          sval[so] = ve;
-          sidx[so] = (int)(pe & 0x1FFFFFFFu);
-        }
-      }
-      if (l == 0) {
-        *(uint4*)&fcnt[wv][0] = make_uint4(cn[0], cn[1], cn[2], cn[3]);
-        *(uint4*)&fcnt[wv][4] = make_uint4(cn[4], cn[5], cn[6], cn[7]);
-      }
-      wcount = 0;
-    }
-  };
 
   wait_vm<NG>();           // own share of tile t0
   wg_barrier();            // E_2t0
@@ -956,16 +860,6 @@ __global__ __launch_bounds__(512) void k_score_pipe(Prob pb, const uint16_t* __r
     // against the opposite order, which is how the kernel was first written).
     __builtin_amdgcn_s_setprio(0);
     issue_tile(t + 2);
-    if constexpr (MODE == 2) {
-      // tile t-2: every wavefront left its partial sum before the barrier just passed
-      if (wv == 0 && t - 2 >= t0) {
-        const int n = (t - 2) * TN + l;
-        float e = 0.f;
-#pragma unroll
-        for (int w2 = 0; w2 < NW; ++w2) e += epart[t & 1][w2][l];
-        if (n < pb.P) fa.ema[(int64_t)g * pb.ld + n] = e;
-      }
-    }
     // ---- matrix half-step ----
     const uint16_t* kt = Ks[t % 3];
     const uint16_t* vt = Vs[t % 3];
@@ -1035,16 +929,8 @@ __global__ __launch_bounds__(512) void k_score_pipe(Prob pb, const uint16_t* __r
     // key of this lane in the two 32-key blocks of the tile
     int nk[2];
 #pragma unroll
-    for (int mb = 0; mb < 2; ++mb) nk[mb] = MODE == 1 ? key_of(kb + 32 * mb + rr) : kb + 32 * mb + rr;
-    bool champ_here = nslane >= kb && nslane < kb + TN;
-    if constexpr (MODE == 1) {             // the tile is four runs of 16 keys
-      champ_here = false;
-#pragma unroll
-      for (int r4 = 0; r4 < 4; ++r4) {
-        const int s0 = key_of(kb + 16 * r4);
-        champ_here = champ_here || (nslane >= s0 && nslane < s0 + 16);
-      }
-    }
+    for (int mb = 0; mb < 2; ++mb) nk[mb] = kb + 32 * mb + rr;
+    const bool champ_here = nslane >= kb && nslane < kb + TN;
     if (__ballot(champ_here) != 0ull) {    // a champion of this wavefront is here
 #pragma unroll
       for (int j = 0; j < 16; ++j) {       // register j of lane half hf is local row 8 (j/4) + 4 hf + j%4
@@ -1095,14 +981,6 @@ __global__ __launch_bounds__(512) void k_score_pipe(Prob pb, const uint16_t* __r
       }
     };
     if (pb.gmax) group_reduce(std::true_type{}); else group_reduce(std::false_type{});
-    if constexpr (MODE == 1) {
-#pragma unroll
-      for (int mb = 0; mb < 2; ++mb)
-#pragma unroll
-        for (int a = 0; a < NOUT; ++a)
-          if (i0 + out_pos0(a) < pb.W)
-            fa.smp[(int64_t)(g * pb.W + i0 + out_pos0(a)) * fa.ns + kb + 32 * mb + rr] = outv[mb][a];
-    } else {
     const uint32_t toff = (uint32_t)kb * 4u;
     if (rows_full && kb + TN <= pb.P) {             // wave-uniform: no lane needs a guard
 #pragma unroll
@@ -1118,106 +996,10 @@ __global__ __launch_bounds__(512) void k_score_pipe(Prob pb, const uint16_t* __r
           if (i0 + out_pos0(a) < pb.W && kb + 32 * mb + rr < pb.P)
             *(float*)(sbase + (voff0 + toff + (uint32_t)(128 * mb) + (uint32_t)out_pos0(a) * ld4)) = outv[mb][a];
     }
-    }
-    if constexpr (MODE == 2) {
-      bool cin[2][NOUT];
-      float tlo[4], thi[4], wq[4];
-      {
-        const f32x4 x0 = *(const f32x4*)&frow[wv][0][4 * hf], x1 = *(const f32x4*)&frow[wv][1][4 * hf],
-                    x2 = *(const f32x4*)&frow[wv][2][4 * hf];
-#pragma unroll
-        for (int a = 0; a < 4; ++a) { tlo[a] = x0[a]; thi[a] = x1[a]; wq[a] = x2[a]; }
-      }
-#pragma unroll
-      for (int mb = 0; mb < 2; ++mb) {
-        const bool inp = nk[mb] < pb.P;            // keys past the prefix count for nothing
-        // temporal smoothing: this lane's rows, the other lane half's, then LDS
-        float es = 0.f;
-#pragma unroll
-        for (int a = 0; a < NOUT; ++a) es = fmaf(wq[a], outv[mb][a], es);
-        if constexpr (HS != 0) es = xhalf_sum(es);
-        if (hf == 0) epart[t & 1][wv][32 * mb + rr] = inp ? es : 0.f;
-        // spatial statistics against the bracket of each row
-#pragma unroll
-        for (int a = 0; a < NOUT; ++a) {
-          const float x = outv[mb][a];
-          const bool hi = inp && x > thi[a];
-          hc[a] += hi ? 1u : 0u;
-          hsm[a] += hi ? (uint32_t)nk[mb] : 0u;
-          cin[mb][a] = inp && x > tlo[a] && !hi;   // inside the bracket
-        }
-      }
-      // candidates of this tile: a prefix sum over the lanes' counts (rotations-free DPP shifts
-      // inside the 16-lane rows, the four row totals through scalar registers) gives every lane
-      // its place in the wavefront's list
-      uint32_t myc = 0;
-#pragma unroll
-      for (int mb = 0; mb < 2; ++mb)
-#pragma unroll
-        for (int a = 0; a < NOUT; ++a) myc += cin[mb][a] ? 1u : 0u;
-      if (__ballot(myc != 0u) != 0ull) {            // wave-uniform
-        uint32_t s = myc;
-#define RK_SHR(n) s += __builtin_amdgcn_update_dpp(0u, s, 0x110 + (n), 0xF, 0xF, true)
-        RK_SHR(1); RK_SHR(2); RK_SHR(4); RK_SHR(8);   // inclusive sums inside each row of 16 lanes
-#undef RK_SHR
-        const uint32_t r0 = (uint32_t)__builtin_amdgcn_readlane((int)s, 15), r1 = (uint32_t)__builtin_amdgcn_readlane((int)s, 31),
-                       r2 = (uint32_t)__builtin_amdgcn_readlane((int)s, 47), r3 = (uint32_t)__builtin_amdgcn_readlane((int)s, 63);
-        const int lr = l >> 4;
-        const uint32_t before = lr == 0 ? 0u : (lr == 1 ? r0 : (lr == 2 ? r0 + r1 : r0 + r1 + r2));
-        const uint32_t tot = r0 + r1 + r2 + r3;
-        if (wcount + tot > (uint32_t)FUSE_CAPL) flush();   // (rare: the regular flushes below keep the list short)
-        uint32_t e = wcount + before + s - myc;
-#pragma unroll
-        for (int mb = 0; mb < 2; ++mb)
-#pragma unroll
-          for (int a = 0; a < NOUT; ++a)
-            if (cin[mb][a]) {
-              fval[wv][e] = outv[mb][a];
-              fpos[wv][e] = (uint32_t)nk[mb] | ((uint32_t)a << 29) | ((uint32_t)hf << 31);
-              ++e;
-            }
-        wcount += tot;
-      }
-      // every wavefront empties its list at the same tiles, so that the workgroup pays for one
-      // flush, not for eight at different barriers
-      if (((t - t0) & 31) == 31 && wcount) flush();
-    }
     wg_barrier();
   }
   if (!late) wg_barrier();
   wait_vm<0>();            // no copy may land in LDS after the workgroup has gone
-  if constexpr (MODE == 2) {
-    // the last two tiles' EMA (every partial sum is in LDS after the barriers above)
-    if (wv == 0) {
-      for (int t = max(t0, t1 - 2); t < t1; ++t) {
-        const int n = t * TN + l;
-        float e = 0.f;
-#pragma unroll
-        for (int w2 = 0; w2 < NW; ++w2) e += epart[t & 1][w2][l];
-        if (n < pb.P) fa.ema[(int64_t)g * pb.ld + n] = e;
-      }
-    }
-    flush();
-    // per row: statistics over the 32 lanes of the half (rotations inside the 16-lane rows, one
-    // row swap), slice fill count
-#pragma unroll
-    for (int a = 0; a < NOUT; ++a) {
-      uint32_t c = hc[a];
-      unsigned long long s = hsm[a];                // a lane's sum fits 32 bits (checked on the host)
-#pragma unroll
-      for (int sh = 1; sh < 32; sh <<= 1) {
-        c += (uint32_t)__shfl_xor((int)c, sh, 64);
-        s += ((unsigned long long)(uint32_t)__shfl_xor((int)(s >> 32), sh, 64) << 32) |
-             (unsigned long long)(uint32_t)__shfl_xor((int)(uint32_t)s, sh, 64);
-      }
-      const int i = i0 + out_pos0(a);
-      if (rr == 0 && i < pb.W) {
-        const int row = g * pb.W + i;
-        if (c) { atomicAdd(&fa.cnt_hi[row], c); atomicAdd(&fa.sum_hi[row], s); }
-        fa.scnt[(int64_t)row * gridDim.x + blockIdx.x] = fcnt[wv][a + 4 * hf];
-      }
-    }
-  }
 }
 
 // geometry of the score pass: padded group size, row blocks, tiles per workgroup, key chunks
@@ -1238,7 +1020,7 @@ ScoreGeom score_geom(const Prob& pb) {
 
 template <int D>
 int run_mfma(const Prob& pb, const void* q, const void* k, const void* v, const float* gram,
-             float* score, char* ws, const ScoreWs& lay, hipStream_t st, const FusedPtrs* fp) {
+             float* score, char* ws, const ScoreWs& lay, hipStream_t st) {
   const uint16_t* qq = (const uint16_t*)q;
   const uint16_t* kk = (const uint16_t*)k;
   const uint16_t* vp = (const uint16_t*)v;
@@ -1285,43 +1067,17 @@ int run_mfma(const Prob& pb, const void* q, const void* k, const void* v, const 
   }
   // score pass: one resident workgroup per compute unit, each walking a run of tiles
   const ScoreGeom sg = score_geom(pb);
-  const int tpp = sg.tpp;
   const dim3 g2(sg.chunks, sg.gy, pb.Hkv);
-  FuseArgs fa = {};
-#define RK_SCORE(GPV, MODE, GRID, TPW)                                                              \
-  RK_LAUNCH(ST_SCORE, st, (k_score_pipe<D, GPV, MODE>), GRID, dim3(512), 0, st, pb, qq, kk, vp, w,  \
-            lay.ldv, score, TPW, lay.nwb, fa)
-  if (fp) {
-    // sample pass -> brackets -> fused pass
-    fa.smp = fp->smp; fa.ns = fp->ns; fa.ns_tiles = fp->ns / TN;
-    fa.step = (double)(pb.P - 16) / (double)(fp->ns / 16 - 1);
-    fa.thr = fp->thr; fa.cnt_hi = fp->cnt_hi; fa.sum_hi = fp->sum_hi;
-    fa.scnt = fp->scnt; fa.sval = fp->sval; fa.sidx = fp->sidx; fa.caps = fp->caps;
-    fa.ema = fp->ema; fa.alpha = pb.alpha;
-    int tps = (int)(((int64_t)fa.ns_tiles * pb.Hkv + n_cu() - 1) / n_cu());
-    if (tps < 1) tps = 1;
-    const dim3 gs((fa.ns_tiles + tps - 1) / tps, 1, pb.Hkv);
-    switch (sg.gp) {
-      case 4: RK_SCORE(4, 1, gs, tps); break;
-      case 8: RK_SCORE(8, 1, gs, tps); break;
-      default: return RESTKV_EUNSUPPORTED;
-    }
-    const int rc = launch_bracket_samples(pb, fp->smp, fp->ns, fp->thr, fp->cnt_hi, fp->sum_hi, st);
-    if (rc) return rc;
-    switch (sg.gp) {
-      case 4: RK_SCORE(4, 2, g2, tpp); break;
-      case 8: RK_SCORE(8, 2, g2, tpp); break;
-      default: return RESTKV_EUNSUPPORTED;
-    }
-    return hip_status();
-  }
+#define RK_SCORE(GPV)                                                                                            \
+  RK_LAUNCH(ST_SCORE, st, (k_score_pipe<D, GPV>), g2, dim3(512), 0, st, pb, qq, kk, vp, w, lay.ldv, score, sg.tpp, \
+            lay.nwb)
   switch (sg.gp) {
-    case 1: RK_SCORE(1, 0, g2, tpp); break;
-    case 2: RK_SCORE(2, 0, g2, tpp); break;
-    case 4: RK_SCORE(4, 0, g2, tpp); break;
-    case 8: RK_SCORE(8, 0, g2, tpp); break;
-    case 16: RK_SCORE(16, 0, g2, tpp); break;
-    case 32: RK_SCORE(32, 0, g2, tpp); break;
+    case 1: RK_SCORE(1); break;
+    case 2: RK_SCORE(2); break;
+    case 4: RK_SCORE(4); break;
+    case 8: RK_SCORE(8); break;
+    case 16: RK_SCORE(16); break;
+    case 32: RK_SCORE(32); break;
     default: break;
   }
 #undef RK_SCORE
@@ -1344,27 +1100,8 @@ bool mfma_eligible(const Prob& pb, const void* q, const void* k, const void* v) 
 
 int launch_score_mfma(const Prob& pb, const void* q, const void* k, const void* v, const float* gram,
                       float* score, char* ws, const ScoreWs& lay, hipStream_t st) {
-  return pb.d == 64 ? run_mfma<64>(pb, q, k, v, gram, score, ws, lay, st, nullptr)
-                    : run_mfma<128>(pb, q, k, v, gram, score, ws, lay, st, nullptr);
-}
-
-int launch_score_fused(const Prob& pb, const void* q, const void* k, const void* v, const float* gram,
-                       float* score, char* ws, const ScoreWs& lay, const FusedPtrs& fp, hipStream_t st) {
-  return pb.d == 64 ? run_mfma<64>(pb, q, k, v, gram, score, ws, lay, st, &fp)
-                    : run_mfma<128>(pb, q, k, v, gram, score, ws, lay, st, &fp);
-}
-
-int score_pass_chunks(const Prob& pb) { return score_geom(pb).chunks; }
-
-bool fused_eligible(const Prob& pb, const void* q, const void* k, const void* v) {
-  if (!mfma_eligible(pb, q, k, v) || !pb.adaptive) return false;
-  if (pb.ind != 0 || pb.gmax || pb.tmode != 0 || pb.pmax) return false;
-  const ScoreGeom sg = score_geom(pb);
-  if (sg.gy != 1 || sg.gp < 4 || sg.gp > 8) return false;
-  if (pb.P < 32768 || pb.P >= (1 << 29)) return false;          // sampling pays off; 29-bit positions
-  if (2ull * (uint64_t)sg.tpp * (uint64_t)pb.P >= (1ull << 32)) return false;   // a lane's position sum
-  if (sg.chunks > 256) return false;                             // slice directory of the finishing kernel
-  return true;
+  return pb.d == 64 ? run_mfma<64>(pb, q, k, v, gram, score, ws, lay, st)
+                    : run_mfma<128>(pb, q, k, v, gram, score, ws, lay, st);
 }
 
 }  // namespace restkv

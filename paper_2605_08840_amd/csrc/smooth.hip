@@ -2,7 +2,7 @@
 // the per-query top-B positions, adaptive window size / shift, shifted box mean.
 //
 // The raw score [Hkv, W, P] is read from HBM once: a sorted sample of every (head, query) row
-// brackets the row's top-B threshold; the fused pass computes the EMA and, per row, counts and
+// brackets the row's top-B threshold; one pass computes the EMA and, per row, counts and
 // sums the positions above the bracket and collects the few entries inside it; a finishing
 // kernel decides the threshold exactly among those candidates.
 #include <type_traits>
@@ -14,7 +14,6 @@ namespace restkv {
 namespace {
 
 constexpr int CAND_CAP = 4096;      // candidates kept per (head, query) row
-constexpr int SMP_NS = 8192;        // samples per row that the fused score pass may leave for the bracket
 constexpr int ROW_NS = 4096;        // samples per row that the bracket kernel fetches itself
 
 // Bracket of the top-min(B,P) threshold of one (head, query) row from a sample of the row.
@@ -37,37 +36,6 @@ __global__ __launch_bounds__(256) void k_sample_bracket(Prob pb, const float* __
   int it = 0;
   uint32_t klo, khi;
   block_bracket<ROW_NS / 256, 16>(row, pb.P, k, cs, it, klo, khi);
-  if (threadIdx.x == 0)
-    thr[r] = make_float2(klo ? key_float(klo) : -INFINITY, khi != 0xFFFFFFFFu ? key_float(khi) : INFINITY);
-}
-
-// The same bracket from scores of sampled keys that the score pass left contiguously:
-// smp [Hkv*W, ns], ns a multiple of 256.  grid (W, Hkv), 256 threads.
-__global__ __launch_bounds__(256) void k_bracket_samples(Prob pb, const float* __restrict__ smp, int ns,
-                                                         float2* __restrict__ thr,
-                                                         uint32_t* __restrict__ cnt_hi,
-                                                         unsigned long long* __restrict__ sum_hi) {
-  constexpr int NPT = SMP_NS / 256;
-  __shared__ CountSmem cs;
-  const int i = blockIdx.x, g = blockIdx.y, r = g * pb.W + i;
-  const int k = min(head_budget(pb, g), pb.P);
-  if (threadIdx.x == 0) { cnt_hi[r] = 0; sum_hi[r] = 0ull; }
-  if (k >= pb.P) {
-    if (threadIdx.x == 0) thr[r] = make_float2(INFINITY, INFINITY);
-    return;
-  }
-  uint32_t keys[NPT];
-#pragma unroll
-  for (int j = 0; j < NPT; ++j) {
-    const int x = threadIdx.x + j * 256;
-    keys[j] = x < ns ? float_key(smp[(int64_t)r * ns + x]) : 0u;
-  }
-  int r_hi, r_lo, it = 0;
-  bracket_ranks(pb.P, ns, k, r_hi, r_lo);
-  uint32_t thi, tlo;
-  block_kth2<NPT>(keys, (uint32_t)max(r_hi, 1), (uint32_t)min(r_lo, ns), cs, it, thi, tlo, 16);
-  const uint32_t khi = r_hi >= 1 ? (thi | 0xFFFFu) : 0xFFFFFFFFu;
-  const uint32_t klo = r_lo <= ns ? tlo : 0u;
   if (threadIdx.x == 0)
     thr[r] = make_float2(klo ? key_float(klo) : -INFINITY, khi != 0xFFFFFFFFu ? key_float(khi) : INFINITY);
 }
@@ -294,7 +262,7 @@ __device__ inline unsigned long long finish_candidates(const uint32_t (&ck)[NPT]
 }
 
 // Sum of the positions of the top-min(B,P) entries of one (head, query) row: the entries above
-// the bracket were summed by the fused pass; the entries inside it arrive as bit masks (one
+// the bracket were summed by the scan; the entries inside it arrive as bit masks (one
 // 16-bit string per lane of the scan, see k_ema_scan), are expanded into positions here and
 // their values fetched from the raw score.  The threshold is found among them by bisection on
 // their keys; equal values are taken in position order (a second bisection on the position,
@@ -381,80 +349,6 @@ __global__ __launch_bounds__(256) void k_row_finish(Prob pb, const float* __rest
   if ((threadIdx.x & 63) == 0) isum[threadIdx.x >> 6] = acc;
   __syncthreads();
   if (threadIdx.x == 0) rowsum[r] = isum[0] + isum[1] + isum[2] + isum[3] + shi;
-}
-
-// The finishing step when the candidates of a row sit in per-chunk slices
-// (sval / sidx [row, nchunks, caps], fill counts scnt [row, nchunks]; nchunks <= 256).
-// grid (W, Hkv), 256 threads.
-__global__ __launch_bounds__(256) void k_row_finish_slices(Prob pb, const float* __restrict__ score,
-                                                           const uint32_t* __restrict__ cnt_hi,
-                                                           const unsigned long long* __restrict__ sum_hi,
-                                                           const uint32_t* __restrict__ scnt,
-                                                           const float* __restrict__ sval,
-                                                           const int* __restrict__ sidx, int nchunks, int caps,
-                                                           const float2* __restrict__ thr,
-                                                           unsigned long long* __restrict__ rowsum) {
-  constexpr int NPT = CAND_CAP / 256;
-  __shared__ CountSmem cs;
-  __shared__ unsigned long long isum[4];
-  __shared__ uint32_t pre[257];              // exclusive prefix of the slice fill counts
-  __shared__ uint32_t over;
-  __shared__ SelectSmem sm;                  // (exact search only)
-  const int i = blockIdx.x, g = blockIdx.y, r = g * pb.W + i;
-  const int k = min(head_budget(pb, g), pb.P);
-  if (k >= pb.P) {
-    if (threadIdx.x == 0) rowsum[r] = (unsigned long long)pb.P * (unsigned long long)(pb.P - 1) / 2ull;
-    return;
-  }
-  if (threadIdx.x == 0) {
-    uint32_t run = 0, ov = 0;
-    for (int c = 0; c < nchunks; ++c) {
-      const uint32_t n = scnt[(int64_t)r * nchunks + c];
-      pre[c] = run;
-      run += min(n, (uint32_t)caps);
-      ov |= n > (uint32_t)caps ? 1u : 0u;
-    }
-    pre[nchunks] = run;
-    over = ov;
-  }
-  __syncthreads();
-  const uint32_t ch = cnt_hi[r], nc = pre[nchunks];
-  const bool ok = !over && ch < (uint32_t)k && (uint32_t)k <= ch + nc && nc <= (uint32_t)CAND_CAP;
-  if (!ok) {
-    const unsigned long long tot = row_exact_sum(score + (int64_t)r * pb.ld, pb.P, k, sm);
-    if (threadIdx.x == 0) rowsum[r] = tot;
-    return;
-  }
-  const uint32_t need = (uint32_t)k - ch;
-  uint32_t ck[NPT], ci[NPT];
-  {
-    float fv[NPT];
-    int iv[NPT];
-#pragma unroll
-    for (int j = 0; j < NPT; ++j) {          // unconditional loads: see k_row_finish
-      const uint32_t x0 = threadIdx.x + j * 256, x = x0 < nc ? x0 : 0u;
-      int lo = 0, hi = nchunks - 1;           // last chunk whose prefix is <= x
-      while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (pre[mid] <= x) lo = mid; else hi = mid - 1;
-      }
-      const int64_t o = ((int64_t)r * nchunks + lo) * caps + (x - pre[lo]);
-      fv[j] = sval[o];
-      iv[j] = sidx[o];
-    }
-#pragma unroll
-    for (int j = 0; j < NPT; ++j) {
-      const bool in = (uint32_t)(threadIdx.x + j * 256) < nc;
-      ck[j] = in ? float_key(fv[j]) : 0u;
-      ci[j] = in ? (uint32_t)iv[j] : 0u;
-    }
-  }
-  unsigned long long acc = finish_candidates<NPT>(ck, ci, need, thr[r], cs);
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) acc += __shfl_xor(acc, o, 64);
-  if ((threadIdx.x & 63) == 0) isum[threadIdx.x >> 6] = acc;
-  __syncthreads();
-  if (threadIdx.x == 0) rowsum[r] = isum[0] + isum[1] + isum[2] + isum[3] + sum_hi[r];
 }
 
 // Window size and shift from the drift statistic (device function so that every block of
@@ -616,25 +510,6 @@ int launch_smooth(const Prob& pb, const float* score, float* ema, float* fin, in
               cmask, thr, rowsum);
   }
   RK_LAUNCH(ST_BOX, st, k_box, dim3((pb.P + 256 * BOX_PT - 1) / (256 * BOX_PT), pb.Hkv), dim3(256), 0, st, pb, e, rowsum, fin,
-            aws_info, aws_d);
-  return hip_status();
-}
-
-int launch_bracket_samples(const Prob& pb, const float* smp, int ns, float2* thr, uint32_t* cnt_hi,
-                           unsigned long long* sum_hi, hipStream_t st) {
-  if (ns > SMP_NS) return RESTKV_EINVAL;
-  RK_LAUNCH(ST_ROWTOPK, st, k_bracket_samples, dim3(pb.W, pb.Hkv), dim3(256), 0, st, pb, smp, ns, thr,
-            cnt_hi, sum_hi);
-  return hip_status();
-}
-
-int launch_smooth_fused_tail(const Prob& pb, const float* score, const float* ema, float* fin,
-                             int32_t* aws_info, double* aws_d, char* ws, const SmoothWs& lay,
-                             const FusedPtrs& fp, int nchunks, hipStream_t st) {
-  unsigned long long* rowsum = (unsigned long long*)(ws + lay.rowsum);
-  RK_LAUNCH(ST_ROWTOPK, st, k_row_finish_slices, dim3(pb.W, pb.Hkv), dim3(256), 0, st, pb, score, fp.cnt_hi,
-            fp.sum_hi, fp.scnt, fp.sval, fp.sidx, nchunks, fp.caps, fp.thr, rowsum);
-  RK_LAUNCH(ST_BOX, st, k_box, dim3((pb.P + 256 * BOX_PT - 1) / (256 * BOX_PT), pb.Hkv), dim3(256), 0, st, pb, ema, rowsum, fin,
             aws_info, aws_d);
   return hip_status();
 }
