@@ -9,6 +9,8 @@
 // result.
 #pragma once
 
+#include <type_traits>
+
 #include "common.hpp"
 
 namespace restkv {
@@ -101,162 +103,211 @@ __device__ __forceinline__ float key_float(uint32_t k) {
 
 constexpr int SEL_NS = 4096;     // samples of the bracketed search
 
-// Block-wide counting on keys held in registers (NPT per thread; empty slots hold key 0, which
-// no pivot >= 1 counts).  One barrier per call; `it` alternates the two reduction buffers.
-struct CountSmem { uint32_t red[2][3][SEL_NW]; };
-
-// counts of keys >= piv[0..NP) (NP <= 6): per-lane counts on the vector ALU, several counts per
-// register through the wave reduction (three of 10 bits while a wavefront holds fewer than 1024
-// keys, else two of 16 bits), one LDS word per register and wavefront.
-// NWV: wavefronts that take part (0: all of the block; otherwise the first NWV, the others having left)
-template <int NPT, int NP, int NWV = 0>
-__device__ __forceinline__ void block_count_geN(const uint32_t (&k)[NPT], const uint32_t (&piv)[NP],
-                                                CountSmem& cs, int& it, uint32_t (&cnt)[NP]) {
-  static_assert(NP >= 1 && NP <= 6, "three packed registers");
-  constexpr int BITS = NPT * 64 < 1024 ? 10 : 16, PER = 32 / BITS;
-  constexpr int NR = (NP + PER - 1) / PER;
-  constexpr uint32_t FM = (1u << BITS) - 1u;
-  uint32_t c[NP];
-#pragma unroll
-  for (int q = 0; q < NP; ++q) c[q] = 0;
-#pragma unroll
-  for (int j = 0; j < NPT; ++j)
-#pragma unroll
-    for (int q = 0; q < NP; ++q) c[q] += k[j] >= piv[q] ? 1u : 0u;
-  const int w = threadIdx.x >> 6, nw = NWV ? NWV : (int)(blockDim.x >> 6), p = it & 1;
-#pragma unroll
-  for (int r = 0; r < NR; ++r) {
-    uint32_t pk = 0;
-#pragma unroll
-    for (int u = 0; u < PER; ++u)
-      if (PER * r + u < NP) pk |= c[PER * r + u] << (BITS * u);
-    const uint32_t packed = wave_sum(pk);
-    if ((threadIdx.x & 63) == 0) cs.red[p][r][w] = packed;
-  }
-  __syncthreads();
-#pragma unroll
-  for (int q = 0; q < NP; ++q) cnt[q] = 0;
-  auto add_wave = [&](int j) {
-#pragma unroll
-    for (int r = 0; r < NR; ++r) {
-      const uint32_t x = cs.red[p][r][j];
-#pragma unroll
-      for (int u = 0; u < PER; ++u)
-        if (PER * r + u < NP) cnt[PER * r + u] += (x >> (BITS * u)) & FM;
-    }
-  };
-  if constexpr (NWV != 0) {
-#pragma unroll
-    for (int j = 0; j < NWV; ++j) add_wave(j);
-  } else {
-    for (int j = 0; j < nw; ++j) add_wave(j);
-  }
-  ++it;
+// largest / smallest value of the 64 lanes, in every lane (no LDS traffic)
+__device__ __forceinline__ uint32_t wave_max_u(uint32_t x) {
+#define RK_ROR(n) x = max(x, (uint32_t)__builtin_amdgcn_update_dpp(0u, x, 0x120 + (n), 0xF, 0xF, false))
+  RK_ROR(1); RK_ROR(2); RK_ROR(4); RK_ROR(8);
+#undef RK_ROR
+  auto r = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+  x = max(r[0], r[1]);
+  r = __builtin_amdgcn_permlane32_swap(x, x, false, false);
+  return max(r[0], r[1]);
+}
+// inclusive sum over the lanes up to this one
+__device__ __forceinline__ uint32_t wave_incl_scan(uint32_t x) {
+#define RK_DPP(ctrl, rows) x += __builtin_amdgcn_update_dpp(0u, x, (ctrl), (rows), 0xF, false)
+  RK_DPP(0x111, 0xF); RK_DPP(0x112, 0xF); RK_DPP(0x114, 0xF); RK_DPP(0x118, 0xF);   // row_shr 1, 2, 4, 8
+  RK_DPP(0x142, 0xA); RK_DPP(0x143, 0xC);                                           // row_bcast 15, 31
+#undef RK_DPP
+  return x;
 }
 
-template <int NPT, int NWV = 0>
-__device__ __forceinline__ void block_count_ge2(const uint32_t (&k)[NPT], uint32_t va, uint32_t vb,
-                                                CountSmem& cs, int& it, uint32_t& ca, uint32_t& cb) {
-  const uint32_t piv[2] = {va, vb};
-  uint32_t cnt[2];
-  block_count_geN<NPT, 2, NWV>(k, piv, cs, it, cnt);
-  ca = cnt[0]; cb = cnt[1];
-}
+// ---- selection among keys held in registers ---------------------------------------------------
+// A histogram over the keys' own range (2048 bins in LDS, equally wide on the order-preserving
+// integer image, i.e. logarithmic with linear pieces in value) finds the bin of the k-th largest
+// key; its few members are then ranked one against the other, or the bin is cut again.  Five
+// barriers for one round against the ten to twenty of a bisection on the key's bits.
+constexpr int CUT_BINS = 2048;
+constexpr int CUT_MEMB = 64;
+struct CutSmem {
+  uint32_t hist[CUT_BINS];
+  uint32_t ws[2][SEL_NW];
+  uint32_t res[2][3];                    // bin, entries above it, entries in it (per wanted rank)
+  uint32_t n;
+  uint32_t ck[CUT_MEMB], cp[CUT_MEMB];
+};
 
-// One bisection step on `nb` (1 or 2) bits starting at `bit`: a becomes the largest of
-// a | (x << (bit - nb + 1)), x in [0, 2^nb), whose count is >= kk, given the counts of x = 1..3.
-__device__ __forceinline__ uint32_t bisect_pick(uint32_t a, int sh, uint32_t kk, uint32_t c1, uint32_t c2,
-                                                uint32_t c3) {
-  if (c3 >= kk) return a | (3u << sh);
-  if (c2 >= kk) return a | (2u << sh);
-  if (c1 >= kk) return a | (1u << sh);
-  return a;
-}
-
-// A threshold t for the k largest keys of the block: count(key >= t) >= k, and either the count
-// is exactly k (t then need not be a key: the search stops as soon as a pivot separates the k
-// largest from the rest) or t is the k-th largest key itself (equal keys straddle the cut).  Bits
-// above `top_bit` are known (`prefix`, e.g. the common leading bits of a bracket that holds every
-// key); the others are resolved two per barrier (three pivots at a time).
-template <int NPT, int NWV = 0>
-__device__ inline uint32_t block_kth(const uint32_t (&k)[NPT], uint32_t kk, CountSmem& cs, int& it,
-                                     int top_bit = 31, uint32_t prefix = 0u) {
-  uint32_t a = prefix;
-  int bit = top_bit;
-  if ((bit & 1) == 0) {                 // odd number of bits: one single-bit step first
-    const uint32_t piv[1] = {a | (1u << bit)};
-    uint32_t c[1];
-    block_count_geN<NPT, 1, NWV>(k, piv, cs, it, c);
-    if (c[0] == kk) return piv[0];
-    if (c[0] >= kk) a = piv[0];
-    --bit;
-  }
-  for (; bit >= 1; bit -= 2) {
-    const int sh = bit - 1;
-    const uint32_t piv[3] = {a | (1u << sh), a | (2u << sh), a | (3u << sh)};
-    uint32_t c[3];
-    block_count_geN<NPT, 3, NWV>(k, piv, cs, it, c);
-    // a pivot with exactly kk keys at or above it separates the kk largest from the rest: the
-    // lower bits do not matter any more (block-uniform: every thread holds the same counts)
-    if (c[0] == kk) return piv[0];
-    if (c[1] == kk) return piv[1];
-    if (c[2] == kk) return piv[2];
-    a = bisect_pick(a, sh, kk, c[0], c[1], c[2]);
-  }
-  return a;
-}
-
-// Largest values ta, tb with count(key >= ta) >= ka and count(key >= tb) >= kb, i.e. the
-// ka-th and kb-th largest keys of the block (0 if fewer keys than that), bit by bit (with many
-// keys per thread the counting, not the barrier, is what a step costs).
-// With low_bit > 0 only the bits from it up are resolved (ta, tb are then lower bounds with the
-// unresolved bits zero).  Bits above `top_bit` are known (`prefix`: the leading bits that every
-// key shares).
-template <int NPT>
-__device__ inline void block_kth2(const uint32_t (&k)[NPT], uint32_t ka, uint32_t kb, CountSmem& cs,
-                                  int& it, uint32_t& ta, uint32_t& tb, int low_bit = 0, int top_bit = 31,
-                                  uint32_t prefix = 0u) {
-  uint32_t a = prefix, b = prefix;
-  for (int bit = top_bit; bit >= low_bit; --bit) {
-    const uint32_t pa = a | (1u << bit), pb = b | (1u << bit);
-    uint32_t ca, cb;
-    block_count_ge2<NPT>(k, pa, pb, cs, it, ca, cb);
-    if (ca >= ka) a = pa;
-    if (cb >= kb) b = pb;
-  }
-  ta = a; tb = b;
-}
-
-// Highest bit in which two keys differ (-1 if equal) and their common bits above it: every key
-// between them shares that prefix.
-__device__ __forceinline__ void common_prefix(uint32_t klo, uint32_t khi, int& top_bit, uint32_t& prefix) {
-  const uint32_t x = klo ^ khi;
-  top_bit = x ? 31 - __builtin_clz(x) : -1;
-  prefix = top_bit >= 31 ? 0u : (khi & ~((2u << max(top_bit, 0)) - 1u)) | (top_bit < 0 ? khi : 0u);
-}
-
-// Smallest and largest key of the block, empty slots (key 0) aside; kmin = 0xFFFFFFFF and kmax = 0
-// if there is no key.  One barrier, same buffers and turn-taking as the counting step.
-template <int NPT>
-__device__ inline void block_key_range(const uint32_t (&k)[NPT], CountSmem& cs, int& it, uint32_t& kmin,
-                                       uint32_t& kmax) {
-  uint32_t lo = 0xFFFFFFFFu, hi = 0u;
+// Smallest and largest key of the block, empty slots (key 0) aside; lo = 0xFFFFFFFF and hi = 0 if
+// there is no key.  One barrier; nothing of sm but ws is touched.
+template <int NT, int NPT>
+__device__ __forceinline__ void block_range(const uint32_t (&key)[NPT], CutSmem& sm, uint32_t& lo, uint32_t& hi) {
+  uint32_t nlo = 0u, mx = 0u;            // largest inverted key = smallest key
 #pragma unroll
   for (int j = 0; j < NPT; ++j) {
-    hi = max(hi, k[j]);
-    lo = k[j] ? min(lo, k[j]) : lo;
+    mx = max(mx, key[j]);
+    nlo = key[j] ? max(nlo, ~key[j]) : nlo;
+  }
+  mx = wave_max_u(mx);
+  nlo = wave_max_u(nlo);
+  if ((threadIdx.x & 63) == 0) { sm.ws[0][threadIdx.x >> 6] = mx; sm.ws[1][threadIdx.x >> 6] = nlo; }
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < NT / 64; ++j) { mx = max(mx, sm.ws[0][j]); nlo = max(nlo, sm.ws[1][j]); }
+  lo = ~nlo;
+  hi = mx;
+}
+
+// width of a bin (log2) that covers [lo, hi] with CUT_BINS of them
+__device__ __forceinline__ int cut_shift(uint32_t lo, uint32_t hi) {
+  const uint32_t range = hi - lo;
+  return range < (uint32_t)CUT_BINS ? 0 : 21 - __builtin_clz(range);
+}
+
+// Histogram of val(j), j < NPT, over [lo, hi] (values outside are left out; 0 never counts: lo >= 1),
+// then the bins that hold the ranks k[r] (1-based, from the top; every rank must exist): res[r].
+// Four barriers, the first of which also separates this from what used sm before.
+template <int NT, int NPT, int NR, typename V>
+__device__ __forceinline__ void block_bins(V val, uint32_t lo, uint32_t hi, int shift, const uint32_t (&k)[NR],
+                                           CutSmem& sm) {
+  constexpr int R = CUT_BINS / NT;
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < R; ++i) sm.hist[threadIdx.x + i * NT] = 0u;
+  if (threadIdx.x == 0) sm.n = 0u;
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < NPT; ++j) {
+    const uint32_t d = val(j) - lo;
+    if (d <= hi - lo) atomicAdd(&sm.hist[d >> shift], 1u);
+  }
+  __syncthreads();
+  // thread t owns the bins CUT_BINS - R (t + 1) .. + R - 1: thread order is descending
+  const int base = CUT_BINS - R * ((int)threadIdx.x + 1), w = threadIdx.x >> 6;
+  uint32_t h[R], own = 0;
+#pragma unroll
+  for (int i = 0; i < R; ++i) { h[i] = sm.hist[base + i]; own += h[i]; }
+  uint32_t incl = wave_incl_scan(own);
+  if ((threadIdx.x & 63) == 63) sm.ws[0][w] = incl;
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < NT / 64 - 1; ++j) incl += j < w ? sm.ws[0][j] : 0u;
+#pragma unroll
+  for (int r = 0; r < NR; ++r) {
+    uint32_t before = incl - own;
+    if (before < k[r] && k[r] <= incl) {           // exactly one thread
+#pragma unroll
+      for (int i = R - 1; i >= 0; --i) {
+        if (before < k[r] && k[r] <= before + h[i]) {
+          sm.res[r][0] = (uint32_t)(base + i); sm.res[r][1] = before; sm.res[r][2] = h[i];
+        }
+        before += h[i];
+      }
+    }
+  }
+  __syncthreads();
+}
+
+// Cut of the k largest entries: an entry is one of them iff (key, ~position) >= (tau, ~cut), i.e.
+// equal keys are taken lowest position first.  key: NPT per thread, 0 where a slot is empty; pos(j):
+// position of slot j (below 2^31); every key lies in [lo, hi] (lo >= 1) and there are at least k >= 1
+// of them.  All NT threads call, all receive the result.  pos gets the thread index as an argument
+// that the compiler cannot see through: it would keep NPT positions in registers otherwise.
+template <int NT, int NPT, typename P>
+__device__ __forceinline__ void block_cut(const uint32_t (&key)[NPT], P pos, uint32_t k, uint32_t lo, uint32_t hi,
+                                          CutSmem& sm, uint32_t& tau, uint32_t& cut) {
+  bool tie = false;                      // equal keys straddle the cut: the search goes on over inverted positions
+  uint32_t tkey = 0;
+  for (;;) {                             // (block-uniform; the range shrinks by 2^11 a round)
+    int t = threadIdx.x;
+    asm volatile("" : "+v"(t));
+    auto val = [&](int j) { return tie ? (key[j] == tkey ? ~(uint32_t)pos(j, t) : 0u) : key[j]; };
+    const int shift = cut_shift(lo, hi);
+    const uint32_t kk[1] = {k};
+    if (tie) block_bins<NT, NPT, 1>(val, lo, hi, shift, kk, sm);
+    else block_bins<NT, NPT, 1>([&](int j) { return key[j]; }, lo, hi, shift, kk, sm);
+    const uint32_t cnt = sm.res[0][2];
+    k -= sm.res[0][1];
+    const uint32_t off = sm.res[0][0] << shift;
+    hi = lo + off + min(hi - lo - off, (1u << shift) - 1u);      // (no sum that could wrap)
+    lo += off;
+    if (cnt == k) {                      // the whole bin is taken
+      tau = tie ? tkey : lo;
+      cut = tie ? ~lo : 0xFFFFFFFFu;
+      return;
+    }
+    if (cnt <= (uint32_t)CUT_MEMB) {
+#pragma unroll
+      for (int j = 0; j < NPT; ++j) {
+        const uint32_t d = val(j) - lo;
+        if (d <= hi - lo) {
+          const uint32_t e = atomicAdd(&sm.n, 1u);
+          sm.ck[e] = key[j];
+          sm.cp[e] = (uint32_t)pos(j, t);
+        }
+      }
+      __syncthreads();
+      // every wavefront ranks the members for itself
+      const uint32_t l = threadIdx.x & 63;
+      const uint32_t mk = l < cnt ? sm.ck[l] : 0u, mp = l < cnt ? sm.cp[l] : 0u;
+      const unsigned long long mine = ((unsigned long long)mk << 32) | (unsigned long long)(uint32_t)~mp;
+      uint32_t rank = 0;
+      for (uint32_t e = 0; e < cnt; ++e) {
+        const unsigned long long x = ((unsigned long long)sm.ck[e] << 32) | (unsigned long long)(uint32_t)~sm.cp[e];
+        rank += x > mine ? 1u : 0u;
+      }
+      const int sel = __builtin_ctzll(__ballot(l < cnt && rank == k - 1u));
+      tau = (uint32_t)__builtin_amdgcn_readlane((int)mk, sel);
+      cut = (uint32_t)__builtin_amdgcn_readlane((int)mp, sel);
+      return;
+    }
+    if (shift == 0) {                    // more equal keys than members are ranked
+      tie = true;
+      tkey = lo;
+      lo = 0x80000000u;
+      hi = 0xFFFFFFFFu;
+    }
+  }
+}
+// (key, inverted position) of an entry and of a cut as one comparison.  (The form "key > tau ||
+// (key == tau && position <= cut)" is miscompiled by hipcc 7.2 at -O3: the addend of the tie case is dropped.)
+__device__ __forceinline__ bool in_cut(uint32_t key, uint32_t pos, uint32_t tau, uint32_t cut) {
+  const unsigned long long a = ((unsigned long long)key << 32) | (unsigned long long)(uint32_t)~pos;
+  const unsigned long long b = ((unsigned long long)tau << 32) | (unsigned long long)(uint32_t)~cut;
+  return a >= b;
+}
+
+// One row of floats in the registers of a block of NT threads (NPT each): its keys, 0 past the end.
+// VEC (the row 16-byte aligned, readable up to the next multiple of four): quads NT apart.
+template <int NT, int NPT, bool VEC>
+__device__ __forceinline__ int row_pos(int j, int t) {
+  return VEC ? 4 * ((j >> 2) * NT + t) + (j & 3) : j * NT + t;
+}
+template <int NT, int NPT, bool VEC>
+__device__ __forceinline__ void load_row_keys(const float* __restrict__ row, int n, uint32_t (&key)[NPT]) {
+  float f[NPT];
+  if constexpr (VEC) {
+    const int last = (n - 1) & ~3;
+#pragma unroll
+    for (int q = 0; q < NPT / 4; ++q) {
+      const float4 v4 = *(const float4*)(row + min(4 * (q * NT + (int)threadIdx.x), last));
+      f[4 * q] = v4.x; f[4 * q + 1] = v4.y; f[4 * q + 2] = v4.z; f[4 * q + 3] = v4.w;
+    }
+  } else {
+#pragma unroll
+    for (int j = 0; j < NPT; ++j) f[j] = row[min(j * NT + (int)threadIdx.x, n - 1)];
   }
 #pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) {
-    hi = max(hi, (uint32_t)__shfl_xor((int)hi, o, 64));
-    lo = min(lo, (uint32_t)__shfl_xor((int)lo, o, 64));
-  }
-  const int w = threadIdx.x >> 6, nw = (int)(blockDim.x >> 6), p = it & 1;
-  if ((threadIdx.x & 63) == 0) { cs.red[p][0][w] = hi; cs.red[p][1][w] = lo; }
-  __syncthreads();
-  kmin = 0xFFFFFFFFu; kmax = 0u;
-  for (int j = 0; j < nw; ++j) { kmax = max(kmax, cs.red[p][0][j]); kmin = min(kmin, cs.red[p][1][j]); }
-  ++it;
+  for (int j = 0; j < NPT; ++j) key[j] = row_pos<NT, NPT, VEC>(j, threadIdx.x) < n ? float_key(f[j]) : 0u;
+}
+// largest row that load_row_keys is instantiated for, and f(NT, NPT) with the instance for n <= that
+constexpr int ROW_REG_MAX = 32768;
+template <typename F>
+inline void with_row_block(int n, F f) {
+  if (n <= 2048) f(std::integral_constant<int, 256>{}, std::integral_constant<int, 8>{});
+  else if (n <= 4096) f(std::integral_constant<int, 256>{}, std::integral_constant<int, 16>{});
+  else if (n <= 8192) f(std::integral_constant<int, 512>{}, std::integral_constant<int, 16>{});
+  else if (n <= 16384) f(std::integral_constant<int, 1024>{}, std::integral_constant<int, 16>{});
+  else f(std::integral_constant<int, 1024>{}, std::integral_constant<int, 32>{});
 }
 
 // Sample ranks that bracket the k-th largest of a population of n from a sample of ns
@@ -295,26 +346,34 @@ __device__ inline int block_sample_regs(const float* __restrict__ row, int n, ui
 }
 
 // Bracket {klo, khi} (keys) of the k-th largest of row[0..n): the k-th largest key lies in
-// (klo, khi] unless the sample misled us.  khi = 0xFFFFFFFF / klo = 0 mean "unbounded".
-template <int NPT, int RUN>
-__device__ inline void block_bracket(const float* __restrict__ row, int n, int k, CountSmem& cs, int& it,
-                                     uint32_t& klo, uint32_t& khi) {
+// (klo, khi] unless the sample misled us.  khi = 0xFFFFFFFF / klo = 0 mean "unbounded".  The bins of
+// the two ranks are bracket enough, unless a few outliers stretch the bins until they are wide
+// next to the bracket itself: then the range between them is cut again.
+template <int NT, int NPT, int RUN>
+__device__ __forceinline__ void block_bracket(const float* __restrict__ row, int n, int k, CutSmem& sm, uint32_t& klo,
+                                              uint32_t& khi) {
   uint32_t keys[NPT];
   const int ns = block_sample_regs<NPT, RUN>(row, n, keys);
   int r_hi, r_lo;
   bracket_ranks(n, ns, k, r_hi, r_lo);
-  // a bracket only has to hold the threshold: 16 resolved bits (sign, exponent, 7 mantissa
-  // bits) are plenty; the upper end is rounded up, the lower end down.  The leading bits that
-  // the smallest and the largest sample share need no search.
-  uint32_t kmin, kmax, prefix;
-  int top_bit;
-  block_key_range<NPT>(keys, cs, it, kmin, kmax);
-  common_prefix(kmin, kmax, top_bit, prefix);
-  uint32_t thi, tlo;
-  block_kth2<NPT>(keys, (uint32_t)max(r_hi, 1), (uint32_t)min(r_lo, ns), cs, it, thi, tlo, 16, top_bit,
-                  prefix & 0xFFFF0000u);
-  khi = r_hi >= 1 ? (thi | 0xFFFFu) : 0xFFFFFFFFu;
-  klo = r_lo <= ns ? tlo : 0u;
+  uint32_t lo, hi;
+  block_range<NT>(keys, sm, lo, hi);
+  const bool up = r_hi >= 1, dn = r_lo <= ns;
+  uint32_t kk[2] = {(uint32_t)max(r_hi, 1), (uint32_t)min(r_lo, ns)};
+  for (int round = 0; round < 2; ++round) {
+    const int shift = cut_shift(lo, hi);
+    block_bins<NT, NPT, 2>([&](int j) { return keys[j]; }, lo, hi, shift, kk, sm);
+    const uint32_t off = sm.res[0][0] << shift, bot = lo + (sm.res[1][0] << shift);
+    const uint32_t top = lo + off + min(hi - lo - off, (1u << shift) - 1u);
+    const uint32_t above = sm.res[0][1];
+    hi = top;
+    lo = bot;
+    if (shift == 0 || (1u << shift) <= ((hi - lo) >> 4)) break;     // (block-uniform)
+    kk[0] -= above;
+    kk[1] -= above;
+  }
+  khi = up ? hi : 0xFFFFFFFFu;
+  klo = dn ? lo - 1u : 0u;
 }
 
 // Calls f(word index, word) for every 32-bit word of a row of ndw mask words (ndw a multiple of

@@ -19,12 +19,12 @@ constexpr int ROW_NS = 4096;        // samples per row that the bracket kernel f
 // Bracket of the top-min(B,P) threshold of one (head, query) row from a sample of the row.
 // thr[row] = {lo, hi}: the threshold lies in (lo, hi] unless the sample misled us (then the
 // finishing kernel falls back to the exact radix search).  Also clears the row's counters.
-// grid (W, Hkv), 256 threads, ROW_NS / 256 samples per thread in registers.
-__global__ __launch_bounds__(256) void k_sample_bracket(Prob pb, const float* __restrict__ score,
+// grid (W, Hkv), 512 threads, ROW_NS / 512 samples per thread in registers.
+__global__ __launch_bounds__(512) void k_sample_bracket(Prob pb, const float* __restrict__ score,
                                                         float2* __restrict__ thr,
                                                         uint32_t* __restrict__ cnt_hi,
                                                         unsigned long long* __restrict__ sum_hi) {
-  __shared__ CountSmem cs;
+  __shared__ CutSmem cs;
   const int i = blockIdx.x, g = blockIdx.y, r = g * pb.W + i;
   const float* row = score + (int64_t)r * pb.ld;
   const int k = min(head_budget(pb, g), pb.P);
@@ -33,9 +33,8 @@ __global__ __launch_bounds__(256) void k_sample_bracket(Prob pb, const float* __
     if (threadIdx.x == 0) thr[r] = make_float2(INFINITY, INFINITY);
     return;
   }
-  int it = 0;
   uint32_t klo, khi;
-  block_bracket<ROW_NS / 256, 16>(row, pb.P, k, cs, it, klo, khi);
+  block_bracket<512, ROW_NS / 512, 16>(row, pb.P, k, cs, klo, khi);
   if (threadIdx.x == 0)
     thr[r] = make_float2(klo ? key_float(klo) : -INFINITY, khi != 0xFFFFFFFFu ? key_float(khi) : INFINITY);
 }
@@ -228,56 +227,22 @@ __device__ inline unsigned long long row_exact_sum(const float* __restrict__ row
   return tot;
 }
 
-// Exact threshold among the candidates of one row (keys ck, positions ci, NPT per thread, 256
-// threads; empty slots have key 0): `need` of them belong to the top-B, ties cut by position.
-// Returns this thread's share of the position sum of the taken candidates.
-template <int NPT>
-__device__ inline unsigned long long finish_candidates(const uint32_t (&ck)[NPT], const uint32_t (&ci)[NPT],
-                                                       uint32_t need, float2 th, CountSmem& cs) {
-  int it = 0, top_bit;
-  uint32_t prefix, cge, cgt;
-  common_prefix(float_key(th.x), float_key(th.y), top_bit, prefix);   // every candidate lies inside the bracket
-  const uint32_t t = block_kth<NPT, 4>(ck, need, cs, it, top_bit, prefix);
-  block_count_ge2<NPT, 4>(ck, t, t + 1u, cs, it, cge, cgt);
-  const uint32_t k_eq = need - cgt;              // ties at t to take, lowest positions first
-  uint32_t pos_cut = 0xFFFFFFFFu;                // take tied entries with position <= pos_cut
-  if (cge - cgt > k_eq) {
-    // k_eq-th smallest position among the ties = k_eq-th largest inverted position
-    uint32_t inv[NPT];
-#pragma unroll
-    for (int j = 0; j < NPT; ++j) inv[j] = ck[j] == t ? 0xFFFFFFFFu - ci[j] : 0u;
-    pos_cut = 0xFFFFFFFFu - block_kth<NPT, 4>(inv, k_eq, cs, it);
-  }
-  // One 64-bit comparison per entry: (key, inverted position) >= (t, inverted cut).  (The form
-  // "key > t || (key == t && position <= cut)" is miscompiled by hipcc 7.2 at -O3: the addend of
-  // the tie case is dropped.)
-  const unsigned long long cut = ((unsigned long long)t << 32) | (unsigned long long)(0xFFFFFFFFu - pos_cut);
-  unsigned long long acc = 0;
-#pragma unroll
-  for (int j = 0; j < NPT; ++j) {
-    const unsigned long long kj = ((unsigned long long)ck[j] << 32) | (unsigned long long)(0xFFFFFFFFu - ci[j]);
-    acc += kj >= cut ? (unsigned long long)ci[j] : 0ull;
-  }
-  return acc;
-}
-
 // Sum of the positions of the top-min(B,P) entries of one (head, query) row: the entries above
 // the bracket were summed by the scan; the entries inside it arrive as bit masks (one
 // 16-bit string per lane of the scan, see k_ema_scan), are expanded into positions here and
-// their values fetched from the raw score.  The threshold is found among them by bisection on
-// their keys; equal values are taken in position order (a second bisection on the position,
-// only when a tie straddles the cut).  A row whose bracket missed, or that has more than
+// their values fetched from the raw score.  The threshold is found among them exactly (block_cut;
+// equal values in position order).  A row whose bracket missed, or that has more than
 // CAND_CAP candidates, is searched exactly (radix select over the whole row) on the spot.
-// grid (W, Hkv), 256 threads.
-__global__ __launch_bounds__(256) void k_row_finish(Prob pb, const float* __restrict__ score,
+// grid (W, Hkv), 512 threads.
+__global__ __launch_bounds__(512) void k_row_finish(Prob pb, const float* __restrict__ score,
                                                     const uint32_t* __restrict__ cnt_hi,
                                                     const unsigned long long* __restrict__ sum_hi,
                                                     const uint16_t* __restrict__ cmask,
                                                     const float2* __restrict__ thr,
                                                     unsigned long long* __restrict__ rowsum) {
-  constexpr int NPT = CAND_CAP / 256;
-  __shared__ CountSmem cs;
-  __shared__ unsigned long long isum[4];
+  constexpr int NT = 512, NPT = CAND_CAP / NT;
+  __shared__ CutSmem cs;
+  __shared__ unsigned long long isum[NT / 64];
   __shared__ uint32_t wsum[SEL_NW];
   __shared__ int cpos[CAND_CAP];                 // positions of the row's candidates
   __shared__ SelectSmem sm;                      // (exact search only)
@@ -294,10 +259,10 @@ __global__ __launch_bounds__(256) void k_row_finish(Prob pb, const float* __rest
   const int nwt = scan_waves(pb.P), ndw = nwt * 32;
   const uint32_t* mrow = (const uint32_t*)(cmask + (int64_t)r * nwt * 64);
   uint32_t c = 0;
-  for_each_mask_word<256>(mrow, ndw, [&](int, uint32_t m) { c += (uint32_t)__popc(m); });
+  for_each_mask_word<NT>(mrow, ndw, [&](int, uint32_t m) { c += (uint32_t)__popc(m); });
   const uint32_t incl = block_incl_scan(c, wsum);
   __syncthreads();
-  if (threadIdx.x == 255) wsum[0] = incl;            // (every thread has read the wave sums)
+  if (threadIdx.x == NT - 1) wsum[0] = incl;            // (every thread has read the wave sums)
   __syncthreads();
   const uint32_t nc = wsum[0];
   const bool ok = ch < (uint32_t)k && (uint32_t)k <= ch + nc && nc <= (uint32_t)CAND_CAP;
@@ -307,7 +272,7 @@ __global__ __launch_bounds__(256) void k_row_finish(Prob pb, const float* __rest
     return;
   }
   uint32_t slot = incl - c;
-  for_each_mask_word<256>(mrow, ndw, [&](int x, uint32_t m) {
+  for_each_mask_word<NT>(mrow, ndw, [&](int x, uint32_t m) {
     while (m) {
       const int b = __builtin_ctz(m);
       m &= m - 1;
@@ -323,32 +288,101 @@ __global__ __launch_bounds__(256) void k_row_finish(Prob pb, const float* __rest
   // slots per thread as the row's candidates need (block-uniform), so a short list is counted quickly.
   auto run = [&](auto nsc) {
     constexpr int NS = decltype(nsc)::value;
-    uint32_t ck[NS], ci[NS];
+    uint32_t ck[NS];
     float fv[NS];
     int iv[NS];
 #pragma unroll
     for (int j = 0; j < NS; ++j) {
-      const uint32_t x = threadIdx.x + j * 256;
+      const uint32_t x = threadIdx.x + j * NT;
       iv[j] = cpos[x < nc ? x : 0u];
       fv[j] = row[iv[j]];
     }
 #pragma unroll
-    for (int j = 0; j < NS; ++j) {
-      const bool in = (uint32_t)(threadIdx.x + j * 256) < nc;
-      ck[j] = in ? float_key(fv[j]) : 0u;
-      ci[j] = in ? (uint32_t)iv[j] : 0u;
-    }
-    return finish_candidates<NS>(ck, ci, need, th, cs);
+    for (int j = 0; j < NS; ++j) ck[j] = (uint32_t)(threadIdx.x + j * NT) < nc ? float_key(fv[j]) : 0u;
+    uint32_t tau, cut;
+    // every candidate lies inside the bracket (th.x, th.y]
+    block_cut<NT>(ck, [&](int j, int) { return iv[j]; }, need, float_key(th.x) + 1u, float_key(th.y), cs, tau, cut);
+    unsigned long long acc = 0;
+#pragma unroll
+    for (int j = 0; j < NS; ++j) acc += ck[j] && in_cut(ck[j], (uint32_t)iv[j], tau, cut) ? (unsigned long long)iv[j] : 0ull;
+    return acc;
   };
-  unsigned long long acc = nc <= 1024u  ? run(std::integral_constant<int, 4>{})
-                           : nc <= 2048u ? run(std::integral_constant<int, 8>{})
-                           : nc <= 3072u ? run(std::integral_constant<int, 12>{})
+  unsigned long long acc = nc <= 1024u  ? run(std::integral_constant<int, 2>{})
+                           : nc <= 2048u ? run(std::integral_constant<int, 4>{})
+                           : nc <= 3072u ? run(std::integral_constant<int, 6>{})
                                          : run(std::integral_constant<int, NPT>{});
 #pragma unroll
   for (int o = 32; o >= 1; o >>= 1) acc += __shfl_xor(acc, o, 64);
   if ((threadIdx.x & 63) == 0) isum[threadIdx.x >> 6] = acc;
   __syncthreads();
-  if (threadIdx.x == 0) rowsum[r] = isum[0] + isum[1] + isum[2] + isum[3] + shi;
+  if (threadIdx.x == 0) {
+    unsigned long long tot = shi;
+#pragma unroll
+    for (int j = 0; j < NT / 64; ++j) tot += isum[j];
+    rowsum[r] = tot;
+  }
+}
+
+// Both statistics of a prefix of at most ROW_REG_MAX positions in ONE launch: workgroups x < nrow
+// take a (head, query) row each, the whole of it in registers, and find its top-min(B,P) exactly;
+// the others take NT positions each and add up the weighted window queries.  Three launches (sample
+// bracket, scan, finish) are latency at these sizes: 33.5 us at 8k tokens, 8 KV heads, window 32,
+// against 8.1 here; 27.4 against 4.5 us at 1k tokens, 2 heads.  grid (nrow + ceil(P / NT), Hkv).
+template <int NT, int NPT, bool VEC>
+__global__ __launch_bounds__(NT, NT == 1024 && NPT == 16 ? 8 : 4) void k_short_rows(Prob pb, const float* __restrict__ score,
+                                                                      float* __restrict__ ema,
+                                                                      unsigned long long* __restrict__ rowsum, int nrow) {
+  __shared__ CutSmem cs;
+  __shared__ unsigned long long isum[NT / 64];
+  const int g = blockIdx.y;
+  if ((int)blockIdx.x < nrow) {
+    const int r = g * pb.W + blockIdx.x;
+    const int k = min(head_budget(pb, g), pb.P);
+    if (k >= pb.P) {                               // every prefix position is taken
+      if (threadIdx.x == 0) rowsum[r] = (unsigned long long)pb.P * (unsigned long long)(pb.P - 1) / 2ull;
+      return;
+    }
+    uint32_t key[NPT], lo, hi, tau, cut;
+    load_row_keys<NT, NPT, VEC>(score + (int64_t)r * pb.ld, pb.P, key);
+    block_range<NT>(key, cs, lo, hi);
+    auto pos = [](int j, int t) { return row_pos<NT, NPT, VEC>(j, t); };
+    block_cut<NT>(key, pos, (uint32_t)k, lo, hi, cs, tau, cut);
+    uint32_t acc = 0;                              // (NPT positions below 2^15)
+#pragma unroll
+    for (int j = 0; j < NPT; ++j) {
+      const uint32_t p = (uint32_t)pos(j, threadIdx.x);
+      acc += in_cut(key[j], p, tau, cut) ? p : 0u;
+    }
+    acc = wave_sum(acc);                           // below 2^26
+    if ((threadIdx.x & 63) == 0) isum[threadIdx.x >> 6] = acc;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      unsigned long long tot = 0;
+#pragma unroll
+      for (int j = 0; j < NT / 64; ++j) tot += isum[j];
+      rowsum[r] = tot;
+    }
+    return;
+  }
+  // temporal smoothing: a thread adds up one position's window queries, oldest first
+  float* wts = (float*)cs.hist;
+  const int n = ((int)blockIdx.x - nrow) * NT + threadIdx.x;
+  const float* s = score + (int64_t)g * pb.W * pb.ld + min(n, pb.P - 1);
+  float e = 0.f;
+  for (int b0 = 0; b0 < pb.W; b0 += CUT_BINS) {
+    const int nb = min(pb.W - b0, CUT_BINS);
+    if (b0) __syncthreads();
+    for (int i = threadIdx.x; i < nb; i += NT) wts[i] = temporal_weight(pb, b0 + i);
+    __syncthreads();
+    for (int i = 0; i < nb; i += 16) {
+      float x[16];
+#pragma unroll
+      for (int u = 0; u < 16; ++u) x[u] = s[(int64_t)(b0 + min(i + u, nb - 1)) * pb.ld];
+#pragma unroll
+      for (int u = 0; u < 16; ++u) e = fmaf(i + u < nb ? wts[min(i + u, nb - 1)] : 0.f, x[u], e);
+    }
+  }
+  if (n < pb.P) ema[(int64_t)g * pb.ld + n] = e;
 }
 
 // Window size and shift from the drift statistic (device function so that every block of
@@ -493,21 +527,34 @@ int launch_smooth(const Prob& pb, const float* score, float* ema, float* fin, in
   uint16_t* cmask = (uint16_t*)(ws + lay.cmask);
   float* e = ema ? ema : (float*)(ws + lay.ema);
   const bool vec = (pb.ld & 3) == 0 && (((uintptr_t)score | (uintptr_t)e) & 15u) == 0;
-  if (pb.adaptive)
-    RK_LAUNCH(ST_ROWTOPK, st, k_sample_bracket, dim3(pb.W, pb.Hkv), dim3(256), 0, st, pb, score, thr,
-              cnt_hi, sum_hi);
-  // short prefixes: 2 or 4 wavefronts per run of positions, until about a thousand wavefronts stream
-  const int64_t runs = (int64_t)scan_waves(pb.P) * pb.Hkv;
-  const int rs = runs >= 1024 ? 1 : (runs >= 512 ? 2 : 4);
-  const int ppw = 4 / rs;
-  const dim3 ge((scan_waves(pb.P) + ppw - 1) / ppw, pb.Hkv);
-  if (vec)
-    RK_LAUNCH(ST_EMA, st, k_ema_scan<true>, ge, dim3(256), 0, st, pb, score, e, thr, cnt_hi, sum_hi, cmask, rs);
-  else
-    RK_LAUNCH(ST_EMA, st, k_ema_scan<false>, ge, dim3(256), 0, st, pb, score, e, thr, cnt_hi, sum_hi, cmask, rs);
-  if (pb.adaptive) {
-    RK_LAUNCH(ST_ROWTOPK, st, k_row_finish, dim3(pb.W, pb.Hkv), dim3(256), 0, st, pb, score, cnt_hi, sum_hi,
-              cmask, thr, rowsum);
+  // One launch for short prefixes.  Rows above 16384 positions take a compute unit each: two rounds of
+  // them (512 rows of 32k: 37 us) lose against three launches that stream (34 us), one (132 rows of 20k:
+  // 12 us against 31) does not.
+  if (pb.P <= 16384 || (pb.P <= ROW_REG_MAX && pb.W * pb.Hkv <= n_cu())) {
+    const int nrow = pb.adaptive ? pb.W : 0;
+    with_row_block(pb.P, [&](auto nt, auto npt) {
+      constexpr int NT = decltype(nt)::value, NPT = decltype(npt)::value;
+      const dim3 gr(nrow + (pb.P + NT - 1) / NT, pb.Hkv);
+      if (vec) RK_LAUNCH(ST_EMA, st, (k_short_rows<NT, NPT, true>), gr, dim3(NT), 0, st, pb, score, e, rowsum, nrow);
+      else RK_LAUNCH(ST_EMA, st, (k_short_rows<NT, NPT, false>), gr, dim3(NT), 0, st, pb, score, e, rowsum, nrow);
+    });
+  } else {
+    if (pb.adaptive)
+      RK_LAUNCH(ST_ROWTOPK, st, k_sample_bracket, dim3(pb.W, pb.Hkv), dim3(512), 0, st, pb, score, thr,
+                cnt_hi, sum_hi);
+    // short prefixes: 2 or 4 wavefronts per run of positions, until about a thousand wavefronts stream
+    const int64_t runs = (int64_t)scan_waves(pb.P) * pb.Hkv;
+    const int rs = runs >= 1024 ? 1 : (runs >= 512 ? 2 : 4);
+    const int ppw = 4 / rs;
+    const dim3 ge((scan_waves(pb.P) + ppw - 1) / ppw, pb.Hkv);
+    if (vec)
+      RK_LAUNCH(ST_EMA, st, k_ema_scan<true>, ge, dim3(256), 0, st, pb, score, e, thr, cnt_hi, sum_hi, cmask, rs);
+    else
+      RK_LAUNCH(ST_EMA, st, k_ema_scan<false>, ge, dim3(256), 0, st, pb, score, e, thr, cnt_hi, sum_hi, cmask, rs);
+    if (pb.adaptive) {
+      RK_LAUNCH(ST_ROWTOPK, st, k_row_finish, dim3(pb.W, pb.Hkv), dim3(512), 0, st, pb, score, cnt_hi, sum_hi,
+                cmask, thr, rowsum);
+    }
   }
   RK_LAUNCH(ST_BOX, st, k_box, dim3((pb.P + 256 * BOX_PT - 1) / (256 * BOX_PT), pb.Hkv), dim3(256), 0, st, pb, e, rowsum, fin,
             aws_info, aws_d);

@@ -6,7 +6,7 @@ import torch
 
 import workloads
 from gpu_util import assert_score_close, oracle_score, params_for
-from test_gpu_parity import _score_against_oracle_then_every_stage_exactly, rk  # noqa: F401
+from test_gpu_parity import _score_against_oracle_then_every_stage_exactly, _smooth_select_inputs, rk  # noqa: F401
 
 pytestmark = pytest.mark.gpu
 
@@ -63,3 +63,36 @@ def test_merge_row_blocks(rk, oracle_mod, Hq, Hkv, d, W, dtype):  # noqa: F811
     """Every number of rows per workgroup of the merge kernel, with keys that hold most of a row's attention."""
     w = workloads.small_case(Hq=Hq, Hkv=Hkv, d=d, L=W + 135, W=W, B=W + 30, dtype=dtype, D=2 * d, structure="sinks", seed=59)
     _score_against_oracle_then_every_stage_exactly(rk, oracle_mod, w, "merge row blocks")
+
+
+@pytest.mark.parametrize("P,W,Hkv,kind", [
+    (2047, 5, 2, "ties"), (2049, 4, 1, "lognormal"), (4096, 3, 2, "constant"), (4097, 5, 2, "ties"),
+    (8192, 2, 1, "lognormal"), (8193, 6, 1, "ties"), (16384, 3, 2, "ties"), (16387, 4, 2, "lognormal"),
+    (32768, 2, 1, "ties"),          # the longest row that one workgroup holds
+    (32769, 2, 1, "ties"),          # ... and one past it
+    (16500, 64, 5, "lognormal"),    # more rows of this length than compute units: the streaming launches
+    (40000, 7, 2, "outliers"),      # a few scores 60 octaves above the rest stretch the sample's bins
+    (20000, 7, 2, "outliers"),
+])
+def test_row_statistics_and_selection_at_launch_rules(rk, oracle_mod, P, W, Hkv, kind):  # noqa: F811
+    """Top-B index sums, window and selection, exactly, around the row lengths where another launch takes over,
+    with many equal values and with values far above the rest."""
+    B, L = W + min(P - 1, 700), P + W
+    s = _smooth_select_inputs(77, Hkv, W, P, "lognormal" if kind == "outliers" else kind)
+    if kind == "outliers":
+        s[:, :, 5::P // 3] *= np.float32(2.0 ** 60)
+    p = rk.make_params(n_q_heads=Hkv, n_kv_heads=Hkv, head_dim=64, seq_len=L, window=W, budget=B, dtype="bf16",
+                       ema_alpha=0.25, base_window=3, beta=50.0)
+    buf = rk.alloc_layer_buffers(p, torch.bfloat16, "cuda")
+    buf.score[..., :P].copy_(torch.from_numpy(s))
+    rk.restkv_smooth(p, buf.score, buf.ema, buf.final, buf.aws_info, buf.aws_d, buf.workspace)
+    rk.restkv_select(p, buf.final, buf.idx, buf.workspace)
+    torch.cuda.synchronize()
+    fin, idx = buf.final.cpu().numpy(), buf.idx.cpu().numpy()
+    info, dd = buf.aws_info.cpu().numpy(), buf.aws_d.cpu().numpy()
+    for g in range(Hkv):
+        sm = oracle_mod.smooth_head(s[g], 0.25, 50.0, 3, True, B)
+        assert dd[g, 0] == sm["d_front"] and dd[g, 1] == sm["d_rear"]
+        assert tuple(info[g]) == (sm["w_s"], sm["gamma"])
+        np.testing.assert_allclose(fin[g, :P], sm["final"], rtol=2e-5, atol=1e-30)
+        np.testing.assert_array_equal(idx[g], oracle_mod.select(fin[g, :P].astype(np.float64), W, B))
