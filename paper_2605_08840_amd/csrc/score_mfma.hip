@@ -228,12 +228,17 @@ __device__ __forceinline__ void wait_vm() {
 // A tile has a matrix part (two 32-key halves of 20 MFMAs) and a vector part (the row dots);
 // wavefronts 0..3 and 4..7 run them in complementary order (see the loop), so the matrix cores
 // stay fed.  The two wavefronts of a head are in the same group.
-// grid (key chunks, ceil(G/HPW), Hkv), 512 threads; HPW = 4 heads per workgroup (8 for D = 64).
-template <int D>
+// KS2 (few heads per KV head): wavefronts 0..3 take keys 0..31 of a tile and wavefronts 4..7 keys
+// 32..63 of the same heads, so that a workgroup holds half as many heads.  A wavefront without a head
+// only copies.
+// grid (key chunks, ceil(G/HPW), Hkv), 512 threads; HPW = 4 heads per workgroup (8 for D = 64), half
+// of that with KS2.
+template <int D, bool KS2>
 __global__ __launch_bounds__(512) void k_vv_pipe(Prob pb, const uint16_t* __restrict__ v,
                                                  const float* __restrict__ gram, float* __restrict__ vv,
                                                  int ldv, int tiles_per_wg) {
-  constexpr int NW = 8, KS = D / 16, CB = D / 32, WPH = CB / 2, HPW = NW / WPH;
+  constexpr int NW = 8, KS = D / 16, CB = D / 32, WPH = CB / 2, HPW = NW / WPH / (KS2 ? 2 : 1);
+  constexpr int NMB = KS2 ? 1 : 2;                  // 32-key blocks of a tile per wavefront
   using Ring = TileRing<D, 0>;
   constexpr int NG = Ring::NI / NW;                 // copies per wavefront and tile
   __shared__ __attribute__((aligned(1024))) uint16_t Vs[4][TN * D];
@@ -241,7 +246,8 @@ __global__ __launch_bounds__(512) void k_vv_pipe(Prob pb, const uint16_t* __rest
   const int g = blockIdx.z;
   const int l = threadIdx.x & 63, wv = threadIdx.x >> 6, rr = l & 31, hf = l >> 5;
   const int wvs = wave_index();                     // the same as a scalar, for the copies' addresses
-  const int hw = wv / WPH, pr = wv % WPH;           // head inside the workgroup, row block pair
+  const int wr = KS2 ? wvs % (NW / 2) : wvs, ko = KS2 ? 32 * (wvs / (NW / 2)) : 0;   // first key of this wavefront in a tile
+  const int hw = wr / WPH, pr = wr % WPH;           // head inside the workgroup, row block pair
   const int hloc = blockIdx.y * HPW + hw;
   const int h = g * pb.G + (hloc < pb.G ? hloc : 0);
   const uint16_t* vg = v + (int64_t)g * pb.kv_sh;
@@ -263,6 +269,18 @@ __global__ __launch_bounds__(512) void k_vv_pipe(Prob pb, const uint16_t* __rest
   };
   issue_tile(t0);
   issue_tile(t0 + 1);
+  if (hloc >= pb.G) {                               // no head: this wavefront's share of the copies only
+    wait_vm<NG>();
+    wg_barrier();
+    for (int t = t0; t < t1; ++t) {
+      issue_tile(t + 2);
+      wait_vm<NG>();
+      wg_barrier();
+    }
+    wg_barrier();
+    wait_vm<0>();
+    return;
+  }
 
   auto body = [&](auto prc) {
     constexpr int PR = decltype(prc)::value;
@@ -292,18 +310,18 @@ __global__ __launch_bounds__(512) void k_vv_pipe(Prob pb, const uint16_t* __rest
     // vv of one tile of this wavefront's head: the partial dots of the head's wavefronts meet here
     auto head_sum = [&](int t) {
       if (PR == 0) {
-        const int n = t * TN + l;
-        if (n < pb.P && hloc < pb.G) {
+        const int n = t * TN + ko + l;
+        if (n < pb.P && (!KS2 || l < 32)) {
           float sum = 0.f;
 #pragma unroll
-          for (int m2 = 0; m2 < WPH; ++m2) sum += part[(t - t0) & 1][hw][m2][l];
+          for (int m2 = 0; m2 < WPH; ++m2) sum += part[(t - t0) & 1][hw][m2][KS2 ? ko + (l & 31) : l];
           vv[(int64_t)h * ldv + n] = sum;
         }
       }
     };
-    f32x16 y0[2], y1[2];
-    uint2 vq0[2][4], vq1[2][4];      // the value entries the row dots of a half need (fetched with its operands)
-    // matrix quarter: Y^T = T V^T for the 32 keys of half nb of tile t
+    f32x16 y0[NMB], y1[NMB];
+    uint2 vq0[NMB][4], vq1[NMB][4];      // the value entries the row dots of a half need (fetched with its operands)
+    // matrix quarter: Y^T = T V^T for block nb of this wavefront's 32-key blocks of tile t
     auto mat = [&](int nb, int t) {
       const uint16_t* vt = Vs[t & 3];
       __builtin_amdgcn_s_setprio(2);
@@ -313,11 +331,11 @@ __global__ __launch_bounds__(512) void k_vv_pipe(Prob pb, const uint16_t* __rest
       // LDS round trip per k-step
       bf16x8 b[N0];
 #pragma unroll
-      for (int a = 0; a < N0; ++a) b[a] = as_bf16x8(*(const uint4*)&vt[Ring::off(32 * nb + rr, 2 * (2 * RB0 + a) + hf)]);
+      for (int a = 0; a < N0; ++a) b[a] = as_bf16x8(*(const uint4*)&vt[Ring::off(ko + 32 * nb + rr, 2 * (2 * RB0 + a) + hf)]);
 #pragma unroll
       for (int jq = 0; jq < 4; ++jq) {
-        vq0[nb][jq] = *(const uint2*)&vt[Ring::off(32 * nb + rr, 4 * RB0 + jq) + 4 * hf];
-        vq1[nb][jq] = *(const uint2*)&vt[Ring::off(32 * nb + rr, 4 * RB1 + jq) + 4 * hf];
+        vq0[nb][jq] = *(const uint2*)&vt[Ring::off(ko + 32 * nb + rr, 4 * RB0 + jq) + 4 * hf];
+        vq1[nb][jq] = *(const uint2*)&vt[Ring::off(ko + 32 * nb + rr, 4 * RB1 + jq) + 4 * hf];
       }
 #pragma unroll
       for (int ks = 2 * RB0; ks < KS; ++ks) {
@@ -345,7 +363,7 @@ __global__ __launch_bounds__(512) void k_vv_pipe(Prob pb, const uint16_t* __rest
       }
       const float acc0 = (a0[0] + a0[1]) + (a0[2] + a0[3]), acc1 = (a1[0] + a1[1]) + (a1[2] + a1[3]);
       const float acc = xhalf_sum(acc0 + acc1);
-      if (hf == 0) part[(t - t0) & 1][hw][PR][32 * nb + rr] = acc;
+      if (hf == 0) part[(t - t0) & 1][hw][PR][ko + 32 * nb + rr] = acc;
     };
 
     // Steps H_t, one tile each, separated by workgroup barriers.  Wavefronts 0..3 run
@@ -365,21 +383,24 @@ __global__ __launch_bounds__(512) void k_vv_pipe(Prob pb, const uint16_t* __rest
       if (!late) {
         if (t > t0) head_sum(t - 1);
         mat(0, t);
-        mat(1, t);
+        if constexpr (NMB > 1) mat(1, t);
         dot(0, t);
-        dot(1, t);
+        if constexpr (NMB > 1) dot(1, t);
       } else {
         if (t > t0 + 1) head_sum(t - 2);
-        if (t > t0) { dot(0, t - 1); dot(1, t - 1); }
+        if (t > t0) {
+          dot(0, t - 1);
+          if constexpr (NMB > 1) dot(1, t - 1);
+        }
         mat(0, t);
-        mat(1, t);
+        if constexpr (NMB > 1) mat(1, t);
       }
       wait_vm<NG>();         // own share of tile t+1 (only the copy of tile t+2 is younger)
       wg_barrier();
     }
     if (late) {
       dot(0, t1 - 1);
-      dot(1, t1 - 1);
+      if constexpr (NMB > 1) dot(1, t1 - 1);
       if (t1 - 2 >= t0) head_sum(t1 - 2);
     } else {
       head_sum(t1 - 1);
@@ -412,21 +433,28 @@ __global__ __launch_bounds__(512) void k_vv_pipe(Prob pb, const uint16_t* __rest
 // tile t-1 and the V slot of tile t-2, both last read by a matrix half that precedes B_t-1; every
 // wavefront waits for its share of tile t+1 (only tile t+2 is younger) before its B_t, the first
 // barrier after which tile t+1 is read.
-template <int D>
+//
+// KS2 (row blocks of 32 that fill at most half of the eight wavefronts): a workgroup holds four row
+// blocks, wavefronts 0..3 take keys 0..31 of every tile and wavefronts 4..7 keys 32..63, and the two
+// halves meet in LDS at the end, so that a split leaves one set of sums either way.  A wavefront
+// without rows only copies.
+template <int D, bool KS2>
 __global__ __launch_bounds__(512) void k_attn_pipe(Prob pb, const uint16_t* __restrict__ q,
                                                    const uint16_t* __restrict__ k,
                                                    const uint16_t* __restrict__ v, int S, int kps,
                                                    int log2iw, ScorePtrs o) {
-  constexpr int NW = 8, KS = D / 16, CB = D / 32;
+  constexpr int NW = 8, KS = D / 16, CB = D / 32, RB = KS2 ? 4 : 8, NMB = KS2 ? 1 : 2;
   using RingK = TileRing<D, 0>;
   using RingV = TileRing<D, 1>;
   constexpr int NG = 2 * (RingK::NI / NW);          // copies per wavefront and tile
-  __shared__ __attribute__((aligned(1024))) uint16_t Ks[3][TN * D];
-  __shared__ __attribute__((aligned(1024))) uint16_t Vs[4][TN * D];
+  __shared__ __attribute__((aligned(1024))) uint16_t ring[7][TN * D];
+  uint16_t (*Ks)[TN * D] = ring, (*Vs)[TN * D] = ring + 3;
 
   const int s = blockIdx.x, g = blockIdx.z;
   const int l = threadIdx.x & 63, wv = wave_index(), rr = l & 31, hf = l >> 5;
-  const RowInfo ri = row_info(pb, g, blockIdx.y * NW + wv, l, log2iw);
+  const RowInfo ri = row_info(pb, g, blockIdx.y * RB + wv % RB, l, log2iw);
+  const int ko = KS2 ? 32 * (wv / RB) : 0;          // first key of this wavefront in a tile
+  const bool idle = (blockIdx.y * RB + wv % RB) << log2iw >= pb.W;   // no row here: this wavefront only copies
   const uint16_t* kg = k + (int64_t)g * pb.kv_sh;
   const uint16_t* vg = v + (int64_t)g * pb.kv_sh;
 
@@ -470,7 +498,7 @@ __global__ __launch_bounds__(512) void k_attn_pipe(Prob pb, const uint16_t* __re
   for (int cb = 0; cb < CB; ++cb)
 #pragma unroll
     for (int j = 0; j < 16; ++j) oacc[cb][j] = 0.f;
-  bf16x8 pv[2][2];
+  bf16x8 pv[NMB][2];
 
   // lane-constant part of the transposing LDS read of the value tile: row and column of the
   // 8 bytes this lane contributes to a 16 x 16 block
@@ -482,7 +510,7 @@ __global__ __launch_bounds__(512) void k_attn_pipe(Prob pb, const uint16_t* __re
   // trip per MFMA.
   auto accumulate = [&](const uint16_t* vt) {
     auto fetch = [&](int grp, bf16x8 (&av)[CB]) {       // grp = 2 mb + kg2
-      const int r0 = 16 * grp + vrow;
+      const int r0 = ko + 16 * grp + vrow;
 #pragma unroll
       for (int cb = 0; cb < CB; ++cb) {
         const int col = 32 * cb + vcol;
@@ -499,14 +527,23 @@ __global__ __launch_bounds__(512) void k_attn_pipe(Prob pb, const uint16_t* __re
     bf16x8 av[2][CB];
     fetch(0, av[0]);
 #pragma unroll
-    for (int grp = 0; grp < 4; ++grp) {
-      if (grp + 1 < 4) fetch(grp + 1, av[(grp + 1) & 1]);
+    for (int grp = 0; grp < 2 * NMB; ++grp) {
+      if (grp + 1 < 2 * NMB) fetch(grp + 1, av[(grp + 1) & 1]);
 #pragma unroll
       for (int cb = 0; cb < CB; ++cb) oacc[cb] = MFMA(av[grp & 1][cb], pv[grp >> 1][grp & 1], oacc[cb]);
     }
   };
 
-  if (ntiles > 0) {
+  if (ntiles > 0 && idle) {
+    wait_vm<NG>();
+    wg_barrier();
+    for (int t = 0; t < ntiles; ++t) {
+      issue_tile(t + 2);
+      wait_vm<NG>();
+      wg_barrier();
+    }
+    wait_vm<0>();
+  } else if (ntiles > 0) {
     wait_vm<NG>();           // own share of tile 0
     wg_barrier();            // B_-1
     const bool late = wv >= NW / 2;
@@ -518,24 +555,24 @@ __global__ __launch_bounds__(512) void k_attn_pipe(Prob pb, const uint16_t* __re
       // ---- matrix half: P.V of the previous tile, logits S^T[key, row] = K Q^T of this one ----
       if (t > 0) accumulate(Vs[(t - 1) & 3]);
       const uint16_t* kt = Ks[t % 3];
-      f32x16 sacc[2];
+      f32x16 sacc[NMB];
 #pragma unroll
-      for (int mb = 0; mb < 2; ++mb)
+      for (int mb = 0; mb < NMB; ++mb)
 #pragma unroll
         for (int j = 0; j < 16; ++j) sacc[mb][j] = 0.f;
       // operand reads in batches of eight ahead of their MFMAs (one LDS round trip per batch)
 #pragma unroll
       for (int k0 = 0; k0 < KS; k0 += 4) {
-        bf16x8 a[4][2];
+        bf16x8 a[4][NMB];
 #pragma unroll
         for (int ks = 0; ks < 4; ++ks)
 #pragma unroll
-          for (int mb = 0; mb < 2; ++mb)
-            a[ks][mb] = as_bf16x8(*(const uint4*)&kt[RingK::off(32 * mb + rr, 2 * (k0 + ks) + hf)]);
+          for (int mb = 0; mb < NMB; ++mb)
+            a[ks][mb] = as_bf16x8(*(const uint4*)&kt[RingK::off(ko + 32 * mb + rr, 2 * (k0 + ks) + hf)]);
 #pragma unroll
         for (int ks = 0; ks < 4; ++ks)
 #pragma unroll
-          for (int mb = 0; mb < 2; ++mb) sacc[mb] = MFMA(a[ks][mb], qf[k0 + ks], sacc[mb]);
+          for (int mb = 0; mb < NMB; ++mb) sacc[mb] = MFMA(a[ks][mb], qf[k0 + ks], sacc[mb]);
       }
       __builtin_amdgcn_s_setprio(2);
       if (late) {            // B_t of the late wavefronts: between the halves
@@ -546,23 +583,30 @@ __global__ __launch_bounds__(512) void k_attn_pipe(Prob pb, const uint16_t* __re
       const bool tile_mask = (kb + TN > kend) || (pb.causal && kb + TN - 1 > pb.P);
       if (tile_mask) {
 #pragma unroll
-        for (int mb = 0; mb < 2; ++mb)
+        for (int mb = 0; mb < NMB; ++mb)
 #pragma unroll
           for (int j = 0; j < 16; ++j) {
-            const int n = kb + 32 * mb + cidx(j, hf);
+            const int n = kb + ko + 32 * mb + cidx(j, hf);
             if (n >= kend || n > vis_last) sacc[mb][j] = -INFINITY;
           }
       }
       // (only one wavefront of the SIMD is in its vector half: independent chains, not one long one)
-      float tq[4];
+      auto tile_max = [&] {
+        float tq[4];
 #pragma unroll
-      for (int c = 0; c < 4; ++c) {
-        tq[c] = fmaxf(fmaxf(sacc[0][c], sacc[0][4 + c]), sacc[0][8 + c]);
-        tq[c] = fmaxf(fmaxf(tq[c], sacc[0][12 + c]), sacc[1][c]);
-        tq[c] = fmaxf(fmaxf(tq[c], sacc[1][4 + c]), sacc[1][8 + c]);
-        tq[c] = fmaxf(tq[c], sacc[1][12 + c]);
-      }
-      float tm = xhalf_max(fmaxf(fmaxf(tq[0], tq[1]), fmaxf(tq[2], tq[3])));
+        for (int c = 0; c < 4; ++c) {
+          tq[c] = fmaxf(fmaxf(sacc[0][c], sacc[0][4 + c]), sacc[0][8 + c]);
+          if constexpr (NMB > 1) {
+            tq[c] = fmaxf(fmaxf(tq[c], sacc[0][12 + c]), sacc[NMB - 1][c]);
+            tq[c] = fmaxf(fmaxf(tq[c], sacc[NMB - 1][4 + c]), sacc[NMB - 1][8 + c]);
+            tq[c] = fmaxf(tq[c], sacc[NMB - 1][12 + c]);
+          } else {
+            tq[c] = fmaxf(tq[c], sacc[0][12 + c]);
+          }
+        }
+        return xhalf_max(fmaxf(fmaxf(tq[0], tq[1]), fmaxf(tq[2], tq[3])));
+      };
+      const float tm = tile_max();
 
       // A key is kept out of the sums only if, on arrival, it is the largest so far AND holds
       // more than half of the mass seen so far (what a key that ends with A > 1/2 always does);
@@ -593,28 +637,20 @@ __global__ __launch_bounds__(512) void k_attn_pipe(Prob pb, const uint16_t* __re
         if (__ballot(dominant) != 0ull) {
           if (dominant) {
 #pragma unroll
-            for (int mb = 0; mb < 2; ++mb)
+            for (int mb = 0; mb < NMB; ++mb)
 #pragma unroll
               for (int j = 0; j < 16; ++j)
-                if (sacc[mb][j] == tm) cand = min(cand, kb + 32 * mb + cidx(j, hf));
+                if (sacc[mb][j] == tm) cand = min(cand, kb + ko + 32 * mb + cidx(j, hf));
           }
           cand = xhalf_min(cand);
           // the new kept-out key leaves the tile: its weight below is exp2(-inf) = 0
           const int cz = dominant ? cand : -1;
 #pragma unroll
-          for (int mb = 0; mb < 2; ++mb)
+          for (int mb = 0; mb < NMB; ++mb)
 #pragma unroll
             for (int j = 0; j < 16; ++j)
-              sacc[mb][j] = (kb + 32 * mb + cidx(j, hf)) == cz ? -INFINITY : sacc[mb][j];
-          float u[4];
-#pragma unroll
-          for (int c = 0; c < 4; ++c) {
-            u[c] = fmaxf(fmaxf(sacc[0][c], sacc[0][4 + c]), sacc[0][8 + c]);
-            u[c] = fmaxf(fmaxf(u[c], sacc[0][12 + c]), sacc[1][c]);
-            u[c] = fmaxf(fmaxf(u[c], sacc[1][4 + c]), sacc[1][8 + c]);
-            u[c] = fmaxf(u[c], sacc[1][12 + c]);
-          }
-          tinc = xhalf_max(fmaxf(fmaxf(u[0], u[1]), fmaxf(u[2], u[3])));
+              sacc[mb][j] = (kb + ko + 32 * mb + cidx(j, hf)) == cz ? -INFINITY : sacc[mb][j];
+          tinc = tile_max();
         }
         // Where nothing of the tile joins (one visible key, and it is kept out) the reference
         // stays; a row without any reference yet takes the kept-out key's logit (any finite
@@ -663,7 +699,7 @@ __global__ __launch_bounds__(512) void k_attn_pipe(Prob pb, const uint16_t* __re
       {
         float ls[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int mb = 0; mb < 2; ++mb)
+        for (int mb = 0; mb < NMB; ++mb)
 #pragma unroll
           for (int b8 = 0; b8 < 16; b8 += 8) {
             float pe[8];
@@ -686,7 +722,71 @@ __global__ __launch_bounds__(512) void k_attn_pipe(Prob pb, const uint16_t* __re
     accumulate(Vs[(ntiles - 1) & 3]);   // its slot is not a target of the copies still in flight
     wait_vm<0>();            // no copy may land in LDS after the workgroup has gone
   }
-  const float ltot = xhalf_sum(lsum);
+  float ltot = xhalf_sum(lsum);
+  if constexpr (KS2) {
+    // The two key halves of a row meet in the ring's memory (every copy has landed, every read is done
+    // after the first barrier).  As in the merge of the splits: a kept-out key stays out if it is the
+    // largest logit of both halves, otherwise it joins the sums, and the reference is the largest
+    // logit that is part of them.  Each half brings its own sums to the common reference, then
+    // wavefronts 4..7 hand theirs over.
+    constexpr int NX = CB * 16 + 1;
+    float* const hx = (float*)&ring[0][0] + (wv % RB) * (NX * 64) + l;                  // sums of the second half
+    float* const sc = (float*)&ring[0][0] + (RB * NX + (wv % RB) * 10 + wv / RB * 5) * 64 + l;   // scalars of the halves
+    const float* const sco = sc + (wv < RB ? 5 : -5) * 64;
+    uint2 vr[CB][4];                       // value row of the own kept-out key
+    const uint16_t* const vp = vg + (int64_t)max(nx, 0) * pb.kv_st + 4 * hf;
+#pragma unroll
+    for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+      for (int jq = 0; jq < 4; ++jq) vr[cb][jq] = *(const uint2*)(vp + 32 * cb + 8 * jq);
+    wg_barrier();
+    sc[0] = mall; sc[64] = mx; sc[128] = __int_as_float(nx); sc[192] = mref; sc[256] = ltot;
+    wg_barrier();
+    const float mall1 = sco[0], mx1 = sco[64], mref1 = sco[192], l1 = sco[256];
+    const int nx1 = __float_as_int(sco[128]);
+    const float M = fmaxf(mall, mall1);
+    // (the sums of a half without a key may hold anything)
+    const bool has0 = mall != -INFINITY && ltot > 0.f, has1 = mall1 != -INFINITY && l1 > 0.f;
+    const bool out0 = nx >= 0 && mx == M, out1 = nx1 >= 0 && mx1 == M;
+    const bool keep0 = out0 && !(out1 && nx1 < nx), keep1 = out1 && !keep0;
+    const bool join0 = nx >= 0 && !keep0, join1 = nx1 >= 0 && !keep1;
+    float R = -INFINITY;
+    if (has0) R = mref;
+    if (has1) R = fmaxf(R, mref1);
+    if (join0) R = fmaxf(R, mx);
+    if (join1) R = fmaxf(R, mx1);
+    if (R == -INFINITY) R = M;             // nothing is part of the sums
+    const float w0 = has0 ? __builtin_amdgcn_exp2f((mref - R) * c2) : 0.f;
+    const float wj = join0 ? __builtin_amdgcn_exp2f((mx - R) * c2) : 0.f;
+    ltot = (has0 ? w0 * ltot : 0.f) + wj;
+#pragma unroll
+    for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+      for (int j = 0; j < 16; ++j) {
+        const uint2 u = vr[cb][j >> 2];
+        const uint32_t e = j & 2 ? u.y : u.x;
+        const float ve = __uint_as_float(j & 1 ? e & 0xFFFF0000u : e << 16);
+        oacc[cb][j] = fmaf(wj, join0 ? ve : 0.f, has0 ? w0 * oacc[cb][j] : 0.f);
+      }
+    if (wv >= RB) {
+#pragma unroll
+      for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+        for (int j = 0; j < 16; ++j) hx[(16 * cb + j) * 64] = oacc[cb][j];
+      hx[16 * CB * 64] = ltot;
+    }
+    wg_barrier();
+    if (wv >= RB) return;
+#pragma unroll
+    for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+      for (int j = 0; j < 16; ++j) oacc[cb][j] += hx[(16 * cb + j) * 64];
+    ltot += hx[16 * CB * 64];
+    nx = keep0 ? nx : (keep1 ? nx1 : -1);
+    mx = M;
+    mall = M;
+    mref = R;
+  }
   if (ri.valid) {
     const int64_t po = (int64_t)ri.row * S + s;
     if (hf == 0) {
@@ -737,12 +837,13 @@ __global__ __launch_bounds__(512) void k_attn_pipe(Prob pb, const uint16_t* __re
 // t-1 (last read before E_2t) and the vv slot of tile t-2 (last read before E_2t-1); each
 // wavefront waits for its own share of tile t+1 before its mid-step barrier, which for both
 // halves precedes E_2t+2, the first barrier after which tile t+1 is read.
-template <int D, int GP>
+// KS2: as in the attention pass, four row blocks per workgroup and 32 keys of a tile per wavefront.
+template <int D, int GP, bool KS2>
 __global__ __launch_bounds__(512) void k_score_pipe(Prob pb, const uint16_t* __restrict__ q,
                                                     const uint16_t* __restrict__ k,
                                                     const uint16_t* __restrict__ v, ScorePtrs o, int ldv,
                                                     float* __restrict__ score, int tiles_per_wg, int nwb) {
-  constexpr int NW = 8, KS = D / 16, LG = ilog2(GP), IW = 32 / GP;
+  constexpr int NW = 8, KS = D / 16, LG = ilog2(GP), IW = 32 / GP, RB = KS2 ? 4 : 8, NMB = KS2 ? 1 : 2;
   constexpr int GV = GP < 4 ? 4 : GP;               // vv rows per ring slot (whole 1 KiB copies)
   constexpr int NVB = GV / 4;                       // 1 KiB copies per vv tile
   constexpr int ND = GP <= 4 ? GP : GP / 2;         // distinct heads among a lane's 16 registers
@@ -756,7 +857,8 @@ __global__ __launch_bounds__(512) void k_score_pipe(Prob pb, const uint16_t* __r
   const int g = blockIdx.z;
   const int l = threadIdx.x & 63, wv = threadIdx.x >> 6, rr = l & 31, hf = l >> 5;
   const int wvs = wave_index();                     // the same as a scalar, for the copies' addresses
-  const int wb = blockIdx.y * NW + wv;              // block of IW window positions
+  const int wb = blockIdx.y * RB + wvs % RB;        // block of IW window positions
+  const int ko = KS2 ? 32 * (wvs / RB) : 0;         // first key of this wavefront in a tile
   const uint16_t* kg = k + (int64_t)g * pb.kv_sh;
   const uint16_t* vg = v + (int64_t)g * pb.kv_sh;
 
@@ -833,7 +935,7 @@ __global__ __launch_bounds__(512) void k_score_pipe(Prob pb, const uint16_t* __r
       rowc[wv][3][rr] = valid ? o.rs_istar[row] * invG : 0.f;
     }
   }
-  const float* vvlane = &vvs[0][0][0] + rr;
+  const float* vvlane = &vvs[0][0][0] + ko + rr;
   // Output a of a lane (after the group mean) belongs to window position i0 + out_pos0(a):
   //   Gp <= 4: registers Gp a .. Gp a + Gp - 1, local row 8 (Gp a / 4) + 4 hf + (Gp a) % 4;
   //   Gp 8, 16: position 2 a + hf after the half swap;   Gp 32: position 0 in both halves.
@@ -846,13 +948,24 @@ __global__ __launch_bounds__(512) void k_score_pipe(Prob pb, const uint16_t* __r
   const bool rows_full = wb * IW + IW <= pb.W;       // wave-uniform: every position of the block exists
   char* sbase = (char*)(score + (int64_t)g * pb.W * pb.ld);
   const uint32_t ld4 = (uint32_t)pb.ld * 4u;
-  const uint32_t voff0 = (uint32_t)i0 * ld4 + (uint32_t)rr * 4u;   // 32-bit: checked on the host
+  const uint32_t voff0 = (uint32_t)i0 * ld4 + (uint32_t)(ko + rr) * 4u;   // 32-bit: checked on the host
 
   wait_vm<NG>();           // own share of tile t0
   wg_barrier();            // E_2t0
   const bool late = wv >= NW / 2;
   if (late) wg_barrier();
 
+  if (wb >= nwb) {         // no row here: this wavefront's share of the copies only
+    for (int t = t0; t < t1; ++t) {
+      issue_tile(t + 2);
+      wait_vm<NG>();
+      wg_barrier();
+      wg_barrier();
+    }
+    if (!late) wg_barrier();
+    wait_vm<0>();
+    return;
+  }
   for (int t = t0; t < t1; ++t) {
     // The wavefront in its vector half-step goes first at the issue port: it is the one with many
     // short instructions, and the half-step that bounds the tile time; the MFMAs of the other
@@ -863,31 +976,34 @@ __global__ __launch_bounds__(512) void k_score_pipe(Prob pb, const uint16_t* __r
     // ---- matrix half-step ----
     const uint16_t* kt = Ks[t % 3];
     const uint16_t* vt = Vs[t % 3];
-    f32x16 sacc[2], cacc[2];
+    f32x16 sacc[NMB], cacc[NMB];
 #pragma unroll
     for (int a = 0; a < 4; ++a) {
       const f32x4 s0 = *(const f32x4*)&rowc[wv][0][8 * a + 4 * hf];
       const f32x4 c0 = *(const f32x4*)&rowc[wv][1][8 * a + 4 * hf];
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        sacc[0][4 * a + e] = s0[e]; sacc[1][4 * a + e] = s0[e];
-        cacc[0][4 * a + e] = c0[e]; cacc[1][4 * a + e] = c0[e];
+#pragma unroll
+        for (int mb = 0; mb < NMB; ++mb) { sacc[mb][4 * a + e] = s0[e]; cacc[mb][4 * a + e] = c0[e]; }
       }
     }
     // consecutive MFMAs never touch the same accumulator
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) {
-      const int of0 = Ring::off(rr, 2 * ks + hf), of1 = Ring::off(32 + rr, 2 * ks + hf);
-      const bf16x8 bk0 = as_bf16x8(*(const uint4*)&kt[of0]);
-      const bf16x8 bv0 = as_bf16x8(*(const uint4*)&vt[of0]);
-      const bf16x8 bk1 = as_bf16x8(*(const uint4*)&kt[of1]);
-      const bf16x8 bv1 = as_bf16x8(*(const uint4*)&vt[of1]);
-      sacc[0] = MFMA(qf[ks], bk0, sacc[0]);
-      cacc[0] = MFMA(uhi[ks], bv0, cacc[0]);
-      sacc[1] = MFMA(qf[ks], bk1, sacc[1]);
-      cacc[1] = MFMA(uhi[ks], bv1, cacc[1]);
-      cacc[0] = MFMA(ulo[ks], bv0, cacc[0]);
-      cacc[1] = MFMA(ulo[ks], bv1, cacc[1]);
+      bf16x8 bk[NMB], bv[NMB];
+#pragma unroll
+      for (int mb = 0; mb < NMB; ++mb) {
+        const int of = Ring::off(ko + 32 * mb + rr, 2 * ks + hf);
+        bk[mb] = as_bf16x8(*(const uint4*)&kt[of]);
+        bv[mb] = as_bf16x8(*(const uint4*)&vt[of]);
+      }
+#pragma unroll
+      for (int mb = 0; mb < NMB; ++mb) {
+        sacc[mb] = MFMA(qf[ks], bk[mb], sacc[mb]);
+        cacc[mb] = MFMA(uhi[ks], bv[mb], cacc[mb]);
+      }
+#pragma unroll
+      for (int mb = 0; mb < NMB; ++mb) cacc[mb] = MFMA(ulo[ks], bv[mb], cacc[mb]);
     }
     wait_vm<NG>();         // own share of tile t+1 (only the copies of tile t+2 are younger)
     wg_barrier();
@@ -896,7 +1012,7 @@ __global__ __launch_bounds__(512) void k_score_pipe(Prob pb, const uint16_t* __r
     const int kb = t * TN;
     const float* vvt = vvlane + (t & 3) * (GV * TN);
 #pragma unroll
-    for (int mb = 0; mb < 2; ++mb) {
+    for (int mb = 0; mb < NMB; ++mb) {
       float vvh[ND];
 #pragma unroll
       for (int jd = 0; jd < ND; ++jd)
@@ -927,9 +1043,9 @@ __global__ __launch_bounds__(512) void k_score_pipe(Prob pb, const uint16_t* __r
       }
     }
     // key of this lane in the two 32-key blocks of the tile
-    int nk[2];
+    int nk[NMB];
 #pragma unroll
-    for (int mb = 0; mb < 2; ++mb) nk[mb] = kb + 32 * mb + rr;
+    for (int mb = 0; mb < NMB; ++mb) nk[mb] = kb + ko + 32 * mb + rr;
     const bool champ_here = nslane >= kb && nslane < kb + TN;
     if (__ballot(champ_here) != 0ull) {    // a champion of this wavefront is here
 #pragma unroll
@@ -938,16 +1054,16 @@ __global__ __launch_bounds__(512) void k_score_pipe(Prob pb, const uint16_t* __r
         const int ns = __float_as_int(rowc[wv][2][m_]);
         const float is = rowc[wv][3][m_];
 #pragma unroll
-        for (int mb = 0; mb < 2; ++mb)
+        for (int mb = 0; mb < NMB; ++mb)
           if (nk[mb] == ns) sacc[mb][j] = is;
       }
     }
     // ---- mean (or maximum) over the group (in-lane, one half swap from GP = 8 on), store ----
-    float outv[2][NOUT];
+    float outv[NMB][NOUT];
     auto group_reduce = [&](auto maxc) {
       auto comb = [](float x, float y) { return decltype(maxc)::value ? fmaxf(x, y) : x + y; };
 #pragma unroll
-      for (int mb = 0; mb < 2; ++mb) {
+      for (int mb = 0; mb < NMB; ++mb) {
         if constexpr (GP <= 4) {
 #pragma unroll
           for (int a = 0; a < NOUT; ++a) {
@@ -984,16 +1100,16 @@ __global__ __launch_bounds__(512) void k_score_pipe(Prob pb, const uint16_t* __r
     const uint32_t toff = (uint32_t)kb * 4u;
     if (rows_full && kb + TN <= pb.P) {             // wave-uniform: no lane needs a guard
 #pragma unroll
-      for (int mb = 0; mb < 2; ++mb)
+      for (int mb = 0; mb < NMB; ++mb)
 #pragma unroll
         for (int a = 0; a < NOUT; ++a)
           *(float*)(sbase + (voff0 + toff + (uint32_t)(128 * mb) + (uint32_t)out_pos0(a) * ld4)) = outv[mb][a];
     } else {
 #pragma unroll
-      for (int mb = 0; mb < 2; ++mb)
+      for (int mb = 0; mb < NMB; ++mb)
 #pragma unroll
         for (int a = 0; a < NOUT; ++a)
-          if (i0 + out_pos0(a) < pb.W && kb + 32 * mb + rr < pb.P)
+          if (i0 + out_pos0(a) < pb.W && kb + ko + 32 * mb + rr < pb.P)
             *(float*)(sbase + (voff0 + toff + (uint32_t)(128 * mb) + (uint32_t)out_pos0(a) * ld4)) = outv[mb][a];
     }
     wg_barrier();
@@ -1002,20 +1118,42 @@ __global__ __launch_bounds__(512) void k_score_pipe(Prob pb, const uint16_t* __r
   wait_vm<0>();            // no copy may land in LDS after the workgroup has gone
 }
 
-// geometry of the score pass: padded group size, row blocks, tiles per workgroup, key chunks
-struct ScoreGeom { int gp, gy, tpp, chunks; };
-ScoreGeom score_geom(const Prob& pb) {
-  ScoreGeom s;
-  s.gp = 1;
-  while (s.gp < pb.G) s.gp <<= 1;
-  const int iw = 32 / s.gp;
+// Row blocks of 32 (padded group x window positions) that a workgroup of 8 wavefronts holds: eight, or
+// four whose tiles are split between two wavefronts (KS2) where that leaves fewer wavefronts without a
+// row and a workgroup walks at least min_tiles tiles of n.
+struct RowGeom { int gp, log2iw, gy; bool ks2; };
+RowGeom row_geom(const Prob& pb, int n, int min_tiles) {
+  RowGeom r;
+  r.gp = 1;
+  while (r.gp < pb.G) r.gp <<= 1;
+  const int iw = 32 / r.gp;
+  r.log2iw = ilog2(iw);
   const int nwr = (pb.W + iw - 1) / iw;            // wavefronts needed to cover the window
-  s.gy = (nwr + 7) / 8;                            // row blocks of 8 wavefronts
+  const int gy4 = (nwr + 3) / 4, gy8 = (nwr + 7) / 8;
+  r.ks2 = gy4 < 2 * gy8 && (int64_t)((n + TN - 1) / TN) * gy4 * pb.Hkv >= (int64_t)min_tiles * n_cu();
+  r.gy = r.ks2 ? gy4 : gy8;
+  return r;
+}
+// Both halves of a tile pay the first tile's bookkeeping and meet at the end (4-5 us): 32/8 heads of 128,
+// window 32, four tiles a workgroup 21 us against 24 with KS2, 32 tiles 70 against 63 (80 when wavefronts
+// without a row still multiplied).
+constexpr int ATTN_KS2_TILES = 16;
+// Score pass, same shapes: two tiles a workgroup 8.4 us against 9.2, four 16.6 against 15.6, 32 tiles 79
+// against 69 (98 when wavefronts without a row still multiplied).
+constexpr int SCORE_KS2_TILES = 4;
+
+template <int D, int GP>
+void launch_score_pipe(const Prob& pb, const uint16_t* q, const uint16_t* k, const uint16_t* v, const ScorePtrs& w, int ldv,
+                       float* score, int nwb, hipStream_t st) {
+  const RowGeom rg = row_geom(pb, pb.P, SCORE_KS2_TILES);
+  // one resident workgroup per compute unit, each walking a run of tiles
   const int NT = (pb.P + TN - 1) / TN;
-  s.tpp = (int)(((int64_t)NT * s.gy * pb.Hkv + n_cu() - 1) / n_cu());
-  if (s.tpp < 1) s.tpp = 1;
-  s.chunks = (NT + s.tpp - 1) / s.tpp;
-  return s;
+  const int tpp = max(1, (int)(((int64_t)NT * rg.gy * pb.Hkv + n_cu() - 1) / n_cu()));
+  const dim3 gr((NT + tpp - 1) / tpp, rg.gy, pb.Hkv);
+  if (rg.ks2)
+    RK_LAUNCH(ST_SCORE, st, (k_score_pipe<D, GP, true>), gr, dim3(512), 0, st, pb, q, k, v, w, ldv, score, tpp, nwb);
+  else
+    RK_LAUNCH(ST_SCORE, st, (k_score_pipe<D, GP, false>), gr, dim3(512), 0, st, pb, q, k, v, w, ldv, score, tpp, nwb);
 }
 
 template <int D>
@@ -1025,13 +1163,9 @@ int run_mfma(const Prob& pb, const void* q, const void* k, const void* v, const 
   const uint16_t* kk = (const uint16_t*)k;
   const uint16_t* vp = (const uint16_t*)v;
   const ScorePtrs w = score_ptrs(ws, lay);
-  int gp = 1;
-  while (gp < pb.G) gp <<= 1;
-  const int iw = 32 / gp, log2iw = ilog2(iw);
-  const int nwr = (pb.W + iw - 1) / iw;            // wavefronts needed to cover the window
-  const int gy = (nwr + 7) / 8;                    // row blocks of 8 wavefronts
+  const RowGeom rg = row_geom(pb, pb.L, ATTN_KS2_TILES);
   // attention pass: about one workgroup per compute unit, whole tiles per split
-  int S = n_cu() / (pb.Hkv * gy);
+  int S = n_cu() / (pb.Hkv * rg.gy);
   const int max_s = (pb.L + TN - 1) / TN;
   if (S > max_s) S = max_s;
   if (S > lay.S_max) S = lay.S_max;
@@ -1048,30 +1182,31 @@ int run_mfma(const Prob& pb, const void* q, const void* k, const void* v, const 
               w.part_m, w.part_mx, w.part_n, w.part_ref, w.part_l);
     part_z = pb.ext_out;
   } else {
-    RK_LAUNCH(ST_ATTN, st, (k_attn_pipe<D>), dim3(S, gy, pb.Hkv), dim3(512), 0, st, pb, qq, kk, vp, S, kps,
-              log2iw, w);
+    const dim3 ga(S, rg.gy, pb.Hkv);
+    if (rg.ks2)
+      RK_LAUNCH(ST_ATTN, st, (k_attn_pipe<D, true>), ga, dim3(512), 0, st, pb, qq, kk, vp, S, kps, rg.log2iw, w);
+    else
+      RK_LAUNCH(ST_ATTN, st, (k_attn_pipe<D, false>), ga, dim3(512), 0, st, pb, qq, kk, vp, S, kps, rg.log2iw, w);
   }
   if (pb.ind != 0) gram = nullptr;                 // the attention-weight and value-norm indicators have no projection
-  launch_combine<bf16_t, D>(pb, (const bf16_t*)v, S, gram, w, part_z, (const bf16_t*)q, 1, ilog2(gp), lay.nwb, st);
+  launch_combine<bf16_t, D>(pb, (const bf16_t*)v, S, gram, w, part_z, (const bf16_t*)q, 1, ilog2(rg.gp), lay.nwb, st);
   if (gram) {
     constexpr int HPW = D == 128 ? 4 : 8;
+    const bool ks2 = (pb.G + HPW / 2 - 1) / (HPW / 2) * (HPW / 2) < (pb.G + HPW - 1) / HPW * HPW;   // as for the rows
+    const int hpw = ks2 ? HPW / 2 : HPW;
     const int NTv = (pb.P + TN - 1) / TN;
-    const int hg = (pb.G + HPW - 1) / HPW;
+    const int hg = (pb.G + hpw - 1) / hpw;
     int tpv = (int)(((int64_t)NTv * hg * pb.Hkv + n_cu() - 1) / n_cu());
     if (tpv < 1) tpv = 1;
-    RK_LAUNCH(ST_VV, st, (k_vv_pipe<D>), dim3((NTv + tpv - 1) / tpv, hg, pb.Hkv), dim3(512), 0, st, pb, vp,
-              gram, w.vv, lay.ldv, tpv);
+    const dim3 gv((NTv + tpv - 1) / tpv, hg, pb.Hkv);
+    if (ks2) RK_LAUNCH(ST_VV, st, (k_vv_pipe<D, true>), gv, dim3(512), 0, st, pb, vp, gram, w.vv, lay.ldv, tpv);
+    else RK_LAUNCH(ST_VV, st, (k_vv_pipe<D, false>), gv, dim3(512), 0, st, pb, vp, gram, w.vv, lay.ldv, tpv);
   } else {
     RK_LAUNCH(ST_VV, st, (k_vnorm2<D>), dim3((pb.P + 255) / 256, pb.Hkv), dim3(256), 0, st, pb, vp,
               w.vv, lay.ldv);
   }
-  // score pass: one resident workgroup per compute unit, each walking a run of tiles
-  const ScoreGeom sg = score_geom(pb);
-  const dim3 g2(sg.chunks, sg.gy, pb.Hkv);
-#define RK_SCORE(GPV)                                                                                            \
-  RK_LAUNCH(ST_SCORE, st, (k_score_pipe<D, GPV>), g2, dim3(512), 0, st, pb, qq, kk, vp, w, lay.ldv, score, sg.tpp, \
-            lay.nwb)
-  switch (sg.gp) {
+#define RK_SCORE(GPV) launch_score_pipe<D, GPV>(pb, qq, kk, vp, w, lay.ldv, score, lay.nwb, st)
+  switch (rg.gp) {
     case 1: RK_SCORE(1); break;
     case 2: RK_SCORE(2); break;
     case 4: RK_SCORE(4); break;

@@ -65,6 +65,20 @@ def test_merge_row_blocks(rk, oracle_mod, Hq, Hkv, d, W, dtype):  # noqa: F811
     _score_against_oracle_then_every_stage_exactly(rk, oracle_mod, w, "merge row blocks")
 
 
+@pytest.mark.parametrize("Hq,Hkv,d,L,W,structure", [
+    (32, 32, 64, 64 * 32 + 5, 16, "sinks"),       # score pass with its tiles split, five keys in the last one; one row block
+    (64, 32, 128, 64 * 32 + 40, 33, "plain"),     # three row blocks; prefix seven past a tile
+    (64, 64, 64, 64 * 64 + 33, 32, "sinks"),      # attention pass too; one key in the second half of the last tile
+    (128, 64, 128, 64 * 64 + 1, 9, "lowrank"),    # one key in the first half, none in the second, for the last splits
+    (256, 64, 128, 64 * 65, 8, "sinks"),          # whole tiles; two row blocks, the second one full
+    (154, 22, 64, 64 * 62 + 31, 33, "drift"),     # nine row blocks in three workgroups
+])
+def test_tiles_split_between_wavefronts(rk, oracle_mod, Hq, Hkv, d, L, W, structure):  # noqa: F811
+    """Few rows per KV head: two wavefronts share a tile's keys and their sums meet, kept-out keys of both halves among them."""
+    w = workloads.small_case(Hq=Hq, Hkv=Hkv, d=d, L=L, W=W, B=W + 200, dtype="bf16", D=2 * d, structure=structure, seed=61)
+    _score_against_oracle_then_every_stage_exactly(rk, oracle_mod, w, "tiles split between wavefronts")
+
+
 @pytest.mark.parametrize("P,W,Hkv,kind", [
     (2047, 5, 2, "ties"), (2049, 4, 1, "lognormal"), (4096, 3, 2, "constant"), (4097, 5, 2, "ties"),
     (8192, 2, 1, "lognormal"), (8193, 6, 1, "ties"), (16384, 3, 2, "ties"), (16387, 4, 2, "lognormal"),
