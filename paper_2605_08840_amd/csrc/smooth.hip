@@ -1,10 +1,11 @@
 // Spatial-temporal smoothing (Sec. 3.3): EMA over the window queries, drift statistic of
 // the per-query top-B positions, adaptive window size / shift, shifted box mean.
 //
-// The raw score [Hkv, W, P] is read from HBM once: a sorted sample of every (head, query) row
-// brackets the row's top-B threshold; one pass computes the EMA and, per row, counts and
-// sums the positions above the bracket and collects the few entries inside it; a finishing
-// kernel decides the threshold exactly among those candidates.
+// The raw score [Hkv, W, P] of a short prefix is read by one launch that holds a row per workgroup
+// (k_short_rows).  A longer one is read from HBM once: a sample of every (head, query) row brackets
+// the row's top-B threshold; one pass computes the EMA and, per row, counts and sums the positions
+// above the bracket and collects the few entries inside it; a finishing kernel decides the threshold
+// exactly among those candidates.
 #include <type_traits>
 
 #include "rowselect.hpp"
