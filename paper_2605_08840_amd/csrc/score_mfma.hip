@@ -108,6 +108,26 @@ __global__ __launch_bounds__(256) void k_vnorm2(Prob pb, const uint16_t* __restr
 constexpr int ilog2(int x) { return x <= 1 ? 0 : 1 + ilog2(x / 2); }
 
 // ------------------------------------------------------------------------------------------
+// Order of the workgroups of the three passes over (KV head, row block, key chunk).  Workgroups go
+// round the eight XCDs by their id.  With a multiple of eight KV heads of 128 the head runs fastest: a
+// head's workgroups then share one XCD, whose L2 holds the head's Gram matrices, queries and operands,
+// and what one pass leaves (split sums, vv, operands) is read by the next on the same XCD.  Score +
+// smoothing, 32/8 heads, 8k tokens, window 32: 72.3 -> 70.4 us; 64k and 128k unchanged.  Otherwise the
+// chunk runs fastest: with four heads (28/4 of 64, 20k tokens) the row blocks of a key chunk would land
+// on two XCDs and fetch its tiles twice, 82.2 -> 84.2 us, and choosing at run time costs the kernels for
+// heads of 64 1 %.
+template <int D>
+__host__ __device__ __forceinline__ bool heads_first(const Prob& pb) { return D == 128 && (pb.Hkv & 7) == 0; }
+template <int D>
+__device__ __forceinline__ int wg_head(const Prob& pb) { return heads_first<D>(pb) ? blockIdx.x : blockIdx.z; }
+template <int D>
+__device__ __forceinline__ int wg_chunk(const Prob& pb) { return heads_first<D>(pb) ? blockIdx.z : blockIdx.x; }
+template <int D>
+inline dim3 wg_grid(const Prob& pb, int chunks, int y) {
+  return heads_first<D>(pb) ? dim3(pb.Hkv, y, chunks) : dim3(chunks, y, pb.Hkv);
+}
+
+// ------------------------------------------------------------------------------------------
 // Asynchronous tile ring shared by the pipelined kernels.
 //
 // A 64-key tile of a [tokens, D] bf16 matrix is copied global -> LDS by global_load_lds_dwordx4:
@@ -231,7 +251,7 @@ __device__ __forceinline__ void wait_vm() {
 // KS2 (few heads per KV head): wavefronts 0..3 take keys 0..31 of a tile and wavefronts 4..7 keys
 // 32..63 of the same heads, so that a workgroup holds half as many heads.  A wavefront without a head
 // only copies.
-// grid (key chunks, ceil(G/HPW), Hkv), 512 threads; HPW = 4 heads per workgroup (8 for D = 64), half
+// wg_grid(key chunks, ceil(G/HPW)), 512 threads; HPW = 4 heads per workgroup (8 for D = 64), half
 // of that with KS2.
 template <int D, bool KS2>
 __global__ __launch_bounds__(512) void k_vv_pipe(Prob pb, const uint16_t* __restrict__ v,
@@ -243,7 +263,7 @@ __global__ __launch_bounds__(512) void k_vv_pipe(Prob pb, const uint16_t* __rest
   constexpr int NG = Ring::NI / NW;                 // copies per wavefront and tile
   __shared__ __attribute__((aligned(1024))) uint16_t Vs[4][TN * D];
   __shared__ float part[2][HPW][WPH][TN];
-  const int g = blockIdx.z;
+  const int g = wg_head<D>(pb);
   const int l = threadIdx.x & 63, wv = threadIdx.x >> 6, rr = l & 31, hf = l >> 5;
   const int wvs = wave_index();                     // the same as a scalar, for the copies' addresses
   const int wr = KS2 ? wvs % (NW / 2) : wvs, ko = KS2 ? 32 * (wvs / (NW / 2)) : 0;   // first key of this wavefront in a tile
@@ -254,7 +274,7 @@ __global__ __launch_bounds__(512) void k_vv_pipe(Prob pb, const uint16_t* __rest
   const uint32_t pitch = (uint32_t)pb.kv_st * 2u;
 
   const int NT = (pb.P + TN - 1) / TN;
-  const int t0 = blockIdx.x * tiles_per_wg;
+  const int t0 = wg_chunk<D>(pb) * tiles_per_wg;
   const int t1 = min(NT, t0 + tiles_per_wg);
   if (t0 >= t1) return;
   uint32_t voff[NG];
@@ -420,7 +440,7 @@ __global__ __launch_bounds__(512) void k_vv_pipe(Prob pb, const uint16_t* __rest
 // ------------------------------------------------------------------------------------------
 // Attention pass, pipelined: per key split, champion-excluded online softmax statistics and
 // A.V sums (outputs: the per-split statistics described in score_common.hpp).
-// grid (S, row blocks, Hkv), 512 threads.
+// wg_grid(S, row blocks), 512 threads.
 //
 // K tiles travel through a 3-deep, V tiles through a 4-deep asynchronous LDS ring.  A step t has a
 // matrix half (P.V of tile t-1, then Q.K of tile t: 48 MFMAs) and a vector half (softmax
@@ -450,7 +470,7 @@ __global__ __launch_bounds__(512) void k_attn_pipe(Prob pb, const uint16_t* __re
   __shared__ __attribute__((aligned(1024))) uint16_t ring[7][TN * D];
   uint16_t (*Ks)[TN * D] = ring, (*Vs)[TN * D] = ring + 3;
 
-  const int s = blockIdx.x, g = blockIdx.z;
+  const int s = wg_chunk<D>(pb), g = wg_head<D>(pb);
   const int l = threadIdx.x & 63, wv = wave_index(), rr = l & 31, hf = l >> 5;
   const RowInfo ri = row_info(pb, g, blockIdx.y * RB + wv % RB, l, log2iw);
   const int ko = KS2 ? 32 * (wv / RB) : 0;          // first key of this wavefront in a tile
@@ -809,7 +829,7 @@ __global__ __launch_bounds__(512) void k_attn_pipe(Prob pb, const uint16_t* __re
 
 // ------------------------------------------------------------------------------------------
 // Score pass: logits again, cross term u.v_n, closed form, mean over the group.
-// grid (key chunks, row blocks, Hkv), 512 threads = 8 wavefronts of 32 query rows each.
+// wg_grid(key chunks, row blocks), 512 threads = 8 wavefronts of 32 query rows each.
 //
 // Per element (query row r of head h, key n), with M, l, zz the row's softmax maximum,
 // denominator and z M_h z^T from the attention pass:
@@ -854,7 +874,7 @@ __global__ __launch_bounds__(512) void k_score_pipe(Prob pb, const uint16_t* __r
   __shared__ __attribute__((aligned(1024))) float vvs[4][GV][TN];
   __shared__ __attribute__((aligned(16))) float rowc[NW][4][32];   // per local row: accumulator start values, champion key and score
 
-  const int g = blockIdx.z;
+  const int g = wg_head<D>(pb);
   const int l = threadIdx.x & 63, wv = threadIdx.x >> 6, rr = l & 31, hf = l >> 5;
   const int wvs = wave_index();                     // the same as a scalar, for the copies' addresses
   const int wb = blockIdx.y * RB + wvs % RB;        // block of IW window positions
@@ -863,7 +883,7 @@ __global__ __launch_bounds__(512) void k_score_pipe(Prob pb, const uint16_t* __r
   const uint16_t* vg = v + (int64_t)g * pb.kv_sh;
 
   const int NT = (pb.P + TN - 1) / TN;
-  const int t0 = blockIdx.x * tiles_per_wg;
+  const int t0 = wg_chunk<D>(pb) * tiles_per_wg;
   const int t1 = min(NT, t0 + tiles_per_wg);
   if (t0 >= t1) return;
 
@@ -1149,7 +1169,7 @@ void launch_score_pipe(const Prob& pb, const uint16_t* q, const uint16_t* k, con
   // one resident workgroup per compute unit, each walking a run of tiles
   const int NT = (pb.P + TN - 1) / TN;
   const int tpp = max(1, (int)(((int64_t)NT * rg.gy * pb.Hkv + n_cu() - 1) / n_cu()));
-  const dim3 gr((NT + tpp - 1) / tpp, rg.gy, pb.Hkv);
+  const dim3 gr = wg_grid<D>(pb, (NT + tpp - 1) / tpp, rg.gy);
   if (rg.ks2)
     RK_LAUNCH(ST_SCORE, st, (k_score_pipe<D, GP, true>), gr, dim3(512), 0, st, pb, q, k, v, w, ldv, score, tpp, nwb);
   else
@@ -1182,7 +1202,7 @@ int run_mfma(const Prob& pb, const void* q, const void* k, const void* v, const 
               w.part_m, w.part_mx, w.part_n, w.part_ref, w.part_l);
     part_z = pb.ext_out;
   } else {
-    const dim3 ga(S, rg.gy, pb.Hkv);
+    const dim3 ga = wg_grid<D>(pb, S, rg.gy);
     if (rg.ks2)
       RK_LAUNCH(ST_ATTN, st, (k_attn_pipe<D, true>), ga, dim3(512), 0, st, pb, qq, kk, vp, S, kps, rg.log2iw, w);
     else
@@ -1198,7 +1218,7 @@ int run_mfma(const Prob& pb, const void* q, const void* k, const void* v, const 
     const int hg = (pb.G + hpw - 1) / hpw;
     int tpv = (int)(((int64_t)NTv * hg * pb.Hkv + n_cu() - 1) / n_cu());
     if (tpv < 1) tpv = 1;
-    const dim3 gv((NTv + tpv - 1) / tpv, hg, pb.Hkv);
+    const dim3 gv = wg_grid<D>(pb, (NTv + tpv - 1) / tpv, hg);
     if (ks2) RK_LAUNCH(ST_VV, st, (k_vv_pipe<D, true>), gv, dim3(512), 0, st, pb, vp, gram, w.vv, lay.ldv, tpv);
     else RK_LAUNCH(ST_VV, st, (k_vv_pipe<D, false>), gv, dim3(512), 0, st, pb, vp, gram, w.vv, lay.ldv, tpv);
   } else {
