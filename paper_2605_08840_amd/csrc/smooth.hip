@@ -126,17 +126,19 @@ __global__ __launch_bounds__(256) void k_ema_scan(Prob pb, const float* __restri
   for (int k = 0; k < EW_NE; ++k) e[k] = 0.f;
   uint32_t acc_cnt = 0, acc_sum = 0;             // lane (row % 64): totals of that row above its bracket
 
-  // `live` is false for the rows that pad a block to a multiple of EPF: weight 0, no bracket
+  // `live` is false for the rows that pad a block to a multiple of EPF: nothing of them is used (a
+  // weight of 0 would turn an infinite score into a NaN)
   auto process = [&](int i, bool live, float (&x)[EW_NE]) {
+    if (!live) return;                           // (wave-uniform)
     if (tail) {
 #pragma unroll
       for (int k = 0; k < EW_NE; ++k)
         if (scan_position(wbase, l, k) >= pb.P) x[k] = -INFINITY;   // counts for nothing, never stored
     }
-    const float w = live ? temporal_weight(pb, i) : 0.f;
+    const float w = temporal_weight(pb, i);
 #pragma unroll
     for (int k = 0; k < EW_NE; ++k) e[k] = fmaf(w, x[k], e[k]);
-    if (!scan || !live) return;
+    if (!scan) return;
     const float2 th = thr[g * pb.W + i];         // the threshold lies in (th.x, th.y]
     float tlo = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, th.x)));
     float thi = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, th.y)));
@@ -179,7 +181,7 @@ __global__ __launch_bounds__(256) void k_ema_scan(Prob pb, const float* __restri
 #pragma unroll
       for (int u = 0; u < EPF; ++u) {
         // every group issues its EPF row loads whatever the row count (past the end: the last row
-        // again, processed with weight 0): the number of loads in flight is then known at
+        // again, not processed): the number of loads in flight is then known at
         // compile time and a row only waits for its own
         const int i = i0 + u;
         process(min(i, r1 - 1), i < r1, xs[u]);
@@ -380,7 +382,8 @@ __global__ __launch_bounds__(NT, NT == 1024 && NPT == 16 ? 8 : 4) void k_short_r
 #pragma unroll
       for (int u = 0; u < 16; ++u) x[u] = s[(int64_t)(b0 + min(i + u, nb - 1)) * pb.ld];
 #pragma unroll
-      for (int u = 0; u < 16; ++u) e = fmaf(i + u < nb ? wts[min(i + u, nb - 1)] : 0.f, x[u], e);
+      for (int u = 0; u < 16; ++u)       // (past the end neither weight nor score: 0 times infinity is a NaN)
+        e = fmaf(i + u < nb ? wts[min(i + u, nb - 1)] : 0.f, i + u < nb ? x[u] : 0.f, e);
     }
   }
   if (n < pb.P) ema[(int64_t)g * pb.ld + n] = e;

@@ -110,3 +110,31 @@ def test_row_statistics_and_selection_at_launch_rules(rk, oracle_mod, P, W, Hkv,
         assert tuple(info[g]) == (sm["w_s"], sm["gamma"])
         np.testing.assert_allclose(fin[g, :P], sm["final"], rtol=2e-5, atol=1e-30)
         np.testing.assert_array_equal(idx[g], oracle_mod.select(fin[g, :P].astype(np.float64), W, B))
+
+
+@pytest.mark.parametrize("W", [1, 5, 8, 16, 20, 33])
+@pytest.mark.parametrize("P", [700, 17000, 40003])     # one launch for the statistics; the streaming launches, also unaligned
+def test_infinite_scores_stay_infinite(rk, W, P):  # noqa: F811
+    """A score of +-inf (a position that a caller forces in or out) in the newest, the oldest or a middle query
+    makes the position's temporal and spatial sums +-inf and touches no other position: the rows
+    that pad the window for the kernels add nothing.  Selection keeps the positions at +inf and drops those at -inf."""
+    Hkv, B = 7, W + 300
+    rng = np.random.default_rng(W * 7 + P)
+    s = rng.lognormal(size=(Hkv, W, P)).astype(np.float32)
+    hi, lo = [11, P // 2, P - 2], [3, P // 3, P - 30]
+    s[:, W - 1, hi[0]] = s[:, 0, hi[1]] = s[:, W // 2, hi[2]] = np.inf
+    s[:, W - 1, lo[0]] = s[:, 0, lo[1]] = s[:, W // 2, lo[2]] = -np.inf
+    p = rk.make_params(n_q_heads=Hkv, n_kv_heads=Hkv, head_dim=64, seq_len=P + W, window=W, budget=B, dtype="bf16",
+                       ema_alpha=0.25, base_window=1, adaptive=False)
+    buf = rk.alloc_layer_buffers(p, torch.bfloat16, "cuda")
+    buf.score.copy_(torch.from_numpy(s))
+    rk.restkv_smooth(p, buf.score, buf.ema, buf.final, buf.aws_info, buf.aws_d, buf.workspace)
+    rk.restkv_select(p, buf.final, buf.idx, buf.workspace)
+    torch.cuda.synchronize()
+    e = s[:, 0].astype(np.float64)
+    for i in range(1, W):
+        e = 0.25 * s[:, i] + 0.75 * e
+    for got in (buf.ema.cpu().numpy(), buf.final.cpu().numpy()):
+        np.testing.assert_allclose(got, e, rtol=2e-5)          # (also: infinities at the same places, no NaN)
+    idx = buf.idx.cpu().numpy()
+    assert all(set(hi) <= set(r.tolist()) and not set(lo) & set(r.tolist()) for r in idx)
