@@ -141,10 +141,12 @@ __device__ __forceinline__ int head_budget(const Prob& pb, int g) {
   return min(max(pb.hb[g], pb.W + 1), pb.B);
 }
 
-// Order-preserving map float -> uint32 (larger float <=> larger key; -0 < +0).
+// Order-preserving map float -> uint32 (larger float <=> larger key; -0 < +0; NaNs at the ends).  Never
+// 0, which stands for "no entry" in the searches: the one value that would be (a NaN with every bit
+// set, as memory filled with 0xFF holds) shares the key of the NaN next to it.
 __device__ __forceinline__ uint32_t float_key(float f) {
   const uint32_t b = __float_as_uint(f);
-  return b ^ ((b >> 31) ? 0xFFFFFFFFu : 0x80000000u);
+  return max(b ^ ((b >> 31) ? 0xFFFFFFFFu : 0x80000000u), 1u);
 }
 
 }  // namespace restkv

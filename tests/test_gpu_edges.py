@@ -138,3 +138,47 @@ def test_infinite_scores_stay_infinite(rk, W, P):  # noqa: F811
         np.testing.assert_allclose(got, e, rtol=2e-5)          # (also: infinities at the same places, no NaN)
     idx = buf.idx.cpu().numpy()
     assert all(set(hi) <= set(r.tolist()) and not set(lo) & set(r.tolist()) for r in idx)
+
+
+def _keys(x):
+    """The order the searches work in: larger float <=> larger key, -0 < +0, NaNs at the ends."""
+    b = np.ascontiguousarray(x, dtype=np.float32).view(np.uint32)
+    return np.maximum(np.where(b >> 31, ~b, b ^ np.uint32(0x80000000)), 1).astype(np.int64)
+
+
+def _top_by_key(row, k):
+    """Positions of the k largest entries (equal keys: lower position first), ascending."""
+    return np.sort(np.argsort(-_keys(row), kind="stable")[:k])
+
+
+def _statistics_and_selection_by_key(rk, s, fin, B):
+    """Top-B position sums of the raw score s [Hkv, W, P] and selection on fin [Hkv, P], against the order of the keys."""
+    Hkv, W, P = s.shape
+    p = rk.make_params(n_q_heads=Hkv, n_kv_heads=Hkv, head_dim=64, seq_len=P + W, window=W, budget=B, dtype="bf16",
+                       ema_alpha=0.25, base_window=1, beta=1e6)
+    buf = rk.alloc_layer_buffers(p, torch.bfloat16, "cuda")
+    buf.score.copy_(torch.from_numpy(s.view(np.int32)).cuda().view(torch.float32))
+    rk.restkv_smooth(p, buf.score, buf.ema, buf.final, buf.aws_info, buf.aws_d, buf.workspace)
+    buf.final.copy_(torch.from_numpy(fin.view(np.int32)).cuda().view(torch.float32))
+    rk.restkv_select(p, buf.final, buf.idx, buf.workspace)
+    torch.cuda.synchronize()
+    dd, idx = buf.aws_d.cpu().numpy(), buf.idx.cpu().numpy()
+    bt = min(B, P)
+    for g in range(Hkv):
+        sums = [int(_top_by_key(s[g, i], bt).sum()) for i in range(W)]
+        assert dd[g, 0] == sum(sums[:W // 2]) / (float(bt) * (W // 2))
+        assert dd[g, 1] == sum(sums[W // 2:]) / (float(bt) * (W - W // 2))
+        np.testing.assert_array_equal(idx[g], np.r_[_top_by_key(fin[g], B - W), np.arange(P, P + W)])
+
+
+@pytest.mark.parametrize("P", [90, 2048, 5000, 16385, 32768, 40001])
+@pytest.mark.parametrize("finite", [0, 9, 70])
+def test_rows_of_unset_memory(rk, P, finite):  # noqa: F811
+    """Rows of all-ones words (memory filled with 0xFF: NaNs) with fewer ordinary values than are to be chosen:
+    the ordinary values are taken, then the lowest positions."""
+    Hkv, W, B = 2, 2, 82
+    rng = np.random.default_rng(P + finite)
+    s = np.full((Hkv, W, P), 0xFFFFFFFF, dtype=np.uint32).view(np.float32)
+    for r in s.reshape(-1, P):
+        r[rng.choice(P, finite, replace=False)] = rng.normal(size=finite).astype(np.float32)
+    _statistics_and_selection_by_key(rk, s, np.ascontiguousarray(s[:, 0]), B)
