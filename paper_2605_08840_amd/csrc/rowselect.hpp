@@ -164,8 +164,8 @@ __device__ __forceinline__ int cut_shift(uint32_t lo, uint32_t hi) {
 }
 
 // Histogram of val(j), j < NPT, over [lo, hi] (values outside are left out; 0 never counts: lo >= 1),
-// then the bins that hold the ranks k[r] (1-based, from the top; every rank must exist): res[r].
-// Four barriers, the first of which also separates this from what used sm before.
+// then the bins that hold the ranks k[r] (1-based, from the top): res[r], with 0 entries in the bin if
+// there is no such rank.  Four barriers, the first of which also separates this from what used sm before.
 template <int NT, int NPT, int NR, typename V>
 __device__ __forceinline__ void block_bins(V val, uint32_t lo, uint32_t hi, int shift, const uint32_t (&k)[NR],
                                            CutSmem& sm) {
@@ -173,7 +173,11 @@ __device__ __forceinline__ void block_bins(V val, uint32_t lo, uint32_t hi, int 
   __syncthreads();
 #pragma unroll
   for (int i = 0; i < R; ++i) sm.hist[threadIdx.x + i * NT] = 0u;
-  if (threadIdx.x == 0) sm.n = 0u;
+  if (threadIdx.x == 0) {
+    sm.n = 0u;
+#pragma unroll
+    for (int r = 0; r < NR; ++r) sm.res[r][2] = 0u;
+  }
   __syncthreads();
 #pragma unroll
   for (int j = 0; j < NPT; ++j) {
@@ -210,10 +214,12 @@ __device__ __forceinline__ void block_bins(V val, uint32_t lo, uint32_t hi, int 
 // Cut of the k largest entries: an entry is one of them iff (key, ~position) >= (tau, ~cut), i.e.
 // equal keys are taken lowest position first.  key: NPT per thread, 0 where a slot is empty; pos(j):
 // position of slot j (below 2^31); every key lies in [lo, hi] (lo >= 1) and there are at least k >= 1
-// of them.  All NT threads call, all receive the result.  pos gets the thread index as an argument
+// of them.  False (nothing found) where there are fewer: the caller then searches the row in another
+// way, or knows that it cannot be (a whole row in [its smallest key, its largest]).  The search ends for any
+// input.  All NT threads call, all receive the result.  pos gets the thread index as an argument
 // that the compiler cannot see through: it would keep NPT positions in registers otherwise.
 template <int NT, int NPT, typename P>
-__device__ __forceinline__ void block_cut(const uint32_t (&key)[NPT], P pos, uint32_t k, uint32_t lo, uint32_t hi,
+__device__ __forceinline__ bool block_cut(const uint32_t (&key)[NPT], P pos, uint32_t k, uint32_t lo, uint32_t hi,
                                           CutSmem& sm, uint32_t& tau, uint32_t& cut) {
   bool tie = false;                      // equal keys straddle the cut: the search goes on over inverted positions
   uint32_t tkey = 0;
@@ -226,6 +232,7 @@ __device__ __forceinline__ void block_cut(const uint32_t (&key)[NPT], P pos, uin
     if (tie) block_bins<NT, NPT, 1>(val, lo, hi, shift, kk, sm);
     else block_bins<NT, NPT, 1>([&](int j) { return key[j]; }, lo, hi, shift, kk, sm);
     const uint32_t cnt = sm.res[0][2];
+    if (cnt == 0u) return false;
     k -= sm.res[0][1];
     const uint32_t off = sm.res[0][0] << shift;
     hi = lo + off + min(hi - lo - off, (1u << shift) - 1u);      // (no sum that could wrap)
@@ -233,7 +240,7 @@ __device__ __forceinline__ void block_cut(const uint32_t (&key)[NPT], P pos, uin
     if (cnt == k) {                      // the whole bin is taken
       tau = tie ? tkey : lo;
       cut = tie ? ~lo : 0xFFFFFFFFu;
-      return;
+      return true;
     }
     if (cnt <= (uint32_t)CUT_MEMB) {
 #pragma unroll
@@ -258,7 +265,7 @@ __device__ __forceinline__ void block_cut(const uint32_t (&key)[NPT], P pos, uin
       const int sel = __builtin_ctzll(__ballot(l < cnt && rank == k - 1u));
       tau = (uint32_t)__builtin_amdgcn_readlane((int)mk, sel);
       cut = (uint32_t)__builtin_amdgcn_readlane((int)mp, sel);
-      return;
+      return true;
     }
     if (shift == 0) {                    // more equal keys than members are ranked
       tie = true;
@@ -374,6 +381,17 @@ __device__ __forceinline__ void block_bracket(const float* __restrict__ row, int
   }
   khi = up ? hi : 0xFFFFFFFFu;
   klo = dn ? lo - 1u : 0u;
+}
+
+// The bracket (klo, khi] as floats {x, y} for comparisons: "above" is f > y, "inside" is x < f, not
+// above.  Comparisons and keys order the same, but for -0 = +0 where the keys of the zeros differ: an
+// end between the two moves outwards past both, so that what is counted by comparison and what is
+// ranked by key are the same entries.  (A NaN is neither above nor inside.)
+__device__ __forceinline__ float2 bracket_ends(uint32_t klo, uint32_t khi) {
+  constexpr uint32_t NEG0 = 0x7FFFFFFFu;       // key of -0
+  klo = klo == NEG0 ? NEG0 - 1u : klo;
+  khi = khi == NEG0 ? NEG0 + 1u : khi;
+  return make_float2(klo ? key_float(klo) : -INFINITY, khi != 0xFFFFFFFFu ? key_float(khi) : INFINITY);
 }
 
 // Calls f(word index, word) for every 32-bit word of a row of ndw mask words (ndw a multiple of

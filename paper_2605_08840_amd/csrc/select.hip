@@ -85,7 +85,7 @@ __global__ __launch_bounds__(NT, NT == 1024 ? 4 : 1) void k_sel_row(Prob pb, con
   for (int x = tid; x < NWORD; x += NT) bits[x] = 0u;
   block_range<NT>(key, cs, lo, hi);
   auto pos = [](int j, int t) { return row_pos<NT, NPT, VEC>(j, t); };
-  block_cut<NT>(key, pos, (uint32_t)k, lo, hi, cs, tau, cut);
+  block_cut<NT>(key, pos, (uint32_t)k, lo, hi, cs, tau, cut);      // (the row has its k entries)
 #pragma unroll
   for (int j0 = 0; j0 < NPT; j0 += 4) {
     uint32_t m[4];
@@ -147,7 +147,7 @@ __global__ __launch_bounds__(256) void k_sel_scan(Prob pb, const float* __restri
   if (k < pb.P) {                                       // block-uniform
     uint32_t klo, khi;
     block_bracket<256, SEL_NS / 256, 1>(row, pb.P, k, cs, klo, khi);   // smoothed rows: single, spread samples
-    th = make_float2(klo ? key_float(klo) : -INFINITY, khi != 0xFFFFFFFFu ? key_float(khi) : INFINITY);
+    th = bracket_ends(klo, khi);
   }
   if (ch == 0 && tid == 0) w.thr[g] = th;
   float tlo = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, th.x)));
@@ -214,7 +214,8 @@ __global__ __launch_bounds__(512) void k_sel_emit(Prob pb, const float* __restri
 #pragma unroll
     for (int j = 0; j < NW; ++j) { n_above += red[0][j]; n_before += red[1][j]; }
     uint32_t sel_before = 0;                     // this thread's share of the selected candidates before `first`
-    if (n_above < (uint32_t)k && (uint32_t)k <= n_above + nc && nc <= (uint32_t)SCAP) {      // workgroup-uniform
+    bool found = n_above < (uint32_t)k && (uint32_t)k <= n_above + nc && nc <= (uint32_t)SCAP;      // workgroup-uniform
+    if (found) {
       uint32_t slot = incl - c_mine;
       for_each_mask_word<NT>(mrow, ndw, [&](int x, uint32_t m) {
         while (m) {
@@ -236,11 +237,13 @@ __global__ __launch_bounds__(512) void k_sel_emit(Prob pb, const float* __restri
 #pragma unroll
       for (int j = 0; j < FPT; ++j) ck[j] = (uint32_t)(tid + j * NT) < nc ? float_key(fv[j]) : 0u;
       // every candidate lies inside the bracket (th.x, th.y]
-      block_cut<NT>(ck, [&](int j, int) { return iv[j]; }, (uint32_t)k - n_above, float_key(th.x) + 1u, float_key(th.y), cs, tau, cut);
+      found = block_cut<NT>(ck, [&](int j, int) { return iv[j]; }, (uint32_t)k - n_above, float_key(th.x) + 1u, float_key(th.y), cs, tau, cut);
 #pragma unroll
       for (int j = 0; j < FPT; ++j)
         sel_before += ck[j] && (uint32_t)iv[j] < first && in_cut(ck[j], (uint32_t)iv[j], tau, cut) ? 1u : 0u;
-    } else {
+    }
+    if (!found) {
+      sel_before = 0;
       // exact search of the whole row: threshold, then an ordered visit that finds the last tie that
       // is taken and counts the selected entries before this workgroup's
       uint32_t n_gt, k_eq;

@@ -36,8 +36,7 @@ __global__ __launch_bounds__(512) void k_sample_bracket(Prob pb, const float* __
   }
   uint32_t klo, khi;
   block_bracket<512, ROW_NS / 512, 16>(row, pb.P, k, cs, klo, khi);
-  if (threadIdx.x == 0)
-    thr[r] = make_float2(klo ? key_float(klo) : -INFINITY, khi != 0xFFFFFFFFu ? key_float(khi) : INFINITY);
+  if (threadIdx.x == 0) thr[r] = bracket_ends(klo, khi);
 }
 
 // Fused single read of the raw score: EMA over the window queries and, per (head, query) row,
@@ -268,9 +267,10 @@ __global__ __launch_bounds__(512) void k_row_finish(Prob pb, const float* __rest
   if (threadIdx.x == NT - 1) wsum[0] = incl;            // (every thread has read the wave sums)
   __syncthreads();
   const uint32_t nc = wsum[0];
+  const float* row = score + (int64_t)r * pb.ld;
   const bool ok = ch < (uint32_t)k && (uint32_t)k <= ch + nc && nc <= (uint32_t)CAND_CAP;
   if (!ok) {                                         // block-uniform
-    const unsigned long long tot = row_exact_sum(score + (int64_t)r * pb.ld, pb.P, k, sm);
+    const unsigned long long tot = row_exact_sum(row, pb.P, k, sm);
     if (threadIdx.x == 0) rowsum[r] = tot;
     return;
   }
@@ -285,10 +285,10 @@ __global__ __launch_bounds__(512) void k_row_finish(Prob pb, const float* __rest
   });
   __syncthreads();
   const uint32_t need = (uint32_t)k - ch;
-  const float* row = score + (int64_t)r * pb.ld;
   // All loads unconditional (an empty slot re-reads the first candidate and is then masked):
   // independent loads in flight together instead of one round trip per slot.  Only as many
   // slots per thread as the row's candidates need (block-uniform), so a short list is counted quickly.
+  unsigned long long acc = 0;
   auto run = [&](auto nsc) {
     constexpr int NS = decltype(nsc)::value;
     uint32_t ck[NS];
@@ -304,16 +304,20 @@ __global__ __launch_bounds__(512) void k_row_finish(Prob pb, const float* __rest
     for (int j = 0; j < NS; ++j) ck[j] = (uint32_t)(threadIdx.x + j * NT) < nc ? float_key(fv[j]) : 0u;
     uint32_t tau, cut;
     // every candidate lies inside the bracket (th.x, th.y]
-    block_cut<NT>(ck, [&](int j, int) { return iv[j]; }, need, float_key(th.x) + 1u, float_key(th.y), cs, tau, cut);
-    unsigned long long acc = 0;
+    if (!block_cut<NT>(ck, [&](int j, int) { return iv[j]; }, need, float_key(th.x) + 1u, float_key(th.y), cs, tau, cut)) return false;
 #pragma unroll
     for (int j = 0; j < NS; ++j) acc += ck[j] && in_cut(ck[j], (uint32_t)iv[j], tau, cut) ? (unsigned long long)iv[j] : 0ull;
-    return acc;
+    return true;
   };
-  unsigned long long acc = nc <= 1024u  ? run(std::integral_constant<int, 2>{})
-                           : nc <= 2048u ? run(std::integral_constant<int, 4>{})
-                           : nc <= 3072u ? run(std::integral_constant<int, 6>{})
-                                         : run(std::integral_constant<int, NPT>{});
+  const bool found = nc <= 1024u   ? run(std::integral_constant<int, 2>{})
+                     : nc <= 2048u ? run(std::integral_constant<int, 4>{})
+                     : nc <= 3072u ? run(std::integral_constant<int, 6>{})
+                                   : run(std::integral_constant<int, NPT>{});
+  if (!found) {                                      // block-uniform
+    const unsigned long long tot = row_exact_sum(row, pb.P, k, sm);
+    if (threadIdx.x == 0) rowsum[r] = tot;
+    return;
+  }
 #pragma unroll
   for (int o = 32; o >= 1; o >>= 1) acc += __shfl_xor(acc, o, 64);
   if ((threadIdx.x & 63) == 0) isum[threadIdx.x >> 6] = acc;
@@ -349,7 +353,7 @@ __global__ __launch_bounds__(NT, NT == 1024 && NPT == 16 ? 8 : 4) void k_short_r
     load_row_keys<NT, NPT, VEC>(score + (int64_t)r * pb.ld, pb.P, key);
     block_range<NT>(key, cs, lo, hi);
     auto pos = [](int j, int t) { return row_pos<NT, NPT, VEC>(j, t); };
-    block_cut<NT>(key, pos, (uint32_t)k, lo, hi, cs, tau, cut);
+    block_cut<NT>(key, pos, (uint32_t)k, lo, hi, cs, tau, cut);      // (the row has its k entries)
     uint32_t acc = 0;                              // (NPT positions below 2^15)
 #pragma unroll
     for (int j = 0; j < NPT; ++j) {

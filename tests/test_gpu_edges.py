@@ -182,3 +182,19 @@ def test_rows_of_unset_memory(rk, P, finite):  # noqa: F811
     for r in s.reshape(-1, P):
         r[rng.choice(P, finite, replace=False)] = rng.normal(size=finite).astype(np.float32)
     _statistics_and_selection_by_key(rk, s, np.ascontiguousarray(s[:, 0]), B)
+
+
+@pytest.mark.parametrize("P", [40001, 90000])
+@pytest.mark.parametrize("seen,unseen", [(-0.0, 0.0), (0.0, -0.0), (-0.0, -0.0)])
+def test_zeros_of_both_signs_at_a_bracket_end(rk, P, seen, unseen):  # noqa: F811
+    """The sampled searches bracket the threshold with an end at a zero, and zeros of the other sign lie where
+    neither samples (positions 22 .. 28: runs of 16 from 0 on and hundreds apart, single ones at 19 | 29 and 21 | 43):
+    entries counted by comparison (-0 = +0) and ranked by key (-0 < +0) are the same ones."""
+    Hkv, W, zeros = 2, 2, 600 if P < 50000 else 1400
+    B = W + zeros + 100
+    rng = np.random.default_rng(P)
+    row = -1.0 - rng.random(P).astype(np.float32)               # the zeros are the largest entries, the cut lies below them
+    row[rng.choice(np.arange(200, P), zeros, replace=False)] = seen
+    row[22:29] = unseen
+    s = np.broadcast_to(row, (Hkv, W, P)).copy()
+    _statistics_and_selection_by_key(rk, s, np.ascontiguousarray(s[:, 0]), B)
