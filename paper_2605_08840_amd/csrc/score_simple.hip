@@ -233,7 +233,8 @@ __global__ __launch_bounds__(NW * 64, 2) void k_attn_f32(Prob pb, const T* __res
       }
     }
     if (__ballot((tinc - mref) * c2 > RESCALE_TH) != 0ull) rescale(tinc);
-    // weights relative to the reference (a row that has none yet has nothing to add)
+    // weights relative to the reference (a row that has none yet has nothing to add).  The instruction
+    // makes 0 of weights below 2^-126: the sums hold the reference's own weight, 1, and do not notice.
     const float nm = mref == -INFINITY ? 0.f : -mref * c2;
 #pragma unroll
     for (int j = 0; j < 16; ++j) sacc[j] = __builtin_amdgcn_exp2f(fmaf(sacc[j], c2, nm));
@@ -461,7 +462,7 @@ __global__ __launch_bounds__(NW * 64, NW == 1 ? 1 : 2) void k_score_f32(Prob pb,
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         const int j = 4 * jq + e;
-        const float ex = __builtin_amdgcn_exp2f(fmaf(sacc[j], c2, -m_[e]));
+        const float ex = exp2f(fmaf(sacc[j], c2, -m_[e]));     // (the instruction alone would make 0 of a subnormal weight)
         const float dist2 = fmaf(-2.f, cacc[j], z_[e]) + vvn;
         float val = ex / fmaf(-rec, ex, l_[e]) * sqrtf(fmaxf(dist2, 0.f));
         val = n == __float_as_int(n_[e]) ? s_[e] : val;

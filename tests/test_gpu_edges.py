@@ -5,7 +5,7 @@ import pytest
 import torch
 
 import workloads
-from gpu_util import assert_score_close, oracle_score, params_for
+from gpu_util import assert_score_close, oracle_score, params_for, run_gpu_layer
 from test_gpu_parity import _score_against_oracle_then_every_stage_exactly, _smooth_select_inputs, rk  # noqa: F401
 
 pytestmark = pytest.mark.gpu
@@ -198,3 +198,26 @@ def test_zeros_of_both_signs_at_a_bracket_end(rk, P, seen, unseen):  # noqa: F81
     row[22:29] = unseen
     s = np.broadcast_to(row, (Hkv, W, P)).copy()
     _statistics_and_selection_by_key(rk, s, np.ascontiguousarray(s[:, 0]), B)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_fp32_scores_of_subnormal_weights(rk, oracle_mod, d):  # noqa: F811
+    """Keys 87 to 103 nats below the largest have attention weights below the smallest normal FP32 number: their scores
+    keep what FP32 holds of them.  A weight is off by half a unit of 2^-149, times the distance I/A, and its product with
+    the distance by half a unit again; everything else is within the tolerance of gpu_util.py."""
+    w = workloads.small_case(Hq=2, Hkv=2, d=d, L=400, W=9, B=60, dtype="f32", D=2 * d, seed=71)
+    q, k, v = workloads.make_qkv(w)
+    wo = workloads.make_wo(w)
+    q[:], k[..., 0] = 0.0, -16.0 * torch.rand(k.shape[:2], generator=torch.Generator().manual_seed(5))
+    q[..., 0] = float(d) ** 0.5                                  # logit of a key = its first component
+    k[:, 7, 0] = 87.0
+    got = run_gpu_layer(rk, w, q, k, v, wo)["score"]
+    fac = oracle_mod.gram_factor(wo.double().numpy().reshape(w.n_q_heads, d, -1))
+    for g in range(w.n_kv_heads):
+        Ig, I, A, _ = oracle_mod.score_head(q[g:g + 1].numpy(), k[g].numpy(), v[g].numpy(), fac[g:g + 1], w.window,
+                                             1.0 / np.sqrt(d), True, aux=True)
+        sub = (Ig > 0) & (Ig < 2.0 ** -126)
+        assert sub.mean() > 0.5
+        tol = 1e-3 * Ig + 2.0 ** -149 * 0.5 * (I[0] / np.where(A[0] > 0, A[0], np.inf) + 1.0)
+        bad = np.abs(got[g] - Ig) > tol
+        assert not bad.any(), (got[g][bad][:3], Ig[bad][:3], tol[bad][:3])
