@@ -123,7 +123,9 @@ int restkv_prepare_wo(const restkv_params* p, const float* w_o, int64_t d_model,
  *     I[h,i,n] = A[n] / (1 - A[n]) * || (z_{h,i} - v_n) W_O^h ||_2 ,
  * A = softmax(scale * q_{h,i} K^T) over the visible keys (Eq. softmax), z = A V.
  * The token holding the largest weight of a query is evaluated by the equivalent
- * leave-one-out form (Eq. ori with Eq. relation), which stays finite as A -> 1.
+ * leave-one-out form (Eq. ori with Eq. relation), which stays finite as A -> 1 (matrix-core kernels:
+ * if it held more than half of the weight its key split had seen when it came, as every token with
+ * A > 1/2 does).
  * Output is the mean over the G query heads of each KV head:
  *     score[g,i,n] = (1/G) sum_{h in g} I[h,i,n]          [Hkv, W, ld_score] float32
  *   q     [Hq, W, d]  (strides q_stride_*),  k, v  [Hkv, L, d] (strides kv_stride_*)

@@ -29,7 +29,8 @@ inline ScorePtrs score_ptrs(char* ws, const ScoreWs& lay) {
 // Per split s and query row the attention pass leaves (all logits in log2 units, scaled):
 //   part_m    largest logit seen, -inf if the split saw no key
 //   part_mx   logit of the key the split kept OUT of its sums (valid if part_n >= 0)
-//   part_n    index of that key, or -1
+//   part_n    index of that key; without one -2 - (index of the largest logit's key) where the pass
+//             tracks it (FP32 path, which keeps a key out only while it is the largest), else -1
 //   part_ref  reference the sums are relative to
 //   part_l    sum over the included keys of 2^(logit - ref)
 //   part_z    sum over the included keys of 2^(logit - ref) * v
@@ -40,10 +41,12 @@ inline ScorePtrs score_ptrs(char* ws, const ScoreWs& lay) {
 // bf16 weight is exact).
 // The merge keeps out the excluded key that is the overall maximum (if any) and folds every
 // other excluded key back in.  With a key kept out ("champion", weight A* = 1/l):
-//   l = 1 + l_rest, z = (v* + z_rest)/l, u = z M_h, zz = u.z, and, if A* > 1/2, the champion's
-//   indicator in its leave-one-out form I* = A* ||(z_rest/l_rest - v*) W_O||  (Eq. ori with
-//   Eq. relation; equals Eq. rec_ei).  Without one, l and z are the plain softmax sums relative to
-//   the maximum.
+//   l = 1 + l_rest, z = (v* + z_rest)/l, u = z M_h, zz = u.z, and the champion's indicator in its
+//   leave-one-out form I* = A* ||(z_rest/l_rest - v*) W_O||  (Eq. ori with Eq. relation; equals
+//   Eq. rec_ei).  Without one, l and z are the plain softmax sums relative to the maximum; the largest
+//   key, where its index is known, then has A* <= 1/2, and the same form is the difference
+//   A*/(1 - A*) ||(z - v*) W_O||.  Either way the difference is taken before its norm: the expanded
+//   distance of the score pass cancels where v* lies near z.
 
 // Statistics of a caller's own attention kernel as ONE split of the attention pass: the log-sum-exp
 // of a row (natural log) is both the reference and the "largest logit", the sum of weights is 1, no
@@ -194,20 +197,27 @@ __global__ __launch_bounds__(4 * D, 4) void k_attn_combine(Prob pb, const T* __r
       s_jn[r][e] = pn;
     }
     s_w[r][sub] = w;
-    const int nst = __shfl(pn, sl < 0 ? l : sl, 64);
+    // without one: the earliest split whose largest logit, part of its sums, is the overall maximum
+    const unsigned long long cin = __ballot(pn <= -2 && pm == M0) & mine;
+    const int sc = cand ? sl : (cin ? __builtin_ctzll(cin) : -1);
+    const int nst = __shfl(pn, sc < 0 ? l : sc, 64);
     if (sub == 0) {
       s_fr[r] = R == -INFINITY ? 0.f : exp2f(R - M0);
       s_lrest[r] = lrest;
       s_nj[r] = __popcll(jm);
-      s_nstar[r] = sl >= 0 ? nst : -1;
+      s_nstar[r] = sc >= 0 ? nst : -1;       // as part_n
       if (i0 + r < pb.W) o.rs_m[row] = M0;
     }
   }
   __syncthreads();
-  // The key that the score pass is to evaluate in its leave-one-out form: the kept-out key if it ended
-  // with more than half of the mass (1 / l > 1/2); a smaller share is well conditioned in Eq. rec_ei.
-  auto loo = [&](int r) { return pb.ind == 0 && s_lrest[r] * s_fr[r] < 1.f ? s_nstar[r] : -1; };
-  const bool champ = __ballot(loo(l & (RQ - 1)) >= 0) != 0ull;
+  // the key that the score pass is to evaluate in its leave-one-out form
+  auto key_of = [](int n) { return n >= 0 ? n : (n <= -2 ? -2 - n : -1); };
+  auto loo = [&](int r) { return pb.ind == 0 ? key_of(s_nstar[r]) : -1; };
+  // rows that have one (a bit each), and the slot of a row's x among them
+  unsigned long long cm = __ballot(loo(l & (RQ - 1)) >= 0);
+  if constexpr (RQ < 64) cm &= (1ull << RQ) - 1ull;
+  const bool champ = cm != 0ull;
+  auto slot_of = [&](int r) { return RQ <= 8 ? r : __popcll(cm & ((1ull << r) - 1ull)); };
 #pragma unroll
   for (int m = 0; m < MB; ++m) {
     const int r = rz + 16 * m;
@@ -220,7 +230,7 @@ __global__ __launch_bounds__(4 * D, 4) void k_attn_combine(Prob pb, const T* __r
       for (int k = 0; k < JB; ++k)
         __builtin_memcpy(&tj[k][0], vg + (int64_t)s_jn[r][min(j + k * NP, nj - 1)] * pb.kv_st + c4, 4 * sizeof(T));
     };
-    const f32x4_t vs = quad_of(vg + (int64_t)max(nstar, 0) * pb.kv_st + c4);
+    const f32x4_t vs = quad_of(vg + (int64_t)max(key_of(nstar), 0) * pb.kv_st + c4);
     if (part < nj) fetch_joins(part);
     f32x4_t z = {0.f, 0.f, 0.f, 0.f};
     for (int s = part; s < S; s += SB * NP) {
@@ -261,63 +271,82 @@ __global__ __launch_bounds__(4 * D, 4) void k_attn_combine(Prob pb, const T* __r
         }
       } else {
 #pragma unroll
-        for (int e = 0; e < 4; ++e) zz[e] = z[e] / lrest;
+        for (int e = 0; e < 4; ++e) {
+          zz[e] = z[e] / lrest;
+          x[e] = nstar <= -2 ? zz[e] - vs[e] : 0.f;
+        }
       }
       *(f32x4_t*)&zs[r][c4] = zz;
-      if (champ) *(f32x4_t*)&xs[r][c4] = x;                    // (its own partial sum, or nothing, was there)
+      if (RQ <= 8 || ((cm >> r) & 1ull)) *(f32x4_t*)&xs[slot_of(r)][c4] = x;      // (its own partial sum, or nothing, was there)
     }
   }
   __syncthreads();
-  // u and y: register j of a lane is row 16 m + 4 (l / 16) + j, column 16 wv + l % 16
+  // u and y: register j of a lane is row 4 (l / 16) + j of a 16-row block, column 16 wv + l % 16.  With at
+  // most eight rows z takes the first half of one block and x the second; with more, the x of the rows
+  // that have one follow in blocks of their own.
   const int c = 16 * wv + (l & 15), kq = l >> 4;
-  f32x4_t u[MB], y[MB];
+  // acc[m]: product of block m, whose row i lies in LDS at row_of(m, i)
+  auto product = [&](auto row_of, auto& acc) {
+    constexpr int NB = sizeof(acc) / sizeof(f32x4_t);
 #pragma unroll
-  for (int m = 0; m < MB; ++m) { u[m] = f32x4_t{0.f, 0.f, 0.f, 0.f}; y[m] = u[m]; }
-  if (pb.ind != 0) {
-    // attention-weight and value-norm indicators: no output term (u = 0, zz = 0), no key is
-    // evaluated by the leave-one-out form; the score pass then sees sqrt(vv) with vv = 1 or ||v||^2
-  } else if (gram) {
-    auto product = [&](const float (*x)[ZST], f32x4_t (&acc)[MB]) {
+    for (int m = 0; m < NB; ++m) acc[m] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    // (attention-weight and value-norm indicators: no output term (u = 0, zz = 0), no key is evaluated by the
+    // leave-one-out form; the score pass then sees sqrt(vv) with vv = 1 or ||v||^2)
+    if (pb.ind != 0) return;
+    if (gram) {
 #pragma unroll
       for (int a = 0; a < D / 16; ++a) {
-        f32x4_t xa[MB];
+        f32x4_t xa[NB];
 #pragma unroll
-        for (int m = 0; m < MB; ++m) xa[m] = *(const f32x4_t*)&x[(16 * m + (l & 15)) & (RQ - 1)][16 * a + 4 * kq];
+        for (int m = 0; m < NB; ++m) xa[m] = *(const f32x4_t*)&row_of(m, l & 15)[16 * a + 4 * kq];
 #pragma unroll
         for (int e = 0; e < 4; ++e)
 #pragma unroll
-          for (int m = 0; m < MB; ++m) acc[m] = __builtin_amdgcn_mfma_f32_16x16x4f32(xa[m][e], mreg[a][e], acc[m], 0, 0, 0);
+          for (int m = 0; m < NB; ++m) acc[m] = __builtin_amdgcn_mfma_f32_16x16x4f32(xa[m][e], mreg[a][e], acc[m], 0, 0, 0);
       }
       // wait states between the last MFMA and the first read of its result, spelled out because a
       // branch lies in between (the compiler inserts too few on one of the merging paths)
 #pragma unroll
-      for (int m = 0; m < MB; ++m) asm volatile("s_nop 15" : "+v"(acc[m]));
-    };
-    product(zs, u);
-    if (champ) product(xs, y);                   // workgroup-uniform
+      for (int m = 0; m < NB; ++m) asm volatile("s_nop 15" : "+v"(acc[m]));
+    } else {
+#pragma unroll
+      for (int m = 0; m < NB; ++m)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) acc[m][j] = row_of(m, 4 * kq + j)[c];
+    }
+  };
+  // zz = u.z and |x|_M^2 = y.x: sums over 16 lanes here, across the wavefronts below
+  f32x4_t u[MB];
+  if constexpr (RQ <= 8) {
+    auto row_of = [&](int, int i) -> const float* { return i < 8 ? zs[i & (RQ - 1)] : xs[i & (RQ - 1)]; };
+    product(row_of, u);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int i = 4 * kq + j;
+      const float s0 = row16_sum(u[0][j] * row_of(0, i)[c]);
+      if ((i & 7) < RQ && (l & 15) == 0) red[wv][i & 7][i >> 3] = s0;
+    }
   } else {
+    product([&](int m, int i) -> const float* { return zs[16 * m + i]; }, u);
 #pragma unroll
     for (int m = 0; m < MB; ++m)
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
-        const int r = (16 * m + 4 * kq + j) & (RQ - 1);
-        u[m][j] = zs[r][c];
-        if (champ) y[m][j] = xs[r][c];
+        const float s0 = row16_sum(u[m][j] * zs[16 * m + 4 * kq + j][c]);
+        if ((l & 15) == 0) red[wv][16 * m + 4 * kq + j][0] = s0;
       }
-  }
-  // zz = u.z and |x|_M^2 = y.x of the rows: sums over 16 lanes, then across the wavefronts
+    const int nx = __popcll(cm);
+    for (int m0 = 0; m0 < nx; m0 += 16) {        // (rows past the last are whatever LDS holds, and are not used)
+      auto row_of = [&](int, int i) -> const float* { return xs[m0 + i]; };
+      f32x4_t y[1];
+      product(row_of, y);
 #pragma unroll
-  for (int m = 0; m < MB; ++m)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int r = 16 * m + 4 * kq + j, rc = r & (RQ - 1);
-      float s0 = u[m][j] * zs[rc][c], s1 = 0.f;
-      s0 = row16_sum(s0);
-      if (champ) {
-        s1 = row16_sum(y[m][j] * xs[rc][c]);
+      for (int j = 0; j < 4; ++j) {
+        const float s1 = row16_sum(y[0][j] * row_of(0, 4 * kq + j)[c]);
+        if ((l & 15) == 0) red[wv][m0 + 4 * kq + j][1] = s1;
       }
-      if (r < RQ && (l & 15) == 0) { red[wv][r][0] = s0; red[wv][r][1] = s1; }
     }
+  }
   if (champ) __syncthreads();                    // (x has been read; u takes its place)
 #pragma unroll
   for (int m = 0; m < MB; ++m)
@@ -328,14 +357,17 @@ __global__ __launch_bounds__(4 * D, 4) void k_attn_combine(Prob pb, const T* __r
   for (int r = tid; r < RQ; r += NT) {
     if (i0 + r >= pb.W) break;
     const int row = h * pb.W + i0 + r;
+    const bool has_x = (cm >> r) & 1ull;
+    const int sl = has_x ? slot_of(r) : 0;
     float zz = 0.f, qx = 0.f;
 #pragma unroll
-    for (int k = 0; k < NWV; ++k) { zz += red[k][r][0]; qx += red[k][r][1]; }
+    for (int k = 0; k < NWV; ++k) { zz += red[k][r][0]; qx += has_x ? red[k][sl][1] : 0.f; }
     const float lr = s_lrest[r] * s_fr[r], l_ = s_nstar[r] >= 0 ? 1.f + lr : lr;
     o.rs_l[row] = l_;
     o.rs_zz[row] = zz;
     o.rs_nstar[row] = loo(r);
-    o.rs_istar[row] = sqrtf(fmaxf(qx, 0.f)) / l_;       // A* ||(z_rest - v*) W_O||,  A* = 1/l
+    // A* ||(z_rest - v*) W_O|| with A* = 1/l, or A*/(1 - A*) ||(z - v*) W_O|| with A*/(1 - A*) = 1/(l - 1)
+    o.rs_istar[row] = sqrtf(fmaxf(qx, 0.f)) / (s_nstar[r] >= 0 ? l_ : l_ - 1.f);
   }
   if (use_op) {
     // q, and u split into bf16 high and low parts, in the order the score pass feeds them to the

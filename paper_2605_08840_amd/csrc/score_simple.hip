@@ -125,6 +125,7 @@ __global__ __launch_bounds__(NW * 64, 2) void k_attn_f32(Prob pb, const T* __res
   const float c2 = pb.scale * LOG2E;
   float mall = -INFINITY, mref = -INFINITY, mx = -INFINITY, lsum = 0.f;
   int nx = -1;                       // key kept out of the sums, -1: none
+  int ni = 0;                        // key of the largest logit (the one kept out, if any)
   f32x16 oacc[CB];
 #pragma unroll
   for (int cb = 0; cb < CB; ++cb)
@@ -184,7 +185,7 @@ __global__ __launch_bounds__(NW * 64, 2) void k_attn_f32(Prob pb, const T* __res
     // The reference of the exponentials is a logit that is part of the sums; it moves when a
     // joining logit runs RESCALE_TH ahead of it.  A key is kept out when it is the largest so far
     // and holds more than half of the mass including its own block's (what a key that ends with
-    // more than half of the total always does).
+    // more than half of the total always does), and only as long as it is the largest.
     const bool newmax = tm > mall;
     mall = fmaxf(mall, tm);
     float tinc = tm;                   // largest logit of the block that joins the sums
@@ -199,10 +200,12 @@ __global__ __launch_bounds__(NW * 64, 2) void k_attn_f32(Prob pb, const T* __res
       }
       rest = half_sum(rest) - 1.f;
       cand = half_min(cand);
+      ni = newmax ? cand : ni;
       if (nx >= 0) rest += __builtin_amdgcn_exp2f((mx - tm) * c2);
       // (rest carries the rounding of the sum it was taken from: a tie may go either way)
       const bool dominant = newmax && tm > -INFINITY && rest < 1.0001f;
-      if (__ballot(dominant) != 0ull) {
+      const bool joins = newmax && nx >= 0;          // the key kept out so far is not the largest any more: it joins the sums
+      if (__ballot(dominant || joins) != 0ull) {
         const int cz = dominant ? cand : -1;
         tinc = -INFINITY;
 #pragma unroll
@@ -211,7 +214,6 @@ __global__ __launch_bounds__(NW * 64, 2) void k_attn_f32(Prob pb, const T* __res
           tinc = fmaxf(tinc, sacc[j]);
         }
         tinc = half_max(tinc);
-        const bool joins = dominant && nx >= 0;      // the key kept out so far joins the sums
         if (joins) tinc = fmaxf(tinc, mx);
         rescale(tinc);
         if (joins) {
@@ -229,7 +231,10 @@ __global__ __launch_bounds__(NW * 64, 2) void k_attn_f32(Prob pb, const T* __res
               oacc[cb][4 * jq + 3] = fmaf(w, x.w, oacc[cb][4 * jq + 3]);
             }
         }
-        if (dominant) { mx = tm; nx = cand; }
+        if (dominant || joins) {
+          mx = tm;
+          nx = dominant ? cand : -1;
+        }
       }
     }
     if (__ballot((tinc - mref) * c2 > RESCALE_TH) != 0ull) rescale(tinc);
@@ -260,7 +265,7 @@ __global__ __launch_bounds__(NW * 64, 2) void k_attn_f32(Prob pb, const T* __res
     if (hf == 0) {
       o.part_m[po] = mall * c2;
       o.part_mx[po] = mx * c2;
-      o.part_n[po] = nx;
+      o.part_n[po] = nx >= 0 ? nx : -2 - ni;
       o.part_ref[po] = mref == -INFINITY ? 0.f : mref * c2;
       o.part_l[po] = ltot;
     }

@@ -381,13 +381,20 @@ __global__ __launch_bounds__(NT, NT == 1024 && NPT == 16 ? 8 : 4) void k_short_r
     if (b0) __syncthreads();
     for (int i = threadIdx.x; i < nb; i += NT) wts[i] = temporal_weight(pb, b0 + i);
     __syncthreads();
-    for (int i = 0; i < nb; i += 16) {
+    int i = 0;
+    for (; i + 16 <= nb; i += 16) {
+      float x[16];
+#pragma unroll
+      for (int u = 0; u < 16; ++u) x[u] = s[(int64_t)(b0 + i + u) * pb.ld];
+#pragma unroll
+      for (int u = 0; u < 16; ++u) e = fmaf(wts[i + u], x[u], e);
+    }
+    if (i < nb) {                        // (past the end neither weight nor score: 0 times infinity is a NaN)
       float x[16];
 #pragma unroll
       for (int u = 0; u < 16; ++u) x[u] = s[(int64_t)(b0 + min(i + u, nb - 1)) * pb.ld];
 #pragma unroll
-      for (int u = 0; u < 16; ++u)       // (past the end neither weight nor score: 0 times infinity is a NaN)
-        e = fmaf(i + u < nb ? wts[min(i + u, nb - 1)] : 0.f, i + u < nb ? x[u] : 0.f, e);
+      for (int u = 0; u < 16; ++u) e = fmaf(i + u < nb ? wts[min(i + u, nb - 1)] : 0.f, i + u < nb ? x[u] : 0.f, e);
     }
   }
   if (n < pb.P) ema[(int64_t)g * pb.ld + n] = e;

@@ -221,3 +221,31 @@ def test_fp32_scores_of_subnormal_weights(rk, oracle_mod, d):  # noqa: F811
         tol = 1e-3 * Ig + 2.0 ** -149 * 0.5 * (I[0] / np.where(A[0] > 0, A[0], np.inf) + 1.0)
         bad = np.abs(got[g] - Ig) > tol
         assert not bad.any(), (got[g][bad][:3], Ig[bad][:3], tol[bad][:3])
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("d,late", [(64, False), (128, False), (128, True)])
+def test_largest_key_whose_value_lies_near_the_output(rk, oracle_mod, dtype, d, late):  # noqa: F811
+    """A query's largest key holds 0.4 of its attention and its value differs from every other's, c, by 2^-7 c: in the
+    expanded distance |z|^2 - 2 z.v + |v|^2 the terms cancel to 2^-14 of their size, the difference z_rest - v of
+    the leave-one-out form (0 for the other keys, whose value is the output of the others) does not.  Weights of equal
+    logits are equal, so the output of the other keys is c to FP32 rounding and the key's score to a few 2^-24 * 2^7.
+    late: the key comes last, and never held more than half of the mass (the matrix-core path keeps only such keys)."""
+    if late and dtype == "bf16":
+        pytest.skip("the matrix-core path evaluates a key by the leave-one-out form if it held more than half on arrival")
+    w = workloads.small_case(Hq=2, Hkv=2, d=d, L=606, W=6, B=60, dtype=dtype, D=2 * d, seed=73)
+    q, k, v = workloads.make_qkv(w)
+    wo = workloads.make_wo(w)
+    n = w.prefix - 3 if late else 1
+    q[:], k[:] = 0.0, 0.0
+    q[..., 0] = float(d) ** 0.5 if d == 64 else 11.3125           # (a bf16 value near sqrt(128))
+    k[:, n, 0] = 6.0
+    c = torch.from_numpy(np.random.default_rng(3).choice([-1.0, 0.5, 2.0], size=d)).to(v.dtype)
+    v[:] = c
+    v[:, n] = (c.float() * (1 + 2.0 ** -7)).to(v.dtype)
+    got = run_gpu_layer(rk, w, q, k, v, wo)["score"]
+    ref = oracle_score(oracle_mod, w, q, k, v, wo, with_amax=True)
+    for g in range(w.n_kv_heads):
+        Ig, _, A = ref[g]
+        assert ((A[:, n] > 0.3) & (A[:, n] < 0.5)).all()
+        np.testing.assert_allclose(got[g][:, n], Ig[:, n], rtol=1e-3)
