@@ -1,12 +1,11 @@
-// Block-wide exact top-k of one row of floats held in global memory (gfx950, 64-wide waves).
+// Block-wide top-k searches of rows of floats (gfx950, 64-wide waves).
 //
-// A radix select on the order-preserving integer image of the floats finds the
-// value of the k-th largest element in three histogram passes (11 + 11 + 10
-// bits); an ordered pass then visits the row once more in position order so
-// that, among elements equal to the threshold, the lowest positions win.  The
-// visitor either sums the selected positions or writes them out in ascending
-// order.  The row is re-read from L2 on every pass; nothing is written but the
-// result.
+// Rows, or candidates of a row, that fit a block's registers: a histogram over the keys' own range whose
+// threshold bin is ranked directly (block_cut).  A long row is bracketed from a sample first (block_bracket), so
+// that one streaming pass leaves few candidates.  Where the bracket misses or holds too many, the row
+// is searched exactly in global memory: a radix select on the order-preserving integer image of the
+// floats (three histogram passes of 11 + 11 + 10 bits), then, in position order, the entries equal to the
+// threshold, lowest positions first.
 #pragma once
 
 #include <type_traits>
@@ -51,13 +50,15 @@ __device__ __forceinline__ uint32_t rank_in_ballot(unsigned long long ballot) {
   return (uint32_t)__popcll(below);
 }
 
-// Threshold of the k-th largest (1 <= k <= n): on return `tau` is its key, `n_gt`
-// the number of keys above it and `k_eq` how many keys equal to tau belong to the
-// top k (>= 1).  All threads of the block must call; all receive the result.
+// Threshold of the k-th largest (1 <= k <= n): on return `tau` is its key, `n_eq` the number of
+// keys equal to it and `k_eq` how many of these belong to the top k (>= 1).  All threads of the
+// block must call; all receive the result.
 // Any block of 64 .. SEL_NT threads whose size divides SEL_BINS.
+// Bound by the latency of the row's loads, eight of which a thread has in flight, and by LDS atomics on
+// few bins (keys of one exponent, equal keys): a wavefront adds the entries of its first entry's bin at once.
 __device__ inline void block_kth_key(const float* __restrict__ row, int n, int k, SelectSmem& sm,
-                                     uint32_t& tau, uint32_t& n_gt, uint32_t& k_eq) {
-  uint32_t prefix = 0, mask = 0, krem = (uint32_t)k, above = 0;
+                                     uint32_t& tau, uint32_t& n_eq, uint32_t& k_eq) {
+  uint32_t prefix = 0, mask = 0, krem = (uint32_t)k;
   const int shifts[3] = {21, 10, 0};
   const int nbits[3] = {11, 11, 10};
 #pragma unroll
@@ -67,9 +68,31 @@ __device__ inline void block_kth_key(const float* __restrict__ row, int n, int k
     const int nt = (int)blockDim.x, bpt = SEL_BINS / nt;
     for (int b = threadIdx.x; b < SEL_BINS; b += nt) sm.hist[b] = 0;
     __syncthreads();
-    for (int x = threadIdx.x; x < n; x += nt) {
-      const uint32_t key = float_key(row[x]);
-      if ((key & mask) == prefix) atomicAdd(&sm.hist[(key >> sh) & (nb - 1)], 1u);
+    for (int x0 = 0; x0 < n; x0 += 8 * nt) {     // (block-uniform: every lane takes part in the ballots)
+      float f[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) f[u] = row[min(x0 + u * nt + (int)threadIdx.x, n - 1)];
+      uint32_t bin[8];
+      unsigned long long all[8], same[8];
+      int lead[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        const uint32_t key = float_key(f[u]);
+        const bool in = x0 + u * nt + (int)threadIdx.x < n && (key & mask) == prefix;
+        bin[u] = in ? (key >> sh) & (nb - 1) : 0xFFFFFFFFu;
+        all[u] = __ballot(in);
+      }
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        lead[u] = all[u] ? __builtin_ctzll(all[u]) : 0;
+        same[u] = __ballot(bin[u] == (uint32_t)__builtin_amdgcn_readlane((int)bin[u], lead[u]));
+      }
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        if (all[u] == 0ull) continue;
+        if ((int)(threadIdx.x & 63) == lead[u]) atomicAdd(&sm.hist[bin[u]], (uint32_t)__popcll(same[u]));
+        else if (((all[u] & ~same[u]) >> (threadIdx.x & 63)) & 1ull) atomicAdd(&sm.hist[bin[u]], 1u);
+      }
     }
     __syncthreads();
     // bins in descending order: thread t owns the reversed bins bpt t .. bpt t + bpt - 1
@@ -81,20 +104,55 @@ __device__ inline void block_kth_key(const float* __restrict__ row, int n, int k
     if (before < krem && krem <= incl) {        // exactly one thread
       for (int j = 0; j < bpt; ++j) {
         const uint32_t hj = r0 + j < (int)nb ? sm.hist[nb - 1 - (r0 + j)] : 0u;
-        if (krem <= before + hj) { sm.bin = nb - 1 - (r0 + j); sm.below = before; break; }
+        if (krem <= before + hj) { sm.bin = nb - 1 - (r0 + j); sm.below = before; sm.take = hj; break; }
         before += hj;
       }
     }
     __syncthreads();
     prefix |= sm.bin << sh;
     mask |= (nb - 1) << sh;
-    above += sm.below;
     krem -= sm.below;
+    n_eq = sm.take;
     __syncthreads();
   }
   tau = prefix;
-  n_gt = above;
   k_eq = krem;
+}
+
+// Position of the k_eq-th entry (1 <= k_eq <= their number) whose key is tau, in position order: a
+// wavefront counts them in its part of the row, the one that has it looks again.  All threads of
+// the block must call; all receive the result.
+__device__ inline uint32_t block_tie_cut(const float* __restrict__ row, int n, uint32_t tau, uint32_t k_eq, SelectSmem& sm) {
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, nw = (int)(blockDim.x >> 6);
+  const int seg = ((n + nw - 1) / nw + 63) / 64 * 64;
+  const int beg = min(n, w * seg), end = min(n, beg + seg);
+  auto each = [&](auto f) {                      // f(position of lane 0, ballot of the ties), until it returns false
+    for (int x0 = beg; x0 < end; x0 += 512) {
+      float v[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) v[u] = row[min(x0 + 64 * u + lane, n - 1)];
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+        if (!f(x0 + 64 * u, __ballot(x0 + 64 * u + lane < end && float_key(v[u]) == tau))) return;
+    }
+  };
+  uint32_t c = 0;
+  each([&](int, unsigned long long b) { c += (uint32_t)__popcll(b); return true; });
+  __syncthreads();
+  if (lane == 0) sm.cnt_eq[w] = c;
+  __syncthreads();
+  uint32_t run = 0;
+  for (int j = 0; j < w; ++j) run += sm.cnt_eq[j];
+  if (run < k_eq && k_eq <= run + c) {           // exactly one wavefront
+    each([&](int x0, unsigned long long b) {
+      const uint32_t m = (uint32_t)__popcll(b);
+      if (run + m < k_eq) { run += m; return true; }
+      if (((b >> lane) & 1ull) && rank_in_ballot(b) == k_eq - run - 1u) sm.bin = (uint32_t)(x0 + lane);
+      return false;
+    });
+  }
+  __syncthreads();
+  return sm.bin;
 }
 
 __device__ __forceinline__ float key_float(uint32_t k) {

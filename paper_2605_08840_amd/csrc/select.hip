@@ -169,7 +169,9 @@ __global__ __launch_bounds__(256) void k_sel_scan(Prob pb, const float* __restri
 // heads: 16.5 + 15.8 + 4.0 us in three launches, 11.3 + 11.6 in two):
 //   * it adds up the chunks' counts, expands the head's masks into candidate positions, fetches
 //     their values (at most SCAP) and finds the cut among them;
-//   * or, if the bracket missed or holds too many candidates, searches the row exactly;
+//   * or, if the bracket missed or holds too many candidates, searches the row exactly (every workgroup
+//     of the head on its own: 128k equal scores, 8 heads, 182 us, 400k distinct ones 404; with one
+//     workgroup per head and a launch in between, a load in flight per thread, 461 and 463);
 //   * the selected entries before its first chunk are the counts above the bracket plus the
 //     selected candidates there; from there on it emits its chunks (thread t owns 8 consecutive
 //     positions of each).  Window tokens and the unused tail of a smaller per-head budget are
@@ -181,7 +183,7 @@ __global__ __launch_bounds__(512) void k_sel_emit(Prob pb, const float* __restri
   __shared__ CutSmem cs;
   __shared__ SelectSmem sm;                      // (exact search only)
   __shared__ uint32_t red[2][NW];
-  __shared__ uint32_t flag, maxpos;
+  __shared__ uint32_t flag;
   __shared__ int cpos[SCAP];
   const int g = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const float* row = fin + (int64_t)g * pb.ld;
@@ -243,20 +245,21 @@ __global__ __launch_bounds__(512) void k_sel_emit(Prob pb, const float* __restri
         sel_before += ck[j] && (uint32_t)iv[j] < first && in_cut(ck[j], (uint32_t)iv[j], tau, cut) ? 1u : 0u;
     }
     if (!found) {
+      // exact search of the whole row: threshold, the last tie that is taken, and a count of the
+      // selected entries before this workgroup's
+      uint32_t n_eq, k_eq;
+      block_kth_key(row, pb.P, k, sm, tau, n_eq, k_eq);
+      cut = k_eq < n_eq ? block_tie_cut(row, pb.P, tau, k_eq, sm) : 0xFFFFFFFFu;
       sel_before = 0;
-      // exact search of the whole row: threshold, then an ordered visit that finds the last tie that
-      // is taken and counts the selected entries before this workgroup's
-      uint32_t n_gt, k_eq;
-      block_kth_key(row, pb.P, k, sm, tau, n_gt, k_eq);
-      if (tid == 0) maxpos = 0;
-      __syncthreads();
-      block_visit_topk(row, pb.P, tau, k_eq, sm, [&](int x, uint32_t) {
-        if (float_key(row[x]) == tau) atomicMax(&maxpos, (uint32_t)x);
-        sel_before += (uint32_t)x < first ? 1u : 0u;
-      });
-      __syncthreads();
-      cut = maxpos;
-      n_before = 0;                              // (the visit has counted every entry)
+      for (uint32_t x0 = tid; x0 < first; x0 += 8u * NT) {
+        float f[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) f[u] = row[min(x0 + (uint32_t)(u * NT), first - 1u)];
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+          sel_before += x0 + (uint32_t)(u * NT) < first && in_cut(float_key(f[u]), x0 + (uint32_t)(u * NT), tau, cut) ? 1u : 0u;
+      }
+      n_before = 0;                              // (every entry has been counted)
     }
     __syncthreads();
     sel_before = wave_sum(sel_before);

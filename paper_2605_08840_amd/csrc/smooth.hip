@@ -215,8 +215,8 @@ __global__ __launch_bounds__(256) void k_ema_scan(Prob pb, const float* __restri
 // Exact search (radix select + ordered visit) of a row whose bracket missed or overflowed: the
 // sum of the positions of its top k, for thread 0.  Every thread of the block calls.
 __device__ inline unsigned long long row_exact_sum(const float* __restrict__ row, int n, int k, SelectSmem& sm) {
-  uint32_t tau, n_gt, k_eq;
-  block_kth_key(row, n, k, sm, tau, n_gt, k_eq);
+  uint32_t tau, n_eq, k_eq;
+  block_kth_key(row, n, k, sm, tau, n_eq, k_eq);
   unsigned long long acc = 0;
   block_visit_topk(row, n, tau, k_eq, sm, [&](int x, uint32_t) { acc += (unsigned long long)x; });
 #pragma unroll

@@ -249,3 +249,23 @@ def test_largest_key_whose_value_lies_near_the_output(rk, oracle_mod, dtype, d, 
         Ig, _, A = ref[g]
         assert ((A[:, n] > 0.3) & (A[:, n] < 0.5)).all()
         np.testing.assert_allclose(got[g][:, n], Ig[:, n], rtol=1e-3)
+
+
+@pytest.mark.parametrize("P", [32769, 70001, 270000])
+@pytest.mark.parametrize("kind", ["constant", "four values", "mostly zero", "lognormal", "one tie too many"])
+def test_exact_search_of_long_rows(rk, P, kind):  # noqa: F811
+    """Rows with more candidates than the streaming searches hold (many equal values; a bracket too wide at this
+    length): the exact search of the row, with and without equal values at the cut."""
+    Hkv, W, B = 2, 2, 2 + 4000
+    rng = np.random.default_rng(P)
+    s = rng.lognormal(size=(Hkv, W, P)).astype(np.float32)
+    if kind == "constant":
+        s[:] = 1.5
+    elif kind == "four values":
+        s = rng.integers(0, 4, size=s.shape).astype(np.float32)
+    elif kind == "mostly zero":
+        s[rng.random(s.shape) < 0.99] = 0.0
+    elif kind == "one tie too many":                   # 4001 entries at the top value: the last is left out (select), none (statistics)
+        s[:] = 0.25
+        s[:, :, P - 4001:] = 8.0
+    _statistics_and_selection_by_key(rk, s, np.ascontiguousarray(s[:, 0]), B)
