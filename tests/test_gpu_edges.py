@@ -86,7 +86,7 @@ def test_tiles_split_between_wavefronts(rk, oracle_mod, Hq, Hkv, d, L, W, struct
     (32769, 2, 1, "ties"),          # ... and one past it
     (16500, 64, 5, "lognormal"),    # more rows of this length than compute units: the streaming launches
     (40000, 7, 2, "outliers"),      # a few scores 60 octaves above the rest stretch the sample's bins
-    (20000, 7, 2, "outliers"),
+    (20000, 7, 2, "outliers"), (150001, 6, 2, "outliers"),
 ])
 def test_row_statistics_and_selection_at_launch_rules(rk, oracle_mod, P, W, Hkv, kind):  # noqa: F811
     """Top-B index sums, window and selection, exactly, around the row lengths where another launch takes over,
