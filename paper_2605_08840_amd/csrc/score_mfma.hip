@@ -19,6 +19,7 @@
 // run of 64-key tiles) and stream their K/V tiles through asynchronous LDS rings (TileRing).
 #include <limits.h>
 
+#include <algorithm>
 #include <type_traits>
 
 #include "score_common.hpp"
@@ -1138,34 +1139,46 @@ __global__ __launch_bounds__(512) void k_score_pipe(Prob pb, const uint16_t* __r
   wait_vm<0>();            // no copy may land in LDS after the workgroup has gone
 }
 
+// Tiles that the busiest compute unit walks when `per` workgroups share every tile of the nt and each
+// takes a run of them: a run, twice if the workgroups are more than the compute units.
+int64_t span_tiles(int nt, int64_t per) {
+  const int64_t tpw = std::max<int64_t>(1, (nt * per + n_cu() - 1) / n_cu());
+  return tpw * (((nt + tpw - 1) / tpw * per + n_cu() - 1) / n_cu());
+}
+
 // Row blocks of 32 (padded group x window positions) that a workgroup of 8 wavefronts holds: eight, or
-// four whose tiles are split between two wavefronts (KS2) where that leaves fewer wavefronts without a
-// row and a workgroup walks at least min_tiles tiles of n.
+// four whose tiles are split between two wavefronts (KS2).  KS2 where a workgroup walks at least
+// min_tiles tiles of n and either four row blocks are all there is, or (wide) the busiest compute unit walks
+// at most 3/2 of the tiles, which cost 0.6 each: heads of 64 with nine to twelve blocks, if the workgroups fit the chip
+// at once.  Score pass, heads of 64, twelve blocks: 4 KV heads, 20k tokens 25.9 us against 28.2; 8 KV heads
+// (264 workgroups), 100k tokens 270 against 207.  Fifteen blocks for eight 1285 against 1006.  With heads of
+// 128 a tile costs 0.7: nine to twelve blocks 31.7 against 31.6 and 36.5 against 33.3.  Attention pass, nine and
+// ten blocks, 16 tiles for every KV head 69.2 against 67.5, 49 tiles 173 ... 184 against 182 ... 189.
 struct RowGeom { int gp, log2iw, gy; bool ks2; };
-RowGeom row_geom(const Prob& pb, int n, int min_tiles) {
+RowGeom row_geom(const Prob& pb, int n, int min_tiles, bool wide) {
   RowGeom r;
   r.gp = 1;
   while (r.gp < pb.G) r.gp <<= 1;
   const int iw = 32 / r.gp;
   r.log2iw = ilog2(iw);
   const int nwr = (pb.W + iw - 1) / iw;            // wavefronts needed to cover the window
-  const int gy4 = (nwr + 3) / 4, gy8 = (nwr + 7) / 8;
-  r.ks2 = gy4 < 2 * gy8 && (int64_t)((n + TN - 1) / TN) * gy4 * pb.Hkv >= (int64_t)min_tiles * n_cu();
+  const int gy4 = (nwr + 3) / 4, gy8 = (nwr + 7) / 8, nt = (n + TN - 1) / TN;
+  r.ks2 = (int64_t)nt * gy4 * pb.Hkv >= (int64_t)min_tiles * n_cu() &&
+          (gy4 == gy8 || (wide && 2 * span_tiles(nt, (int64_t)gy4 * pb.Hkv) <= 3 * span_tiles(nt, (int64_t)gy8 * pb.Hkv)));
   r.gy = r.ks2 ? gy4 : gy8;
   return r;
 }
-// Both halves of a tile pay the first tile's bookkeeping and meet at the end (4-5 us): 32/8 heads of 128,
-// window 32, four tiles a workgroup 21 us against 24 with KS2, 32 tiles 70 against 63 (80 when wavefronts
-// without a row still multiplied).
+// Both halves of a tile pay the first tile's bookkeeping and meet at the end (4-5 us).  32/8 heads of 128,
+// window 32: four tiles a workgroup 19.8 us against 23.4 with KS2, 16 tiles 36.4 against 37.8, 32 tiles 65.6
+// against 58.9; window 16: eight tiles 23.0 against 23.2, 16 tiles 32.3 against 31.2; six shapes at 16 tiles -1.1 ... +1.4.
 constexpr int ATTN_KS2_TILES = 16;
-// Score pass, same shapes: two tiles a workgroup 8.4 us against 9.2, four 16.6 against 15.6, 32 tiles 79
-// against 69 (98 when wavefronts without a row still multiplied).
+// Score pass, window 32: two tiles a workgroup 12.2 us against 12.6, four 16.5 against 15.8, 32 tiles 72.6 against 63.8.
 constexpr int SCORE_KS2_TILES = 4;
 
 template <int D, int GP>
 void launch_score_pipe(const Prob& pb, const uint16_t* q, const uint16_t* k, const uint16_t* v, const ScorePtrs& w, int ldv,
                        float* score, int nwb, hipStream_t st) {
-  const RowGeom rg = row_geom(pb, pb.P, SCORE_KS2_TILES);
+  const RowGeom rg = row_geom(pb, pb.P, SCORE_KS2_TILES, D == 64);
   // one resident workgroup per compute unit, each walking a run of tiles
   const int NT = (pb.P + TN - 1) / TN;
   const int tpp = max(1, (int)(((int64_t)NT * rg.gy * pb.Hkv + n_cu() - 1) / n_cu()));
@@ -1183,7 +1196,7 @@ int run_mfma(const Prob& pb, const void* q, const void* k, const void* v, const 
   const uint16_t* kk = (const uint16_t*)k;
   const uint16_t* vp = (const uint16_t*)v;
   const ScorePtrs w = score_ptrs(ws, lay);
-  const RowGeom rg = row_geom(pb, pb.L, ATTN_KS2_TILES);
+  const RowGeom rg = row_geom(pb, pb.L, ATTN_KS2_TILES, false);
   // attention pass: about one workgroup per compute unit, whole tiles per split
   int S = n_cu() / (pb.Hkv * rg.gy);
   const int max_s = (pb.L + TN - 1) / TN;
@@ -1212,9 +1225,11 @@ int run_mfma(const Prob& pb, const void* q, const void* k, const void* v, const 
   launch_combine<bf16_t, D>(pb, (const bf16_t*)v, S, gram, w, part_z, (const bf16_t*)q, 1, ilog2(rg.gp), lay.nwb, st);
   if (gram) {
     constexpr int HPW = D == 128 ? 4 : 8;
-    const bool ks2 = (pb.G + HPW / 2 - 1) / (HPW / 2) * (HPW / 2) < (pb.G + HPW - 1) / HPW * HPW;   // as for the rows
-    const int hpw = ks2 ? HPW / 2 : HPW;
     const int NTv = (pb.P + TN - 1) / TN;
+    // as for the rows: half as many heads per workgroup, at most 3/2 of the tiles
+    const int hg4 = (pb.G + HPW / 2 - 1) / (HPW / 2), hg8 = (pb.G + HPW - 1) / HPW;
+    const bool ks2 = 2 * span_tiles(NTv, (int64_t)hg4 * pb.Hkv) <= 3 * span_tiles(NTv, (int64_t)hg8 * pb.Hkv);
+    const int hpw = ks2 ? HPW / 2 : HPW;
     const int hg = (pb.G + hpw - 1) / hpw;
     int tpv = (int)(((int64_t)NTv * hg * pb.Hkv + n_cu() - 1) / n_cu());
     if (tpv < 1) tpv = 1;

@@ -71,7 +71,9 @@ def test_merge_row_blocks(rk, oracle_mod, Hq, Hkv, d, W, dtype):  # noqa: F811
     (64, 64, 64, 64 * 64 + 33, 32, "sinks"),      # attention pass too; one key in the second half of the last tile
     (128, 64, 128, 64 * 64 + 1, 9, "lowrank"),    # one key in the first half, none in the second, for the last splits
     (256, 64, 128, 64 * 65, 8, "sinks"),          # whole tiles; two row blocks, the second one full
-    (154, 22, 64, 64 * 62 + 31, 33, "drift"),     # nine row blocks in three workgroups
+    (154, 22, 64, 64 * 62 + 31, 33, "drift"),     # nine row blocks in three workgroups of the score pass
+    (150, 25, 64, 64 * 62 + 31, 33, "sinks"),     # ... in two that take whole tiles: three would be more than the chip holds
+    (35, 7, 128, 64 * 73 - 11, 9, "drift"),       # value-Gram pass: five heads in three workgroups
 ])
 def test_tiles_split_between_wavefronts(rk, oracle_mod, Hq, Hkv, d, L, W, structure):  # noqa: F811
     """Few rows per KV head: two wavefronts share a tile's keys and their sums meet, kept-out keys of both halves among them."""
