@@ -1174,6 +1174,10 @@ RowGeom row_geom(const Prob& pb, int n, int min_tiles, bool wide) {
 constexpr int ATTN_KS2_TILES = 16;
 // Score pass, window 32: two tiles a workgroup 12.2 us against 12.6, four 16.5 against 15.8, 32 tiles 72.6 against 63.8.
 constexpr int SCORE_KS2_TILES = 4;
+// Value-Gram pass, heads of 128 in groups of 2: one tile a workgroup 8.1 us against 10.3, four 12.3 against 13.4,
+// eight 17.3 against 17.3, 32 tiles 45.1 against 41.7; groups of 1: 7.1 and 8.0, 11.0 and 10.7, 15.8 and 14.5, 42.8
+// and 34.9; heads of 64 in groups of 4: 7.0 and 8.1, 10.2 and 10.4, 14.4 and 13.5, 36.1 and 30.0.
+constexpr int VV_KS2_TILES = 6;
 
 template <int D, int GP>
 void launch_score_pipe(const Prob& pb, const uint16_t* q, const uint16_t* k, const uint16_t* v, const ScorePtrs& w, int ldv,
@@ -1226,9 +1230,10 @@ int run_mfma(const Prob& pb, const void* q, const void* k, const void* v, const 
   if (gram) {
     constexpr int HPW = D == 128 ? 4 : 8;
     const int NTv = (pb.P + TN - 1) / TN;
-    // as for the rows: half as many heads per workgroup, at most 3/2 of the tiles
+    // as for the rows: half as many heads per workgroup, at most 3/2 of the tiles, VV_KS2_TILES of them
     const int hg4 = (pb.G + HPW / 2 - 1) / (HPW / 2), hg8 = (pb.G + HPW - 1) / HPW;
-    const bool ks2 = 2 * span_tiles(NTv, (int64_t)hg4 * pb.Hkv) <= 3 * span_tiles(NTv, (int64_t)hg8 * pb.Hkv);
+    const int64_t t4 = span_tiles(NTv, (int64_t)hg4 * pb.Hkv);
+    const bool ks2 = t4 >= VV_KS2_TILES && 2 * t4 <= 3 * span_tiles(NTv, (int64_t)hg8 * pb.Hkv);
     const int hpw = ks2 ? HPW / 2 : HPW;
     const int hg = (pb.G + hpw - 1) / hpw;
     int tpv = (int)(((int64_t)NTv * hg * pb.Hkv + n_cu() - 1) / n_cu());
