@@ -123,7 +123,7 @@ __global__ __launch_bounds__(4 * D, 4) void k_attn_combine(Prob pb, const T* __r
   constexpr int NP = RQ < 16 ? 16 / RQ : 1;              // threads that share a row's columns
   constexpr int MB = RQ < 16 ? 1 : RQ / 16;              // rows per thread, 16-row blocks of the product
   constexpr int SB = MB >= 4 ? 2 : (RQ <= 8 ? 8 : 4);    // splits in flight per row
-  constexpr int JB = MB >= 2 ? 4 : 8;   // joining keys in flight per row
+  constexpr int JB = MB >= 2 || sizeof(T) == 4 ? 4 : 8;  // joining keys in flight per row (eight of float spill registers at D = 128)
   __shared__ __attribute__((aligned(16))) float zs[RQ][ZST];             // z of the rows
   __shared__ __attribute__((aligned(16))) float xs[RQ * NP][ZST];        // partial sums of the splits, then x, then u
   __shared__ float red[NWV][RQ][2];
