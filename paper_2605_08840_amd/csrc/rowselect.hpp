@@ -385,20 +385,11 @@ __device__ __forceinline__ void bracket_ranks(int n, int ns, int k, int& r_hi, i
   r_lo = (int)kp + 2 + margin;      // > ns: no lower bound
 }
 
-// Evenly spread sample of a row in runs of RUN consecutive floats, NPT keys per thread
-// (the whole row if it has at most NPT*blockDim.x entries).  Returns the sample size.
+// Evenly spread sample of a row of more than NPT * blockDim.x entries in runs of RUN consecutive floats, NPT
+// keys per thread.  Returns the sample size.
 template <int NPT, int RUN>
 __device__ inline int block_sample_regs(const float* __restrict__ row, int n, uint32_t (&k)[NPT]) {
-  const int cap = NPT * blockDim.x;
-  if (n <= cap) {
-    float f[NPT];            // unconditional loads (clamped, then masked): all in flight together
-#pragma unroll
-    for (int j = 0; j < NPT; ++j) f[j] = row[min((int)(threadIdx.x + j * blockDim.x), n - 1)];
-#pragma unroll
-    for (int j = 0; j < NPT; ++j) k[j] = (int)(threadIdx.x + j * blockDim.x) < n ? float_key(f[j]) : 0u;
-    return n;
-  }
-  const int nch = cap / RUN;
+  const int cap = NPT * blockDim.x, nch = cap / RUN;
   const double step = (double)(n - RUN) / (double)(nch - 1);     // no integer division per sample
 #pragma unroll
   for (int j = 0; j < NPT; ++j) {
