@@ -66,11 +66,14 @@ def test_merge_row_blocks(rk, oracle_mod, Hq, Hkv, d, W, dtype):  # noqa: F811
 
 
 @pytest.mark.parametrize("Hq,Hkv,d,L,W,structure", [
-    (32, 32, 64, 64 * 32 + 5, 16, "sinks"),       # score pass with its tiles split, five keys in the last one; one row block
-    (64, 32, 128, 64 * 32 + 40, 33, "plain"),     # three row blocks; prefix seven past a tile
+    (32, 32, 64, 64 * 32 + 5, 16, "sinks"),       # score pass with its tiles split, 53 keys in the last one; one row block
+    (64, 32, 128, 64 * 32 + 40, 33, "plain"),     # three row blocks; 7 keys in the last tile
     (64, 64, 64, 64 * 64 + 33, 32, "sinks"),      # attention pass too; one key in the second half of the last tile
     (128, 64, 128, 64 * 64 + 1, 9, "lowrank"),    # one key in the first half, none in the second, for the last splits
-    (256, 64, 128, 64 * 65, 8, "sinks"),          # whole tiles; two row blocks, the second one full
+    (256, 64, 128, 64 * 65, 8, "sinks"),          # whole tiles; one row block, full
+    (256, 64, 128, 64 * 64 + 50, 16, "sinks"),    # two, both full
+    (256, 64, 128, 64 * 64 + 40, 20, "lowrank"),  # three, the last one half full
+    (256, 64, 128, 64 * 66 + 3, 32, "sinks"),     # four
     (154, 22, 64, 64 * 62 + 31, 33, "drift"),     # nine row blocks in three workgroups of the score pass
     (150, 25, 64, 64 * 62 + 31, 33, "sinks"),     # ... in two that take whole tiles: three would be more than the chip holds
     (35, 7, 128, 64 * 73 - 11, 9, "drift"),       # value-Gram pass: five heads in three workgroups

@@ -54,7 +54,7 @@ def test_score_small_cases(rk, oracle_mod, name):
 
 @pytest.mark.parametrize("name", ["bf16_mha", "bf16_sinks_g8"])
 def test_bf16_inputs_through_the_fp32_kernels(rk, oracle_mod, name):
-    """restkv_debug_force_fp32: bf16 inputs take the vector-ALU kernels (every product in FP32)."""
+    """restkv_debug_force_fp32: bf16 inputs take the FP32 kernels (every product in FP32)."""
     w = _case(name)
     q, k, v = workloads.make_qkv(w)
     wo = workloads.make_wo(w)
@@ -638,37 +638,39 @@ def test_lowrank_32k_budgets(rk, oracle_mod, budget):
                            budget=budget)
 
 
+def _both_ways(rk, w, layer):
+    """Buffers of the whole path with the two separate calls, and with restkv_score_smooth."""
+    q, k, v = workloads.make_qkv(w, layer, "cuda")
+    wo = workloads.make_wo(w, layer, "cuda")
+    p = params_for(rk, w)
+    gram = torch.empty((w.n_q_heads, w.head_dim, w.head_dim), dtype=torch.float32, device="cuda")
+    rk.restkv_prepare_wo(p, wo, gram)
+    bufs = [rk.alloc_layer_buffers(p, q.dtype, "cuda") for _ in range(2)]
+    for b, fused in zip(bufs, (False, True)):
+        rk.evict_layer(p, q, k, v, gram, b, fused=fused)
+    torch.cuda.synchronize()
+    return bufs
+
+
+def _assert_same_bits(a, b):
+    for name in ("score", "ema", "final", "aws_info", "aws_d", "idx", "k_out", "v_out"):
+        assert torch.equal(getattr(a, name), getattr(b, name)), name
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("Hq,Hkv,W,L,B,structure", [
-    (8, 2, 64, 40000, 1500, "drift"),     # G = 4, 256 rows: the fused path, several key chunks per head
+    (8, 2, 64, 40000, 1500, "drift"),     # G = 4, 256 rows, several key chunks per head
     (16, 2, 30, 33000, 700, "plain"),     # G = 8, a row block that is not full
-    (6, 2, 40, 36000, 3000, "sinks"),     # G = 3 padded to 4, budget above the sample-based bracket
+    (6, 2, 40, 36000, 3000, "sinks"),     # G = 3 padded to 4, a large budget
 ])
-def test_fused_score_smooth_matches_separate_calls(rk, Hq, Hkv, W, L, B, structure):
-    """restkv_score_smooth against restkv_score + restkv_smooth on the same inputs: same raw score
-    bit for bit, EMA to rounding (weighted sum vs recursion), identical top-B statistics, window
-    and final score to rounding, identical selection unless two final scores are within rounding."""
+def test_fused_score_smooth_matches_separate_calls(rk, oracle_mod, Hq, Hkv, W, L, B, structure):
+    """restkv_score_smooth at prefixes beyond the one-launch statistics: every stage against the oracle, and the
+    outputs of restkv_score + restkv_smooth bit for bit (it runs these two)."""
     w = workloads.WORKLOADS["drift_128k"].with_(n_layers=1, n_q_heads=Hq, n_kv_heads=Hkv, seq_len=L, window=W,
                                                budget=B, structure=structure, d_model=512, beta=300.0)
-    q, k, v = workloads.make_qkv(w, 0, "cuda")
-    wo = workloads.make_wo(w, 0, "cuda")
-    p = params_for(rk, w)
-    gram = torch.empty((Hq, w.head_dim, w.head_dim), dtype=torch.float32, device="cuda")
-    rk.restkv_prepare_wo(p, wo, gram)
-    a = rk.alloc_layer_buffers(p, q.dtype, "cuda")
-    b = rk.alloc_layer_buffers(p, q.dtype, "cuda")
-    rk.evict_layer(p, q, k, v, gram, a)
-    rk.evict_layer(p, q, k, v, gram, b, fused=True)
-    torch.cuda.synchronize()
-    P = w.prefix
-    assert torch.equal(a.score[..., :P], b.score[..., :P])
-    np.testing.assert_allclose(b.ema[..., :P].cpu().numpy(), a.ema[..., :P].cpu().numpy(), rtol=2e-5, atol=1e-30)
-    assert torch.equal(a.aws_d, b.aws_d), (a.aws_d, b.aws_d)
-    assert torch.equal(a.aws_info, b.aws_info)
-    fa, fb = a.final[..., :P].cpu().numpy(), b.final[..., :P].cpu().numpy()
-    np.testing.assert_allclose(fb, fa, rtol=5e-5, atol=1e-30)
-    for g in range(Hkv):
-        check_selection(b.idx[g].cpu().numpy(), fa[g].astype(np.float64), W, B, 2e-4)
+    _full_size_layer_check(rk, oracle_mod, w, layer=0, heads=range(Hkv), fused=True)
+    _assert_same_bits(*_both_ways(rk, w, 0))
+
 
 @pytest.mark.gpu
 def test_decode_reeviction_folded_layers(rk, oracle_mod):
@@ -702,27 +704,9 @@ def test_decode_reeviction_folded_layers(rk, oracle_mod):
             np.testing.assert_array_equal(buf.k_out[r].float().cpu().numpy(), kl[g].float().numpy()[idx[r]])
 
 def test_fused_call_full_size_matches_separate_calls(rk):
-    """The fused call at the benchmark configuration (drift_128k, one layer): same raw score,
-    same top-B statistics and window, final score to rounding, selection equal up to near-ties."""
-    w = workloads.WORKLOADS["drift_128k"]
-    q, k, v = workloads.make_qkv(w, 1, "cuda")
-    wo = workloads.make_wo(w, 1, "cuda")
-    p = params_for(rk, w)
-    gram = torch.empty((w.n_q_heads, w.head_dim, w.head_dim), dtype=torch.float32, device="cuda")
-    rk.restkv_prepare_wo(p, wo, gram)
-    del wo
-    a = rk.alloc_layer_buffers(p, q.dtype, "cuda")
-    b = rk.alloc_layer_buffers(p, q.dtype, "cuda")
-    rk.evict_layer(p, q, k, v, gram, a)
-    rk.evict_layer(p, q, k, v, gram, b, fused=True)
-    torch.cuda.synchronize()
-    P = w.prefix
-    assert torch.equal(a.score[..., :P], b.score[..., :P])
-    assert torch.equal(a.aws_d, b.aws_d) and torch.equal(a.aws_info, b.aws_info)
-    fa, fb = a.final[..., :P].cpu().numpy(), b.final[..., :P].cpu().numpy()
-    np.testing.assert_allclose(fb, fa, rtol=5e-5, atol=1e-30)
-    for g in range(w.n_kv_heads):
-        check_selection(b.idx[g].cpu().numpy(), fa[g].astype(np.float64), w.window, w.budget, 2e-4)
+    """The fused call at the benchmark configuration (drift_128k, one layer): the outputs of the two separate
+    calls bit for bit.  (test_drift_128k_fused_call_against_oracle checks them.)"""
+    _assert_same_bits(*_both_ways(rk, workloads.WORKLOADS["drift_128k"], 1))
 
 
 @pytest.mark.gpu
