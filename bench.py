@@ -93,29 +93,19 @@ STAGE_KERNEL = {"attn_partial": "k_attn_pipe", "vv": "k_vv_pipe", "score": "k_sc
                 "compact": "k_compact", "box": "k_box"}
 
 
-def measured_traffic(workload: str, stage: str):
-    """HBM bytes per launch of the stage's kernel from the committed counter summary
-    (profiles/hbm_traffic_<workload>.md, column 'HBM bytes'), or None."""
+def measured_traffic(workload: str, kern):
+    """HBM bytes per launch of a kernel from the committed counter summary
+    (profiles/hbm_traffic_<workload>.md, column 'HBM bytes'), or None: also if the summary was taken
+    with other sources than the library's present ones (its line "Sources <digest>")."""
+    from paper_2605_08840_amd.build import source_digest
     path = os.path.join(ROOT, "profiles", f"hbm_traffic_{workload}.md")
-    kern = STAGE_KERNEL.get(stage)
     if kern is None or not os.path.exists(path):
         return None
-    for line in open(path):
-        cells = [c.strip() for c in line.strip().strip("|").split("|")]
-        if len(cells) >= 6 and cells[0].strip("`") == kern:
-            try:
-                return float(cells[5])
-            except ValueError:
-                return None
-    return None
-
-
-def measured_traffic_kernel(workload: str, kern: str):
-    """The same lookup by kernel name."""
-    path = os.path.join(ROOT, "profiles", f"hbm_traffic_{workload}.md")
-    if not os.path.exists(path):
+    with open(path) as f:
+        lines = f.read().splitlines()
+    if not any(line.startswith(f"Sources {source_digest()}") for line in lines):
         return None
-    for line in open(path):
+    for line in lines:
         cells = [c.strip() for c in line.strip().strip("|").split("|")]
         if len(cells) >= 6 and cells[0].strip("`") == kern:
             try:
@@ -245,7 +235,7 @@ def main():
         dom = max((s for s in probe if s != "gram" and stage_work(w, s) != (0.0, 0.0)), key=lambda s: probe[s][0])
 
     # Timed region: exactly `steps` steps.  Only the dominant stage keeps its events (two per
-    # layer); bracketing all seventeen kernels of a layer costs about a tenth of the step time.
+    # layer); bracketing every kernel of a layer costs about a tenth of the step time.
     rk.restkv_timing_enable([dom] if dom else False)
     torch.cuda.synchronize()
     marks = [torch.cuda.Event(enable_timing=True) for _ in range(args.steps + 1)]   # step boundaries on the launch stream
@@ -284,7 +274,7 @@ def main():
         div = 1e12 if s["bound"] == "mfma" else 1e9
         roof = {"kernel": STAGE_KERNEL.get(dom, dom), "stage": dom, "bound": s["bound"],
                 "achieved": s["achieved"] / div, "peak": s["peak"] / div,
-                "unit": unit, "frac": s["achieved"] / s["peak"], "traffic": measured_traffic(w.name, dom),
+                "unit": unit, "frac": s["achieved"] / s["peak"], "traffic": measured_traffic(w.name, STAGE_KERNEL.get(dom)),
                 "avg_ms": s["ms"] / s["launches"]}
         # the same byte mix through a plain streaming kernel on this part, measured now
         rw = stage_read_write(w, dom)
@@ -306,24 +296,6 @@ def main():
         torch.cuda.synchronize()
         ms_alt = (time.perf_counter() - t3) * 1e3 / args.steps
         overlap = {"streams": n_alt, "ms_per_step": ms_alt, "value": tokens / (ms_alt * 1e-3)}
-
-    # The same steps with restkv_score_smooth in place of restkv_score + restkv_smooth.
-    fused_call = None
-    if not args.fused and not args.no_overlap:
-        rk.restkv_timing_enable(False)
-
-        def step_fused():
-            for (q, k, v, gram) in layers:
-                rk.evict_layer(p, q, k, v, gram, bufs[0], fused=True)
-
-        step_fused()
-        torch.cuda.synchronize()
-        t5 = time.perf_counter()
-        for _ in range(args.steps):
-            step_fused()
-        torch.cuda.synchronize()
-        ms_fu = (time.perf_counter() - t5) * 1e3 / args.steps
-        fused_call = {"ms_per_step": ms_fu, "value": tokens / (ms_fu * 1e-3)}
 
     # The same steps with the window rows' attention output and log-sum-exp handed in (as a prefill
     # attention kernel would have them): restkv_score_from_attention replaces restkv_score.
@@ -437,9 +409,8 @@ def main():
         f_exec = 2.0 * unit + 3.0 * 2.0 * Hq * Wn * Pn * d + 2.0 * tri * 2.0 * Hq * Pn * d * d
         ms_call = sum(per[n]["ms"] for n in call_stages)
         b_alg = 2.0 * Hkv * Ln * d * (4 if w.dtype == "f32" else 2) + 4.0 * Hkv * Wn * Pn
-        tr = [measured_traffic(w.name, n) for n in ("attn_partial", "vv", "score")]
-        trc = measured_traffic_kernel(w.name, "k_attn_combine")
-        traffic = sum(tr) + (trc or 0.0) if all(x is not None for x in tr) else None
+        tr = [measured_traffic(w.name, n) for n in ("k_attn_pipe", "k_attn_combine", "k_vv_pipe", "k_score_pipe")]
+        traffic = sum(tr) if all(x is not None for x in tr) else None
         score_call = {"ms_per_layer": ms_call, "f_alg": f_alg, "frac_mfma_alg": f_alg / (ms_call * 1e-3) / peak_mfma,
                       "executed_over_alg": f_exec / f_alg, "algorithmic_bytes": b_alg,
                       "traffic_over_alg": (traffic / b_alg) if traffic else None}
@@ -461,7 +432,6 @@ def main():
         "roofline": roof,
         "cpu_baseline": cpu,
         "overlap": overlap,
-        "fused_call": fused_call,
         "stats_in": stats_in,
         "score_call": score_call,
         "folded": folded,

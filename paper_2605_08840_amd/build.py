@@ -2,6 +2,7 @@
 from __future__ import annotations
 
 import glob
+import hashlib
 import os
 import subprocess
 import sys
@@ -27,6 +28,18 @@ FLAGS = [
 
 def sources():
     return sorted(glob.glob(os.path.join(CSRC, "*.hip")))
+
+
+def source_digest() -> str:
+    """First 16 hex digits of a hash over the library's sources and build flags: measurements kept in files
+    name it, so that a reader can tell whether they were taken with the kernels at hand."""
+    h = hashlib.sha256()
+    for path in sorted(glob.glob(os.path.join(CSRC, "*")) + glob.glob(os.path.join(ROOT, "include", "*.h"))):
+        h.update(os.path.basename(path).encode() + b"\0")
+        with open(path, "rb") as f:
+            h.update(f.read())
+    h.update(" ".join(x for x in FLAGS if not os.path.isabs(x)).encode())
+    return h.hexdigest()[:16]
 
 
 # host-side sanitizers only: each -fsanitize= directly after -Xarch_host, device code untouched

@@ -109,3 +109,17 @@ def test_product_and_oracle_do_not_know_each_other():
         text = open(path).read()
         assert "paper_2605_08840_amd" not in text and "librestkv.so" not in text and "restkv.h" not in text, path
     assert not re.search(r"\boracle\b", open(os.path.join(root, "include", "restkv.h")).read())
+
+
+def test_bench_reports_counters_of_the_present_kernels_only(tmp_path, monkeypatch):
+    """HBM bytes of a counter summary are reported if it names the digest of the library's sources, else None."""
+    import bench
+    from paper_2605_08840_amd.build import source_digest
+    (tmp_path / "profiles").mkdir()
+    monkeypatch.setattr(bench, "ROOT", str(tmp_path))
+    row = "| `k_box` | 1 | 2 | 3 | 4 | 7 | 7 | 1.00 |\n"
+    for digest, want in ((source_digest(), 7.0), ("0" * 16, None)):
+        (tmp_path / "profiles" / "hbm_traffic_x.md").write_text(f"# counters\n\nSources {digest}.\n\n{row}")
+        assert bench.measured_traffic("x", "k_box") == want
+        assert bench.measured_traffic("x", "k_none") is None
+    assert bench.measured_traffic("y", "k_box") is None and bench.measured_traffic("x", None) is None
