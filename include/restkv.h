@@ -111,7 +111,7 @@ size_t restkv_workspace_bytes(const restkv_params* p);
  *         h*d .. (h+1)*d-1 belong to query head h (a framework weight stored
  *         [out,in] must be passed transposed).
  *   gram  [Hq, d, d] float32 out; symmetric by construction (restkv_score relies
- *         on M_h[i][j] == M_h[j][i] and reads the upper triangle only).
+ *         on M_h[i][j] == M_h[j][i]: some kernels read one triangle, some all).
  * Weight-only: run once per layer, not per request.  Accumulates in float64.
  */
 int restkv_prepare_wo(const restkv_params* p, const float* w_o, int64_t d_model,
@@ -273,8 +273,8 @@ int restkv_stream_reference(const void* src, size_t read_bytes, void* dst, size_
                             void* stream);
 
 /*
- * Debug aid: with on != 0 restkv_score runs bf16 inputs through the FP32 vector kernels
- * instead of the MFMA kernels (same stages, every product in FP32).  Process-wide.
+ * Debug aid: with on != 0 restkv_score runs bf16 inputs through the kernels for float32 inputs
+ * (same stages, every product in FP32 on the matrix cores).  Process-wide.
  */
 int restkv_debug_force_fp32(int on);
 

@@ -167,7 +167,7 @@ __global__ __launch_bounds__(4 * D, 4) void k_attn_combine(Prob pb, const T* __r
   if (gram) {
     const float* Mh = gram + ((int64_t)h * D + 16 * wv + (l & 15)) * D + 4 * (l >> 4);
 #pragma unroll
-    for (int a = 0; a < D / 16; ++a) mreg[a] = *(const f32x4_t*)(Mh + 16 * a);
+    for (int a = 0; a < D / 16; ++a) mreg[a] = quad_of(Mh + 16 * a);      // (the caller's array: float alignment)
   }
   for (int r = tid / SW; r < RQ; r += NT / SW) {
     const int row = h * pb.W + min(i0 + r, pb.W - 1);

@@ -311,8 +311,7 @@ __global__ __launch_bounds__(512) void k_vv_pipe(Prob pb, const uint16_t* __rest
     auto load_frag = [&](int rb, int ks, bf16x8& hi8, bf16x8& lo8) {
       const int i = 32 * rb + rr;                    // Gram row of this lane
       const float* mrow = gram + ((int64_t)h * D + i) * D + 16 * ks + 8 * hf;
-      const f32x4 x0 = *(const f32x4*)mrow;
-      const f32x4 x1 = *(const f32x4*)(mrow + 4);
+      const f32x4 x0 = quad_of(mrow), x1 = quad_of(mrow + 4);     // (the caller's array: float alignment)
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
         const int j = 16 * ks + 8 * hf + e;

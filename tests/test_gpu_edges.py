@@ -5,7 +5,7 @@ import pytest
 import torch
 
 import workloads
-from gpu_util import assert_score_close, oracle_score, params_for, run_gpu_layer
+from gpu_util import assert_score_close, attention_statistics, oracle_score, params_for, run_gpu_layer
 from test_gpu_parity import _score_against_oracle_then_every_stage_exactly, _smooth_select_inputs, rk  # noqa: F401
 
 pytestmark = pytest.mark.gpu
@@ -274,3 +274,29 @@ def test_exact_search_of_long_rows(rk, P, kind):  # noqa: F811
         s[:] = 0.25
         s[:, :, P - 4001:] = 8.0
     _statistics_and_selection_by_key(rk, s, np.ascontiguousarray(s[:, 0]), B)
+
+
+@pytest.mark.parametrize("dtype,d", [("f32", 64), ("bf16", 64), ("bf16", 128)])
+def test_gram_and_statistics_at_any_float_address(rk, dtype, d):  # noqa: F811
+    """gram, attn_out and lse need no more than the alignment of their floats: same results as from aligned arrays."""
+    w = workloads.small_case(Hq=4, Hkv=2, d=d, L=300, W=9, B=40, dtype=dtype, D=96, seed=79)
+    q, k, v = (x.cuda() for x in workloads.make_qkv(w))
+    p = params_for(rk, w)
+    gram = torch.empty((4, d, d), dtype=torch.float32, device="cuda")
+    rk.restkv_prepare_wo(p, workloads.make_wo(w).cuda(), gram)
+    out, lse = attention_statistics(q.cpu(), k.cpu(), v.cpu(), w.window)
+
+    def shifted(x):
+        y = torch.empty(x.numel() + 1, dtype=x.dtype, device="cuda")[1:].view(x.shape)
+        return y.copy_(x)
+
+    got = []
+    for move in (lambda x: x.cuda(), shifted):
+        buf = rk.alloc_layer_buffers(p, q.dtype, "cuda")
+        g, o, s = move(gram), move(out), move(lse)
+        rk.restkv_score(p, q, k, v, g, buf.score, buf.workspace)
+        one = buf.score.clone()
+        rk.restkv_score_from_attention(p, q, k, v, g, o, s, buf.score, buf.workspace)
+        torch.cuda.synchronize()
+        got.append((one, buf.score.clone()))
+    assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
