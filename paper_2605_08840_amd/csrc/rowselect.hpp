@@ -420,9 +420,10 @@ __device__ inline int block_sample_regs(const float* __restrict__ row, int n, ui
 // Bracket {klo, khi} (keys) of the k-th largest of row[0..n): the k-th largest key lies in
 // (klo, khi] unless the sample misled us.  khi = 0xFFFFFFFF / klo = 0 mean "unbounded".  The bins of
 // the two ranks are bracket enough, unless a few outliers stretch the bins until they are wide
-// next to the bracket itself: then the range between them is cut again.  (Bins up to 1/64 of it pass:
-// rows of 128k log-normal scores need no second cut.  With 1/16, rows of 150k scores, four of them 2^60 above
-// the rest, held more than 4096 candidates and were searched exactly: smoothing 386 us against 103.)
+// next to the bracket itself: then the range between them is cut again.  (Bins up to 1/32 of it pass:
+// log-normal scores need no second cut, which costs 1 us; with 1/64, rows of 40k of them do.  With 1/16,
+// rows of 150k scores, four of them 2^60 above the rest, held more than 4096 candidates and were
+// searched exactly: smoothing 386 us against 103.)
 template <int NT, int NPT, int RUN>
 __device__ __forceinline__ void block_bracket(const float* __restrict__ row, int n, int k, CutSmem& sm, uint32_t& klo,
                                               uint32_t& khi) {
@@ -442,7 +443,7 @@ __device__ __forceinline__ void block_bracket(const float* __restrict__ row, int
     const uint32_t above = sm.res[0][1];
     hi = top;
     lo = bot;
-    if (shift == 0 || (1u << shift) <= ((hi - lo) >> 6)) break;     // (block-uniform)
+    if (shift == 0 || (1u << shift) <= ((hi - lo) >> 5)) break;     // (block-uniform)
     kk[0] -= above;
     kk[1] -= above;
   }
