@@ -71,7 +71,8 @@ __global__ __launch_bounds__(256) void k_stats_fill(int rows, const float* __res
 //     columns and take every (16 / RQ)-th split, so that few rows still mean many loads in flight.
 //   * u = z M_h (and y = x M_h where a row has a champion) is a 16-row product on
 //     v_mfma_f32_16x16x4_f32: a wavefront owns 16 columns, its Gram entries stay in registers
-//     (loaded first, every entry needed by exactly one lane), z and x are LDS operands.
+//     (loaded first, every entry needed by exactly one lane), z and x are LDS operands.  Up to eight rows
+//     z and x share the block (a second block for x: whole path at 2112 tokens 70.5 us instead of 67.7).
 // Bound by latency (three dependent round trips to memory) until the rows fill the chip, then by the
 // partial sums, Gram matrices and operands it moves.  Against a kernel of four rows per workgroup
 // with u on the vector ALU and value rows fetched for every split: 65536 rows x 1 split (32 layers of

@@ -64,7 +64,8 @@ SelPtrs sel_ptrs(const Prob& pb, char* ws, size_t* bytes) {
 
 // One head by one workgroup, its row in registers: cut, selected positions as a bit per position in
 // LDS, ordered write.  Three launches (scan, finish, emission) took 25.9 us at 2k tokens, 8 heads, and
-// 22 us at 1k, 2 heads; this takes 6.3 and 4.2.  grid (Hkv), NT threads.
+// 22 us at 1k, 2 heads; this takes 6.3 and 4.2.  At the longest row that fits, 32768 positions, 8 heads:
+// 12.3 us, and 14.9 by the two launches for longer rows.  grid (Hkv), NT threads.
 template <int NT, int NPT, bool VEC>
 __global__ __launch_bounds__(NT, NT == 1024 ? 4 : 1) void k_sel_row(Prob pb, const float* __restrict__ fin,
                                                                    int32_t* __restrict__ idx) {
