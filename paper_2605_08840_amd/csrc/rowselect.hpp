@@ -214,8 +214,10 @@ __device__ __forceinline__ void block_range(const uint32_t (&key)[NPT], CutSmem&
   __syncthreads();
 #pragma unroll
   for (int j = 0; j < NT / 64; ++j) { mx = max(mx, sm.ws[0][j]); nlo = max(nlo, sm.ws[1][j]); }
-  lo = ~nlo;
-  hi = mx;
+  // (scalars where vector registers are short: a spill in the 1024 x 16 kernel costs 3 us; rows of 20k and more,
+  // with registers to spare, are 0.2 us faster without the two instructions)
+  lo = NPT <= 16 ? uniform(~nlo) : ~nlo;
+  hi = NPT <= 16 ? uniform(mx) : mx;
 }
 
 // width of a bin (log2) that covers [lo, hi] with CUT_BINS of them
@@ -275,11 +277,13 @@ __device__ __forceinline__ void block_bins(V val, uint32_t lo, uint32_t hi, int 
 // Cut of the k largest entries: an entry is one of them iff (key, ~position) >= (tau, ~cut), i.e.
 // equal keys are taken lowest position first.  key: NPT per thread, 0 where a slot is empty; pos(j):
 // position of slot j (below 2^31); every key lies in [lo, hi] (lo >= 1) and there are at least k >= 1
-// of them.  False (nothing found) where there are fewer: the caller then searches the row in another
-// way, or knows that it cannot be (a whole row in [its smallest key, its largest]).  The search ends for any
-// input.  All NT threads call, all receive the result.  pos gets the thread index as an argument
+// of them.  False (nothing found) where there are fewer: the caller then searches the row in another way.
+// WHOLE: the keys are a whole row of at least k entries (every float is one, whatever its bits) and [lo, hi] is
+// their block_range, so that every rank exists and the way out for one that does not, which costs
+// the 1024 x 16 kernel two spilled registers, is left out.  Either way each round narrows the range, and
+// the search ends.  All NT threads call, all receive the result.  pos gets the thread index as an argument
 // that the compiler cannot see through: it would keep NPT positions in registers otherwise.
-template <int NT, int NPT, typename P>
+template <int NT, bool WHOLE, int NPT, typename P>
 __device__ __forceinline__ bool block_cut(const uint32_t (&key)[NPT], P pos, uint32_t k, uint32_t lo, uint32_t hi,
                                           CutSmem& sm, uint32_t& tau, uint32_t& cut) {
   bool tie = false;                      // equal keys straddle the cut: the search goes on over inverted positions
@@ -293,7 +297,7 @@ __device__ __forceinline__ bool block_cut(const uint32_t (&key)[NPT], P pos, uin
     if (tie) block_bins<NT, NPT, 1>(val, lo, hi, shift, kk, sm);
     else block_bins<NT, NPT, 1>([&](int j) { return key[j]; }, lo, hi, shift, kk, sm);
     const uint32_t cnt = uniform(sm.res[0][2]);
-    if (cnt == 0u) return false;
+    if (!WHOLE && cnt == 0u) return false;
     k -= uniform(sm.res[0][1]);
     const uint32_t off = uniform(sm.res[0][0]) << shift;
     hi = lo + off + min(hi - lo - off, (1u << shift) - 1u);      // (no sum that could wrap)
@@ -329,11 +333,12 @@ __device__ __forceinline__ bool block_cut(const uint32_t (&key)[NPT], P pos, uin
       return true;
     }
     bool equal = shift == 0;
-    if (NPT <= 16 && !tie && !equal) {
-      // Many entries in one bin are often equal ones at its lower end (the smallest of the row: scores that
+    if (NPT <= 16 && !tie && !equal && cnt > 2u * NT) {
+      // That many entries in one bin are nearly always equal ones at its lower end (the smallest of the row: scores that
       // underflowed to 0).  The further histograms would be chains of adds to one word: count them.  (512 rows
-      // of 16384 scores, 99.9 % zeros: 233 -> 109 us.  Not with 32 entries per thread, where the longer code costs
-      // every row of 20k 2 % and one workgroup fills a compute unit.)
+      // of 16384 scores, 99.9 % zeros: 233 -> 109 us.  Not for any bin that is cut again: 256 heavy-tailed rows of
+      // 10k 12.4 -> 16.0 us.  Not with 32 entries per thread, where the longer code costs every row of 20k 2 % and
+      // one workgroup fills a compute unit.)
       uint32_t c = 0;
 #pragma unroll
       for (int j = 0; j < NPT; ++j) c += (uint32_t)__popcll(__ballot(key[j] == lo));

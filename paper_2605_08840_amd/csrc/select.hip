@@ -86,7 +86,7 @@ __global__ __launch_bounds__(NT, NT == 1024 ? 4 : 1) void k_sel_row(Prob pb, con
   for (int x = tid; x < NWORD; x += NT) bits[x] = 0u;
   block_range<NT>(key, cs, lo, hi);
   auto pos = [](int j, int t) { return row_pos<NT, NPT, VEC>(j, t); };
-  block_cut<NT>(key, pos, (uint32_t)k, lo, hi, cs, tau, cut);      // (the row has its k entries)
+  block_cut<NT, true>(key, pos, (uint32_t)k, lo, hi, cs, tau, cut);
 #pragma unroll
   for (int j0 = 0; j0 < NPT; j0 += 4) {
     uint32_t m[4];
@@ -240,7 +240,7 @@ __global__ __launch_bounds__(512) void k_sel_emit(Prob pb, const float* __restri
 #pragma unroll
       for (int j = 0; j < FPT; ++j) ck[j] = (uint32_t)(tid + j * NT) < nc ? float_key(fv[j]) : 0u;
       // every candidate lies inside the bracket (th.x, th.y]
-      found = block_cut<NT>(ck, [&](int j, int) { return iv[j]; }, (uint32_t)k - n_above, float_key(th.x) + 1u, float_key(th.y), cs, tau, cut);
+      found = block_cut<NT, false>(ck, [&](int j, int) { return iv[j]; }, (uint32_t)k - n_above, float_key(th.x) + 1u, float_key(th.y), cs, tau, cut);
 #pragma unroll
       for (int j = 0; j < FPT; ++j)
         sel_before += ck[j] && (uint32_t)iv[j] < first && in_cut(ck[j], (uint32_t)iv[j], tau, cut) ? 1u : 0u;

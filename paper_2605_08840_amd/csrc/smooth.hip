@@ -304,7 +304,7 @@ __global__ __launch_bounds__(512) void k_row_finish(Prob pb, const float* __rest
     for (int j = 0; j < NS; ++j) ck[j] = (uint32_t)(threadIdx.x + j * NT) < nc ? float_key(fv[j]) : 0u;
     uint32_t tau, cut;
     // every candidate lies inside the bracket (th.x, th.y]
-    if (!block_cut<NT>(ck, [&](int j, int) { return iv[j]; }, need, float_key(th.x) + 1u, float_key(th.y), cs, tau, cut)) return false;
+    if (!block_cut<NT, false>(ck, [&](int j, int) { return iv[j]; }, need, float_key(th.x) + 1u, float_key(th.y), cs, tau, cut)) return false;
 #pragma unroll
     for (int j = 0; j < NS; ++j) acc += ck[j] && in_cut(ck[j], (uint32_t)iv[j], tau, cut) ? (unsigned long long)iv[j] : 0ull;
     return true;
@@ -353,7 +353,7 @@ __global__ __launch_bounds__(NT, NT == 1024 && NPT == 16 ? 8 : 4) void k_short_r
     load_row_keys<NT, NPT, VEC>(score + (int64_t)r * pb.ld, pb.P, key);
     block_range<NT>(key, cs, lo, hi);
     auto pos = [](int j, int t) { return row_pos<NT, NPT, VEC>(j, t); };
-    block_cut<NT>(key, pos, (uint32_t)k, lo, hi, cs, tau, cut);      // (the row has its k entries)
+    block_cut<NT, true>(key, pos, (uint32_t)k, lo, hi, cs, tau, cut);
     uint32_t acc = 0;                              // (NPT positions below 2^15)
 #pragma unroll
     for (int j = 0; j < NPT; ++j) {
