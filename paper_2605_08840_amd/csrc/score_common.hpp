@@ -348,12 +348,14 @@ __global__ __launch_bounds__(4 * D, 4) void k_attn_combine(Prob pb, const T* __r
       }
     }
   }
-  if (champ) __syncthreads();                    // (x has been read; u takes its place)
+  // u takes the place of the x that have been read, or of partial sums that nobody reads any more
+  constexpr int UB = RQ <= 8 ? RQ : 0;
+  if (RQ > 8 && champ) __syncthreads();
 #pragma unroll
   for (int m = 0; m < MB; ++m)
 #pragma unroll
     for (int j = 0; j < 4; ++j)
-      if (16 * m + 4 * kq + j < RQ) xs[16 * m + 4 * kq + j][c] = u[m][j];
+      if (16 * m + 4 * kq + j < RQ) xs[UB + 16 * m + 4 * kq + j][c] = u[m][j];
   __syncthreads();
   for (int r = tid; r < RQ; r += NT) {
     if (i0 + r >= pb.W) break;
@@ -384,7 +386,7 @@ __global__ __launch_bounds__(4 * D, 4) void k_attn_combine(Prob pb, const T* __r
       uint32_t hi[4], lo[4];
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
-        const float ue = xs[r][8 * c8 + e];
+        const float ue = xs[UB + r][8 * c8 + e];
         const uint32_t ub = __float_as_uint(ue);
         const uint32_t hb = (ub + 0x7FFFu + ((ub >> 16) & 1u)) & 0xFFFF0000u;      // round to nearest even (u is finite)
         const uint32_t lb = __float_as_uint(ue - __uint_as_float(hb));
@@ -399,7 +401,7 @@ __global__ __launch_bounds__(4 * D, 4) void k_attn_combine(Prob pb, const T* __r
   } else {
     for (int x = tid; x < RQ * (D / 4); x += NT) {
       const int r = x / (D / 4), cc = 4 * (x % (D / 4));
-      if (i0 + r < pb.W) *(f32x4_t*)(o.rs_u + ((int64_t)h * pb.W + i0 + r) * D + cc) = *(const f32x4_t*)&xs[r][cc];
+      if (i0 + r < pb.W) *(f32x4_t*)(o.rs_u + ((int64_t)h * pb.W + i0 + r) * D + cc) = *(const f32x4_t*)&xs[UB + r][cc];
     }
   }
 }

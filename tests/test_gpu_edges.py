@@ -228,16 +228,14 @@ def test_fp32_scores_of_subnormal_weights(rk, oracle_mod, d):  # noqa: F811
         assert not bad.any(), (got[g][bad][:3], Ig[bad][:3], tol[bad][:3])
 
 
-@pytest.mark.parametrize("dtype", ["bf16", "f32"])
-@pytest.mark.parametrize("d,late", [(64, False), (128, False), (128, True)])
+@pytest.mark.parametrize("dtype,d,late", [("bf16", 64, False), ("bf16", 128, False), ("f32", 64, False), ("f32", 128, False),
+                                          ("f32", 128, True)])
 def test_largest_key_whose_value_lies_near_the_output(rk, oracle_mod, dtype, d, late):  # noqa: F811
     """A query's largest key holds 0.4 of its attention and its value differs from every other's, c, by 2^-7 c: in the
     expanded distance |z|^2 - 2 z.v + |v|^2 the terms cancel to 2^-14 of their size, the difference z_rest - v of
     the leave-one-out form (0 for the other keys, whose value is the output of the others) does not.  Weights of equal
     logits are equal, so the output of the other keys is c to FP32 rounding and the key's score to a few 2^-24 * 2^7.
-    late: the key comes last, and never held more than half of the mass (the matrix-core path keeps only such keys)."""
-    if late and dtype == "bf16":
-        pytest.skip("the matrix-core path evaluates a key by the leave-one-out form if it held more than half on arrival")
+    late: the key comes last and never held more than half of the mass (the matrix-core path keeps no such key)."""
     w = workloads.small_case(Hq=2, Hkv=2, d=d, L=606, W=6, B=60, dtype=dtype, D=2 * d, seed=73)
     q, k, v = workloads.make_qkv(w)
     wo = workloads.make_wo(w)
