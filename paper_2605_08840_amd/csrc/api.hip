@@ -2,7 +2,9 @@
 // Everything behind these entry points is a hand-written HIP kernel for gfx950.
 #include <math.h>
 
-#include "common.hpp"
+#include <algorithm>
+
+#include "score_common.hpp"
 
 namespace restkv {
 
@@ -59,7 +61,6 @@ ScoreWs score_ws(const Prob& pb) {
   w.rs_zz = take(rows * 4);
   w.rs_nstar = take(rows * 4);
   w.rs_istar = take(rows * 4);
-  w.rs_u = take(rows * (size_t)pb.d * 4);
   w.vv = take((size_t)pb.Hq * w.ldv * 4);
   // operand-ordered copies for the matrix-core path: 32-row blocks hold Gp (power of two >= G)
   // heads of 32/Gp window positions
@@ -70,7 +71,8 @@ ScoreWs score_ws(const Prob& pb) {
     const int iw = 32 / gp;
     w.nwb = (pb.W + iw - 1) / iw;
   }
-  w.op = take((size_t)3 * pb.Hkv * w.nwb * 32 * pb.d * 2);
+  // (the FP32 path leaves q and u of every head in planes there instead)
+  w.op = take(std::max((size_t)3 * pb.Hkv * w.nwb * 32 * pb.d * 2, (size_t)pb.Hq * row_items(pb.W) * 2 * row_item(pb.d)));
   w.bytes = off;
   return w;
 }

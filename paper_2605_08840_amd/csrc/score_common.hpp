@@ -8,7 +8,7 @@ namespace restkv {
 
 struct ScorePtrs {
   float* part_m; float* part_mx; int* part_n; float* part_ref; float* part_l; float* part_z;
-  float* rs_m; float* rs_l; float* rs_zz; int* rs_nstar; float* rs_istar; float* rs_u;
+  float* rs_m; float* rs_l; float* rs_zz; int* rs_nstar; float* rs_istar;
   float* vv;
   uint16_t* op;
 };
@@ -21,10 +21,77 @@ inline ScorePtrs score_ptrs(char* ws, const ScoreWs& lay) {
   p.part_z = (float*)(ws + lay.part_z);
   p.rs_m = (float*)(ws + lay.rs_m); p.rs_l = (float*)(ws + lay.rs_l); p.rs_zz = (float*)(ws + lay.rs_zz);
   p.rs_nstar = (int*)(ws + lay.rs_nstar); p.rs_istar = (float*)(ws + lay.rs_istar);
-  p.rs_u = (float*)(ws + lay.rs_u); p.vv = (float*)(ws + lay.vv);
+  p.vv = (float*)(ws + lay.vv);
   p.op = (uint16_t*)(ws + lay.op);
   return p;
 }
+
+// One 1 KiB asynchronous copy global -> LDS: lane i moves the 16 bytes at base + voff_i to LDS bytes
+// [16 i, 16 i + 16) of lds_dst.  base and lds_dst are wave-uniform.  Issued from inline asm and waited for
+// with explicit s_waitcnt vmcnt(n).
+__device__ __forceinline__ void dma_1k(const void* base, uint32_t voff, void* lds_dst) {
+  const uint32_t dst =
+      __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)lds_dst);
+  const uint64_t sb = (uint64_t)base;
+  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)sb);
+  const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(sb >> 32));
+  const uint64_t ub = ((uint64_t)hi << 32) | lo;
+  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(voff), "s"(ub), "s"(dst)
+               : "memory", "m0");
+}
+
+// ---- planes -------------------------------------------------------------------
+// FP32 values as bf16 planes: x = h + m + l, h the bf16 nearest to x, m the nearest to what is left, l the rest
+// (exact: 8 + 8 + 8 bits).  A bf16 value has one plane.
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+template <typename T> inline constexpr int planes_of = 3;
+template <> inline constexpr int planes_of<bf16_t> = 1;
+
+// NP planes of eight values, as operand registers
+template <int NP>
+struct Op { uint4 p[NP]; };
+__device__ __forceinline__ bf16x8 as_bf16x8(uint4 u) {
+  union { uint4 u; bf16x8 b; } x;
+  x.u = u;
+  return x.b;
+}
+template <int NP>
+__device__ __forceinline__ Op<NP> split8(const float (&x)[8]) {
+  Op<NP> o;
+  uint32_t w[NP][4];
+  // (-1, 0) and (0, -1) as scalar registers: which half an inline constant of this instruction fills is not relied on
+  uint32_t lo = 0x0000BF80u, hi = 0xBF800000u;
+  if (NP > 1) asm("" : "+s"(lo), "+s"(hi));
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    float a = x[2 * e], b = x[2 * e + 1];
+#pragma unroll
+    for (int p = 0; p < NP; ++p) {
+      const bf16x2 h = __builtin_convertvector(f32x2{a, b}, bf16x2);
+      w[p][e] = __builtin_bit_cast(uint32_t, h);
+      if (p + 1 < NP) {      // what is left (exact), each in one instruction
+        a = __builtin_amdgcn_fdot2_f32_bf16(h, __builtin_bit_cast(bf16x2, lo), a, false);
+        b = __builtin_amdgcn_fdot2_f32_bf16(h, __builtin_bit_cast(bf16x2, hi), b, false);
+      }
+    }
+  }
+#pragma unroll
+  for (int p = 0; p < NP; ++p) o.p[p] = make_uint4(w[p][0], w[p][1], w[p][2], w[p][3]);
+  return o;
+}
+template <int NP>
+__device__ __forceinline__ Op<NP> split8(float4 a, float4 b) {
+  const float x[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+  return split8<NP>(x);
+}
+
+// Rows of a head as the FP32 score pass takes them, an item per 32 window positions of a query head and kind (q, u):
+// the planes in operand order ([plane][d/16][lane half][32 rows][8] bf16, so that an operand register is one 1 KiB
+// run), then the rows' statistics ([32][4] f32; q: maximum, denominator; u: zz, champion, its score).
+constexpr int row_item(int d) { return (3 * d / 16 + 1) * 1024; }
+inline __host__ __device__ int row_items(int W) { return (W + 31) / 32; }
 
 // Per split s and query row the attention pass leaves (all logits in log2 units, scaled):
 //   part_m    largest logit seen, -inf if the split saw no key
@@ -115,11 +182,11 @@ __device__ __forceinline__ f32x4_t quad_of(const bf16_t* p) {
 // splits that the LDS lists of a workgroup hold (many rows come with few splits)
 constexpr int combine_max_splits(int rq) { return rq >= 64 ? 8 : (rq >= 32 ? 16 : 64); }
 
-template <typename T, int D, int RQ>
+template <typename T, int D, int RQ, int USE_OP>
 __global__ __launch_bounds__(4 * D, 4) void k_attn_combine(Prob pb, const T* __restrict__ v, int S,
                                                            const float* __restrict__ gram, ScorePtrs o,
                                                            const float* __restrict__ part_z, const T* __restrict__ q,
-                                                           int use_op, int log2gp, int nwb) {
+                                                           int log2gp, int nwb) {
   constexpr int SMAX = combine_max_splits(RQ), NT = 4 * D, NWV = D / 16, CQ = D / 4, ZST = D + 4;
   constexpr int NP = RQ < 16 ? 16 / RQ : 1;              // threads that share a row's columns
   constexpr int MB = RQ < 16 ? 1 : RQ / 16;              // rows per thread, 16-row blocks of the product
@@ -141,6 +208,10 @@ __global__ __launch_bounds__(4 * D, 4) void k_attn_combine(Prob pb, const T* __r
   const T* vg = v + (int64_t)g * pb.kv_sh;
   const int SW = S <= 1 ? 1 : 1 << (32 - __builtin_clz((unsigned)(S - 1)));      // lanes per row
   const int sub = l & (SW - 1);
+  // FP32 score pass: statistic k of window position i with the q rows (which = 0) or the u rows
+  char* const items = (char*)o.op + (int64_t)h * row_items(pb.W) * 2 * row_item(D);
+  auto item_of = [&](int i, int which) { return items + ((i >> 5) * 2 + which) * (int64_t)row_item(D); };
+  auto stat = [&](int i, int which, int k) { return (float*)(item_of(i, which) + 3 * D / 16 * 1024) + (i & 31) * 4 + k; };
   const unsigned long long mine = SW >= 64 ? ~0ull : ((1ull << SW) - 1ull) << (l & ~(SW - 1));
   // what the workgroup needs from memory is asked for in the order in which it will be waited for:
   // the scalars, the first splits' sums, the Gram entries
@@ -207,7 +278,7 @@ __global__ __launch_bounds__(4 * D, 4) void k_attn_combine(Prob pb, const T* __r
       s_lrest[r] = lrest;
       s_nj[r] = __popcll(jm);
       s_nstar[r] = sc >= 0 ? nst : -1;       // as part_n
-      if (i0 + r < pb.W) o.rs_m[row] = M0;
+      if (i0 + r < pb.W) *(USE_OP == 1 ? o.rs_m + row : stat(i0 + r, 0, 0)) = M0;
     }
   }
   __syncthreads();
@@ -366,13 +437,21 @@ __global__ __launch_bounds__(4 * D, 4) void k_attn_combine(Prob pb, const T* __r
 #pragma unroll
     for (int k = 0; k < NWV; ++k) { zz += red[k][r][0]; qx += has_x ? red[k][sl][1] : 0.f; }
     const float lr = s_lrest[r] * s_fr[r], l_ = s_nstar[r] >= 0 ? 1.f + lr : lr;
-    o.rs_l[row] = l_;
-    o.rs_zz[row] = zz;
-    o.rs_nstar[row] = loo(r);
     // A* ||(z_rest - v*) W_O|| with A* = 1/l, or A*/(1 - A*) ||(z - v*) W_O|| with A*/(1 - A*) = 1/(l - 1)
-    o.rs_istar[row] = sqrtf(fmaxf(qx, 0.f)) / (s_nstar[r] >= 0 ? l_ : l_ - 1.f);
+    const float is = sqrtf(fmaxf(qx, 0.f)) / (s_nstar[r] >= 0 ? l_ : l_ - 1.f);
+    if constexpr (USE_OP == 1) {
+      o.rs_l[row] = l_;
+      o.rs_zz[row] = zz;
+      o.rs_nstar[row] = loo(r);
+      o.rs_istar[row] = is;
+    } else {
+      *stat(i0 + r, 0, 1) = l_;
+      *stat(i0 + r, 1, 0) = zz;
+      *stat(i0 + r, 1, 1) = __int_as_float(loo(r));
+      *stat(i0 + r, 1, 2) = is;
+    }
   }
-  if (use_op) {
+  if constexpr (USE_OP == 1) {
     // q, and u split into bf16 high and low parts, in the order the score pass feeds them to the
     // matrix cores: [which][32-row block][d/16][lane half][local row][8], local row =
     // position * Gp + head, so that a wavefront fetches each operand register as one 1 KiB run
@@ -399,32 +478,46 @@ __global__ __launch_bounds__(4 * D, 4) void k_attn_combine(Prob pb, const T* __r
       *(uint4*)(o.op + 2 * plane + at) = make_uint4(lo[0], lo[1], lo[2], lo[3]);
     }
   } else {
-    for (int x = tid; x < RQ * (D / 4); x += NT) {
-      const int r = x / (D / 4), cc = 4 * (x % (D / 4));
-      if (i0 + r < pb.W) *(f32x4_t*)(o.rs_u + ((int64_t)h * pb.W + i0 + r) * D + cc) = *(const f32x4_t*)&xs[UB + r][cc];
+    // planes of q and u (see row_item)
+    for (int x = tid; x < RQ * (D / 8); x += NT) {
+      const int r = x / (D / 8), c8 = x % (D / 8), i = i0 + r;
+      if (i >= pb.W) continue;
+      const T* qp = q + (int64_t)h * pb.q_sh + (int64_t)i * pb.q_st + 8 * c8;
+      const f32x4_t qa = quad_of(qp), qb = quad_of(qp + 4);
+      const float qv[8] = {qa[0], qa[1], qa[2], qa[3], qb[0], qb[1], qb[2], qb[3]};
+      float uv[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) uv[e] = xs[UB + r][8 * c8 + e];
+      const Op<planes_of<T>> qo = split8<planes_of<T>>(qv);
+      const Op<3> uo = split8<3>(uv);
+      const int at = c8 * 512 + (i & 31) * 16;
+#pragma unroll
+      for (int p = 0; p < planes_of<T>; ++p) *(uint4*)(item_of(i, 0) + p * (D / 16) * 1024 + at) = qo.p[p];
+#pragma unroll
+      for (int p = 0; p < 3; ++p) *(uint4*)(item_of(i, 1) + p * (D / 16) * 1024 + at) = uo.p[p];
     }
   }
 }
 
-// use_op: leave the score pass's operands (bf16 path) instead of u in FP32.
-template <typename T, int D, int RQ>
+// USE_OP: what the score pass takes, 1: operands of the bf16 path, 2: items of the FP32 path.
+template <typename T, int D, int RQ, int USE_OP>
 inline void launch_combine_rows(const Prob& pb, const T* v, int S, const float* gram, const ScorePtrs& w, const float* part_z,
-                                const T* q, int use_op, int log2gp, int nwb, hipStream_t st) {
-  RK_LAUNCH(ST_COMBINE, st, (k_attn_combine<T, D, RQ>), dim3(pb.Hq * ((pb.W + RQ - 1) / RQ)), dim3(4 * D), 0, st, pb, v, S, gram,
-            w, part_z, q, use_op, log2gp, nwb);
+                                const T* q, int log2gp, int nwb, hipStream_t st) {
+  RK_LAUNCH(ST_COMBINE, st, (k_attn_combine<T, D, RQ, USE_OP>), dim3(pb.Hq * ((pb.W + RQ - 1) / RQ)), dim3(4 * D), 0, st, pb, v, S, gram,
+            w, part_z, q, log2gp, nwb);
 }
-template <typename T, int D>
+template <typename T, int D, int USE_OP>
 inline void launch_combine(const Prob& pb, const T* v, int S, const float* gram, const ScorePtrs& w, const float* part_z,
-                           const T* q, int use_op, int log2gp, int nwb, hipStream_t st) {
+                           const T* q, int log2gp, int nwb, hipStream_t st) {
   // As many rows per workgroup (one chain of round trips, one read of the Gram matrix) as still leave
   // a workgroup for every compute unit; where eight rows do not leave two, four rows whose splits are
   // shared by four threads (1024 rows: 10.8 us against 14.1 with eight; one split has nothing to share).
   auto fills = [&](int rq) { return S <= combine_max_splits(rq) && pb.W > rq / 2 && (int64_t)pb.Hq * ((pb.W + rq - 1) / rq) >= n_cu(); };
-  if (fills(64)) launch_combine_rows<T, D, 64>(pb, v, S, gram, w, part_z, q, use_op, log2gp, nwb, st);
-  else if (fills(32)) launch_combine_rows<T, D, 32>(pb, v, S, gram, w, part_z, q, use_op, log2gp, nwb, st);
-  else if (fills(16)) launch_combine_rows<T, D, 16>(pb, v, S, gram, w, part_z, q, use_op, log2gp, nwb, st);
-  else if (S > 1 && (int64_t)pb.Hq * ((pb.W + 7) / 8) < 2 * n_cu()) launch_combine_rows<T, D, 4>(pb, v, S, gram, w, part_z, q, use_op, log2gp, nwb, st);
-  else launch_combine_rows<T, D, 8>(pb, v, S, gram, w, part_z, q, use_op, log2gp, nwb, st);
+  if (fills(64)) launch_combine_rows<T, D, 64, USE_OP>(pb, v, S, gram, w, part_z, q, log2gp, nwb, st);
+  else if (fills(32)) launch_combine_rows<T, D, 32, USE_OP>(pb, v, S, gram, w, part_z, q, log2gp, nwb, st);
+  else if (fills(16)) launch_combine_rows<T, D, 16, USE_OP>(pb, v, S, gram, w, part_z, q, log2gp, nwb, st);
+  else if (S > 1 && (int64_t)pb.Hq * ((pb.W + 7) / 8) < 2 * n_cu()) launch_combine_rows<T, D, 4, USE_OP>(pb, v, S, gram, w, part_z, q, log2gp, nwb, st);
+  else launch_combine_rows<T, D, 8, USE_OP>(pb, v, S, gram, w, part_z, q, log2gp, nwb, st);
 }
 
 }  // namespace restkv

@@ -28,7 +28,6 @@ namespace restkv {
 
 namespace {
 
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef short s16x4 __attribute__((ext_vector_type(4)));
@@ -41,11 +40,6 @@ constexpr float RESCALE_TH = 8.0f;  // log2 units a row maximum may run ahead of
 
 #define MFMA(a, b, c) __builtin_amdgcn_mfma_f32_32x32x16_bf16((a), (b), (c), 0, 0, 0)
 
-__device__ __forceinline__ bf16x8 as_bf16x8(uint4 u) {
-  union { uint4 u; bf16x8 b; } x;
-  x.u = u;
-  return x.b;
-}
 __device__ __forceinline__ float xhalf_max(float x) {   // max with the lane 32 away
   const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
   return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
@@ -139,19 +133,7 @@ inline dim3 wg_grid(const Prob& pb, int chunks, int y) {
 // The copies are issued from inline asm and waited for with explicit s_waitcnt
 // vmcnt(n): a wave's loads retire in order, and a later store can only make the count higher,
 // so "count <= number of loads issued after the group" implies that the group has landed.
-// One 1 KiB asynchronous copy: lane i moves the 16 bytes at base + voff_i to LDS bytes
-// [16 i, 16 i + 16) of lds_dst.  base and lds_dst are wave-uniform.
-__device__ __forceinline__ void dma_1k(const void* base, uint32_t voff, void* lds_dst) {
-  const uint32_t dst =
-      __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)lds_dst);
-  const uint64_t sb = (uint64_t)base;
-  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)sb);
-  const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(sb >> 32));
-  const uint64_t ub = ((uint64_t)hi << 32) | lo;
-  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(voff), "s"(ub), "s"(dst)
-               : "memory", "m0");
-}
-// The same with the LDS byte address given as a number (wave-uniform, like base): nothing of the
+// dma_1k with the LDS byte address given as a number (wave-uniform, like base): nothing of the
 // copy's addressing is left to the vector ALU but the lane's own offset.
 __device__ __forceinline__ void dma_1k_to(const void* base, uint32_t voff, uint32_t lds_dst) {
   asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(voff), "s"(base), "s"(lds_dst)
@@ -1225,7 +1207,7 @@ int run_mfma(const Prob& pb, const void* q, const void* k, const void* v, const 
       RK_LAUNCH(ST_ATTN, st, (k_attn_pipe<D, false>), ga, dim3(512), 0, st, pb, qq, kk, vp, S, kps, rg.log2iw, w);
   }
   if (pb.ind != 0) gram = nullptr;                 // the attention-weight and value-norm indicators have no projection
-  launch_combine<bf16_t, D>(pb, (const bf16_t*)v, S, gram, w, part_z, (const bf16_t*)q, 1, ilog2(rg.gp), lay.nwb, st);
+  launch_combine<bf16_t, D, 1>(pb, (const bf16_t*)v, S, gram, w, part_z, (const bf16_t*)q, ilog2(rg.gp), lay.nwb, st);
   if (gram) {
     constexpr int HPW = D == 128 ? 4 : 8;
     const int NTv = (pb.P + TN - 1) / TN;

@@ -1,22 +1,29 @@
 // Reconstruction indicator in FP32 (float32 inputs, and bf16 inputs whose shape or alignment the
 // bf16 path does not take).
 //
-// The same four stages and scratch layout as the bf16 path, every product in FP32 on
-// v_mfma_f32_32x32x2_f32:
+// The same four stages and scratch layout as the bf16 path.  Every product of FP32 values runs on
+// v_mfma_f32_32x32x16_bf16 with both sides cut into planes: x = h + m + l, each a bf16 (h the nearest
+// to x, m the nearest to what is left, l the rest, exact: 8 + 8 + 8 bits), and x y as the six products
+// h h, h m, m h, m m, h l, l h with FP32 accumulation; what is dropped (m l, l m, l l) is below
+// 2^-25 |x y|, less than the rounding of one FP32 addition.  Six bf16 instructions of 32 cycles take
+// 16 K indices, eight v_mfma_f32_32x32x2_f32 of 64 cycles take the same: 2.7 times the rate.  A bf16
+// input has one plane (it is exact), so its products with FP32 values are three.  Scores are as far from 64 bits as
+// with FP32 products or nearer (8k tokens: 2.4e-7 against 2.9e-7, 2-norm; sixteen other shapes 3 to 30 % nearer).
+// 8k tokens, 32/8 heads of 128, window 32: attention pass 52 -> 38 us, value-Gram pass 54 -> 34, score pass
+// 58 -> 40; score and smoothing 179 -> 131 us.  What bounds them now: per 32 keys a wavefront has 96 to 120 MFMAs
+// (3.1k to 3.8k cycles) and 200 to 350 vector instructions that cut values into planes, and both wavefronts of a
+// SIMD are in the same phase most of the time.
 //
 //   C layout of a 32x32 block:  register j of lane l holds
 //       M index = 8*(j/4) + 4*(l/32) + (j%4),   N index = l % 32;
-//   A / B operands: lane l holds M (or N) index l % 32 and ONE K index, chosen by l / 32.
+//   A / B operands: lane l holds M (or N) index l % 32 and 8 K indices, chosen by l / 32.
 //
-// Which two K indices a step multiplies is free as long as A and B agree.  Contractions over the
-// head dimension take (8a + e, 8a + 4 + e): a lane then reads its operands of four steps as one
-// 16-byte piece.  The contraction over the keys (P.V) takes the pair of keys that register j of a
-// logit block holds in the two lane halves, so the attention weights are operands as they stand.
-// An instruction is 64 cycles for one operand register each: what bounds these kernels is the
-// matrix pipe (157 TFLOP/s), not LDS nor HBM.  Measured at 8k tokens, 32/8 heads of 128, window 32,
-// against vector-ALU kernels that read two LDS words per multiply-add: attention pass 338 -> 55 us,
-// value-Gram pass 478 -> 56 us, score pass 266 -> 60 us (14 GFLOP executed: 82 TFLOP/s).
+// Which 16 K indices a step multiplies in which order is free as long as A and B agree.  The
+// contraction over the keys (P.V) and the one with the Gram matrix take the K indices that the
+// registers of a C block hold in the two lane halves, so that attention weights are operands as they
+// stand, and the value entries a lane holds as operands are the ones its row dots need.
 #include <algorithm>
+#include <type_traits>
 
 #include "score_common.hpp"
 
@@ -25,16 +32,16 @@ namespace restkv {
 namespace {
 
 typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef short s16x8 __attribute__((ext_vector_type(8)));
 
 constexpr int KB = 32;      // keys per block (one side of an MFMA)
 constexpr float LOG2E = 1.4426950408889634f;
 constexpr float RESCALE_TH = 8.0f;  // log2 units a joining logit may run ahead of the reference
 
-#define MFMA32(a, b, c) __builtin_amdgcn_mfma_f32_32x32x2f32((a), (b), (c), 0, 0, 0)
-
-// Wait states between the last MFMA on a block and the first read of its result, spelled out (18 for
-// a 16-pass instruction): where branches lie in between, hipcc 7.2 inserts too few on some path, and
-// the last registers of the block come out stale.
+// Wait states between the last MFMA on a block and the first read of its result, spelled out: where
+// branches lie in between, hipcc 7.2 inserts too few on some path, and the last registers of the block
+// come out stale.
 __device__ __forceinline__ void settle(f32x16& x) { asm volatile("s_nop 15\n\ts_nop 3" : "+v"(x)); }
 
 __device__ __forceinline__ float half_max(float x) {   // with the lane 32 away
@@ -68,43 +75,125 @@ __device__ __forceinline__ float4 load4(const bf16_t* p) {
   }
 }
 
-// A block of KB rows of D floats on its way from global memory to LDS through NT threads' registers.
-template <int D, int NT>
-struct Stage {
-  static constexpr int N = KB * D / 4 / NT;
-  float4 r[N];
-  // ptr_of(row): address of a row's first element, or nullptr for a row of zeros
-  template <bool VEC, typename F>
-  __device__ __forceinline__ void fetch(F ptr_of) {
+// acc += a b over the 16 K indices of a step, the small products first
+template <int NA, int NB>
+__device__ __forceinline__ void mul(f32x16& acc, const Op<NA>& a, const Op<NB>& b) {
 #pragma unroll
-    for (int j = 0; j < N; ++j) {
-      const int x = (int)threadIdx.x + j * NT, row = x / (D / 4), c4 = x % (D / 4);
-      const auto p = ptr_of(row);
-      r[j] = p ? load4<VEC>(p + 4 * c4) : make_float4(0.f, 0.f, 0.f, 0.f);
+  for (int s = NA + NB - 2 < 2 ? NA + NB - 2 : 2; s >= 0; --s)
+#pragma unroll
+    for (int i = 0; i < NA; ++i)
+      if (s - i >= 0 && s - i < NB)
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(a.p[i]), as_bf16x8(b.p[s - i]), acc, 0, 0, 0);
+}
+
+// acc(a) += step a of KS whose A side comes from LDS, read(a, p) being plane p of step a: a plane of the
+// next step is asked for as soon as the current one is done with (l after one product, m after three).  Left to
+// itself the compiler asks for everything first, which spills, or for each operand right before its use, which leaves
+// the matrix cores idle half of the time.
+template <int NA, int NB, int KS, typename Acc, typename F, typename G>
+__device__ __forceinline__ void contract(Acc acc, F read, G other) {
+  uint4 x[NA];
+#pragma unroll
+  for (int p = 0; p < NA; ++p) x[p] = read(0, p);
+#pragma unroll
+  for (int a = 0; a < KS; ++a) {
+    const Op<NB> b = other(a);
+#pragma unroll
+    for (int p = NA - 1; p >= 0; --p) {
+      __builtin_amdgcn_sched_barrier(0);
+      uint4 next;
+      if (p == 0 && a + 1 < KS) next = read(a + 1, 0);
+#pragma unroll
+      for (int i = (NB - 1 < 2 - p ? NB - 1 : 2 - p); i >= 0; --i)
+        acc(a) = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(x[p]), as_bf16x8(b.p[i]), acc(a), 0, 0, 0);
+      if (p > 0 && a + 1 < KS) next = read(a + 1, p);
+      x[p] = next;
     }
   }
-  __device__ __forceinline__ void store(float* lds, int stride) const {
+  __builtin_amdgcn_sched_barrier(0);
+}
+
+// Planes of KB rows of D values in LDS, read as operand columns (32 rows x 8 K indices): chunk c (8 values) of a row
+// lies c column strides from the first, which keeps one address per lane for all reads, and the odd stride spreads
+// the writes of a row's chunks over the banks.
+template <int D, int NP>
+struct ColTile {
+  static constexpr int CST = KB * 8 + 8, PLANE = D / 8 * CST;      // (in bf16)
+  uint16_t x[NP][PLANE];
+  __device__ static __forceinline__ int at(int r, int c) { return c * CST + r * 8; }
+  // plane p of the operand of step ks: rows rr on one side, K indices 16 ks + 8 hf .. + 7
+  __device__ __forceinline__ uint4 cols(int rr, int hf, int ks, int p) const { return *(const uint4*)&x[p][at(rr, hf) + 2 * ks * CST]; }
+};
+// The same read through the transposing 8-byte read (4 rows x 4 chunks per lane half): a row is D bf16, its groups of
+// four chunks permuted by the row.
+template <int D, int NP>
+struct RowTile {
+  static constexpr int CH = D / 8, SH = CH == 16 ? 0 : 1;
+  uint16_t x[NP][KB * D];
+  __device__ static __forceinline__ int at(int r, int c) { return r * D + ((c ^ (((r >> SH) & (CH / 4 - 1)) << 2)) << 3); }
+  // plane p of the operand with the 32 columns 32 cb .. on one side and the rows (keys) 16 grp .. as K indices in the order
+  // of the registers of a C block; r0, c0: row and column of this lane's 8 bytes inside a 16 x 32 piece
+  __device__ __forceinline__ uint4 rows(int grp, int cb, int r0, int c0, int p) const {
+    const int c = 32 * cb + c0;
+    const uint16_t* b = &x[p][at(r0, c >> 3) + (c & 7) + 16 * grp * D];           // rows r, r + 8 and r + 16 share their permutation
+    const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(b));
+    const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(b + 8 * D));
+    union { s16x8 s; uint4 u; } a;
+    a.s = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+    return a.u;
+  }
+};
+
+// A block of KB rows of D values on its way from global memory to a tile through NT threads' registers.
+template <int D, int NT>
+struct Stage {
+  static constexpr int CH = D / 8, N = KB * CH / NT;
+  static_assert(KB * CH % NT == 0, "every thread takes the same number of chunks");
+  float4 r[N][2];
+  // the first of `rows` rows (the others become zeros) at base (wave-uniform), `stride` elements apart
+  template <bool VEC, typename T>
+  __device__ __forceinline__ void fetch(const T* base, int64_t stride, int rows) {
+    const int row = (int)threadIdx.x / CH, c = (int)threadIdx.x % CH;
+    const int64_t lane = row * stride + 8 * c;
 #pragma unroll
     for (int j = 0; j < N; ++j) {
-      const int x = (int)threadIdx.x + j * NT, row = x / (D / 4), c4 = x % (D / 4);
-      *(float4*)&lds[row * stride + 4 * c4] = r[j];
+      const T* p = base + (int64_t)(j * (NT / CH)) * stride + lane;
+      if (rows < KB && row + j * (NT / CH) >= rows) p = base;
+      r[j][0] = load4<VEC>(p);
+      r[j][1] = load4<VEC>(p + 4);
+    }
+    if (rows < KB)                                     // (uniform)
+#pragma unroll
+      for (int j = 0; j < N; ++j)
+        if (row + j * (NT / CH) >= rows) r[j][0] = r[j][1] = make_float4(0.f, 0.f, 0.f, 0.f);
+  }
+  template <typename Tile>
+  __device__ __forceinline__ void store(Tile& t) const {
+    constexpr int NP = sizeof(t.x) / sizeof(t.x[0]);
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+      const int x = (int)threadIdx.x + j * NT, row = x / CH, c = x % CH;
+      const Op<NP> o = split8<NP>(r[j][0], r[j][1]);
+      const int at = t.at(row, c);
+#pragma unroll
+      for (int p = 0; p < NP; ++p) *(uint4*)&t.x[p][at] = o.p[p];
     }
   }
 };
 
 // Attention pass: per key split, online softmax of every window query with its dominant key kept
 // out of the sums (outputs described in score_common.hpp).  A wavefront owns 32 query rows, on the
-// N side: a lane is half of a row, its softmax state is scalar.  K and V blocks of 32 keys are
-// double-buffered in LDS, the next block's loads are in flight while a block is worked on.  Row
-// strides in LDS: D + 4 floats for K (16-byte reads down the rows), D + 8 for V (4-byte reads along
-// a row, the lane halves four rows apart), so that neither read meets a bank twice.
+// N side: a lane is half of a row, its softmax state is scalar.  The planes of a K and a V block of 32
+// keys are in LDS (48 KiB for D = 128, two workgroups per compute unit); the next block's loads are in
+// flight while a block is worked on, its K planes are written when the logits have been formed, its V
+// planes when the values have been added up: two barriers per block of 96 MFMAs per wavefront.
 // grid (S, ceil(R / (32 NW)), Hkv), 64 NW threads.
 template <typename T, int D, int NW, bool VEC>
-__global__ __launch_bounds__(NW * 64, 2) void k_attn_f32(Prob pb, const T* __restrict__ q, const T* __restrict__ k,
+__global__ __launch_bounds__(NW * 64, NW == 2 ? 1 : 2) void k_attn_f32(Prob pb, const T* __restrict__ q, const T* __restrict__ k,
                                                          const T* __restrict__ v, int S, int kps, ScorePtrs o) {
-  constexpr int CB = D / 32, KST = D + 4, VST = D + 8;
-  __shared__ __attribute__((aligned(16))) float Ks[2][KB * KST];
-  __shared__ __attribute__((aligned(16))) float Vs[2][KB * VST];
+  constexpr int CB = D / 32, NP = planes_of<T>;
+  __shared__ __attribute__((aligned(16))) ColTile<D, NP> Ks;
+  __shared__ __attribute__((aligned(16))) RowTile<D, NP> Vs;
   const int s = blockIdx.x, g = blockIdx.z;
   const int l = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), rr = l & 31, hf = l >> 5;
   const int r = (blockIdx.y * NW + wv) * 32 + rr;       // row inside the KV head
@@ -116,12 +205,14 @@ __global__ __launch_bounds__(NW * 64, 2) void k_attn_f32(Prob pb, const T* __res
   const int kbeg = s * kps, kend = min(pb.L, kbeg + kps);
   const int nblk = kend > kbeg ? (kend - kbeg + KB - 1) / KB : 0;
 
-  float4 qf[D / 8];
+  Op<NP> qf[D / 16];
   {
-    const T* qp = q + (int64_t)(g * pb.G + hl) * pb.q_sh + (int64_t)i * pb.q_st + 4 * hf;
+    const T* qp = q + (int64_t)(g * pb.G + hl) * pb.q_sh + (int64_t)i * pb.q_st + 8 * hf;
 #pragma unroll
-    for (int a = 0; a < D / 8; ++a) qf[a] = load4<VEC>(qp + 8 * a);
+    for (int a = 0; a < D / 16; ++a) qf[a] = split8<NP>(load4<VEC>(qp + 16 * a), load4<VEC>(qp + 16 * a + 4));
   }
+  // row and column of the 8 bytes that this lane contributes to a transposing read
+  const int s16 = l & 15, vrow = 4 * hf + (s16 >> 2), vcol = 16 * ((l >> 4) & 1) + 4 * (s16 & 3);
   const float c2 = pb.scale * LOG2E;
   float mall = -INFINITY, mref = -INFINITY, mx = -INFINITY, lsum = 0.f;
   int nx = -1;                       // key kept out of the sums, -1: none
@@ -143,32 +234,30 @@ __global__ __launch_bounds__(NW * 64, 2) void k_attn_f32(Prob pb, const T* __res
       for (int j = 0; j < 16; ++j) oacc[cb][j] *= f;
     mref = mv ? to : mref;
   };
-  Stage<D, NW * 64> sk, sv;
-  auto fetch = [&](int t) {
+  Stage<D, NW * 64> sg;                // K rows, then V rows of the next block on their way to LDS
+  auto fetch = [&](const T* base, int t) {
     const int k0 = kbeg + t * KB;
-    sk.template fetch<VEC>([&](int row) { return k0 + row < kend ? kg + (int64_t)(k0 + row) * pb.kv_st : nullptr; });
-    sv.template fetch<VEC>([&](int row) { return k0 + row < kend ? vg + (int64_t)(k0 + row) * pb.kv_st : nullptr; });
+    sg.template fetch<VEC>(base + (int64_t)k0 * pb.kv_st, pb.kv_st, kend - k0);
   };
   if (nblk > 0) {
-    fetch(0);
-    sk.store(Ks[0], KST);
-    sv.store(Vs[0], VST);
+    fetch(kg, 0);
+    const Stage<D, NW * 64> sk = sg;
+    fetch(vg, 0);
+    sk.store(Ks);
+    sg.store(Vs);
     __syncthreads();
   }
   for (int t = 0; t < nblk; ++t) {
     const int k0 = kbeg + t * KB;
-    if (t + 1 < nblk) fetch(t + 1);
+    if (t + 1 < nblk) fetch(kg, t + 1);
     f32x16 sacc;
 #pragma unroll
     for (int j = 0; j < 16; ++j) sacc[j] = 0.f;
-    const float* kt = &Ks[t & 1][rr * KST + 4 * hf];
-#pragma unroll
-    for (int a = 0; a < D / 8; ++a) {
-      const float4 kf = *(const float4*)(kt + 8 * a);
-      sacc = MFMA32(kf.x, qf[a].x, sacc);
-      sacc = MFMA32(kf.y, qf[a].y, sacc);
-      sacc = MFMA32(kf.z, qf[a].z, sacc);
-      sacc = MFMA32(kf.w, qf[a].w, sacc);
+    contract<NP, NP, D / 16>([&](int) -> f32x16& { return sacc; }, [&](int a, int p) { return Ks.cols(rr, hf, a, p); }, [&](int a) { return qf[a]; });
+    __syncthreads();                   // the K planes have been read, the V planes of this block are complete
+    if (t + 1 < nblk) {
+      sg.store(Ks);
+      fetch(vg, t + 1);
     }
     settle(sacc);
     if (k0 + KB > kend || (pb.causal && k0 + KB - 1 > pb.P)) {
@@ -190,20 +279,24 @@ __global__ __launch_bounds__(NW * 64, 2) void k_attn_f32(Prob pb, const T* __res
     mall = fmaxf(mall, tm);
     float tinc = tm;                   // largest logit of the block that joins the sums
     if (__ballot(newmax) != 0ull) {
-      // mass without the candidate, relative to the candidate itself
-      float rest = lsum * __builtin_amdgcn_exp2f((mref - tm) * c2);    // (empty sums: 0 * 0)
       int cand = 0x7FFFFFFF;
 #pragma unroll
-      for (int j = 0; j < 16; ++j) {
-        rest += __builtin_amdgcn_exp2f((sacc[j] - tm) * c2);
+      for (int j = 0; j < 16; ++j)
         if (sacc[j] == tm) cand = min(cand, k0 + cidx(j, hf));
-      }
-      rest = half_sum(rest) - 1.f;
       cand = half_min(cand);
       ni = newmax ? cand : ni;
-      if (nx >= 0) rest += __builtin_amdgcn_exp2f((mx - tm) * c2);
-      // (rest carries the rounding of the sum it was taken from: a tie may go either way)
-      const bool dominant = newmax && tm > -INFINITY && rest < 1.0001f;
+      // (this lane's share of the sum alone outweighs most candidates)
+      bool dominant = newmax && tm > -INFINITY && lsum < 1.0002f * __builtin_amdgcn_exp2f((tm - mref) * c2);
+      if (__ballot(dominant) != 0ull) {
+        // mass without the candidate, relative to the candidate itself
+        float rest = lsum * __builtin_amdgcn_exp2f((mref - tm) * c2);    // (empty sums: 0 * 0)
+#pragma unroll
+        for (int j = 0; j < 16; ++j) rest += __builtin_amdgcn_exp2f((sacc[j] - tm) * c2);
+        rest = half_sum(rest) - 1.f;
+        if (nx >= 0) rest += __builtin_amdgcn_exp2f((mx - tm) * c2);
+        // (rest carries the rounding of the sum it was taken from: a tie may go either way)
+        dominant = dominant && rest < 1.0001f;
+      }
       const bool joins = newmax && nx >= 0;          // the key kept out so far is not the largest any more: it joins the sums
       if (__ballot(dominant || joins) != 0ull) {
         const int cz = dominant ? cand : -1;
@@ -245,16 +338,18 @@ __global__ __launch_bounds__(NW * 64, 2) void k_attn_f32(Prob pb, const T* __res
     for (int j = 0; j < 16; ++j) sacc[j] = __builtin_amdgcn_exp2f(fmaf(sacc[j], c2, nm));
     lsum += ((sacc[0] + sacc[1]) + (sacc[2] + sacc[3])) + ((sacc[4] + sacc[5]) + (sacc[6] + sacc[7])) +
             (((sacc[8] + sacc[9]) + (sacc[10] + sacc[11])) + ((sacc[12] + sacc[13]) + (sacc[14] + sacc[15])));
-    const float* vt = &Vs[t & 1][4 * hf * VST + rr];
 #pragma unroll
-    for (int j = 0; j < 16; ++j)
+    for (int grp = 0; grp < 2; ++grp) {
+      float pe[8];
 #pragma unroll
-      for (int cb = 0; cb < CB; ++cb)
-        oacc[cb] = MFMA32(vt[(8 * (j >> 2) + (j & 3)) * VST + 32 * cb], sacc[j], oacc[cb]);
-    if (t + 1 < nblk) {                // the other buffers were last read before the barrier that ended block t-1
-      sk.store(Ks[(t + 1) & 1], KST);
-      sv.store(Vs[(t + 1) & 1], VST);
-      __syncthreads();
+      for (int e = 0; e < 8; ++e) pe[e] = sacc[8 * grp + e];
+      const Op<3> pv = split8<3>(pe);
+      contract<NP, 3, CB>([&](int cb) -> f32x16& { return oacc[cb]; }, [&](int cb, int p) { return Vs.rows(grp, cb, vrow, vcol, p); },
+                          [&](int) { return pv; });
+    }
+    if (t + 1 < nblk) {
+      __syncthreads();                 // the V planes have been read, the K planes of the next block are complete
+      sg.store(Vs);
     }
   }
 #pragma unroll
@@ -280,56 +375,82 @@ __global__ __launch_bounds__(NW * 64, 2) void k_attn_f32(Prob pb, const T* __res
 }
 
 // vv[h, n] = v_n M_h v_n^T = sum_i v_i (T v)_i with the upper triangular T = diag(M) + 2 triu(M, 1)
-// (M is symmetric), so that 32x32 blocks below the diagonal are skipped.  T of the workgroup's head
-// stays in LDS (row stride D + 4 floats); a wavefront takes 32 keys at a time, on the N side, whose
-// values are operand registers and, because the K pairs were chosen like the rows a lane holds in
-// the C layout, also exactly the factors of the row dot.  grid (chunks, Hq), 256 threads.
+// (M is symmetric), so that 32x16 pieces below the diagonal are skipped.  The planes of T of the
+// workgroup's head stay in LDS in operand order (one 1 KiB run per piece and plane); a wavefront takes
+// 32 keys at a time, on the N side.  K indices are taken in the order of a C block's registers: the
+// values a lane holds as operands are also the factors of its row dots.  grid (chunks, Hq), 256 threads.
 template <typename T, int D, bool VEC>
 __global__ __launch_bounds__(256, 2) void k_vv_f32(Prob pb, const T* __restrict__ v, const float* __restrict__ gram,
                                                    float* __restrict__ vv, int ldv) {
-  constexpr int CB = D / 32, ST = D + 4;
-  __shared__ __attribute__((aligned(16))) float Ts[D * ST];
+  constexpr int CB = D / 32, KS = D / 16, NP = planes_of<T>;
+  constexpr int NB = CB * (CB + 1);                    // pieces on or above the diagonal: KS - 2 cb of row block cb
+  __shared__ __attribute__((aligned(16))) uint4 Ts[NB][3][64];
   const int h = blockIdx.y, g = h / pb.G;
   const int l = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), rr = l & 31, hf = l >> 5;
   const T* vg = v + (int64_t)g * pb.kv_sh;
   const int nb = (pb.P + KB - 1) / KB;
-  float4 vf[D / 8];
+  float4 vf[KS][2];                                    // dims 16 ks + 4 hf .. + 3 and 16 ks + 8 + 4 hf .. + 3 of key rr
   auto fetch = [&](int b) {
     const T* vr = vg + (int64_t)min(b * KB + rr, pb.P - 1) * pb.kv_st + 4 * hf;
 #pragma unroll
-    for (int a = 0; a < D / 8; ++a) vf[a] = load4<VEC>(vr + 8 * a);
+    for (int a = 0; a < KS; ++a) {
+      vf[a][0] = load4<VEC>(vr + 16 * a);
+      vf[a][1] = load4<VEC>(vr + 16 * a + 8);
+    }
   };
   int b = blockIdx.x * 4 + wv;
   if (b < nb) fetch(b);
+  // (all loads first: one round trip)
+  constexpr int NPC = (NB + 3) / 4;                    // pieces per wavefront
   const float* Mh = gram + (int64_t)h * D * D;
-  for (int x = threadIdx.x; x < D * D / 4; x += 256) {
-    const int i = x / (D / 4), j0 = 4 * (x % (D / 4));
-    float m[4] = {Mh[i * D + j0], Mh[i * D + j0 + 1], Mh[i * D + j0 + 2], Mh[i * D + j0 + 3]};
+  f32x4_t m[NPC][2];
 #pragma unroll
-    for (int e = 0; e < 4; ++e) m[e] = j0 + e > i ? 2.f * m[e] : (j0 + e == i ? m[e] : 0.f);
-    *(float4*)&Ts[i * ST + j0] = make_float4(m[0], m[1], m[2], m[3]);
+  for (int j = 0; j < NPC; ++j) {
+    int cb = 0, a = min(wv + 4 * j, NB - 1);           // piece: row block cb, step 2 cb + a
+    while (a >= KS - 2 * cb) { a -= KS - 2 * cb; ++cb; }
+    const float* p = Mh + (32 * cb + rr) * D + 16 * (2 * cb + a) + 4 * hf;
+    m[j][0] = quad_of(p);
+    m[j][1] = quad_of(p + 8);
+  }
+#pragma unroll
+  for (int j = 0; j < NPC; ++j) {
+    if (wv + 4 * j >= NB) break;
+    int cb = 0, a = wv + 4 * j;
+    while (a >= KS - 2 * cb) { a -= KS - 2 * cb; ++cb; }
+    const int i = 32 * cb + rr, j0 = 16 * (2 * cb + a) + 4 * hf;
+    float x[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const int c = j0 + 8 * (e >> 2) + (e & 3);
+      const float f = m[j][e >> 2][e & 3];
+      x[e] = c > i ? 2.f * f : (c == i ? f : 0.f);
+    }
+    const Op<3> t = split8<3>(x);
+#pragma unroll
+    for (int p = 0; p < 3; ++p) Ts[wv + 4 * j][p][l] = t.p[p];
   }
   __syncthreads();
   for (; b < nb; b += 4 * gridDim.x) {
+    Op<NP> vo[KS];
+#pragma unroll
+    for (int a = 0; a < KS; ++a) vo[a] = split8<NP>(vf[a][0], vf[a][1]);
     float acc = 0.f;
 #pragma unroll
     for (int cb = 0; cb < CB; ++cb) {
       f32x16 y;
 #pragma unroll
       for (int j = 0; j < 16; ++j) y[j] = 0.f;
-      const float* tr = &Ts[(32 * cb + rr) * ST + 4 * hf];
 #pragma unroll
-      for (int a = 4 * cb; a < D / 8; ++a) {
-        const float4 tf = *(const float4*)(tr + 8 * a);
-        y = MFMA32(tf.x, vf[a].x, y);
-        y = MFMA32(tf.y, vf[a].y, y);
-        y = MFMA32(tf.z, vf[a].z, y);
-        y = MFMA32(tf.w, vf[a].w, y);
+      for (int a = 2 * cb; a < KS; ++a) {
+        Op<3> t;
+#pragma unroll
+        for (int p = 0; p < 3; ++p) t.p[p] = Ts[cb * (KS + 1 - cb) + a - 2 * cb][p][l];
+        mul(y, t, vo[a]);
       }
       settle(y);
 #pragma unroll
       for (int jq = 0; jq < 4; ++jq) {
-        const float4 x = vf[4 * cb + jq];
+        const float4 x = vf[2 * cb + (jq >> 1)][jq & 1];
         acc = fmaf(y[4 * jq + 0], x.x, acc);
         acc = fmaf(y[4 * jq + 1], x.y, acc);
         acc = fmaf(y[4 * jq + 2], x.z, acc);
@@ -363,141 +484,140 @@ __global__ __launch_bounds__(256) void k_vnorm2_f32(Prob pb, const T* __restrict
 }
 
 // Score pass: logits again, cross term u.v_n, closed form, mean (or maximum) over the group.  A
-// wavefront owns 32 keys (N side: a store writes 32 consecutive keys of a row), whose K and V rows
-// are its B operands in registers for the whole kernel, and 32 window positions (M side); it walks
-// the heads of the group, whose q and u rows and statistics all wavefronts share through double-
-// buffered LDS.  grid (ceil(P / (32 NW)), ceil(W / 32), Hkv), 64 NW threads.
+// wavefront owns 32 keys (N side: a store writes 32 consecutive keys of a row) and 32 window positions
+// (M side), and walks the heads of the group HC at a time: first the logits of HC heads with the planes
+// of its K rows in registers, then the cross terms with the planes of its V rows in the same registers
+// (both at once are 192 registers, and two wavefronts per SIMD have 256 each).  The planes of a head's
+// q and u rows pass through double-buffered LDS, shared by the workgroup's wavefronts, the next rows' loads in
+// flight while a head is worked on.  grid (ceil(P / (32 NW)), ceil(W / 32), Hkv), 64 NW threads.
 template <typename T, int D, int NW, bool VEC>
 __global__ __launch_bounds__(NW * 64, NW == 1 ? 1 : 2) void k_score_f32(Prob pb, const T* __restrict__ q, const T* __restrict__ k,
                                                           const T* __restrict__ v, ScorePtrs o, int ldv,
                                                           float* __restrict__ score) {
-  constexpr int ST = D + 4, NT = NW * 64;
-  __shared__ __attribute__((aligned(16))) float Qs[2][KB * ST];
-  __shared__ __attribute__((aligned(16))) float Us[2][KB * ST];
-  __shared__ __attribute__((aligned(16))) float st[2][5][32];    // per row: max, denominator, zz, champion key, its score
+  constexpr int KS = D / 16, NP = planes_of<T>, HC = 2;
+  __shared__ __attribute__((aligned(1024))) char rows[2][row_item(D)];
   const int g = blockIdx.z, i0 = blockIdx.y * 32;
   const int l = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), rr = l & 31, hf = l >> 5;
   const int n = (blockIdx.x * NW + wv) * KB + rr, nc = min(n, pb.P - 1);
-  float4 kf[D / 8], vf[D / 8];
-  {
-    const T* kr = k + (int64_t)g * pb.kv_sh + (int64_t)nc * pb.kv_st + 4 * hf;
-    const T* vr = v + (int64_t)g * pb.kv_sh + (int64_t)nc * pb.kv_st + 4 * hf;
-#pragma unroll
-    for (int a = 0; a < D / 8; ++a) kf[a] = load4<VEC>(kr + 8 * a);
-#pragma unroll
-    for (int a = 0; a < D / 8; ++a) vf[a] = load4<VEC>(vr + 8 * a);
-  }
+  const T* kr = k + (int64_t)g * pb.kv_sh + (int64_t)nc * pb.kv_st + 8 * hf;
+  const T* vr = v + (int64_t)g * pb.kv_sh + (int64_t)nc * pb.kv_st + 8 * hf;
   const float c2 = pb.scale * LOG2E;
   // The attention-weight and value-norm indicators come out of the same expression without the
   // 1 - A (their u, zz and champion are empty, vv is 1 or ||v||^2).
   const float rec = pb.ind == 0 ? 1.f : 0.f;
-  Stage<D, NT> sg;                // q, then u of the next head on its way to LDS
-  float sst[3];
-  auto fetch_q = [&](int hl) {
-    const int h = g * pb.G + hl;
-    sg.template fetch<VEC>([&](int row) { return i0 + row < pb.W ? q + (int64_t)h * pb.q_sh + (int64_t)(i0 + row) * pb.q_st : nullptr; });
+  // Item (head, which) on its way to LDS: q rows with the statistics of their weights (maximum, denominator), or
+  // u rows with zz, the champion's key and its score.
+  const char* const items = (const char*)o.op + (int64_t)(g * pb.G * gridDim.y + blockIdx.y) * 2 * row_item(D);
+  auto copy_item = [&](int hl, int which, int bf) {
+    const int np = which ? 3 : NP;
+    const char* src = items + ((int64_t)hl * gridDim.y * 2 + which) * row_item(D);
+    // (a row past the window's end becomes a copy of the last one)
+    const int row = min(rr, pb.W - 1 - i0);
+    for (int x = wv; x < np * KS; x += NW) dma_1k(src + x * 1024, 16u * (uint32_t)(32 * hf + row), &rows[bf][x * 1024]);
+    if (wv == NW - 1) dma_1k(src + 3 * KS * 1024, 16u * (uint32_t)row, &rows[bf][3 * KS * 1024]);
   };
-  // u, and the rows' statistics through the first 32 threads (max, denominator, zz) and the last 32 (champion)
-  auto fetch_u = [&](int hl) {
-    const int h = g * pb.G + hl;
-    sg.template fetch<true>([&](int row) { return i0 + row < pb.W ? o.rs_u + ((int64_t)h * pb.W + i0 + row) * D : (const float*)nullptr; });
-    if (threadIdx.x < 32) {
-      const int row = h * pb.W + min(i0 + (int)threadIdx.x, pb.W - 1);
-      sst[0] = o.rs_m[row]; sst[1] = o.rs_l[row]; sst[2] = o.rs_zz[row];
-    } else if (threadIdx.x >= NT - 32) {
-      const int row = h * pb.W + min(i0 + (int)threadIdx.x - (NT - 32), pb.W - 1);
-      sst[0] = __int_as_float(o.rs_nstar[row]); sst[1] = o.rs_istar[row];
-    }
+  auto stat = [&](int bf, int j) { return *(const float4*)&rows[bf][3 * KS * 1024 + cidx(j, hf) * 16]; };
+  auto row_op = [&](int bf, int a, int p) { return *(const uint4*)&rows[bf][(p * KS + a) * 1024 + l * 16]; };
+  // what has been copied is complete, and what was read is free, after this
+  auto turn = [] {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
   };
-  auto store_u = [&](int bf) {
-    sg.store(Us[bf], ST);
-    if (threadIdx.x < 32) {
-      st[bf][0][threadIdx.x] = sst[0]; st[bf][1][threadIdx.x] = sst[1]; st[bf][2][threadIdx.x] = sst[2];
-    } else if (threadIdx.x >= NT - 32) {
-      st[bf][3][threadIdx.x - (NT - 32)] = sst[0]; st[bf][4][threadIdx.x - (NT - 32)] = sst[1];
+  Op<NP> kv[KS];                  // planes of this lane's K row, then of its V row
+  auto load_kv = [&](const T* p) {
+    asm volatile("" : "+v"(p));   // (both rows' planes would be taken out of the loop over the chunks, and spill)
+#pragma unroll
+    for (int a = 0; a < KS; ++a) {
+      kv[a] = split8<NP>(load4<VEC>(p + 16 * a), load4<VEC>(p + 16 * a + 4));
+      if (a % 4 == 3) __builtin_amdgcn_sched_barrier(0);      // (eight loads in flight)
     }
   };
   float out[16];
 #pragma unroll
   for (int j = 0; j < 16; ++j) out[j] = 0.f;
-  fetch_q(0);
-  sg.store(Qs[0], ST);
-  fetch_u(0);
-  store_u(0);
-  __syncthreads();
-  for (int hl = 0; hl < pb.G; ++hl) {
-    const int bf = hl & 1;
-    const bool more = hl + 1 < pb.G;
-    const float vvn = o.vv[(int64_t)(g * pb.G + hl) * ldv + nc];
-    if (more) fetch_q(hl + 1);
-    f32x16 sacc, cacc;
+  copy_item(0, 0, 0);
+  turn();
+  int bf = 0;                     // buffer of the current rows; the other one was last read before the last barrier
+  for (int h0 = 0; h0 < pb.G; h0 += HC) {
+    f32x16 wt[HC];                // logits, then A / (1 - A), of the heads of this chunk
+    load_kv(kr);
 #pragma unroll
-    for (int j = 0; j < 16; ++j) { sacc[j] = 0.f; cacc[j] = 0.f; }
-    const float* qt = &Qs[bf][rr * ST + 4 * hf];
-    const float* ut = &Us[bf][rr * ST + 4 * hf];
+    for (int c = 0; c < HC; ++c) {
+      if (h0 + c >= pb.G) break;                       // (uniform)
+      const bool last = c == HC - 1 || h0 + c + 1 == pb.G;
+      if (last) copy_item(h0, 1, bf ^ 1); else copy_item(h0 + c + 1, 0, bf ^ 1);
+      f32x16 sacc;
 #pragma unroll
-    for (int a = 0; a < D / 8; ++a) {
-      const float4 qa = *(const float4*)(qt + 8 * a);
-      sacc = MFMA32(qa.x, kf[a].x, sacc);
-      sacc = MFMA32(qa.y, kf[a].y, sacc);
-      sacc = MFMA32(qa.z, kf[a].z, sacc);
-      sacc = MFMA32(qa.w, kf[a].w, sacc);
-    }
-    if (more) {                       // the other buffers were last read before the barrier that ended the last head
-      sg.store(Qs[bf ^ 1], ST);
-      fetch_u(hl + 1);
-    }
+      for (int j = 0; j < 16; ++j) sacc[j] = 0.f;
+      contract<NP, NP, KS>([&](int) -> f32x16& { return sacc; }, [&](int a, int p) { return row_op(bf, a, p); }, [&](int a) { return kv[a]; });
+      settle(sacc);
+      // Attention weights relative to the row's maximum.  The instruction makes 0 of one below 2^-126: where
+      // a wavefront has such a weight the library call, which scales it, takes all of them (for every
+      // weight it costs the pass 3 %).
+      float low = INFINITY;
 #pragma unroll
-    for (int a = 0; a < D / 8; ++a) {
-      const float4 ua = *(const float4*)(ut + 8 * a);
-      cacc = MFMA32(ua.x, vf[a].x, cacc);
-      cacc = MFMA32(ua.y, vf[a].y, cacc);
-      cacc = MFMA32(ua.z, vf[a].z, cacc);
-      cacc = MFMA32(ua.w, vf[a].w, cacc);
-    }
-    settle(sacc);
-    settle(cacc);
-    // Attention weights relative to the row's maximum.  The instruction makes 0 of one below 2^-126: where
-    // a wavefront has such a weight the library call, which scales it, takes all of them (for every
-    // weight it costs the pass 3 %).
-    float low = INFINITY;
-#pragma unroll
-    for (int jq = 0; jq < 4; ++jq) {
-      const float4 rm = *(const float4*)&st[bf][0][8 * jq + 4 * hf];
-      const float m_[4] = {rm.x, rm.y, rm.z, rm.w};
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        sacc[4 * jq + e] = fmaf(sacc[4 * jq + e], c2, -m_[e]);
-        low = fminf(low, sacc[4 * jq + e]);
+      for (int j = 0; j < 16; ++j) {
+        sacc[j] = fmaf(sacc[j], c2, -stat(bf, j).x);   // maximum
+        low = fminf(low, sacc[j]);
       }
-    }
-    if (__ballot(low < -126.f) != 0ull) {
+      if (__ballot(low < -126.f) != 0ull) {
 #pragma unroll
-      for (int j = 0; j < 16; ++j) sacc[j] = exp2f(sacc[j]);
-    } else {
+        for (int j = 0; j < 16; ++j) {
+          sacc[j] = exp2f(sacc[j]);
+          if (j % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+        }
+      } else {
 #pragma unroll
-      for (int j = 0; j < 16; ++j) sacc[j] = __builtin_amdgcn_exp2f(sacc[j]);
-    }
-#pragma unroll
-    for (int jq = 0; jq < 4; ++jq) {
-      const int m0 = 8 * jq + 4 * hf;
-      const float4 rl = *(const float4*)&st[bf][1][m0], rz = *(const float4*)&st[bf][2][m0],
-                   rn = *(const float4*)&st[bf][3][m0], ri = *(const float4*)&st[bf][4][m0];
-      const float l_[4] = {rl.x, rl.y, rl.z, rl.w}, z_[4] = {rz.x, rz.y, rz.z, rz.w},
-                  n_[4] = {rn.x, rn.y, rn.z, rn.w}, s_[4] = {ri.x, ri.y, ri.z, ri.w};
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int j = 4 * jq + e;
-        const float ex = sacc[j];
-        const float dist2 = fmaf(-2.f, cacc[j], z_[e]) + vvn;
-        float val = ex / fmaf(-rec, ex, l_[e]) * sqrtf(fmaxf(dist2, 0.f));
-        val = n == __float_as_int(n_[e]) ? s_[e] : val;
-        out[j] = pb.gmax ? fmaxf(out[j], val) : out[j] + val;
+        for (int j = 0; j < 16; ++j) sacc[j] = __builtin_amdgcn_exp2f(sacc[j]);
       }
+#pragma unroll
+      for (int j = 0; j < 16; ++j) sacc[j] *= __builtin_amdgcn_rcpf(fmaf(-rec, sacc[j], stat(bf, j).y));      // denominator
+      wt[c] = sacc;
+      turn();
+      bf ^= 1;
     }
-    if (more) {
-      store_u(bf ^ 1);
-      __syncthreads();
+    load_kv(vr);
+#pragma unroll
+    for (int c = 0; c < HC; ++c) {
+      if (h0 + c >= pb.G) break;
+      const bool last = c == HC - 1 || h0 + c + 1 == pb.G, end = h0 + c + 1 == pb.G;
+      const float vvn = o.vv[(int64_t)(g * pb.G + h0 + c) * ldv + nc];
+      if (!last) copy_item(h0 + c + 1, 1, bf ^ 1); else if (!end) copy_item(h0 + HC, 0, bf ^ 1);
+      f32x16 cacc;
+#pragma unroll
+      for (int j = 0; j < 16; ++j) cacc[j] = 0.f;
+      contract<3, NP, KS>([&](int) -> f32x16& { return cacc; }, [&](int a, int p) { return row_op(bf, a, p); }, [&](int a) { return kv[a]; });
+      settle(cacc);
+#pragma unroll
+      for (int jq = 0; jq < 4; ++jq) {
+        float4 r[4];                                   // zz, champion, its score
+        float x[4], low = INFINITY;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          r[e] = stat(bf, 4 * jq + e);
+          x[e] = fmaxf(fmaf(-2.f, cacc[4 * jq + e], r[e].x) + vvn, 0.f);
+          low = fminf(low, x[e]);
+        }
+        // (the instruction is one unit in the last place off, and less exact near the smallest normal number)
+        if (__ballot(low < 1e-36f) != 0ull) {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) x[e] = sqrtf(x[e]);
+        } else {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) x[e] = __builtin_amdgcn_sqrtf(x[e]);
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const int j = 4 * jq + e;
+          float val = wt[c][j] * x[e];
+          val = n == __float_as_int(r[e].y) ? r[e].z : val;
+          out[j] = pb.gmax ? fmaxf(out[j], val) : out[j] + val;
+        }
+      }
+      if (!end) {
+        turn();
+        bf ^= 1;
+      }
     }
   }
   const float invG = pb.gmax ? 1.f : 1.0f / (float)pb.G;
@@ -541,7 +661,7 @@ int run(const Prob& pb, const void* q, const void* k, const void* v, const float
     else
       RK_LAUNCH(ST_ATTN, st, (k_attn_f32<T, D, 2, VEC>), dim3(S, gy, pb.Hkv), dim3(128), 0, st, pb, qq, kk, vp, S, kps, w);
   }
-  launch_combine<T, D>(pb, vp, S, gram, w, part_z, (const T*)nullptr, 0, 0, 0, st);
+  launch_combine<T, D, 2>(pb, vp, S, gram, w, part_z, qq, 0, 0, st);
   const int nb = (pb.P + KB - 1) / KB;               // blocks of keys
   if (gram) {
     int chunks = (2 * cu + pb.Hq - 1) / pb.Hq;

@@ -24,6 +24,37 @@ def test_fp32_kernels_block_edges(rk, oracle_mod, Hq, Hkv, d, L, W, B):  # noqa:
     _score_against_oracle_then_every_stage_exactly(rk, oracle_mod, w, "fp32 block edges")
 
 
+@pytest.mark.parametrize("Hq,Hkv,d,L,W,dtype", [
+    (1, 1, 128, 31 + 33, 33, "f32"),      # one head; 31 keys of prefix; the second block of window rows holds one row
+    (4, 2, 128, 300, 32, "f32"),          # two heads: one chunk of heads exactly, window rows fill their block
+    (6, 2, 64, 289, 31, "f32"),           # three: the last chunk holds one; 258 keys, two past eight blocks
+    (5, 1, 128, 1090, 66, "f32"),         # five, three blocks of window rows, 1024 keys
+    (6, 2, 128, 300, 9, "bf16"),          # bf16 inputs (one plane) through the same kernels
+])
+def test_fp32_planes_head_and_row_remainders(rk, oracle_mod, Hq, Hkv, d, L, W, dtype):  # noqa: F811
+    """Heads past the last chunk, window rows past the last block: what the workspace held before (ones in every bit,
+    then zeros) must not show, bit for bit, and the scores lie within the tolerance of gpu_util.py."""
+    w = workloads.small_case(Hq=Hq, Hkv=Hkv, d=d, L=L, W=W, B=W + 20, dtype=dtype, D=2 * d, seed=83)
+    q, k, v = workloads.make_qkv(w)
+    wo = workloads.make_wo(w)
+    p = params_for(rk, w)
+    gram = torch.empty((Hq, d, d), dtype=torch.float32, device="cuda")
+    rk.restkv_prepare_wo(p, wo.cuda(), gram)
+    buf = rk.alloc_layer_buffers(p, q.dtype, "cuda")
+    got = []
+    rk.restkv_debug_force_fp32(True)
+    try:
+        for fill in (255, 0):
+            buf.workspace.view(torch.uint8).fill_(fill)
+            rk.restkv_score(p, q.cuda(), k.cuda(), v.cuda(), gram, buf.score, buf.workspace)
+            got.append(buf.score[..., :w.prefix].cpu().numpy())
+    finally:
+        rk.restkv_debug_force_fp32(False)
+    assert np.array_equal(got[0], got[1])
+    for g, (Ig, tol) in oracle_score(oracle_mod, w, q, k, v, wo).items():
+        assert_score_close(got[0][g], Ig, tol, f"head {g}")
+
+
 @pytest.mark.parametrize("dtype,pad", [("f32", 1), ("f32", 4), ("bf16", 3), ("bf16", 4)])
 def test_fp32_kernels_row_alignment(rk, oracle_mod, dtype, pad):  # noqa: F811
     """Rows that start on no 4-element boundary (element-wise loads) and on one (4-element loads);
