@@ -113,13 +113,12 @@ constexpr int ilog2(int x) { return x <= 1 ? 0 : 1 + ilog2(x / 2); }
 // heads of 64 1 %.
 template <int D>
 __host__ __device__ __forceinline__ bool heads_first(const Prob& pb) { return D == 128 && (pb.Hkv & 7) == 0; }
+struct WgAt { int chunk, y, g; };
+// workgroup id of a pass of chunks x ny x Hkv workgroups
 template <int D>
-__device__ __forceinline__ int wg_head(const Prob& pb) { return heads_first<D>(pb) ? blockIdx.x : blockIdx.z; }
-template <int D>
-__device__ __forceinline__ int wg_chunk(const Prob& pb) { return heads_first<D>(pb) ? blockIdx.z : blockIdx.x; }
-template <int D>
-inline dim3 wg_grid(const Prob& pb, int chunks, int y) {
-  return heads_first<D>(pb) ? dim3(pb.Hkv, y, chunks) : dim3(chunks, y, pb.Hkv);
+__device__ __forceinline__ WgAt wg_at(const Prob& pb, int id, int chunks, int ny) {
+  const int n0 = heads_first<D>(pb) ? pb.Hkv : chunks, x = id % n0, r = id / n0;
+  return heads_first<D>(pb) ? WgAt{r / ny, r % ny, x} : WgAt{x, r % ny, r / ny};
 }
 
 // ------------------------------------------------------------------------------------------
@@ -234,30 +233,36 @@ __device__ __forceinline__ void wait_vm() {
 // KS2 (few heads per KV head): wavefronts 0..3 take keys 0..31 of a tile and wavefronts 4..7 keys
 // 32..63 of the same heads, so that a workgroup holds half as many heads.  A wavefront without a head
 // only copies.
-// wg_grid(key chunks, ceil(G/HPW)), 512 threads; HPW = 4 heads per workgroup (8 for D = 64), half
+// Workgroups: key chunks x ceil(G/HPW) x KV heads, 512 threads; HPW = 4 heads per workgroup (8 for D = 64), half
 // of that with KS2.
 template <int D, bool KS2>
-__global__ __launch_bounds__(512) void k_vv_pipe(Prob pb, const uint16_t* __restrict__ v,
-                                                 const float* __restrict__ gram, float* __restrict__ vv,
-                                                 int ldv, int tiles_per_wg) {
+struct VvSmem {
+  static constexpr int HPW = 8 / (D / 64) / (KS2 ? 2 : 1);
+  __attribute__((aligned(1024))) uint16_t Vs[4][TN * D];
+  float part[2][HPW][D / 64][TN];
+};
+template <int D, bool KS2>
+__device__ __forceinline__ void vv_pass(const Prob& pb, WgAt at, VvSmem<D, KS2>& sm, const uint16_t* __restrict__ v,
+                                        const float* __restrict__ gram, float* __restrict__ vv,
+                                        int ldv, int tiles_per_wg) {
   constexpr int NW = 8, KS = D / 16, CB = D / 32, WPH = CB / 2, HPW = NW / WPH / (KS2 ? 2 : 1);
   constexpr int NMB = KS2 ? 1 : 2;                  // 32-key blocks of a tile per wavefront
   using Ring = TileRing<D, 0>;
   constexpr int NG = Ring::NI / NW;                 // copies per wavefront and tile
-  __shared__ __attribute__((aligned(1024))) uint16_t Vs[4][TN * D];
-  __shared__ float part[2][HPW][WPH][TN];
-  const int g = wg_head<D>(pb);
+  auto& Vs = sm.Vs;
+  auto& part = sm.part;
+  const int g = at.g;
   const int l = threadIdx.x & 63, wv = threadIdx.x >> 6, rr = l & 31, hf = l >> 5;
   const int wvs = wave_index();                     // the same as a scalar, for the copies' addresses
   const int wr = KS2 ? wvs % (NW / 2) : wvs, ko = KS2 ? 32 * (wvs / (NW / 2)) : 0;   // first key of this wavefront in a tile
   const int hw = wr / WPH, pr = wr % WPH;           // head inside the workgroup, row block pair
-  const int hloc = blockIdx.y * HPW + hw;
+  const int hloc = at.y * HPW + hw;
   const int h = g * pb.G + (hloc < pb.G ? hloc : 0);
   const uint16_t* vg = v + (int64_t)g * pb.kv_sh;
   const uint32_t pitch = (uint32_t)pb.kv_st * 2u;
 
   const int NT = (pb.P + TN - 1) / TN;
-  const int t0 = wg_chunk<D>(pb) * tiles_per_wg;
+  const int t0 = at.chunk * tiles_per_wg;
   const int t1 = min(NT, t0 + tiles_per_wg);
   if (t0 >= t1) return;
   uint32_t voff[NG];
@@ -422,7 +427,7 @@ __global__ __launch_bounds__(512) void k_vv_pipe(Prob pb, const uint16_t* __rest
 // ------------------------------------------------------------------------------------------
 // Attention pass, pipelined: per key split, champion-excluded online softmax statistics and
 // A.V sums (outputs: the per-split statistics described in score_common.hpp).
-// wg_grid(S, row blocks), 512 threads.
+// Workgroups: splits x row blocks x KV heads, 512 threads.
 //
 // K tiles travel through a 3-deep, V tiles through a 4-deep asynchronous LDS ring.  A step t has a
 // matrix half (P.V of tile t-1, then Q.K of tile t: 48 MFMAs) and a vector half (softmax
@@ -440,23 +445,25 @@ __global__ __launch_bounds__(512) void k_vv_pipe(Prob pb, const uint16_t* __rest
 // blocks, wavefronts 0..3 take keys 0..31 of every tile and wavefronts 4..7 keys 32..63, and the two
 // halves meet in LDS at the end, so that a split leaves one set of sums either way.  A wavefront
 // without rows only copies.
+template <int D>
+struct AttnSmem { __attribute__((aligned(1024))) uint16_t ring[7][TN * D]; };
 template <int D, bool KS2>
-__global__ __launch_bounds__(512) void k_attn_pipe(Prob pb, const uint16_t* __restrict__ q,
-                                                   const uint16_t* __restrict__ k,
-                                                   const uint16_t* __restrict__ v, int S, int kps,
-                                                   int log2iw, ScorePtrs o) {
+__device__ __forceinline__ void attn_pass(const Prob& pb, WgAt at, AttnSmem<D>& sm, const uint16_t* __restrict__ q,
+                                          const uint16_t* __restrict__ k,
+                                          const uint16_t* __restrict__ v, int S, int kps,
+                                          int log2iw, const ScorePtrs& o) {
   constexpr int NW = 8, KS = D / 16, CB = D / 32, RB = KS2 ? 4 : 8, NMB = KS2 ? 1 : 2;
   using RingK = TileRing<D, 0>;
   using RingV = TileRing<D, 1>;
   constexpr int NG = 2 * (RingK::NI / NW);          // copies per wavefront and tile
-  __shared__ __attribute__((aligned(1024))) uint16_t ring[7][TN * D];
+  auto& ring = sm.ring;
   uint16_t (*Ks)[TN * D] = ring, (*Vs)[TN * D] = ring + 3;
 
-  const int s = wg_chunk<D>(pb), g = wg_head<D>(pb);
+  const int s = at.chunk, g = at.g;
   const int l = threadIdx.x & 63, wv = wave_index(), rr = l & 31, hf = l >> 5;
-  const RowInfo ri = row_info(pb, g, blockIdx.y * RB + wv % RB, l, log2iw);
+  const RowInfo ri = row_info(pb, g, at.y * RB + wv % RB, l, log2iw);
   const int ko = KS2 ? 32 * (wv / RB) : 0;          // first key of this wavefront in a tile
-  const bool idle = (blockIdx.y * RB + wv % RB) << log2iw >= pb.W;   // no row here: this wavefront only copies
+  const bool idle = (at.y * RB + wv % RB) << log2iw >= pb.W;   // no row here: this wavefront only copies
   const uint16_t* kg = k + (int64_t)g * pb.kv_sh;
   const uint16_t* vg = v + (int64_t)g * pb.kv_sh;
 
@@ -809,9 +816,27 @@ __global__ __launch_bounds__(512) void k_attn_pipe(Prob pb, const uint16_t* __re
   }
 }
 
+// The two passes that need nothing of each other, one launch: workgroups [0, n_attn) are the attention pass's, the
+// others the value-Gram pass's, which start as the first ones end (a workgroup fills a compute unit either way).
+// ATTN, VV: 0 that pass is not there, 1 it is, 2 with KS2.  512 threads.
+struct AttnArgs { int n, S, ny, kps, log2iw; };
+struct VvArgs { int chunks, ny, ldv, tiles_per_wg; };
+template <int D, int ATTN, int VV>
+__global__ __launch_bounds__(512) void k_attn_vv(Prob pb, const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
+                                                 const uint16_t* __restrict__ v, const float* __restrict__ gram,
+                                                 ScorePtrs o, AttnArgs aa, VvArgs va) {
+  __shared__ union { AttnSmem<ATTN ? D : 64> a; VvSmem<D, VV == 2> v; } sm;
+  if (ATTN && (!VV || (int)blockIdx.x < aa.n)) {
+    if constexpr (ATTN != 0) attn_pass<D, ATTN == 2>(pb, wg_at<D>(pb, blockIdx.x, aa.S, aa.ny), sm.a, q, k, v, aa.S, aa.kps, aa.log2iw, o);
+  } else {
+    if constexpr (VV != 0)
+      vv_pass<D, VV == 2>(pb, wg_at<D>(pb, (int)blockIdx.x - aa.n, va.chunks, va.ny), sm.v, v, gram, o.vv, va.ldv, va.tiles_per_wg);
+  }
+}
+
 // ------------------------------------------------------------------------------------------
 // Score pass: logits again, cross term u.v_n, closed form, mean over the group.
-// wg_grid(key chunks, row blocks), 512 threads = 8 wavefronts of 32 query rows each.
+// Workgroups: key chunks x row blocks x KV heads, 512 threads = 8 wavefronts of 32 query rows each.
 //
 // Per element (query row r of head h, key n), with M, l, zz the row's softmax maximum,
 // denominator and z M_h z^T from the attention pass:
@@ -844,7 +869,7 @@ template <int D, int GP, bool KS2>
 __global__ __launch_bounds__(512) void k_score_pipe(Prob pb, const uint16_t* __restrict__ q,
                                                     const uint16_t* __restrict__ k,
                                                     const uint16_t* __restrict__ v, ScorePtrs o, int ldv,
-                                                    float* __restrict__ score, int tiles_per_wg, int nwb) {
+                                                    float* __restrict__ score, int tiles_per_wg, int nwb, int chunks, int ny) {
   constexpr int NW = 8, KS = D / 16, LG = ilog2(GP), IW = 32 / GP, RB = KS2 ? 4 : 8, NMB = KS2 ? 1 : 2;
   constexpr int GV = GP < 4 ? 4 : GP;               // vv rows per ring slot (whole 1 KiB copies)
   constexpr int NVB = GV / 4;                       // 1 KiB copies per vv tile
@@ -856,16 +881,17 @@ __global__ __launch_bounds__(512) void k_score_pipe(Prob pb, const uint16_t* __r
   __shared__ __attribute__((aligned(1024))) float vvs[4][GV][TN];
   __shared__ __attribute__((aligned(16))) float rowc[NW][4][32];   // per local row: accumulator start values, champion key and score
 
-  const int g = wg_head<D>(pb);
+  const WgAt at = wg_at<D>(pb, blockIdx.x, chunks, ny);
+  const int g = at.g;
   const int l = threadIdx.x & 63, wv = threadIdx.x >> 6, rr = l & 31, hf = l >> 5;
   const int wvs = wave_index();                     // the same as a scalar, for the copies' addresses
-  const int wb = blockIdx.y * RB + wvs % RB;        // block of IW window positions
+  const int wb = at.y * RB + wvs % RB;        // block of IW window positions
   const int ko = KS2 ? 32 * (wvs / RB) : 0;         // first key of this wavefront in a tile
   const uint16_t* kg = k + (int64_t)g * pb.kv_sh;
   const uint16_t* vg = v + (int64_t)g * pb.kv_sh;
 
   const int NT = (pb.P + TN - 1) / TN;
-  const int t0 = wg_chunk<D>(pb) * tiles_per_wg;
+  const int t0 = at.chunk * tiles_per_wg;
   const int t1 = min(NT, t0 + tiles_per_wg);
   if (t0 >= t1) return;
 
@@ -1167,11 +1193,37 @@ void launch_score_pipe(const Prob& pb, const uint16_t* q, const uint16_t* k, con
   // one resident workgroup per compute unit, each walking a run of tiles
   const int NT = (pb.P + TN - 1) / TN;
   const int tpp = max(1, (int)(((int64_t)NT * rg.gy * pb.Hkv + n_cu() - 1) / n_cu()));
-  const dim3 gr = wg_grid<D>(pb, (NT + tpp - 1) / tpp, rg.gy);
+  const int chunks = (NT + tpp - 1) / tpp;
+  const dim3 gr(chunks * rg.gy * pb.Hkv);
   if (rg.ks2)
-    RK_LAUNCH(ST_SCORE, st, (k_score_pipe<D, GP, true>), gr, dim3(512), 0, st, pb, q, k, v, w, ldv, score, tpp, nwb);
+    RK_LAUNCH(ST_SCORE, st, (k_score_pipe<D, GP, true>), gr, dim3(512), 0, st, pb, q, k, v, w, ldv, score, tpp, nwb, chunks, rg.gy);
   else
-    RK_LAUNCH(ST_SCORE, st, (k_score_pipe<D, GP, false>), gr, dim3(512), 0, st, pb, q, k, v, w, ldv, score, tpp, nwb);
+    RK_LAUNCH(ST_SCORE, st, (k_score_pipe<D, GP, false>), gr, dim3(512), 0, st, pb, q, k, v, w, ldv, score, tpp, nwb, chunks, rg.gy);
+}
+
+// Short contexts: attention pass and value-Gram pass side by side, each on a part of the compute units, where that ends
+// earlier than one after the other on all of them.  A workgroup of the attention pass takes A0 + a t us for t tiles,
+// one of the value-Gram pass V0 + v t (fixed parts: launch, operands, first tile, sums; heads of 128 and 64: a 2.6 and
+// 1.4, v 2.1 and 1.4).  Fewer splits are also fewer sums for the merge.  Clustered logits take up to 1.45 a, so the
+// side by side form has to win with that too (it stops doing so at about eight tiles a workgroup).
+template <int D, typename F>
+void share_the_chip(const Prob& pb, int nt, int S1, AttnArgs& aa, VvArgs& va, F set_splits) {
+  constexpr float A0 = 10.f, V0 = 6.f, a = D == 128 ? 2.6f : 1.4f, v = D == 128 ? 2.1f : 1.4f, slow = 1.45f;
+  const int ntv = (pb.P + TN - 1) / TN;
+  auto attn = [&](int S, float c) { return A0 + c * (float)((nt + S - 1) / S); };
+  const float seq = attn(S1, a) + V0 + v * va.tiles_per_wg, seq_slow = attn(S1, slow * a) + V0 + v * va.tiles_per_wg;
+  float best = seq;
+  int bs = 0, bc = 0;
+  for (int S = min(S1, n_cu() / (pb.Hkv * aa.ny)); S >= 1; --S) {
+    const int c = min(ntv, (n_cu() - S * aa.ny * pb.Hkv) / (va.ny * pb.Hkv));     // chunks for the value-Gram pass
+    if (c < 1) continue;
+    const float tv = V0 + v * (float)((ntv + c - 1) / c), t = max(attn(S, a), tv);
+    if (t < best && max(attn(S, slow * a), tv) <= seq_slow) { best = t; bs = S; bc = c; }
+  }
+  if (bs == 0) return;
+  set_splits(bs);
+  va.tiles_per_wg = (ntv + bc - 1) / bc;
+  va.chunks = (ntv + va.tiles_per_wg - 1) / va.tiles_per_wg;
 }
 
 template <int D>
@@ -1182,49 +1234,67 @@ int run_mfma(const Prob& pb, const void* q, const void* k, const void* v, const 
   const uint16_t* vp = (const uint16_t*)v;
   const ScorePtrs w = score_ptrs(ws, lay);
   const RowGeom rg = row_geom(pb, pb.L, ATTN_KS2_TILES, false);
-  // attention pass: about one workgroup per compute unit, whole tiles per split
-  int S = n_cu() / (pb.Hkv * rg.gy);
-  const int max_s = (pb.L + TN - 1) / TN;
-  if (S > max_s) S = max_s;
-  if (S > lay.S_max) S = lay.S_max;
-  if (S < 1) S = 1;
-  int kps = (pb.L + S - 1) / S;
-  kps = (kps + TN - 1) / TN * TN;
-  S = (pb.L + kps - 1) / kps;                      // (whole tiles: the last splits may have nothing left)
-  const float* part_z = w.part_z;
-  if (pb.ext_lse) {
-    // the caller's attention output and log-sum-exp stand in for the attention pass: one "split"
-    S = 1;
-    const int rows = pb.Hq * pb.W;
-    RK_LAUNCH(ST_ATTN, st, (k_stats_fill<0>), dim3((rows + 255) / 256), dim3(256), 0, st, rows, pb.ext_lse,
-              w.part_m, w.part_mx, w.part_n, w.part_ref, w.part_l);
-    part_z = pb.ext_out;
-  } else {
-    const dim3 ga = wg_grid<D>(pb, S, rg.gy);
-    if (rg.ks2)
-      RK_LAUNCH(ST_ATTN, st, (k_attn_pipe<D, true>), ga, dim3(512), 0, st, pb, qq, kk, vp, S, kps, rg.log2iw, w);
-    else
-      RK_LAUNCH(ST_ATTN, st, (k_attn_pipe<D, false>), ga, dim3(512), 0, st, pb, qq, kk, vp, S, kps, rg.log2iw, w);
-  }
   if (pb.ind != 0) gram = nullptr;                 // the attention-weight and value-norm indicators have no projection
-  launch_combine<bf16_t, D, 1>(pb, (const bf16_t*)v, S, gram, w, part_z, (const bf16_t*)q, ilog2(rg.gp), lay.nwb, st);
+  VvArgs va = {0, 0, lay.ldv, 0};
+  bool vks2 = false;
   if (gram) {
     constexpr int HPW = D == 128 ? 4 : 8;
     const int NTv = (pb.P + TN - 1) / TN;
     // as for the rows: half as many heads per workgroup, at most 3/2 of the tiles, VV_KS2_TILES of them
     const int hg4 = (pb.G + HPW / 2 - 1) / (HPW / 2), hg8 = (pb.G + HPW - 1) / HPW;
     const int64_t t4 = span_tiles(NTv, (int64_t)hg4 * pb.Hkv);
-    const bool ks2 = t4 >= VV_KS2_TILES && 2 * t4 <= 3 * span_tiles(NTv, (int64_t)hg8 * pb.Hkv);
-    const int hpw = ks2 ? HPW / 2 : HPW;
-    const int hg = (pb.G + hpw - 1) / hpw;
-    int tpv = (int)(((int64_t)NTv * hg * pb.Hkv + n_cu() - 1) / n_cu());
-    if (tpv < 1) tpv = 1;
-    const dim3 gv = wg_grid<D>(pb, (NTv + tpv - 1) / tpv, hg);
-    if (ks2) RK_LAUNCH(ST_VV, st, (k_vv_pipe<D, true>), gv, dim3(512), 0, st, pb, vp, gram, w.vv, lay.ldv, tpv);
-    else RK_LAUNCH(ST_VV, st, (k_vv_pipe<D, false>), gv, dim3(512), 0, st, pb, vp, gram, w.vv, lay.ldv, tpv);
-  } else {
+    vks2 = t4 >= VV_KS2_TILES && 2 * t4 <= 3 * span_tiles(NTv, (int64_t)hg8 * pb.Hkv);
+    va.ny = vks2 ? hg4 : hg8;
+    va.tiles_per_wg = max(1, (int)(((int64_t)NTv * va.ny * pb.Hkv + n_cu() - 1) / n_cu()));
+    va.chunks = (NTv + va.tiles_per_wg - 1) / va.tiles_per_wg;
+  }
+  AttnArgs aa = {0, 0, rg.gy, 0, rg.log2iw};
+  if (!pb.ext_lse) {
+    // attention pass: about one workgroup per compute unit, whole tiles per split
+    const int nt = (pb.L + TN - 1) / TN;
+    auto set_splits = [&](int S) {
+      const int t = (nt + S - 1) / S;
+      aa.kps = t * TN;
+      aa.S = (nt + t - 1) / t;                     // (whole tiles: the last splits may have nothing left)
+      aa.n = aa.S * rg.gy * pb.Hkv;
+    };
+    const int S1 = max(1, min(min(n_cu() / (pb.Hkv * rg.gy), nt), lay.S_max));
+    set_splits(S1);
+    if (gram && !rg.ks2 && !vks2) share_the_chip<D>(pb, nt, S1, aa, va, set_splits);
+  }
+  if (!gram) {
     RK_LAUNCH(ST_VV, st, (k_vnorm2<D>), dim3((pb.P + 255) / 256, pb.Hkv), dim3(256), 0, st, pb, vp,
               w.vv, lay.ldv);
+  }
+  const dim3 gav(aa.n + va.chunks * va.ny * pb.Hkv);
+  auto attn_vv = [&](auto a, auto b) {
+    RK_LAUNCH(decltype(a)::value ? ST_ATTN : ST_VV, st, (k_attn_vv<D, decltype(a)::value, decltype(b)::value>), gav, dim3(512), 0, st,
+              pb, qq, kk, vp, gram, w, aa, va);
+  };
+  const std::integral_constant<int, 0> no;
+  const std::integral_constant<int, 1> plain;
+  const std::integral_constant<int, 2> split;
+  auto with_vv = [&](auto a) {
+    if (!gram) { if constexpr (decltype(a)::value != 0) attn_vv(a, no); }
+    else if (vks2) attn_vv(a, split);
+    else attn_vv(a, plain);
+  };
+  const float* part_z = w.part_z;
+  auto combine = [&](int S) {
+    launch_combine<bf16_t, D, 1>(pb, (const bf16_t*)v, S, gram, w, part_z, (const bf16_t*)q, ilog2(rg.gp), lay.nwb, st);
+  };
+  if (pb.ext_lse) {
+    // the caller's attention output and log-sum-exp stand in for the attention pass: one "split"
+    const int rows = pb.Hq * pb.W;
+    RK_LAUNCH(ST_ATTN, st, (k_stats_fill<0>), dim3((rows + 255) / 256), dim3(256), 0, st, rows, pb.ext_lse,
+              w.part_m, w.part_mx, w.part_n, w.part_ref, w.part_l);
+    part_z = pb.ext_out;
+    combine(1);
+    with_vv(no);
+  } else {
+    if (rg.ks2) with_vv(split);
+    else with_vv(plain);
+    combine(aa.S);
   }
 #define RK_SCORE(GPV) launch_score_pipe<D, GPV>(pb, qq, kk, vp, w, lay.ldv, score, lay.nwb, st)
   switch (rg.gp) {
