@@ -1161,7 +1161,7 @@ int64_t span_tiles(int nt, int64_t per) {
 // (264 workgroups), 100k tokens 270 against 207.  Fifteen blocks for eight 1285 against 1006.  With heads of
 // 128 a tile costs 0.7: nine to twelve blocks 31.7 against 31.6 and 36.5 against 33.3.  Attention pass, nine and
 // ten blocks, 16 tiles for every KV head 69.2 against 67.5, 49 tiles 173 ... 184 against 182 ... 189.
-struct RowGeom { int gp, log2iw, gy; bool ks2; };
+struct RowGeom { int gp, log2iw, nwr, gy; bool ks2; };
 RowGeom row_geom(const Prob& pb, int n, int min_tiles, bool wide) {
   RowGeom r;
   r.gp = 1;
@@ -1173,6 +1173,7 @@ RowGeom row_geom(const Prob& pb, int n, int min_tiles, bool wide) {
   r.ks2 = (int64_t)nt * gy4 * pb.Hkv >= (int64_t)min_tiles * n_cu() &&
           (gy4 == gy8 || (wide && 2 * span_tiles(nt, (int64_t)gy4 * pb.Hkv) <= 3 * span_tiles(nt, (int64_t)gy8 * pb.Hkv)));
   r.gy = r.ks2 ? gy4 : gy8;
+  r.nwr = nwr;
   return r;
 }
 // Both halves of a tile pay the first tile's bookkeeping and meet at the end (4-5 us).  32/8 heads of 128,
@@ -1201,29 +1202,36 @@ void launch_score_pipe(const Prob& pb, const uint16_t* q, const uint16_t* k, con
     RK_LAUNCH(ST_SCORE, st, (k_score_pipe<D, GP, false>), gr, dim3(512), 0, st, pb, q, k, v, w, ldv, score, tpp, nwb, chunks, rg.gy);
 }
 
-// Short contexts: attention pass and value-Gram pass side by side, each on a part of the compute units, where that ends
-// earlier than one after the other on all of them.  A workgroup of the attention pass takes A0 + a t us for t tiles,
-// one of the value-Gram pass V0 + v t (fixed parts: launch, operands, first tile, sums; heads of 128 and 64: a 2.6 and
-// 1.4, v 2.1 and 1.4).  Fewer splits are also fewer sums for the merge.  Clustered logits take up to 1.45 a, so the
-// side by side form has to win with that too (it stops doing so at about eight tiles a workgroup).
-template <int D, typename F>
-void share_the_chip(const Prob& pb, int nt, int S1, AttnArgs& aa, VvArgs& va, F set_splits) {
-  constexpr float A0 = 10.f, V0 = 6.f, a = D == 128 ? 2.6f : 1.4f, v = D == 128 ? 2.1f : 1.4f, slow = 1.45f;
+// Attention pass and value-Gram pass side by side, each on a part of the compute units, where that ends earlier than
+// one after the other on all of them: fixed parts (launch, operands, first tile, sums) overlap, fewer splits are fewer
+// sums for the merge, and a unit bound by vector instructions next to one bound by the matrix cores runs at a higher
+// clock.  Model: a workgroup of the attention pass takes A0 + a t us for t tiles, one of the value-Gram pass V0 + v t, one
+// after the other V1 more and 6 % more per tile; clustered logits take up to SLOW a.  Taken is the split count with the
+// smallest sum of plain and clustered time (SPLIT us for each split) that loses in neither.  32/8 heads, window 64,
+// score + smoothing, one after the other / side by side: 4k 67.5 / 58.7 us, 16k 120.4 / 108, 32k 188.7 / 178.8
+// (clustered 208.9 / 207.1), 64k 325.6 / 315.9 (362.9 / 357.0), 128k 599.9 / 594.3 (660.7 / 649.9); 16/4 heads, 40k,
+// 123.0 / 114.7; 64/8, 6k, 93.9 / 83.9.  Only where the workgroups have equal work: a last row block or head group that
+// is mostly empty ends early and leaves its unit idle (28/4 heads, 30k, window 33, clustered 155 against 161).  Heads of
+// 64 fill half a unit, so there the two passes share units anyway (28/4 heads, 50k, clustered 174 against 192).
+inline int share_the_chip(const Prob& pb, int nt, int nwr, int S1, const VvArgs& va, int ny, int* chunks) {
+  constexpr float A0 = 10.f, V0 = 6.f, V1 = 4.f, A = 1.5f, V = 1.2f, SEQ = 1.06f, SLOW = 1.5f, SPLIT = 1.3f;
+  if ((ny > 1 && (nwr - 1) % 8 < 4) || (va.ny > 1 && (pb.G - 1) % 4 < 2)) return 0;
   const int ntv = (pb.P + TN - 1) / TN;
-  auto attn = [&](int S, float c) { return A0 + c * (float)((nt + S - 1) / S); };
-  const float seq = attn(S1, a) + V0 + v * va.tiles_per_wg, seq_slow = attn(S1, slow * a) + V0 + v * va.tiles_per_wg;
-  float best = seq;
-  int bs = 0, bc = 0;
-  for (int S = min(S1, n_cu() / (pb.Hkv * aa.ny)); S >= 1; --S) {
-    const int c = min(ntv, (n_cu() - S * aa.ny * pb.Hkv) / (va.ny * pb.Hkv));     // chunks for the value-Gram pass
-    if (c < 1) continue;
-    const float tv = V0 + v * (float)((ntv + c - 1) / c), t = max(attn(S, a), tv);
-    if (t < best && max(attn(S, slow * a), tv) <= seq_slow) { best = t; bs = S; bc = c; }
+  auto tiles = [](int n, int parts) { return (float)((n + parts - 1) / parts); };
+  auto seq = [&](float a) { return A0 + V0 + V1 + SEQ * (a * tiles(nt, S1) + V * va.tiles_per_wg); };
+  const float seq1 = seq(A), seq2 = seq(SLOW * A);
+  float best = INFINITY;
+  int bs = 0;
+  for (int S = 1; S <= S1; ++S) {
+    const int c = min(ntv, (n_cu() - S * ny * pb.Hkv) / (va.ny * pb.Hkv));     // chunks for the value-Gram pass
+    if (c < 1) break;
+    const float tv = V0 + V * tiles(ntv, c), t1 = max(A0 + A * tiles(nt, S), tv), t2 = max(A0 + SLOW * A * tiles(nt, S), tv);
+    if (t1 >= seq1 || t2 > seq2 || t1 + t2 + SPLIT * S >= best) continue;
+    best = t1 + t2 + SPLIT * S;
+    bs = S;
+    *chunks = c;
   }
-  if (bs == 0) return;
-  set_splits(bs);
-  va.tiles_per_wg = (ntv + bc - 1) / bc;
-  va.chunks = (ntv + va.tiles_per_wg - 1) / va.tiles_per_wg;
+  return bs;
 }
 
 template <int D>
@@ -1260,7 +1268,13 @@ int run_mfma(const Prob& pb, const void* q, const void* k, const void* v, const 
     };
     const int S1 = max(1, min(min(n_cu() / (pb.Hkv * rg.gy), nt), lay.S_max));
     set_splits(S1);
-    if (gram && !rg.ks2 && !vks2) share_the_chip<D>(pb, nt, S1, aa, va, set_splits);
+    int chunks = 0;
+    if (const int S2 = D == 128 && gram && !rg.ks2 && !vks2 ? share_the_chip(pb, nt, rg.nwr, S1, va, rg.gy, &chunks) : 0) {
+      set_splits(S2);
+      const int ntv = (pb.P + TN - 1) / TN;
+      va.tiles_per_wg = (ntv + chunks - 1) / chunks;
+      va.chunks = (ntv + va.tiles_per_wg - 1) / va.tiles_per_wg;
+    }
   }
   if (!gram) {
     RK_LAUNCH(ST_VV, st, (k_vnorm2<D>), dim3((pb.P + 255) / 256, pb.Hkv), dim3(256), 0, st, pb, vp,

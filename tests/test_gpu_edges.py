@@ -329,3 +329,31 @@ def test_gram_and_statistics_at_any_float_address(rk, dtype, d):  # noqa: F811
         torch.cuda.synchronize()
         got.append((one, buf.score.clone()))
     assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
+
+
+@pytest.mark.parametrize("Hq,Hkv,d,L,W", [
+    (8, 8, 128, 64 * 3 + 1 + 16, 16),     # prefix of three tiles and a key: hardly more tiles than units to share
+    (32, 8, 128, 64 * 33, 64),            # 33 tiles a head, prefix ends with a tile
+    (32, 8, 128, 64 * 33 + 1, 64),        # one key in the last tile of the whole context
+    (16, 4, 128, 1500, 40),               # four KV heads, five row blocks
+    (28, 4, 128, 900, 33),                # nine row blocks: the second workgroup of a split is nearly empty, one pass after the other
+    (64, 8, 128, 1200, 64),               # two full workgroups of rows, two of heads
+])
+def test_attention_and_value_gram_passes_share_the_chip(rk, oracle_mod, Hq, Hkv, d, L, W):  # noqa: F811
+    """The two passes in one launch, side by side or one after the other: first and last KV head against the oracle, and
+    the same bits from a workspace full of ones (no sum is read that was not written)."""
+    w = workloads.small_case(Hq=Hq, Hkv=Hkv, d=d, L=L, W=W, B=W + 20, dtype="bf16", D=2 * d, structure="sinks", seed=91)
+    q, k, v = workloads.make_qkv(w)
+    wo = workloads.make_wo(w)
+    p = params_for(rk, w)
+    gram = torch.empty((Hq, d, d), dtype=torch.float32, device="cuda")
+    rk.restkv_prepare_wo(p, wo.cuda(), gram)
+    buf = rk.alloc_layer_buffers(p, q.dtype, "cuda")
+    got = []
+    for fill in (255, 0):
+        buf.workspace.view(torch.uint8).fill_(fill)
+        rk.restkv_score(p, q.cuda(), k.cuda(), v.cuda(), gram, buf.score, buf.workspace)
+        got.append(buf.score[..., :w.prefix].cpu().numpy())
+    assert np.array_equal(got[0], got[1])
+    for g, (Ig, tol) in oracle_score(oracle_mod, w, q, k, v, wo, heads=[0, Hkv - 1]).items():
+        assert_score_close(got[0][g], Ig, tol, f"head {g}")
