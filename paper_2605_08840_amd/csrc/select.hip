@@ -122,12 +122,13 @@ __global__ __launch_bounds__(NT, NT == 1024 ? 4 : 1) void k_sel_row(Prob pb, con
 // compute units idle behind a launch of its own), with the loads of its own chunk already in
 // flight.  Thread t then owns positions chunk * 4096 + 16 t .. + 15: the entries above the bracket
 // are counted (one count per chunk), the entries inside it leave as a 16-bit mask per thread
-// (element e at bit 15 - e).  grid (chunks, Hkv), 256 threads.
+// (element e at bit 15 - e).  head_grid: parts = chunks, 256 threads.
 __global__ __launch_bounds__(256) void k_sel_scan(Prob pb, const float* __restrict__ fin, SelPtrs w,
                                                   int nchunks, int vec) {
   __shared__ CutSmem cs;
   __shared__ uint32_t red[4];
-  const int g = blockIdx.y, ch = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const HeadPart hp = head_part(pb);
+  const int g = hp.g, ch = hp.x, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const float* row = fin + (int64_t)g * pb.ld;
   const int n0 = ch * SCH + 16 * tid;
   float x[16];
@@ -177,7 +178,7 @@ __global__ __launch_bounds__(256) void k_sel_scan(Prob pb, const float* __restri
 //     selected candidates there; from there on it emits its chunks (thread t owns 8 consecutive
 //     positions of each).  Window tokens and the unused tail of a smaller per-head budget are
 //     written by the first workgroup.
-// grid (workgroups, Hkv), 512 threads; workgroup x owns the chunks [x cpw, (x + 1) cpw).
+// head_grid: parts = workgroups of a head, 512 threads; workgroup x owns the chunks [x cpw, (x + 1) cpw).
 __global__ __launch_bounds__(512) void k_sel_emit(Prob pb, const float* __restrict__ fin, SelPtrs w,
                                                   int nchunks, int cpw, int vec, int32_t* __restrict__ idx) {
   constexpr int NT = 512, NW = NT / 64, FPT = SCAP / NT;
@@ -186,14 +187,15 @@ __global__ __launch_bounds__(512) void k_sel_emit(Prob pb, const float* __restri
   __shared__ uint32_t red[2][NW];
   __shared__ uint32_t flag;
   __shared__ int cpos[SCAP];
-  const int g = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const HeadPart hp = head_part(pb);
+  const int g = hp.g, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const float* row = fin + (int64_t)g * pb.ld;
   const int bg = head_budget(pb, g), k = bg - pb.W;
   int32_t* out = idx + (int64_t)g * pb.B;
   const uint32_t* above = w.above + (int64_t)g * nchunks;
-  const int ch0 = blockIdx.x * cpw, ch1 = min(nchunks, ch0 + cpw);
+  const int ch0 = hp.x * cpw, ch1 = min(nchunks, ch0 + cpw);
   const uint32_t first = (uint32_t)ch0 * (uint32_t)SCH;         // first position that is this workgroup's
-  if (blockIdx.x == 0) {
+  if (hp.x == 0) {
     for (int j = tid; j < pb.W; j += NT) out[k + j] = pb.P + j;
     for (int j = bg + tid; j < pb.B; j += NT) out[j] = -1;
   }
@@ -325,9 +327,9 @@ int launch_select(const Prob& pb, const float* fin, int32_t* idx, char* ws, hipS
   }
   const int nch = (pb.P + SCH - 1) / SCH;
   const SelPtrs w = sel_ptrs(pb, ws, nullptr);
-  RK_LAUNCH(ST_SELECT, st, k_sel_scan, dim3(nch, pb.Hkv), dim3(256), 0, st, pb, fin, w, nch, vec ? 1 : 0);
+  RK_LAUNCH(ST_SELECT, st, k_sel_scan, head_grid(pb, nch), dim3(256), 0, st, pb, fin, w, nch, vec ? 1 : 0);
   const int cpw = (nch + EMIT_WGS - 1) / EMIT_WGS;
-  RK_LAUNCH(ST_SELECT, st, k_sel_emit, dim3((nch + cpw - 1) / cpw, pb.Hkv), dim3(512), 0, st, pb, fin, w, nch, cpw, vec ? 1 : 0, idx);
+  RK_LAUNCH(ST_SELECT, st, k_sel_emit, head_grid(pb, (nch + cpw - 1) / cpw), dim3(512), 0, st, pb, fin, w, nch, cpw, vec ? 1 : 0, idx);
   return hip_status();
 }
 

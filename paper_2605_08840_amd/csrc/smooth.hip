@@ -20,13 +20,14 @@ constexpr int ROW_NS = 4096;        // samples per row that the bracket kernel f
 // Bracket of the top-min(B,P) threshold of one (head, query) row from a sample of the row.
 // thr[row] = {lo, hi}: the threshold lies in (lo, hi] unless the sample misled us (then the
 // finishing kernel falls back to the exact radix search).  Also clears the row's counters.
-// grid (W, Hkv), 512 threads, ROW_NS / 512 samples per thread in registers.
+// head_grid: parts = W, 512 threads, ROW_NS / 512 samples per thread in registers.
 __global__ __launch_bounds__(512) void k_sample_bracket(Prob pb, const float* __restrict__ score,
                                                         float2* __restrict__ thr,
                                                         uint32_t* __restrict__ cnt_hi,
                                                         unsigned long long* __restrict__ sum_hi) {
   __shared__ CutSmem cs;
-  const int i = blockIdx.x, g = blockIdx.y, r = g * pb.W + i;
+  const HeadPart hp = head_part(pb);
+  const int i = hp.x, g = hp.g, r = g * pb.W + i;
   const float* row = score + (int64_t)r * pb.ld;
   const int k = min(head_budget(pb, g), pb.P);
   if (threadIdx.x == 0) { cnt_hi[r] = 0; sum_hi[r] = 0ull; }
@@ -59,7 +60,7 @@ __global__ __launch_bounds__(512) void k_sample_bracket(Prob pb, const float* __
 //     row into cmask [row][wavefront][lane].  The finishing kernel expands a row's masks into
 //     positions and fetches those few values itself.
 // EPF rows are in flight per lane, so 16 KiB per wavefront are on their way while a row is
-// processed.  grid (ceil(P / (4 EW_POS)), Hkv), 256 threads.
+// processed.  head_grid: parts = ceil(P / (4 EW_POS)), 256 threads.
 constexpr int EW_POS = 1024;        // prefix positions per wavefront
 constexpr int EW_NE = EW_POS / 64;  // elements per lane and row (16 = four quads)
 constexpr int EPF = 4;              // rows in flight
@@ -91,10 +92,11 @@ __global__ __launch_bounds__(256) void k_ema_scan(Prob pb, const float* __restri
   // among them (short prefixes: more wavefronts, more bytes in flight); their partial weighted
   // sums meet in LDS at the end.  rs = 1: a wavefront works alone, no barrier anywhere.
   __shared__ float esum[4][EW_NE][64];
-  const int g = blockIdx.y, l = threadIdx.x & 63;
+  const HeadPart hp = head_part(pb);
+  const int g = hp.g, l = threadIdx.x & 63;
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);     // (a scalar for the compiler)
   const int part = wv % rs, rpp = 64 / rs;       // this wavefront's share of a block of 64 rows
-  const int wg = blockIdx.x * (4 / rs) + wv / rs;   // run of positions along the prefix
+  const int wg = hp.x * (4 / rs) + wv / rs;   // run of positions along the prefix
   const int wbase = wg * EW_POS;
   const bool active = wbase < pb.P;
   if (rs == 1 && !active) return;
@@ -235,7 +237,7 @@ __device__ inline unsigned long long row_exact_sum(const float* __restrict__ row
 // their values fetched from the raw score.  The threshold is found among them exactly (block_cut;
 // equal values in position order).  A row whose bracket missed, or that has more than
 // CAND_CAP candidates, is searched exactly (radix select over the whole row) on the spot.
-// grid (W, Hkv), 512 threads.
+// head_grid: parts = W, 512 threads.
 __global__ __launch_bounds__(512) void k_row_finish(Prob pb, const float* __restrict__ score,
                                                     const uint32_t* __restrict__ cnt_hi,
                                                     const unsigned long long* __restrict__ sum_hi,
@@ -248,7 +250,8 @@ __global__ __launch_bounds__(512) void k_row_finish(Prob pb, const float* __rest
   __shared__ uint32_t wsum[SEL_NW];
   __shared__ int cpos[CAND_CAP];                 // positions of the row's candidates
   __shared__ SelectSmem sm;                      // (exact search only)
-  const int i = blockIdx.x, g = blockIdx.y, r = g * pb.W + i;
+  const HeadPart hp = head_part(pb);
+  const int i = hp.x, g = hp.g, r = g * pb.W + i;
   const int k = min(head_budget(pb, g), pb.P);
   if (k >= pb.P) {
     if (threadIdx.x == 0) rowsum[r] = (unsigned long long)pb.P * (unsigned long long)(pb.P - 1) / 2ull;
@@ -330,20 +333,21 @@ __global__ __launch_bounds__(512) void k_row_finish(Prob pb, const float* __rest
   }
 }
 
-// Both statistics of a prefix of at most ROW_REG_MAX positions in ONE launch: workgroups x < nrow
+// Both statistics of a prefix of at most ROW_REG_MAX positions in ONE launch: parts below nrow
 // take a (head, query) row each, the whole of it in registers, and find its top-min(B,P) exactly;
 // the others take NT positions each and add up the weighted window queries.  Three launches (sample
 // bracket, scan, finish) are latency at these sizes: 33.5 us at 8k tokens, 8 KV heads, window 32,
-// against 8.1 here; 27.4 against 4.5 us at 1k tokens, 2 heads.  grid (nrow + ceil(P / NT), Hkv).
+// against 8.1 here; 27.4 against 4.5 us at 1k tokens, 2 heads.  head_grid: parts = nrow + ceil(P / NT).
 template <int NT, int NPT, bool VEC>
 __global__ __launch_bounds__(NT, NT == 1024 && NPT == 16 ? 8 : 4) void k_short_rows(Prob pb, const float* __restrict__ score,
                                                                       float* __restrict__ ema,
                                                                       unsigned long long* __restrict__ rowsum, int nrow) {
   __shared__ CutSmem cs;
   __shared__ unsigned long long isum[NT / 64];
-  const int g = blockIdx.y;
-  if ((int)blockIdx.x < nrow) {
-    const int r = g * pb.W + blockIdx.x;
+  const HeadPart hp = head_part(pb);
+  const int g = hp.g;
+  if (hp.x < nrow) {
+    const int r = g * pb.W + hp.x;
     const int k = min(head_budget(pb, g), pb.P);
     if (k >= pb.P) {                               // every prefix position is taken
       if (threadIdx.x == 0) rowsum[r] = (unsigned long long)pb.P * (unsigned long long)(pb.P - 1) / 2ull;
@@ -373,7 +377,7 @@ __global__ __launch_bounds__(NT, NT == 1024 && NPT == 16 ? 8 : 4) void k_short_r
   }
   // temporal smoothing: a thread adds up one position's window queries, oldest first
   float* wts = (float*)cs.hist;
-  const int n = ((int)blockIdx.x - nrow) * NT + threadIdx.x;
+  const int n = (hp.x - nrow) * NT + threadIdx.x;
   const float* s = score + (int64_t)g * pb.W * pb.ld + min(n, pb.P - 1);
   float e = 0.f;
   for (int b0 = 0; b0 < pb.W; b0 += CUT_BINS) {
@@ -419,7 +423,7 @@ __device__ inline void aws_window(const Prob& pb, unsigned long long sf, unsigne
 }
 
 // final[g,n] = (1/W_s) sum_{j=gamma-half}^{gamma+half} ema[g,n+j], zero outside [0,P).
-// grid (ceil(P / (256 BOX_PT)), Hkv), 256 threads; a thread owns BOX_PT positions 256 apart (the
+// head_grid: parts = ceil(P / (256 BOX_PT)), 256 threads; a thread owns BOX_PT positions 256 apart (the
 // loads of a window offset are independent and coalesced); every workgroup derives the head's
 // window from the index sums itself.
 constexpr int BOX_PT = 4;
@@ -427,7 +431,8 @@ __global__ __launch_bounds__(256) void k_box(Prob pb, const float* __restrict__ 
                                              const unsigned long long* __restrict__ rowsum,
                                              float* __restrict__ fin, int32_t* __restrict__ aws_info,
                                              double* __restrict__ aws_d) {
-  const int g = blockIdx.y;
+  const HeadPart hp = head_part(pb);
+  const int g = hp.g;
   __shared__ int sh_ws, sh_gamma;
   __shared__ unsigned long long sh_sum[2][4];
   __shared__ float tile[2 * 256 * BOX_PT];           // span + reach of the window (when it fits)
@@ -450,14 +455,14 @@ __global__ __launch_bounds__(256) void k_box(Prob pb, const float* __restrict__ 
     aws_window(pb, sh_sum[0][0] + sh_sum[0][1] + sh_sum[0][2] + sh_sum[0][3],
                sh_sum[1][0] + sh_sum[1][1] + sh_sum[1][2] + sh_sum[1][3], g, w_s0, gamma0, df, dr);
     sh_ws = w_s0; sh_gamma = gamma0;
-    if (blockIdx.x == 0) {
+    if (hp.x == 0) {
       if (aws_info) { aws_info[2 * g] = w_s0; aws_info[2 * g + 1] = gamma0; }
       if (aws_d) { aws_d[2 * g] = df; aws_d[2 * g + 1] = dr; }
     }
   }
   __syncthreads();
   const int w_s = sh_ws, gamma = sh_gamma;
-  const int n0 = blockIdx.x * (256 * BOX_PT) + threadIdx.x;
+  const int n0 = hp.x * (256 * BOX_PT) + threadIdx.x;
   const float* e = ema + (int64_t)g * pb.ld;
   const int half = w_s / 2;
   float s[BOX_PT];
@@ -471,7 +476,7 @@ __global__ __launch_bounds__(256) void k_box(Prob pb, const float* __restrict__ 
   if (w_s - 1 <= SPAN) {
     // the workgroup's span plus the window's reach goes through LDS: one coalesced read of the
     // smoothed scores instead of W_s reads per position
-    const int t0 = blockIdx.x * SPAN + gamma - half;          // position of tile[0]
+    const int t0 = hp.x * SPAN + gamma - half;          // position of tile[0]
     const int tn = SPAN + 2 * half;
     const float pad = pb.pmax ? -INFINITY : 0.f;
     for (int x = threadIdx.x; x < tn; x += 256) {
@@ -549,29 +554,29 @@ int launch_smooth(const Prob& pb, const float* score, float* ema, float* fin, in
     const int nrow = pb.adaptive ? pb.W : 0;
     with_row_block(pb.P, [&](auto nt, auto npt) {
       constexpr int NT = decltype(nt)::value, NPT = decltype(npt)::value;
-      const dim3 gr(nrow + (pb.P + NT - 1) / NT, pb.Hkv);
+      const dim3 gr = head_grid(pb, nrow + (pb.P + NT - 1) / NT);
       if (vec) RK_LAUNCH(ST_EMA, st, (k_short_rows<NT, NPT, true>), gr, dim3(NT), 0, st, pb, score, e, rowsum, nrow);
       else RK_LAUNCH(ST_EMA, st, (k_short_rows<NT, NPT, false>), gr, dim3(NT), 0, st, pb, score, e, rowsum, nrow);
     });
   } else {
     if (pb.adaptive)
-      RK_LAUNCH(ST_ROWTOPK, st, k_sample_bracket, dim3(pb.W, pb.Hkv), dim3(512), 0, st, pb, score, thr,
+      RK_LAUNCH(ST_ROWTOPK, st, k_sample_bracket, head_grid(pb, pb.W), dim3(512), 0, st, pb, score, thr,
                 cnt_hi, sum_hi);
     // short prefixes: 2 or 4 wavefronts per run of positions, until about a thousand wavefronts stream
     const int64_t runs = (int64_t)scan_waves(pb.P) * pb.Hkv;
     const int rs = runs >= 1024 ? 1 : (runs >= 512 ? 2 : 4);
     const int ppw = 4 / rs;
-    const dim3 ge((scan_waves(pb.P) + ppw - 1) / ppw, pb.Hkv);
+    const dim3 ge = head_grid(pb, (scan_waves(pb.P) + ppw - 1) / ppw);
     if (vec)
       RK_LAUNCH(ST_EMA, st, k_ema_scan<true>, ge, dim3(256), 0, st, pb, score, e, thr, cnt_hi, sum_hi, cmask, rs);
     else
       RK_LAUNCH(ST_EMA, st, k_ema_scan<false>, ge, dim3(256), 0, st, pb, score, e, thr, cnt_hi, sum_hi, cmask, rs);
     if (pb.adaptive) {
-      RK_LAUNCH(ST_ROWTOPK, st, k_row_finish, dim3(pb.W, pb.Hkv), dim3(512), 0, st, pb, score, cnt_hi, sum_hi,
+      RK_LAUNCH(ST_ROWTOPK, st, k_row_finish, head_grid(pb, pb.W), dim3(512), 0, st, pb, score, cnt_hi, sum_hi,
                 cmask, thr, rowsum);
     }
   }
-  RK_LAUNCH(ST_BOX, st, k_box, dim3((pb.P + 256 * BOX_PT - 1) / (256 * BOX_PT), pb.Hkv), dim3(256), 0, st, pb, e, rowsum, fin,
+  RK_LAUNCH(ST_BOX, st, k_box, head_grid(pb, (pb.P + 256 * BOX_PT - 1) / (256 * BOX_PT)), dim3(256), 0, st, pb, e, rowsum, fin,
             aws_info, aws_d);
   return hip_status();
 }
