@@ -1211,14 +1211,15 @@ void launch_score_pipe(const Prob& pb, const uint16_t* q, const uint16_t* k, con
 // sums for the merge, and a unit bound by vector instructions next to one bound by the matrix cores runs at a higher
 // clock.  Model: a workgroup of the attention pass takes A0 + a t us for t tiles, one of the value-Gram pass V0 + v t, one
 // after the other V1 more and 6 % more per tile; clustered logits take up to SLOW a.  Taken is the split count with the
-// smallest sum of plain and clustered time (SPLIT us for each split) that loses in neither.  32/8 heads, window 64,
+// smallest sum of plain and clustered time (SPLIT us for each split) that wins for plain ones and loses at most LOSS by
+// the model, which is nothing by measurement, for clustered ones.  32/8 heads, window 64,
 // score + smoothing, one after the other / side by side: 4k 67.5 / 58.7 us, 16k 120.4 / 108, 32k 188.7 / 178.8
-// (clustered 208.9 / 207.1), 64k 325.6 / 315.9 (362.9 / 357.0), 128k 599.9 / 594.3 (660.7 / 649.9); 16/4 heads, 40k,
-// 123.0 / 114.7; 64/8, 6k, 93.9 / 83.9.  Only where the workgroups have equal work: a last row block or head group that
+// (clustered 208.9 / 207.1), 64k 325.6 / 315.9 (362.9 / 357.0), 128k 599.9 / 587.0 (660.7 / 657.9); 16/4 heads, 40k,
+// 123.0 / 114.7; 64/8, 6k, 93.9 / 83.9, 128k 1004 / 995, 64k clustered 580 / 577.  Only where the workgroups have equal work: a last row block or head group that
 // is mostly empty ends early and leaves its unit idle (28/4 heads, 30k, window 33, clustered 155 against 161).  Heads of
 // 64 fill half a unit, so there the two passes share units anyway (28/4 heads, 50k, clustered 174 against 192).
 inline int share_the_chip(const Prob& pb, int nt, int nwr, int S1, const VvArgs& va, int ny, int* chunks) {
-  constexpr float A0 = 10.f, V0 = 6.f, V1 = 4.f, A = 1.5f, V = 1.2f, SEQ = 1.06f, SLOW = 1.5f, SPLIT = 1.3f;
+  constexpr float A0 = 10.f, V0 = 6.f, V1 = 4.f, A = 1.5f, V = 1.2f, SEQ = 1.06f, SLOW = 1.5f, LOSS = 1.08f, SPLIT = 1.3f;
   if ((ny > 1 && (nwr - 1) % 8 < 4) || (va.ny > 1 && (pb.G - 1) % 4 < 2)) return 0;
   const int ntv = (pb.P + TN - 1) / TN;
   auto tiles = [](int n, int parts) { return (float)((n + parts - 1) / parts); };
@@ -1230,7 +1231,7 @@ inline int share_the_chip(const Prob& pb, int nt, int nwr, int S1, const VvArgs&
     const int c = min(ntv, (n_cu() - S * ny * pb.Hkv) / (va.ny * pb.Hkv));     // chunks for the value-Gram pass
     if (c < 1) break;
     const float tv = V0 + V * tiles(ntv, c), t1 = max(A0 + A * tiles(nt, S), tv), t2 = max(A0 + SLOW * A * tiles(nt, S), tv);
-    if (t1 >= seq1 || t2 > seq2 || t1 + t2 + SPLIT * S >= best) continue;
+    if (t1 >= seq1 || t2 > LOSS * seq2 || t1 + t2 + SPLIT * S >= best) continue;
     best = t1 + t2 + SPLIT * S;
     bs = S;
     *chunks = c;
