@@ -115,20 +115,10 @@ inline __host__ __device__ int row_items(int W) { return (W + 31) / 32; }
 //   A*/(1 - A*) ||(z - v*) W_O||.  Either way the difference is taken before its norm: the expanded
 //   distance of the score pass cancels where v* lies near z.
 
-// Statistics of a caller's own attention kernel as ONE split of the attention pass: the log-sum-exp
-// of a row (natural log) is both the reference and the "largest logit", the sum of weights is 1, no
-// key is kept out; the caller's attention output [Hq*W, d] then serves as part_z unchanged.
-// grid (ceil(rows/256)), 256 threads.  (A template only so that the header can hold it.)
-template <int UNUSED>
-__global__ __launch_bounds__(256) void k_stats_fill(int rows, const float* __restrict__ lse,
-                                                    float* __restrict__ part_m, float* __restrict__ part_mx,
-                                                    int* __restrict__ part_n, float* __restrict__ part_ref,
-                                                    float* __restrict__ part_l) {
-  const int r = blockIdx.x * 256 + threadIdx.x;
-  if (r >= rows) return;
-  const float m2 = lse[r] * 1.4426950408889634f;
-  part_m[r] = m2; part_ref[r] = m2; part_mx[r] = 0.f; part_n[r] = -1; part_l[r] = 1.f;
-}
+// Statistics of a caller's own attention kernel come in as ONE split: the log-sum-exp of a row (pb.ext_lse, natural log) is
+// both the reference and the "largest logit", the sum of weights is 1, no key is kept out, and the caller's attention
+// output [Hq*W, d] is part_z (EXT; a launch that wrote them out took 2.3 us, and a test at run time costs every other
+// merge 0.7 us).
 
 // Merge of the key splits and the per-row quantities of the score pass, RQ query rows of one head
 // per workgroup of 4 D threads.
@@ -182,7 +172,7 @@ __device__ __forceinline__ f32x4_t quad_of(const bf16_t* p) {
 // splits that the LDS lists of a workgroup hold (many rows come with few splits)
 constexpr int combine_max_splits(int rq) { return rq >= 64 ? 8 : (rq >= 32 ? 16 : 64); }
 
-template <typename T, int D, int RQ, int USE_OP>
+template <typename T, int D, int RQ, int USE_OP, bool EXT>
 __global__ __launch_bounds__(4 * D, 4) void k_attn_combine(Prob pb, const T* __restrict__ v, int S,
                                                            const float* __restrict__ gram, ScorePtrs o,
                                                            const float* __restrict__ part_z, const T* __restrict__ q,
@@ -219,7 +209,11 @@ __global__ __launch_bounds__(4 * D, 4) void k_attn_combine(Prob pb, const T* __r
   int pn;
   auto fetch_scalars = [&](int r) {
     const int64_t po = (int64_t)(h * pb.W + min(i0 + r, pb.W - 1)) * S + min(sub, S - 1);
-    pm = o.part_m[po]; pmx = o.part_mx[po]; pn = o.part_n[po]; pref = o.part_ref[po]; pl = o.part_l[po];
+    if constexpr (EXT) {
+      pm = pref = pb.ext_lse[po] * 1.4426950408889634f; pmx = 0.f; pn = -1; pl = 1.f;
+    } else {
+      pm = o.part_m[po]; pmx = o.part_mx[po]; pn = o.part_n[po]; pref = o.part_ref[po]; pl = o.part_l[po];
+    }
   };
   fetch_scalars(min(tid / SW, RQ - 1));
   const int c4 = 4 * (tid % CQ), rz = (tid / CQ) % (RQ / MB), part = tid / (CQ * (RQ / MB));
@@ -503,8 +497,14 @@ __global__ __launch_bounds__(4 * D, 4) void k_attn_combine(Prob pb, const T* __r
 template <typename T, int D, int RQ, int USE_OP>
 inline void launch_combine_rows(const Prob& pb, const T* v, int S, const float* gram, const ScorePtrs& w, const float* part_z,
                                 const T* q, int log2gp, int nwb, hipStream_t st) {
-  RK_LAUNCH(ST_COMBINE, st, (k_attn_combine<T, D, RQ, USE_OP>), dim3(pb.Hq * ((pb.W + RQ - 1) / RQ)), dim3(4 * D), 0, st, pb, v, S, gram,
-            w, part_z, q, log2gp, nwb);
+  const dim3 gr(pb.Hq * ((pb.W + RQ - 1) / RQ));
+  if constexpr (RQ > 4) {                          // (four rows only with several splits)
+    if (pb.ext_lse) {
+      RK_LAUNCH(ST_COMBINE, st, (k_attn_combine<T, D, RQ, USE_OP, true>), gr, dim3(4 * D), 0, st, pb, v, S, gram, w, part_z, q, log2gp, nwb);
+      return;
+    }
+  }
+  RK_LAUNCH(ST_COMBINE, st, (k_attn_combine<T, D, RQ, USE_OP, false>), gr, dim3(4 * D), 0, st, pb, v, S, gram, w, part_z, q, log2gp, nwb);
 }
 template <typename T, int D, int USE_OP>
 inline void launch_combine(const Prob& pb, const T* v, int S, const float* gram, const ScorePtrs& w, const float* part_z,

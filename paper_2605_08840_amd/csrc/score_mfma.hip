@@ -1304,9 +1304,6 @@ int run_mfma(const Prob& pb, const void* q, const void* k, const void* v, const 
   };
   if (pb.ext_lse) {
     // the caller's attention output and log-sum-exp stand in for the attention pass: one "split"
-    const int rows = pb.Hq * pb.W;
-    RK_LAUNCH(ST_ATTN, st, (k_stats_fill<0>), dim3((rows + 255) / 256), dim3(256), 0, st, rows, pb.ext_lse,
-              w.part_m, w.part_mx, w.part_n, w.part_ref, w.part_l);
     part_z = pb.ext_out;
     combine(1);
     with_vv(no);

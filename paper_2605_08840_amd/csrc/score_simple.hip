@@ -535,6 +535,7 @@ __global__ __launch_bounds__(NW * 64, NW == 1 ? 1 : 2) void k_score_f32(Prob pb,
   float out[16];
 #pragma unroll
   for (int j = 0; j < 16; ++j) out[j] = 0.f;
+  // (a lane's rows come in before the turns: their round trip runs beside the copies')
   copy_item(0, 0, 0);
   turn();
   int bf = 0;                     // buffer of the current rows; the other one was last read before the last barrier
@@ -649,11 +650,7 @@ int run(const Prob& pb, const void* q, const void* k, const void* v, const float
   if (pb.ind != 0) gram = nullptr;                 // no projection: vv becomes the squared norm of the value row
   const float* part_z = w.part_z;
   if (pb.ext_lse) {
-    // the caller's attention output and log-sum-exp stand in for the attention pass: one "split"
-    S = 1;
-    const int rows = pb.Hq * pb.W;
-    RK_LAUNCH(ST_ATTN, st, (k_stats_fill<0>), dim3((rows + 255) / 256), dim3(256), 0, st, rows, pb.ext_lse,
-              w.part_m, w.part_mx, w.part_n, w.part_ref, w.part_l);
+    S = 1;                                         // the caller's attention output and log-sum-exp stand in for the pass: one "split"
     part_z = pb.ext_out;
   } else {
     if (nw == 4)
