@@ -510,13 +510,14 @@ template <typename T, int D, int USE_OP>
 inline void launch_combine(const Prob& pb, const T* v, int S, const float* gram, const ScorePtrs& w, const float* part_z,
                            const T* q, int log2gp, int nwb, hipStream_t st) {
   // As many rows per workgroup (one chain of round trips, one read of the Gram matrix) as still leave
-  // a workgroup for every compute unit; where eight rows do not leave two, four rows whose splits are
-  // shared by four threads (1024 rows: 10.8 us against 14.1 with eight; one split has nothing to share).
+  // a workgroup for every compute unit; where eight rows do not, four rows whose splits are shared by
+  // four threads (1024 rows: 10.8 us against 14.1 with eight; 2048 rows, score + smoothing, eight against four: 2112
+  // tokens 56.2 / 59.8 us, 24k 142.0 / 144.6, 32k 176.0 / 178.7; one split has nothing to share).
   auto fills = [&](int rq) { return S <= combine_max_splits(rq) && pb.W > rq / 2 && (int64_t)pb.Hq * ((pb.W + rq - 1) / rq) >= n_cu(); };
   if (fills(64)) launch_combine_rows<T, D, 64, USE_OP>(pb, v, S, gram, w, part_z, q, log2gp, nwb, st);
   else if (fills(32)) launch_combine_rows<T, D, 32, USE_OP>(pb, v, S, gram, w, part_z, q, log2gp, nwb, st);
   else if (fills(16)) launch_combine_rows<T, D, 16, USE_OP>(pb, v, S, gram, w, part_z, q, log2gp, nwb, st);
-  else if (S > 1 && (int64_t)pb.Hq * ((pb.W + 7) / 8) < 2 * n_cu()) launch_combine_rows<T, D, 4, USE_OP>(pb, v, S, gram, w, part_z, q, log2gp, nwb, st);
+  else if (S > 1 && (int64_t)pb.Hq * ((pb.W + 7) / 8) < n_cu()) launch_combine_rows<T, D, 4, USE_OP>(pb, v, S, gram, w, part_z, q, log2gp, nwb, st);
   else launch_combine_rows<T, D, 8, USE_OP>(pb, v, S, gram, w, part_z, q, log2gp, nwb, st);
 }
 
