@@ -31,10 +31,13 @@ def stage_work(w, stage: str):
     Hq, Hkv, d, L, W, P, B = w.n_q_heads, w.n_kv_heads, w.head_dim, w.seq_len, w.window, w.prefix, w.budget
     esz = 4 if w.dtype == "f32" else 2
     if stage == "attn_partial":      # q K^T and A V over all L keys; K and V read once
-        return 2 * (2.0 * Hq * W * L * d), 2.0 * Hkv * L * d * esz + Hq * W * d * (esz + 4.0)
+        flops, nbytes = 2 * (2.0 * Hq * W * L * d), 2.0 * Hkv * L * d * esz + Hq * W * d * (esz + 4.0)
+        if w.dtype != "f32":         # bf16: V M_h for every query head in the same launch, vv written
+            flops, nbytes = flops + 2.0 * Hq * P * d * d, nbytes + 4.0 * Hq * P
+        return flops, nbytes
     if stage == "score":             # cross term u V^T; K, V prefix and vv read, raw score written
         return 2.0 * Hq * W * P * d, 2.0 * Hkv * P * d * esz + 4.0 * Hq * P + 4.0 * Hkv * W * P
-    if stage == "vv":                # V M_h for every query head
+    if stage == "vv":                # V M_h for every query head (float32 layers: a launch of its own)
         return 2.0 * Hq * P * d * d, 1.0 * Hkv * P * d * esz + 4.0 * Hq * P
     if stage == "ema":               # one read of the raw score, EMA written
         return 0.0, 4.0 * Hkv * W * P + 4.0 * Hkv * P
@@ -55,7 +58,7 @@ def stage_read_write(w, stage: str):
     Hq, Hkv, d, L, W, P, B = w.n_q_heads, w.n_kv_heads, w.head_dim, w.seq_len, w.window, w.prefix, w.budget
     esz = 4 if w.dtype == "f32" else 2
     if stage == "attn_partial":
-        return 2.0 * Hkv * L * d * esz + Hq * W * d * esz, 4.0 * Hq * W * d
+        return 2.0 * Hkv * L * d * esz + Hq * W * d * esz, 4.0 * Hq * W * d + (0.0 if w.dtype == "f32" else 4.0 * Hq * P)
     if stage == "score":
         return 2.0 * Hkv * P * d * esz + 4.0 * Hq * P, 4.0 * Hkv * W * P
     if stage == "vv":
@@ -89,7 +92,7 @@ def stream_reference(rk, read_bytes, write_bytes, reps=10):
 
 
 # kernel behind each timed stage whose HBM traffic was measured with rocprofv3 --pmc
-STAGE_KERNEL = {"attn_partial": "k_attn_pipe", "vv": "k_vv_pipe", "score": "k_score_pipe", "ema": "k_ema_scan",
+STAGE_KERNEL = {"attn_partial": "k_attn_vv", "score": "k_score_pipe", "ema": "k_ema_scan",
                 "compact": "k_compact", "box": "k_box"}
 
 
@@ -400,7 +403,7 @@ def main():
     # contractions and V M_h), beside what the kernels execute (logit recompute, two-term u and
     # Gram operands) and the HBM bytes the counters saw against K + V once + the raw score once.
     score_call = None
-    call_stages = ["attn_partial", "attn_combine", "vv", "score"]
+    call_stages = ["attn_partial", "attn_combine", "score"] + (["vv"] if w.dtype == "f32" else [])
     if all(n in per for n in call_stages):
         Wn, Ln, Pn = w.window, w.seq_len, w.prefix
         unit = 2.0 * Hq * Wn * Ln * d
@@ -409,7 +412,7 @@ def main():
         f_exec = 2.0 * unit + 3.0 * 2.0 * Hq * Wn * Pn * d + 2.0 * tri * 2.0 * Hq * Pn * d * d
         ms_call = sum(per[n]["ms"] for n in call_stages)
         b_alg = 2.0 * Hkv * Ln * d * (4 if w.dtype == "f32" else 2) + 4.0 * Hkv * Wn * Pn
-        tr = [measured_traffic(w.name, n) for n in ("k_attn_pipe", "k_attn_combine", "k_vv_pipe", "k_score_pipe")]
+        tr = [measured_traffic(w.name, n) for n in ("k_attn_vv", "k_attn_combine", "k_score_pipe")]
         traffic = sum(tr) if all(x is not None for x in tr) else None
         score_call = {"ms_per_layer": ms_call, "f_alg": f_alg, "frac_mfma_alg": f_alg / (ms_call * 1e-3) / peak_mfma,
                       "executed_over_alg": f_exec / f_alg, "algorithmic_bytes": b_alg,
