@@ -36,10 +36,12 @@ typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 
 constexpr int TN = 64;                 // keys per LDS tile
 constexpr float LOG2E = 1.4426950408889634f;
-// A joining key that holds more than 1/33 of the others' sum on arrival becomes the reference of its row, so that its
-// weight is exact.  (1/9 takes the same time to within 0.5 % at 2k to 128k tokens and is further from 64 bits: 32/8 heads,
-// clustered logits, 2112 tokens 7.7e-6 against 6.0e-6, 32k 2.3e-6 against 1.6e-6.)
-constexpr float HEAVY = 32.0f;
+// A joining key that holds more than 1/9 of the others' sum on arrival becomes the reference of its row, so that its
+// weight is exact.  Side by side with the value-Gram pass (share_the_chip) there are fewer splits, hence fewer keys that
+// are a split's first and exact, and the limit is 1/33: with 1/9 those scores were up to 30 % further from 64 bits (32/8
+// heads, clustered logits, 2112 tokens 7.7e-6 against 6.0e-6, 32k 2.3e-6 against 1.6e-6).  1/33 everywhere costs the other
+// shapes up to 1.4 % (64/8 heads of 64, 40k 262.6 / 266.3 us, 28/4, 20k 81.7 / 82.7, 8/8 of 128, 71k 224.9 / 226.6).
+constexpr float HEAVY_SPLITS = 8.0f, HEAVY_SIDE = 32.0f;
 constexpr float RESCALE_TH = 8.0f;  // log2 units a row maximum may run ahead of its reference
 
 #define MFMA(a, b, c) __builtin_amdgcn_mfma_f32_32x32x16_bf16((a), (b), (c), 0, 0, 0)
@@ -455,7 +457,7 @@ template <int D, bool KS2>
 __device__ __forceinline__ void attn_pass(const Prob& pb, WgAt at, AttnSmem<D>& sm, const uint16_t* __restrict__ q,
                                           const uint16_t* __restrict__ k,
                                           const uint16_t* __restrict__ v, int S, int kps,
-                                          int log2iw, const ScorePtrs& o) {
+                                          int log2iw, float heavy, const ScorePtrs& o) {
   constexpr int NW = 8, KS = D / 16, CB = D / 32, RB = KS2 ? 4 : 8, NMB = KS2 ? 1 : 2;
   using RingK = TileRing<D, 0>;
   using RingV = TileRing<D, 1>;
@@ -636,7 +638,7 @@ __device__ __forceinline__ void attn_pass(const Prob& pb, WgAt at, AttnSmem<D>& 
       // Nothing to do unless the reference has to move or the tile maximum may be heavy: lsum is
       // this lane's share of the row's sum, so the comparison is a necessary condition for both
       // "kept out" and "heavy", which are settled below.
-      if (__ballot((tm - mref) * c2 > RESCALE_TH || pl * HEAVY > lsum) != 0ull) {
+      if (__ballot((tm - mref) * c2 > RESCALE_TH || pl * heavy > lsum) != 0ull) {
         const float oth = xhalf_sum(lsum);
         bool dominant = false;
         if (newmax) {
@@ -673,7 +675,7 @@ __device__ __forceinline__ void attn_pass(const Prob& pb, WgAt at, AttnSmem<D>& 
           if (mref == -INFINITY) tref = tm;
         } else {
           const float pinc = tinc == tm ? pl : __builtin_amdgcn_exp2f((tinc - mref) * c2);   // inf without a reference
-          if (pinc * HEAVY > oth || (tinc - mref) * c2 > RESCALE_TH) tref = tinc;
+          if (pinc * heavy > oth || (tinc - mref) * c2 > RESCALE_TH) tref = tinc;
         }
         // The key kept out so far joins the sums too (in FP32, below): the reference may not
         // stay far under it, however far it lies above the rest.
@@ -820,21 +822,24 @@ __device__ __forceinline__ void attn_pass(const Prob& pb, WgAt at, AttnSmem<D>& 
   }
 }
 
-// The two passes that need nothing of each other, one launch: workgroups [0, n_attn) are the attention pass's, the
-// others the value-Gram pass's, which start as the first ones end (a workgroup fills a compute unit either way).
+// The two passes that need nothing of each other, one launch: workgroups [va.at, va.at + va.n) are the value-Gram pass's,
+// the others the attention pass's; the second pass's start as the first one's end (a workgroup fills a compute unit either way).
 // ATTN, VV: 0 that pass is not there, 1 it is, 2 with KS2.  512 threads.
-struct AttnArgs { int n, S, ny, kps, log2iw; };
-struct VvArgs { int chunks, ny, ldv, tiles_per_wg; };
+struct AttnArgs { int S, ny, kps, log2iw; float heavy; };
+struct VvArgs { int at, n, chunks, ny, ldv, tiles_per_wg; };
 template <int D, int ATTN, int VV>
 __global__ __launch_bounds__(512) void k_attn_vv(Prob pb, const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
                                                  const uint16_t* __restrict__ v, const float* __restrict__ gram,
                                                  ScorePtrs o, AttnArgs aa, VvArgs va) {
   __shared__ union { AttnSmem<ATTN ? D : 64> a; VvSmem<D, VV == 2> v; } sm;
-  if (ATTN && (!VV || (int)blockIdx.x < aa.n)) {
-    if constexpr (ATTN != 0) attn_pass<D, ATTN == 2>(pb, wg_at<D>(pb, blockIdx.x, aa.S, aa.ny), sm.a, q, k, v, aa.S, aa.kps, aa.log2iw, o);
-  } else {
+  const int id = blockIdx.x;
+  if (VV && (!ATTN || (unsigned)(id - va.at) < (unsigned)va.n)) {
     if constexpr (VV != 0)
-      vv_pass<D, VV == 2>(pb, wg_at<D>(pb, (int)blockIdx.x - aa.n, va.chunks, va.ny), sm.v, v, gram, o.vv, va.ldv, va.tiles_per_wg);
+      vv_pass<D, VV == 2>(pb, wg_at<D>(pb, id - va.at, va.chunks, va.ny), sm.v, v, gram, o.vv, va.ldv, va.tiles_per_wg);
+  } else {
+    if constexpr (ATTN != 0)
+      attn_pass<D, ATTN == 2>(pb, wg_at<D>(pb, id - (va.at ? 0 : va.n), aa.S, aa.ny), sm.a, q, k, v, aa.S, aa.kps, aa.log2iw,
+                              aa.heavy, o);
   }
 }
 
@@ -1248,7 +1253,7 @@ int run_mfma(const Prob& pb, const void* q, const void* k, const void* v, const 
   const ScorePtrs w = score_ptrs(ws, lay);
   const RowGeom rg = row_geom(pb, pb.L, ATTN_KS2_TILES, false);
   if (pb.ind != 0) gram = nullptr;                 // the attention-weight and value-norm indicators have no projection
-  VvArgs va = {0, 0, lay.ldv, 0};
+  VvArgs va = {0, 0, 0, 0, lay.ldv, 0};
   bool vks2 = false;
   if (gram) {
     constexpr int HPW = D == 128 ? 4 : 8;
@@ -1261,7 +1266,7 @@ int run_mfma(const Prob& pb, const void* q, const void* k, const void* v, const 
     va.tiles_per_wg = max(1, (int)(((int64_t)NTv * va.ny * pb.Hkv + n_cu() - 1) / n_cu()));
     va.chunks = (NTv + va.tiles_per_wg - 1) / va.tiles_per_wg;
   }
-  AttnArgs aa = {0, 0, rg.gy, 0, rg.log2iw};
+  AttnArgs aa = {0, rg.gy, 0, rg.log2iw, HEAVY_SPLITS};
   if (!pb.ext_lse) {
     // attention pass: about one workgroup per compute unit, whole tiles per split
     const int nt = (pb.L + TN - 1) / TN;
@@ -1269,13 +1274,13 @@ int run_mfma(const Prob& pb, const void* q, const void* k, const void* v, const 
       const int t = (nt + S - 1) / S;
       aa.kps = t * TN;
       aa.S = (nt + t - 1) / t;                     // (whole tiles: the last splits may have nothing left)
-      aa.n = aa.S * rg.gy * pb.Hkv;
     };
     const int S1 = max(1, min(min(n_cu() / (pb.Hkv * rg.gy), nt), lay.S_max));
     set_splits(S1);
     int chunks = 0;
     if (const int S2 = D == 128 && gram && !rg.ks2 && !vks2 ? share_the_chip(pb, nt, rg.nwr, S1, va, rg.gy, &chunks) : 0) {
       set_splits(S2);
+      aa.heavy = HEAVY_SIDE;
       const int ntv = (pb.P + TN - 1) / TN;
       va.tiles_per_wg = (ntv + chunks - 1) / chunks;
       va.chunks = (ntv + va.tiles_per_wg - 1) / va.tiles_per_wg;
@@ -1285,7 +1290,13 @@ int run_mfma(const Prob& pb, const void* q, const void* k, const void* v, const 
     RK_LAUNCH(ST_VV, st, (k_vnorm2<D>), dim3((pb.P + 255) / 256, pb.Hkv), dim3(256), 0, st, pb, vp,
               w.vv, lay.ldv);
   }
-  const dim3 gav(aa.n + va.chunks * va.ny * pb.Hkv);
+  // The attention pass first: the value-Gram pass leaves the values in cache for the score pass (8/8 heads of 128, 71k 220 us
+  // against 227, 82k 299 / 311; 32/8, window 32, 64k 259 / 263).  Heads of 64 and rows of one split (many heads, whose sums
+  // the merge then finds in cache) take it second (64/8 heads of 64, 40k 266 us against 271; 256 KV heads of 2112 tokens
+  // 372 / 376).
+  va.n = va.chunks * va.ny * pb.Hkv;
+  va.at = D == 64 || aa.S <= 1 ? 0 : aa.S * aa.ny * pb.Hkv;
+  const dim3 gav(va.n + aa.S * aa.ny * pb.Hkv);
   auto attn_vv = [&](auto a, auto b) {
     RK_LAUNCH(decltype(a)::value ? ST_ATTN : ST_VV, st, (k_attn_vv<D, decltype(a)::value, decltype(b)::value>), gav, dim3(512), 0, st,
               pb, qq, kk, vp, gram, w, aa, va);
