@@ -84,6 +84,8 @@ def lib() -> ctypes.CDLL:
         L.restkv_stage_name.argtypes = [ctypes.c_int]
         L.restkv_debug_force_fp32.argtypes = [ctypes.c_int]
         L.restkv_debug_force_fp32.restype = ctypes.c_int
+        L.restkv_debug_score_plan.argtypes = [P, vp]
+        L.restkv_debug_score_plan.restype = ctypes.c_int
         L.restkv_stream_reference.argtypes = [vp, sz, vp, sz, vp]
         L.restkv_stream_reference.restype = ctypes.c_int
         for f in ("restkv_timing_enable", "restkv_timing_read", "restkv_prepare_wo", "restkv_score", "restkv_smooth", "restkv_select",
@@ -228,6 +230,13 @@ def restkv_timing_read():
 
 def restkv_debug_force_fp32(on: bool):
     _chk(lib().restkv_debug_force_fp32(int(bool(on))), "restkv_debug_force_fp32")
+
+
+def restkv_debug_score_plan(p):
+    """(key splits, 64-key tiles of a split, side by side) of the attention pass on the bf16 matrix-core path."""
+    plan = (ctypes.c_int32 * 3)()
+    _chk(lib().restkv_debug_score_plan(ctypes.byref(p), plan), "restkv_debug_score_plan")
+    return tuple(plan)
 
 
 def restkv_stream_reference(src: Optional[torch.Tensor], read_bytes: int, dst: Optional[torch.Tensor],

@@ -280,4 +280,12 @@ int restkv_debug_force_fp32(int on) {
   return RESTKV_OK;
 }
 
+int restkv_debug_score_plan(const restkv_params* p, int32_t* plan) {
+  Prob pb;
+  int rc = resolve(p, &pb);
+  if (rc) return rc;
+  if (!plan) return RESTKV_EINVAL;
+  return score_plan(pb, plan);
+}
+
 }  // extern "C"

@@ -1215,16 +1215,20 @@ void launch_score_pipe(const Prob& pb, const uint16_t* q, const uint16_t* k, con
 // one after the other on all of them: fixed parts (launch, operands, first tile, sums) overlap, fewer splits are fewer
 // sums for the merge, and a unit bound by vector instructions next to one bound by the matrix cores runs at a higher
 // clock.  Model: a workgroup of the attention pass takes A0 + a t us for t tiles, one of the value-Gram pass V0 + v t, one
-// after the other V1 more and 6 % more per tile; clustered logits take up to SLOW a.  Taken is the split count with the
-// smallest sum of plain and clustered time (SPLIT us for each split) that wins for plain ones and loses at most LOSS by
-// the model, which is nothing by measurement, for clustered ones.  32/8 heads, window 64,
-// score + smoothing, one after the other / side by side: 4k 67.5 / 58.7 us, 16k 120.4 / 108, 32k 188.7 / 178.8
-// (clustered 208.9 / 207.1), 64k 325.6 / 315.9 (362.9 / 357.0), 128k 599.9 / 587.0 (660.7 / 657.9); 16/4 heads, 40k,
-// 123.0 / 114.7; 64/8, 6k, 93.9 / 83.9, 128k 1004 / 995, 64k clustered 580 / 577.  Only where the workgroups have equal work: a last row block or head group that
-// is mostly empty ends early and leaves its unit idle (28/4 heads, 30k, window 33, clustered 155 against 161).  Heads of
-// 64 fill half a unit, so there the two passes share units anyway (28/4 heads, 50k, clustered 174 against 192).
+// after the other V1 more and 6 % more per tile; clustered logits take up to SLOW a.  Where the workgroups of all
+// splits leave half of the units free (one or two KV heads, whose splits are as many as the merge takes), the splits stay as
+// many and the value-Gram pass has the other units.  Else taken is the split count with the smallest sum of plain and
+// clustered time (SPLIT us for each split) that wins for plain logits and loses at most LOSS by the model, which is nothing
+// by measurement, for clustered ones.  Score + smoothing, plain / clustered logits, against one
+// after the other in two launches: 32/8 heads, window 64, 4k 0.78 / 0.84, 8k 0.84 / 0.89, 32k 0.93 / 0.97, 64k 0.96 / 0.96;
+// window 4, 4k 0.88 / 0.88; 64/8, 4k 0.86 / 0.88; 8/8, 4k 0.86 / 0.90; 16/4, 4k 0.82 / 0.90, 8k 0.84 / 0.92, 32k 0.88 / 0.94;
+// 4/2, 4k 0.86 / 0.89, 8k 0.89 / 0.89, 16k 0.89 / 0.90; 4/1, 8k 0.86 / 0.87.  (With SPLIT 1.3 for any number of heads
+// 4/2, 8k 1.01 / 1.19, 4/1, 16k 0.98 / 1.10, 16/4, 8k, window 16 0.93 / 1.06; with 0.65 32/8, 4k, window 16 0.92 for 0.83.)
+// Only where the workgroups have equal work: a last row block or head group that
+// is mostly empty ends early and leaves its unit idle (28/4 heads, 30k, window 33, clustered 155 us against 161).  Not for heads
+// of 64, whose workgroups do less per tile than these constants say (28/4 heads, 50k, clustered 174 us against 192).
 inline int share_the_chip(const Prob& pb, int nt, int nwr, int S1, const VvArgs& va, int ny, int* chunks) {
-  constexpr float A0 = 10.f, V0 = 6.f, V1 = 4.f, A = 1.5f, V = 1.2f, SEQ = 1.06f, SLOW = 1.5f, LOSS = 1.08f, SPLIT = 1.3f;
+  constexpr float A0 = 10.f, V0 = 6.f, V1 = 4.f, A = 1.5f, V = 1.2f, SEQ = 1.06f, SLOW = 1.5f, LOSS = 1.08f, SPLIT = 0.9f;
   if ((ny > 1 && (nwr - 1) % 8 < 4) || (va.ny > 1 && (pb.G - 1) % 4 < 2)) return 0;
   const int ntv = (pb.P + TN - 1) / TN;
   auto tiles = [](int n, int parts) { return (float)((n + parts - 1) / parts); };
@@ -1232,41 +1236,39 @@ inline int share_the_chip(const Prob& pb, int nt, int nwr, int S1, const VvArgs&
   const float seq1 = seq(A), seq2 = seq(SLOW * A);
   float best = INFINITY;
   int bs = 0;
-  for (int S = 1; S <= S1; ++S) {
+  for (int S = S1; S >= 1; --S) {
     const int c = min(ntv, (n_cu() - S * ny * pb.Hkv) / (va.ny * pb.Hkv));     // chunks for the value-Gram pass
-    if (c < 1) break;
+    if (c < 1) continue;
     const float tv = V0 + V * tiles(ntv, c), t1 = max(A0 + A * tiles(nt, S), tv), t2 = max(A0 + SLOW * A * tiles(nt, S), tv);
-    if (t1 >= seq1 || t2 > LOSS * seq2 || t1 + t2 + SPLIT * S >= best) continue;
+    if (t1 >= seq1 || t2 > LOSS * seq2 || t1 + t2 + SPLIT * S > best) continue;
     best = t1 + t2 + SPLIT * S;
     bs = S;
     *chunks = c;
+    if (S == S1 && t2 <= seq2 && 2 * S * ny * pb.Hkv <= n_cu()) break;
   }
   return bs;
 }
 
+// How the two passes of a layer are launched.
+struct AttnVvPlan { RowGeom rg; AttnArgs aa; VvArgs va; bool vks2, side; };
 template <int D>
-int run_mfma(const Prob& pb, const void* q, const void* k, const void* v, const float* gram,
-             float* score, char* ws, const ScoreWs& lay, hipStream_t st) {
-  const uint16_t* qq = (const uint16_t*)q;
-  const uint16_t* kk = (const uint16_t*)k;
-  const uint16_t* vp = (const uint16_t*)v;
-  const ScorePtrs w = score_ptrs(ws, lay);
-  const RowGeom rg = row_geom(pb, pb.L, ATTN_KS2_TILES, false);
-  if (pb.ind != 0) gram = nullptr;                 // the attention-weight and value-norm indicators have no projection
-  VvArgs va = {0, 0, 0, 0, lay.ldv, 0};
-  bool vks2 = false;
+AttnVvPlan plan_attn_vv(const Prob& pb, const ScoreWs& lay, bool gram) {
+  AttnVvPlan pl = {row_geom(pb, pb.L, ATTN_KS2_TILES, false), {}, {0, 0, 0, 0, lay.ldv, 0}, false, false};
+  const RowGeom& rg = pl.rg;
+  VvArgs& va = pl.va;
+  AttnArgs& aa = pl.aa;
+  const int ntv = (pb.P + TN - 1) / TN;
   if (gram) {
     constexpr int HPW = D == 128 ? 4 : 8;
-    const int NTv = (pb.P + TN - 1) / TN;
     // as for the rows: half as many heads per workgroup, at most 3/2 of the tiles, VV_KS2_TILES of them
     const int hg4 = (pb.G + HPW / 2 - 1) / (HPW / 2), hg8 = (pb.G + HPW - 1) / HPW;
-    const int64_t t4 = span_tiles(NTv, (int64_t)hg4 * pb.Hkv);
-    vks2 = t4 >= VV_KS2_TILES && 2 * t4 <= 3 * span_tiles(NTv, (int64_t)hg8 * pb.Hkv);
-    va.ny = vks2 ? hg4 : hg8;
-    va.tiles_per_wg = max(1, (int)(((int64_t)NTv * va.ny * pb.Hkv + n_cu() - 1) / n_cu()));
-    va.chunks = (NTv + va.tiles_per_wg - 1) / va.tiles_per_wg;
+    const int64_t t4 = span_tiles(ntv, (int64_t)hg4 * pb.Hkv);
+    pl.vks2 = t4 >= VV_KS2_TILES && 2 * t4 <= 3 * span_tiles(ntv, (int64_t)hg8 * pb.Hkv);
+    va.ny = pl.vks2 ? hg4 : hg8;
+    va.tiles_per_wg = max(1, (int)(((int64_t)ntv * va.ny * pb.Hkv + n_cu() - 1) / n_cu()));
+    va.chunks = (ntv + va.tiles_per_wg - 1) / va.tiles_per_wg;
   }
-  AttnArgs aa = {0, rg.gy, 0, rg.log2iw, HEAVY_SPLITS};
+  aa = {0, rg.gy, 0, rg.log2iw, HEAVY_SPLITS};
   if (!pb.ext_lse) {
     // attention pass: about one workgroup per compute unit, whole tiles per split
     const int nt = (pb.L + TN - 1) / TN;
@@ -1278,17 +1280,13 @@ int run_mfma(const Prob& pb, const void* q, const void* k, const void* v, const 
     const int S1 = max(1, min(min(n_cu() / (pb.Hkv * rg.gy), nt), lay.S_max));
     set_splits(S1);
     int chunks = 0;
-    if (const int S2 = D == 128 && gram && !rg.ks2 && !vks2 ? share_the_chip(pb, nt, rg.nwr, S1, va, rg.gy, &chunks) : 0) {
+    if (const int S2 = D == 128 && gram && !rg.ks2 && !pl.vks2 ? share_the_chip(pb, nt, rg.nwr, S1, va, rg.gy, &chunks) : 0) {
+      pl.side = true;
       set_splits(S2);
       aa.heavy = HEAVY_SIDE;
-      const int ntv = (pb.P + TN - 1) / TN;
       va.tiles_per_wg = (ntv + chunks - 1) / chunks;
       va.chunks = (ntv + va.tiles_per_wg - 1) / va.tiles_per_wg;
     }
-  }
-  if (!gram) {
-    RK_LAUNCH(ST_VV, st, (k_vnorm2<D>), dim3((pb.P + 255) / 256, pb.Hkv), dim3(256), 0, st, pb, vp,
-              w.vv, lay.ldv);
   }
   // The attention pass first: the value-Gram pass leaves the values in cache for the score pass (8/8 heads of 128, 71k 220 us
   // against 227, 82k 299 / 311; 32/8, window 32, 64k 259 / 263).  Heads of 64 and rows of one split (many heads, whose sums
@@ -1296,6 +1294,25 @@ int run_mfma(const Prob& pb, const void* q, const void* k, const void* v, const 
   // 372 / 376).
   va.n = va.chunks * va.ny * pb.Hkv;
   va.at = D == 64 || aa.S <= 1 ? 0 : aa.S * aa.ny * pb.Hkv;
+  return pl;
+}
+
+template <int D>
+int run_mfma(const Prob& pb, const void* q, const void* k, const void* v, const float* gram,
+             float* score, char* ws, const ScoreWs& lay, hipStream_t st) {
+  const uint16_t* qq = (const uint16_t*)q;
+  const uint16_t* kk = (const uint16_t*)k;
+  const uint16_t* vp = (const uint16_t*)v;
+  const ScorePtrs w = score_ptrs(ws, lay);
+  if (pb.ind != 0) gram = nullptr;                 // the attention-weight and value-norm indicators have no projection
+  const AttnVvPlan pl = plan_attn_vv<D>(pb, lay, gram != nullptr);
+  const RowGeom& rg = pl.rg;
+  const AttnArgs aa = pl.aa;
+  const VvArgs va = pl.va;
+  if (!gram) {
+    RK_LAUNCH(ST_VV, st, (k_vnorm2<D>), dim3((pb.P + 255) / 256, pb.Hkv), dim3(256), 0, st, pb, vp,
+              w.vv, lay.ldv);
+  }
   const dim3 gav(va.n + aa.S * aa.ny * pb.Hkv);
   auto attn_vv = [&](auto a, auto b) {
     RK_LAUNCH(decltype(a)::value ? ST_ATTN : ST_VV, st, (k_attn_vv<D, decltype(a)::value, decltype(b)::value>), gav, dim3(512), 0, st,
@@ -1306,7 +1323,7 @@ int run_mfma(const Prob& pb, const void* q, const void* k, const void* v, const 
   const std::integral_constant<int, 2> split;
   auto with_vv = [&](auto a) {
     if (!gram) { if constexpr (decltype(a)::value != 0) attn_vv(a, no); }
-    else if (vks2) attn_vv(a, split);
+    else if (pl.vks2) attn_vv(a, split);
     else attn_vv(a, plain);
   };
   const float* part_z = w.part_z;
@@ -1349,6 +1366,16 @@ bool mfma_eligible(const Prob& pb, const void* q, const void* k, const void* v) 
   if ((uint64_t)pb.G * (uint64_t)((pb.P + 3) / 4 * 4) * 4u >= (1ull << 32)) return false;
   if ((uint64_t)(pb.W + 32) * (uint64_t)pb.ld * 4u >= (1ull << 32)) return false;   // one head's score rows
   return true;
+}
+
+int score_plan(const Prob& pb, int32_t* plan) {
+  if (!mfma_eligible(pb, nullptr, nullptr, nullptr)) return RESTKV_EUNSUPPORTED;
+  const ScoreWs lay = score_ws(pb);
+  const AttnVvPlan pl = pb.d == 64 ? plan_attn_vv<64>(pb, lay, pb.ind == 0) : plan_attn_vv<128>(pb, lay, pb.ind == 0);
+  plan[0] = pl.aa.S;
+  plan[1] = pl.aa.kps / TN;
+  plan[2] = pl.side;
+  return RESTKV_OK;
 }
 
 int launch_score_mfma(const Prob& pb, const void* q, const void* k, const void* v, const float* gram,
