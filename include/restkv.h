@@ -280,8 +280,9 @@ int restkv_debug_force_fp32(int on);
 
 /*
  * Debug aid: how restkv_score with Gram matrices runs the attention pass of these parameters on the bf16 matrix-core
- * path (aligned pointers assumed; RESTKV_EUNSUPPORTED where that path does not take them).  plan: HOST array of 3:
- * number of key splits, 64-key tiles of a split, 1 if the value-Gram pass runs beside it on a part of the compute units.
+ * path (aligned pointers assumed; RESTKV_EUNSUPPORTED where that path does not take them).  plan: HOST array of 4:
+ * number of key splits, 64-key tiles of a split, 1 if the value-Gram pass runs beside it on a part of the compute units,
+ * 1 if heavy attention weights enter the sums as two bf16 numbers.
  */
 int restkv_debug_score_plan(const restkv_params* p, int32_t* plan);
 

@@ -233,8 +233,8 @@ def restkv_debug_force_fp32(on: bool):
 
 
 def restkv_debug_score_plan(p):
-    """(key splits, 64-key tiles of a split, side by side) of the attention pass on the bf16 matrix-core path."""
-    plan = (ctypes.c_int32 * 3)()
+    """(key splits, 64-key tiles of a split, side by side, heavy weights in two parts) of the attention pass on the bf16 matrix-core path."""
+    plan = (ctypes.c_int32 * 4)()
     _chk(lib().restkv_debug_score_plan(ctypes.byref(p), plan), "restkv_debug_score_plan")
     return tuple(plan)
 

@@ -37,11 +37,18 @@ typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 constexpr int TN = 64;                 // keys per LDS tile
 constexpr float LOG2E = 1.4426950408889634f;
 // A joining key that holds more than 1/9 of the others' sum on arrival becomes the reference of its row, so that its
-// weight is exact.  Side by side with the value-Gram pass (share_the_chip) there are fewer splits, hence fewer keys that
-// are a split's first and exact, and the limit is 1/33: with 1/9 those scores were up to 30 % further from 64 bits (32/8
-// heads, clustered logits, 2112 tokens 7.7e-6 against 6.0e-6, 32k 2.3e-6 against 1.6e-6).  1/33 everywhere costs the other
-// shapes up to 1.4 % (64/8 heads of 64, 40k 262.6 / 266.3 us, 28/4, 20k 81.7 / 82.7, 8/8 of 128, 71k 224.9 / 226.6).
-constexpr float HEAVY_SPLITS = 8.0f, HEAVY_SIDE = 32.0f;
+// weight is exact.  Side by side with the value-Gram pass (share_the_chip) there may be fewer splits than there are alone,
+// hence fewer keys that are a split's first or kept out, and more weights enter the sums as bf16.  Splits of up to LO_TILES
+// tiles, or half as many as alone, then take the weights above 1/16 of the row's sum so far (half of which a lane has: LO_SHARE) in two bf16 parts,
+// 16 keys at a time, with a second product for the remainders.  Scores then lie nearer to 64 bits than with all splits,
+// whatever the logits.  Distance (2-norm) over that of all splits, plain / sinks / clustered logits, 55 shapes each: mean
+// 0.72 / 0.66 / 0.35, worst 0.99 / 0.98 / 0.72; without the second part 1.01 / 1.00 / 1.22 and 1.17 / 1.43 / 1.94.
+// Score + smoothing with and without it, 32/8 heads, window 64: 4k 56.8 / 54.9 us, clustered 62.9 / 59.5; 16k 108.7 / 108.0,
+// clustered 133.8 / 123.5.  Longer splits lose nothing by being fewer with a limit of 1/33 (clustered, 16k to 50k: 0.80 to
+// 1.02 of the distance; 512/64 heads, 3186 tokens, two splits for four 1.18), and would pay up to 11 % (64/8 heads, 32k, clustered).
+constexpr float HEAVY_SPLITS = 8.0f, HEAVY_SIDE = 32.0f, HEAVY_LO = 16.0f, LO_SHARE = 8.0f;
+constexpr int LO_TILES = 24;
+static_assert(HEAVY_LO >= LO_SHARE, "the branch that looks for heavy weights is entered for all of them");
 constexpr float RESCALE_TH = 8.0f;  // log2 units a row maximum may run ahead of its reference
 
 #define MFMA(a, b, c) __builtin_amdgcn_mfma_f32_32x32x16_bf16((a), (b), (c), 0, 0, 0)
@@ -451,9 +458,11 @@ __device__ __forceinline__ void vv_pass(const Prob& pb, WgAt at, VvSmem<D, KS2>&
 // blocks, wavefronts 0..3 take keys 0..31 of every tile and wavefronts 4..7 keys 32..63, and the two
 // halves meet in LDS at the end, so that a split leaves one set of sums either way.  A wavefront
 // without rows only copies.
+//
+// LO: groups of 16 keys that hold a heavy weight enter P.V a second time with what bf16 has left of their weights.
 template <int D>
 struct AttnSmem { __attribute__((aligned(1024))) uint16_t ring[7][TN * D]; };
-template <int D, bool KS2>
+template <int D, bool KS2, bool LO>
 __device__ __forceinline__ void attn_pass(const Prob& pb, WgAt at, AttnSmem<D>& sm, const uint16_t* __restrict__ q,
                                           const uint16_t* __restrict__ k,
                                           const uint16_t* __restrict__ v, int S, int kps,
@@ -513,7 +522,8 @@ __device__ __forceinline__ void attn_pass(const Prob& pb, WgAt at, AttnSmem<D>& 
   for (int cb = 0; cb < CB; ++cb)
 #pragma unroll
     for (int j = 0; j < 16; ++j) oacc[cb][j] = 0.f;
-  bf16x8 pv[NMB][2];
+  bf16x8 pv[NMB][2], pr[NMB][2];     // weights; LO: their remainders in the groups that have a bit in `two`
+  uint32_t two = 0;
 
   // lane-constant part of the transposing LDS read of the value tile: row and column of the
   // 8 bytes this lane contributes to a 16 x 16 block
@@ -546,6 +556,9 @@ __device__ __forceinline__ void attn_pass(const Prob& pb, WgAt at, AttnSmem<D>& 
       if (grp + 1 < 2 * NMB) fetch(grp + 1, av[(grp + 1) & 1]);
 #pragma unroll
       for (int cb = 0; cb < CB; ++cb) oacc[cb] = MFMA(av[grp & 1][cb], pv[grp >> 1][grp & 1], oacc[cb]);
+      if (LO && (two >> grp & 1u))                        // (uniform)
+#pragma unroll
+        for (int cb = 0; cb < CB; ++cb) oacc[cb] = MFMA(av[grp & 1][cb], pr[grp >> 1][grp & 1], oacc[cb]);
     }
   };
 
@@ -638,7 +651,9 @@ __device__ __forceinline__ void attn_pass(const Prob& pb, WgAt at, AttnSmem<D>& 
       // Nothing to do unless the reference has to move or the tile maximum may be heavy: lsum is
       // this lane's share of the row's sum, so the comparison is a necessary condition for both
       // "kept out" and "heavy", which are settled below.
+      bool any_heavy = false;
       if (__ballot((tm - mref) * c2 > RESCALE_TH || pl * heavy > lsum) != 0ull) {
+        if (LO) any_heavy = __ballot(pl * LO_SHARE > lsum) != 0ull;
         const float oth = xhalf_sum(lsum);
         bool dominant = false;
         if (newmax) {
@@ -722,6 +737,9 @@ __device__ __forceinline__ void attn_pass(const Prob& pb, WgAt at, AttnSmem<D>& 
             for (int e = 0; e < 8; ++e) pe[e] = fmaf(sacc[mb][b8 + e], c2, nm);
 #pragma unroll
             for (int e = 0; e < 8; ++e) pe[e] = __builtin_amdgcn_exp2f(pe[e]);
+            if (LO)
+#pragma unroll
+              for (int e = 0; e < 8; ++e) sacc[mb][b8 + e] = pe[e];
 #pragma unroll
             for (int e = 0; e < 8; ++e) ls[e & 3] += pe[e];
 #pragma unroll
@@ -729,12 +747,34 @@ __device__ __forceinline__ void attn_pass(const Prob& pb, WgAt at, AttnSmem<D>& 
           }
         lsum += (ls[0] + ls[1]) + (ls[2] + ls[3]);
       }
+      if (LO) {
+        two = 0;
+        if (any_heavy) {
+#pragma unroll
+          for (int grp = 0; grp < 2 * NMB; ++grp) {
+            const int mb = grp >> 1, b8 = 8 * (grp & 1);
+            float gm = sacc[mb][b8];
+#pragma unroll
+            for (int e = 1; e < 8; ++e) gm = fmaxf(gm, sacc[mb][b8 + e]);
+            if (__ballot(gm * LO_SHARE > lsum) != 0ull) {
+              two |= 1u << grp;
+#pragma unroll
+              for (int e = 0; e < 8; ++e) pr[mb][grp & 1][e] = (__bf16)(sacc[mb][b8 + e] - (float)pv[mb][grp & 1][e]);
+            }
+          }
+        }
+      }
       if (!late) {           // B_t of the early wavefronts: after both halves
         wait_vm<NG>();
         wg_barrier();
       }
     }
     accumulate(Vs[(ntiles - 1) & 3]);   // its slot is not a target of the copies still in flight
+    // (wait states before the first read of the sums, spelled out: the last products may lie behind a branch, after which the
+    // compiler inserts too few)
+    if (LO)
+#pragma unroll
+      for (int cb = 0; cb < CB; ++cb) asm volatile("s_nop 15\n\ts_nop 3" : "+v"(oacc[cb]));
     wait_vm<0>();            // no copy may land in LDS after the workgroup has gone
   }
   float ltot = xhalf_sum(lsum);
@@ -824,7 +864,7 @@ __device__ __forceinline__ void attn_pass(const Prob& pb, WgAt at, AttnSmem<D>& 
 
 // The two passes that need nothing of each other, one launch: workgroups [va.at, va.at + va.n) are the value-Gram pass's,
 // the others the attention pass's; the second pass's start as the first one's end (a workgroup fills a compute unit either way).
-// ATTN, VV: 0 that pass is not there, 1 it is, 2 with KS2.  512 threads.
+// ATTN, VV: 0 that pass is not there, 1 it is, 2 with KS2, 3 with LO.  512 threads.
 struct AttnArgs { int S, ny, kps, log2iw; float heavy; };
 struct VvArgs { int at, n, chunks, ny, ldv, tiles_per_wg; };
 template <int D, int ATTN, int VV>
@@ -838,7 +878,7 @@ __global__ __launch_bounds__(512) void k_attn_vv(Prob pb, const uint16_t* __rest
       vv_pass<D, VV == 2>(pb, wg_at<D>(pb, id - va.at, va.chunks, va.ny), sm.v, v, gram, o.vv, va.ldv, va.tiles_per_wg);
   } else {
     if constexpr (ATTN != 0)
-      attn_pass<D, ATTN == 2>(pb, wg_at<D>(pb, id - (va.at ? 0 : va.n), aa.S, aa.ny), sm.a, q, k, v, aa.S, aa.kps, aa.log2iw,
+      attn_pass<D, ATTN == 2, ATTN == 3>(pb, wg_at<D>(pb, id - (va.at ? 0 : va.n), aa.S, aa.ny), sm.a, q, k, v, aa.S, aa.kps, aa.log2iw,
                               aa.heavy, o);
   }
 }
@@ -1211,6 +1251,15 @@ void launch_score_pipe(const Prob& pb, const uint16_t* q, const uint16_t* k, con
     RK_LAUNCH(ST_SCORE, st, (k_score_pipe<D, GP, false>), gr, dim3(512), 0, st, pb, q, k, v, w, ldv, score, tpp, nwb, chunks, rg.gy);
 }
 
+// (whole tiles: with S splits asked for the last ones may have nothing left)
+inline int split_tiles(int nt, int S) { return (nt + S - 1) / S; }
+inline int splits_of(int nt, int S) { const int t = split_tiles(nt, S); return (nt + t - 1) / t; }
+// S splits beside the value-Gram pass take heavy weights in two parts (S1: splits of the pass alone; see HEAVY_SIDE).
+inline bool two_parts(int nt, int S, int S1) {
+  const int s = splits_of(nt, S), alone = splits_of(nt, S1);
+  return s < alone && (split_tiles(nt, S) <= LO_TILES || 2 * s <= alone);
+}
+
 // Attention pass and value-Gram pass side by side, each on a part of the compute units, where that ends earlier than
 // one after the other on all of them: fixed parts (launch, operands, first tile, sums) overlap, fewer splits are fewer
 // sums for the merge, and a unit bound by vector instructions next to one bound by the matrix cores runs at a higher
@@ -1219,16 +1268,18 @@ void launch_score_pipe(const Prob& pb, const uint16_t* q, const uint16_t* k, con
 // splits leave half of the units free (one or two KV heads, whose splits are as many as the merge takes), the splits stay as
 // many and the value-Gram pass has the other units.  Else taken is the split count with the smallest sum of plain and
 // clustered time (SPLIT us for each split) that wins for plain logits and loses at most LOSS by the model, which is nothing
-// by measurement, for clustered ones.  Score + smoothing, plain / clustered logits, against one
-// after the other in two launches: 32/8 heads, window 64, 4k 0.78 / 0.84, 8k 0.84 / 0.89, 32k 0.93 / 0.97, 64k 0.96 / 0.96;
-// window 4, 4k 0.88 / 0.88; 64/8, 4k 0.86 / 0.88; 8/8, 4k 0.86 / 0.90; 16/4, 4k 0.82 / 0.90, 8k 0.84 / 0.92, 32k 0.88 / 0.94;
-// 4/2, 4k 0.86 / 0.89, 8k 0.89 / 0.89, 16k 0.89 / 0.90; 4/1, 8k 0.86 / 0.87.  (With SPLIT 1.3 for any number of heads
-// 4/2, 8k 1.01 / 1.19, 4/1, 16k 0.98 / 1.10, 16/4, 8k, window 16 0.93 / 1.06; with 0.65 32/8, 4k, window 16 0.92 for 0.83.)
+// by measurement, for clustered ones; weights in two parts cost clustered ones PARTS a tile, and then they may not lose.
+// Score + smoothing, plain / clustered logits, against one after the other in two launches: 32/8 heads, window 64, 4k
+// 0.82 / 0.88, 8k 0.88 / 0.96, 16k 0.88 / 0.98, 32k 0.93 / 0.96, 64k 0.94 / 0.96; window 16, 4k 0.84 / 0.90; 64/8, 4k 0.90 / 0.93;
+// 8/8, 4k 0.89 / 0.94; 16/4, 4k 0.85 / 0.95, 8k 0.88 / 0.97, 32k 0.91 / 1.02; 28/4, window 32, 32k 0.91 / 1.07, the worst of
+// 500 shapes; 4/2, 4k 0.89 / 0.88, 8k 0.89 / 0.89, 16k 0.89 / 0.90; 4/1, 8k 0.86 / 0.87.  (With SPLIT 1.3 for any number of
+// heads 4/2, 8k 1.01 / 1.20, 4/1, 16k 0.98 / 1.10, 16/4, 8k, window 16 0.93 / 1.06; with 0.65 32/8, 4k, window 16 0.92.
+// With weights in two parts let off as lightly as others 128/32 heads, 4k, one split for two 0.96 / 1.12.)
 // Only where the workgroups have equal work: a last row block or head group that
 // is mostly empty ends early and leaves its unit idle (28/4 heads, 30k, window 33, clustered 155 us against 161).  Not for heads
 // of 64, whose workgroups do less per tile than these constants say (28/4 heads, 50k, clustered 174 us against 192).
 inline int share_the_chip(const Prob& pb, int nt, int nwr, int S1, const VvArgs& va, int ny, int* chunks) {
-  constexpr float A0 = 10.f, V0 = 6.f, V1 = 4.f, A = 1.5f, V = 1.2f, SEQ = 1.06f, SLOW = 1.5f, LOSS = 1.08f, SPLIT = 0.9f;
+  constexpr float A0 = 10.f, V0 = 6.f, V1 = 4.f, A = 1.5f, V = 1.2f, SEQ = 1.06f, SLOW = 1.5f, LOSS = 1.08f, SPLIT = 0.9f, PARTS = 1.1f;
   if ((ny > 1 && (nwr - 1) % 8 < 4) || (va.ny > 1 && (pb.G - 1) % 4 < 2)) return 0;
   const int ntv = (pb.P + TN - 1) / TN;
   auto tiles = [](int n, int parts) { return (float)((n + parts - 1) / parts); };
@@ -1239,8 +1290,10 @@ inline int share_the_chip(const Prob& pb, int nt, int nwr, int S1, const VvArgs&
   for (int S = S1; S >= 1; --S) {
     const int c = min(ntv, (n_cu() - S * ny * pb.Hkv) / (va.ny * pb.Hkv));     // chunks for the value-Gram pass
     if (c < 1) continue;
-    const float tv = V0 + V * tiles(ntv, c), t1 = max(A0 + A * tiles(nt, S), tv), t2 = max(A0 + SLOW * A * tiles(nt, S), tv);
-    if (t1 >= seq1 || t2 > LOSS * seq2 || t1 + t2 + SPLIT * S > best) continue;
+    const bool lo = two_parts(nt, S, S1);
+    const float tv = V0 + V * tiles(ntv, c), t1 = max(A0 + A * tiles(nt, S), tv);
+    const float t2 = max(A0 + (lo ? PARTS : 1.f) * SLOW * A * tiles(nt, S), tv);
+    if (t1 >= seq1 || t2 > (lo ? 1.f : LOSS) * seq2 || t1 + t2 + SPLIT * S > best) continue;
     best = t1 + t2 + SPLIT * S;
     bs = S;
     *chunks = c;
@@ -1250,10 +1303,10 @@ inline int share_the_chip(const Prob& pb, int nt, int nwr, int S1, const VvArgs&
 }
 
 // How the two passes of a layer are launched.
-struct AttnVvPlan { RowGeom rg; AttnArgs aa; VvArgs va; bool vks2, side; };
+struct AttnVvPlan { RowGeom rg; AttnArgs aa; VvArgs va; bool vks2, side, lo; };
 template <int D>
 AttnVvPlan plan_attn_vv(const Prob& pb, const ScoreWs& lay, bool gram) {
-  AttnVvPlan pl = {row_geom(pb, pb.L, ATTN_KS2_TILES, false), {}, {0, 0, 0, 0, lay.ldv, 0}, false, false};
+  AttnVvPlan pl = {row_geom(pb, pb.L, ATTN_KS2_TILES, false), {}, {0, 0, 0, 0, lay.ldv, 0}, false, false, false};
   const RowGeom& rg = pl.rg;
   VvArgs& va = pl.va;
   AttnArgs& aa = pl.aa;
@@ -1273,9 +1326,8 @@ AttnVvPlan plan_attn_vv(const Prob& pb, const ScoreWs& lay, bool gram) {
     // attention pass: about one workgroup per compute unit, whole tiles per split
     const int nt = (pb.L + TN - 1) / TN;
     auto set_splits = [&](int S) {
-      const int t = (nt + S - 1) / S;
-      aa.kps = t * TN;
-      aa.S = (nt + t - 1) / t;                     // (whole tiles: the last splits may have nothing left)
+      aa.kps = split_tiles(nt, S) * TN;
+      aa.S = splits_of(nt, S);
     };
     const int S1 = max(1, min(min(n_cu() / (pb.Hkv * rg.gy), nt), lay.S_max));
     set_splits(S1);
@@ -1283,7 +1335,8 @@ AttnVvPlan plan_attn_vv(const Prob& pb, const ScoreWs& lay, bool gram) {
     if (const int S2 = D == 128 && gram && !rg.ks2 && !pl.vks2 ? share_the_chip(pb, nt, rg.nwr, S1, va, rg.gy, &chunks) : 0) {
       pl.side = true;
       set_splits(S2);
-      aa.heavy = HEAVY_SIDE;
+      pl.lo = two_parts(nt, S2, S1);
+      aa.heavy = pl.lo ? HEAVY_LO : HEAVY_SIDE;
       va.tiles_per_wg = (ntv + chunks - 1) / chunks;
       va.chunks = (ntv + va.tiles_per_wg - 1) / va.tiles_per_wg;
     }
@@ -1336,8 +1389,13 @@ int run_mfma(const Prob& pb, const void* q, const void* k, const void* v, const 
     combine(1);
     with_vv(no);
   } else {
-    if (rg.ks2) with_vv(split);
-    else with_vv(plain);
+    if (rg.ks2) {
+      with_vv(split);
+    } else if (pl.lo) {
+      if constexpr (D == 128) attn_vv(std::integral_constant<int, 3>(), plain);
+    } else {
+      with_vv(plain);
+    }
     combine(aa.S);
   }
 #define RK_SCORE(GPV) launch_score_pipe<D, GPV>(pb, qq, kk, vp, w, lay.ldv, score, lay.nwb, st)
@@ -1375,6 +1433,7 @@ int score_plan(const Prob& pb, int32_t* plan) {
   plan[0] = pl.aa.S;
   plan[1] = pl.aa.kps / TN;
   plan[2] = pl.side;
+  plan[3] = pl.lo;
   return RESTKV_OK;
 }
 

@@ -95,10 +95,10 @@ def test_error_codes_without_launch(rk):
 def test_few_kv_heads_keep_all_key_splits_beside_the_value_gram_pass(rk, Hq, Hkv, L, W):
     """With one or two KV heads the key splits (64 at most) leave half of the units free, so the value-Gram pass beside
     them is no reason for longer ones: that made clustered contexts up to 19 % slower than one pass after the other."""
-    splits, tiles, side = rk.restkv_debug_score_plan(good(rk, n_q_heads=Hq, n_kv_heads=Hkv, head_dim=128, seq_len=L, window=W,
+    splits, tiles, side, two = rk.restkv_debug_score_plan(good(rk, n_q_heads=Hq, n_kv_heads=Hkv, head_dim=128, seq_len=L, window=W,
                                                           budget=W + 64, dtype="bf16"))
     all_tiles = (L + 63) // 64
-    assert side == 1 and tiles == -(-all_tiles // min(64, all_tiles)) and splits == -(-all_tiles // tiles)
+    assert (side, two) == (1, 0) and tiles == -(-all_tiles // min(64, all_tiles)) and splits == -(-all_tiles // tiles)
 
 
 def test_score_plan_covers_the_context_and_both_launch_orders(rk):
@@ -108,11 +108,12 @@ def test_score_plan_covers_the_context_and_both_launch_orders(rk):
             for L in (129, 1100, 2112, 9001, 32768, 131072):
                 for W in (1, 33, 64):
                     p = good(rk, n_q_heads=Hq, n_kv_heads=Hkv, head_dim=d, seq_len=L, window=W, budget=W + 64, dtype="bf16")
-                    splits, tiles, side = rk.restkv_debug_score_plan(p)
+                    splits, tiles, side, two = rk.restkv_debug_score_plan(p)
                     assert 1 <= splits <= 64 and (splits - 1) * tiles * 64 < L <= splits * tiles * 64
                     assert d == 128 or side == 0
-                    seen.add((d, side))
-    assert seen == {(64, 0), (128, 0), (128, 1)}
+                    assert side or not two
+                    seen.add((d, side, two))
+    assert seen == {(64, 0, 0), (128, 0, 0), (128, 1, 0), (128, 1, 1)}
     with pytest.raises(rk.RestkvError):
         rk.restkv_debug_score_plan(good(rk))               # float32
     assert rk.lib().restkv_debug_score_plan(ctypes.byref(good(rk)), None) == -1

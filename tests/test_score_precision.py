@@ -1,0 +1,155 @@
+"""How far the scores may lie from 64 bits: bounds that a kernel with fewer bits in any of its products fails.
+
+The bounds come from the same inputs on the CPU: the scores in float64, and once more with one quantity rounded as a kernel
+would.  The CPU tests show that each planted loss of bits exceeds the bound that the GPU tests then apply."""
+import pytest
+import torch
+
+import workloads
+from gpu_util import params_for
+from test_gpu_parity import rk  # noqa: F401
+
+
+def scores64(q, k, v, gram, W, weights=None, dot=None):
+    """Indicator of one KV head (mean over its query heads) [W, P] in float64; q [G,W,d], k, v [L,d], gram [G,d,d].  The key
+    with a row's largest weight in leave-one-out form.  weights: what becomes of the weights of A V [G,W,L], relative to
+    their row's largest; dot(a, b): the products a b^T."""
+    q, k, v, gram = q.double(), k.double(), v.double(), gram.double()
+    G, _, d = q.shape
+    L = k.shape[0]
+    P = L - W
+    dot = dot or (lambda a, b: a @ b.T)
+    hidden = torch.arange(L)[None, :] > (P + torch.arange(W))[:, None]
+    logits = torch.stack([(dot(q[h], k) / d ** 0.5).masked_fill(hidden, float("-inf")) for h in range(G)])
+    exact = torch.exp(logits - logits.amax(-1, keepdim=True))
+    used = weights(exact) if weights else exact
+    out = torch.zeros((W, P), dtype=torch.float64)
+    for h in range(G):
+        p, pr = exact[h], used[h]
+        den = p.sum(-1, keepdim=True)
+        top = p.argmax(-1, keepdim=True)
+        rest = p.scatter(1, top, 0.0).sum(-1, keepdim=True)
+        z = dot(pr, v.T) / den
+        u = dot(z, gram[h])
+        vv = (dot(v[:P], gram[h]) * v[:P]).sum(-1)
+        x = ((u * z).sum(-1, keepdim=True) - 2.0 * dot(u, v[:P]) + vv[None]).clamp_min(0.0)
+        omit = den - p
+        omit.scatter_(1, top, rest)
+        ind = p[:, :P] / omit[:, :P] * x.sqrt()
+        y = dot(pr.scatter(1, top, 0.0), v.T) / rest - v[top[:, 0]]
+        loo = (p.gather(1, top) / den)[:, 0] * (dot(y, gram[h]) * y).sum(-1).clamp_min(0.0).sqrt()
+        rows = (top[:, 0] < P).nonzero()[:, 0]
+        ind[rows, top[rows, 0]] = loo[rows]
+        out += ind
+    return out / G
+
+
+def distance(a, b):
+    return float((a.double() - b).norm() / b.norm())
+
+
+def heads_of(w, q, k, v, gram, g):
+    G = w.group
+    return q[g * G:(g + 1) * G], k[g], v[g], gram[g * G:(g + 1) * G], w.window
+
+
+def gpu_scores(rk, w, q, k, v, wo):  # noqa: F811
+    p = params_for(rk, w)
+    gram = torch.empty((w.n_q_heads, w.head_dim, w.head_dim), dtype=torch.float32, device="cuda")
+    rk.restkv_prepare_wo(p, wo.cuda(), gram)
+    buf = rk.alloc_layer_buffers(p, q.dtype, "cuda")
+    rk.restkv_score(p, q.cuda(), k.cuda(), v.cuda(), gram, buf.score, buf.workspace)
+    return buf.score[..., :w.prefix].cpu(), gram.cpu()
+
+
+def gram_of(w, wo):
+    x = wo.double().reshape(w.n_q_heads, w.head_dim, -1)
+    return x @ x.transpose(1, 2)
+
+
+# ---- bf16: weights of the attention pass beside the value-Gram pass --------------------------
+
+def in_bf16(p, seed=5):
+    """Weights rounded to bf16 in a frame that is a random fraction of a power of two for every row."""
+    c = 1.0 + torch.rand((*p.shape[:2], 1), generator=torch.Generator().manual_seed(seed), dtype=torch.float64)
+    return (p * c).bfloat16().double() / c
+
+
+def largest_exact(p, keys, share):
+    """What one reference per tile gives: the largest weight of a 64-key tile stays as it is where it is more than `share` of
+    its split's sum (`keys` keys), the others are rounded."""
+    out = in_bf16(p)
+    for k0 in range(0, p.shape[2], keys):
+        total = p[..., k0:k0 + keys].sum(-1, keepdim=True)
+        for t0 in range(k0, min(k0 + keys, p.shape[2]), 64):
+            x, o = p[..., t0:t0 + 64], out[..., t0:t0 + 64]
+            m = x.amax(-1, keepdim=True)
+            o.copy_(torch.where((x == m) & (m > share * total), x, o))
+    return out
+
+
+def heavy_groups_exact(p, keys, share, iw):
+    """What a second part of the weights gives: all weights of 16 keys stay as they are in the `iw` window positions of all
+    heads where one of them is more than `share` of its split's sum."""
+    out = in_bf16(p)
+    for k0 in range(0, p.shape[2], keys):
+        total = p[..., k0:k0 + keys].sum(-1, keepdim=True)
+        for i0 in range(0, p.shape[1], iw):
+            for t0 in range(k0, min(k0 + keys, p.shape[2]), 16):
+                x = p[:, i0:i0 + iw, t0:t0 + 16]
+                if bool((x > share * total[:, i0:i0 + iw]).any()):
+                    out[:, i0:i0 + iw, t0:t0 + 16] = x
+    return out
+
+
+# key splits of few tiles beside the value-Gram pass: (Hq, Hkv, L, W)
+CLUSTERED = [(16, 4, 4096, 16), (28, 4, 3000, 64), (32, 8, 3000, 64), (64, 8, 4096, 16)]
+
+
+def clustered(Hq, Hkv, L, W, strength):
+    """Keys and queries that share a rank-16 component: a few weights carry a row's sum."""
+    w = workloads.small_case(Hq=Hq, Hkv=Hkv, d=128, L=L, W=W, B=W + 100, dtype="bf16", D=256, seed=29)
+    gen = torch.Generator().manual_seed(31)
+    q, k, v = (t.float() for t in workloads.make_qkv(w))
+    f = torch.randn((Hkv, 16, 128), generator=gen) * 0.25 * strength
+    k += torch.randn((Hkv, L, 16), generator=gen) @ f
+    q += torch.randn((Hq, W, 16), generator=gen) @ f.repeat_interleave(w.group, dim=0)
+    return w, q.bfloat16(), k.bfloat16(), v.bfloat16(), workloads.make_wo(w)
+
+
+def weights_bound(w, plan, ref, args):
+    """One and a half times what the weights' rounding gives with 16 keys exact wherever one is above 1/16 of its split's
+    sum, and 1.2e-6 for everything else: u and Gram matrices enter their products as two bf16 parts, whose sum is up to
+    2^-17 = 7.6e-6 of an entry off; over the 128 entries of a product that averages to some 7.6e-6 / sqrt(3 128) = 4e-7
+    for each, and FP32 sums add as much."""
+    gp = 1 << (w.group - 1).bit_length()
+    sim = scores64(*args, weights=lambda p: heavy_groups_exact(p, 64 * plan[1], 1.0 / 16.0, 32 // gp))
+    return 1.5 * distance(sim, ref) + 1.2e-6
+
+
+@pytest.mark.parametrize("strength", [0.7, 1.0])
+@pytest.mark.parametrize("Hq,Hkv,L,W", CLUSTERED)
+def test_one_exact_weight_per_tile_would_exceed_the_bound(Hq, Hkv, L, W, strength):
+    import paper_2605_08840_amd as lib
+    w, q, k, v, wo = clustered(Hq, Hkv, L, W, strength)
+    plan = lib.restkv_debug_score_plan(params_for(lib, w))
+    assert plan[2:] == (1, 1)
+    args = heads_of(w, q, k, v, gram_of(w, wo), 0)
+    ref = scores64(*args)
+    planted = scores64(*args, weights=lambda p: largest_exact(p, 64 * plan[1], 1.0 / 33.0))
+    assert distance(planted, ref) > 2.0 * weights_bound(w, plan, ref, args)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("strength", [0.7, 1.0])
+@pytest.mark.parametrize("Hq,Hkv,L,W", CLUSTERED)
+def test_heavy_weights_beside_the_value_gram_pass(rk, Hq, Hkv, L, W, strength):  # noqa: F811
+    """Few key splits: clustered scores stay as near to 64 bits as the weights that enter in two parts allow."""
+    w, q, k, v, wo = clustered(Hq, Hkv, L, W, strength)
+    plan = rk.restkv_debug_score_plan(params_for(rk, w))
+    assert plan[2:] == (1, 1)
+    got, gram = gpu_scores(rk, w, q, k, v, wo)
+    for g in (0, Hkv - 1):
+        args = heads_of(w, q, k, v, gram, g)
+        ref = scores64(*args)
+        assert distance(got[g], ref) <= weights_bound(w, plan, ref, args), f"head {g}"
