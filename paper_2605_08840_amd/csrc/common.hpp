@@ -141,19 +141,20 @@ __device__ __forceinline__ int head_budget(const Prob& pb, int g) {
   return min(max(pb.hb[g], pb.W + 1), pb.B);
 }
 
-// Workgroup id -> (KV head, part of the head's work): workgroups go round the eight XCDs by their id, so the heads are
+// Workgroup id (x fastest) -> (KV head, part of the head's work): workgroups go round the eight XCDs by their id, so the heads are
 // taken eight at a time, the head running fastest: a head's workgroups share one XCD and find in its L2 what the others
 // have fetched and what the pass before left there, and follow each other closely in time.  Fewer than eight heads (or
 // what is left of them) run fastest too: on as few XCDs as there are.  Against the parts running fastest: select, 8
 // heads, 128k 25.2 -> 23.4 us; score + smoothing, 8k FP32 130 -> 123, 64k 329 -> 318.
 struct HeadPart { int g, x; };
 __device__ __forceinline__ HeadPart head_part(const Prob& pb) {
-  const unsigned id = blockIdx.x, parts = gridDim.x / (unsigned)pb.Hkv, full = (unsigned)pb.Hkv & ~7u;
+  const unsigned id = blockIdx.y * gridDim.x + blockIdx.x, parts = gridDim.x, full = (unsigned)pb.Hkv & ~7u;
   if (id < full * parts) return {(int)(id / (8u * parts) * 8u + (id & 7u)), (int)((id >> 3) % parts)};
   const unsigned left = (unsigned)pb.Hkv - full, r = id - full * parts;
   return {(int)(full + r % left), (int)(r / left)};
 }
-inline dim3 head_grid(const Prob& pb, int parts) { return dim3((unsigned)pb.Hkv * (unsigned)parts); }
+// (two dimensions, for the ids of a launch: the threads along one of them have to stay below 2^32)
+inline dim3 head_grid(const Prob& pb, int parts) { return dim3(parts, pb.Hkv); }
 
 // Order-preserving map float -> uint32 (larger float <=> larger key; -0 < +0; NaNs at the ends).  Never
 // 0, which stands for "no entry" in the searches: the one value that would be (a NaN with every bit

@@ -357,3 +357,22 @@ def test_attention_and_value_gram_passes_share_the_chip(rk, oracle_mod, Hq, Hkv,
     assert np.array_equal(got[0], got[1])
     for g, (Ig, tol) in oracle_score(oracle_mod, w, q, k, v, wo, heads=[0, Hkv - 1]).items():
         assert_score_close(got[0][g], Ig, tol, f"head {g}")
+
+
+def test_smoothing_of_more_rows_than_one_grid_dimension_holds(rk):  # noqa: F811
+    """16.8 million (head, query) rows of 256 threads, 2^32 threads in all: accepted, and the same numbers as torch's."""
+    Hkv, W, P = 8192, 2048, 16
+    p = params_for(rk, workloads.small_case(Hq=Hkv, Hkv=Hkv, d=64, L=P + W, W=W, B=W + 5, dtype="f32", alpha=0.5, beta=1.0))
+    score = torch.rand((Hkv, W, P), device="cuda", generator=torch.Generator("cuda").manual_seed(3))
+    ema = torch.empty((Hkv, P), device="cuda")
+    final = torch.empty_like(ema)
+    info = torch.empty((Hkv, 2), dtype=torch.int32, device="cuda")
+    drift = torch.empty((Hkv, 2), dtype=torch.float64, device="cuda")
+    ws = torch.empty(3 << 30, dtype=torch.uint8, device="cuda")
+    rk.restkv_smooth(p, score, ema, final, info, drift, ws)
+    # the EMA's weights: 2^-(W-1) for the oldest query, then 2^-(W-i)
+    wts = torch.tensor([0.5 ** (W - max(i, 1)) for i in range(W)], dtype=torch.float64, device="cuda")
+    want = torch.einsum("gwp,w->gp", score[:, -40:].double(), wts[-40:])
+    assert torch.allclose(ema.double(), want, rtol=1e-5, atol=1e-9)
+    # (a budget above the window is above the prefix here: every position of a row is taken)
+    assert bool((drift == (P - 1) / 2.0).all()) and bool((info[:, 0] == 5).all())
