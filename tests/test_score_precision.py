@@ -2,6 +2,7 @@
 
 The bounds come from the same inputs on the CPU: the scores in float64, and once more with one quantity rounded as a kernel
 would.  The CPU tests show that each planted loss of bits exceeds the bound that the GPU tests then apply."""
+import numpy as np
 import pytest
 import torch
 
@@ -153,3 +154,26 @@ def test_heavy_weights_beside_the_value_gram_pass(rk, Hq, Hkv, L, W, strength): 
         args = heads_of(w, q, k, v, gram, g)
         ref = scores64(*args)
         assert distance(got[g], ref) <= weights_bound(w, plan, ref, args), f"head {g}"
+
+
+# ---- FP32 ---------------------------------------------------------------------------------
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("Hkv,d,P,W", [(1, 64, 700, 33), (2, 128, 1031, 40), (8, 64, 6001, 64)])
+def test_fp32_division_and_square_root_round_correctly(rk, Hkv, d, P, W):  # noqa: F811
+    """Queries of zeros: a row that sees n keys has weights of exactly 1 / n, and values of two whole numbers have exact
+    squared norms.  The value-norm indicator is then fl(fl(1 / n) fl(sqrt(a^2 + b^2))), bit for bit."""
+    w = workloads.small_case(Hq=Hkv, Hkv=Hkv, d=d, L=P + W, W=W, B=W + 40, dtype="f32")
+    gen = torch.Generator().manual_seed(P)
+    q = torch.zeros((Hkv, W, d))
+    k = torch.randn((Hkv, w.seq_len, d), generator=gen)
+    v = torch.zeros_like(k)
+    v[..., 3] = torch.randint(1, 2048, v.shape[:2], generator=gen).float()
+    v[..., d - 2] = torch.randint(1, 2048, v.shape[:2], generator=gen).float()
+    p = params_for(rk, w, variant=rk.RESTKV_IND_VALUE_NORM)
+    buf = rk.alloc_layer_buffers(p, q.dtype, "cuda")
+    rk.restkv_score(p, q.cuda(), k.cuda(), v.cuda(), None, buf.score, buf.workspace)
+    n = np.arange(P + 1, P + W + 1, dtype=np.float32)
+    norms = np.sqrt((v[:, :P].numpy() ** 2).sum(-1))
+    want = (np.float32(1.0) / n)[None, :, None] * norms[:, None, :]
+    assert want.dtype == np.float32 and np.array_equal(buf.score[..., :P].cpu().numpy(), want)
