@@ -177,3 +177,63 @@ def test_fp32_division_and_square_root_round_correctly(rk, Hkv, d, P, W):  # noq
     norms = np.sqrt((v[:, :P].numpy() ** 2).sum(-1))
     want = (np.float32(1.0) / n)[None, :, None] * norms[:, None, :]
     assert want.dtype == np.float32 and np.array_equal(buf.score[..., :P].cpu().numpy(), want)
+
+
+def planes(x, n):
+    """x as the sum of n bf16 numbers, each the nearest to what the others have left."""
+    out, rest = [], x.float()
+    for _ in range(n):
+        h = rest.bfloat16().float()
+        out.append(h.double())
+        rest = rest - h
+    return out
+
+
+def plane_dot(n=3, without=()):
+    """Products of values in planes: those of planes i and j with i + j < 3 (high, middle, low), less the ones in `without`."""
+    def f(a, b):
+        pa, pb = planes(a, n), planes(b, n)
+        return sum(pa[i] @ pb[j].T for i in range(n) for j in range(n) if i + j < 3 and (i, j) not in without)
+    return f
+
+
+# plain and clustered logits, groups of one and several heads, both head dimensions; one and several key splits
+FP32_LAYERS = [(1, 1, 64, 300, 5, 0.0), (4, 1, 128, 1500, 20, 0.5), (4, 2, 64, 2100, 33, 0.5), (2, 2, 128, 2100, 16, 0.0), (14, 2, 128, 1000, 9, 0.0)]
+
+
+def fp32_layer(Hq, Hkv, d, L, W, strength):
+    w = workloads.small_case(Hq=Hq, Hkv=Hkv, d=d, L=L, W=W, B=W + 60, dtype="f32", D=2 * d, seed=37)
+    gen = torch.Generator().manual_seed(41)
+    q, k, v = workloads.make_qkv(w)
+    f = torch.randn((Hkv, 16, d), generator=gen) * 0.25 * strength
+    k += torch.randn((Hkv, L, 16), generator=gen) @ f
+    q += torch.randn((Hq, W, 16), generator=gen) @ f.repeat_interleave(w.group, dim=0)
+    return w, q, k, v, workloads.make_wo(w)
+
+
+def fp32_bound(w, ref, args):
+    """Twice what products in float32 alone give (torch's, on the CPU), and 3e-7, five roundings of 2^-24, for the exponential, the quotient, the
+    root and the sums outside of the products."""
+    return 2.0 * distance(scores64(*args, dot=lambda a, b: (a.float() @ b.float().T).double()), ref) + 3e-7
+
+
+@pytest.mark.parametrize("layer", FP32_LAYERS)
+def test_planes_with_any_part_missing_would_exceed_the_bound(layer):
+    w, q, k, v, wo = fp32_layer(*layer)
+    args = heads_of(w, q, k, v, gram_of(w, wo).float(), 0)
+    ref = scores64(*args)
+    bound = fp32_bound(w, ref, args)
+    assert distance(scores64(*args, dot=plane_dot()), ref) < 0.2 * bound
+    for lost in (dict(n=2), dict(without={(0, 2)}), dict(without={(2, 0)}), dict(without={(1, 1)}), dict(without={(1, 0)})):
+        assert distance(scores64(*args, dot=plane_dot(**lost)), ref) > 1.5 * bound, lost
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("layer", FP32_LAYERS)
+def test_fp32_scores_are_as_exact_as_fp32_products(rk, layer):  # noqa: F811
+    w, q, k, v, wo = fp32_layer(*layer)
+    got, gram = gpu_scores(rk, w, q, k, v, wo)
+    for g in range(w.n_kv_heads):
+        args = heads_of(w, q, k, v, gram, g)
+        ref = scores64(*args)
+        assert distance(got[g], ref) <= fp32_bound(w, ref, args), f"head {g}"
