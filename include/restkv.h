@@ -136,6 +136,11 @@ int restkv_prepare_wo(const restkv_params* p, const float* w_o, int64_t d_model,
  * three terms cancel (v_n W_O within a few 1e-3 of z W_O, relative to their norms) the rounding
  * residue of that sum enters by its magnitude (matrix-core kernels) or clamped at zero (FP32
  * kernels): the result then is a small non-negative number where the exact one is near zero.
+ * The kernels for float32 inputs form their products from three bf16 parts of each value, to
+ * the accuracy of FP32 products.  Inputs may be any FP32 values: what bf16 parts do not hold
+ * (infinities, magnitudes near either end of the range) is found on the way and goes through
+ * the FP32 instruction, which costs the part concerned (32 keys of a head, or a key split in the attention
+ * pass) two to three times the time.  A key whose logits are -inf, as of a row of -FLT_MAX, has weight and score 0.
  */
 int restkv_score(const restkv_params* p, const void* q, const void* k, const void* v,
                  const float* gram, float* score, void* workspace, size_t workspace_bytes,
@@ -274,7 +279,7 @@ int restkv_stream_reference(const void* src, size_t read_bytes, void* dst, size_
 
 /*
  * Debug aid: with on != 0 restkv_score runs bf16 inputs through the kernels for float32 inputs
- * (same stages, every product in FP32 on the matrix cores).  Process-wide.
+ * (same stages, products as exact as FP32 ones).  Process-wide.
  */
 int restkv_debug_force_fp32(int on);
 

@@ -2,6 +2,8 @@
 // that merges the key splits of the attention pass into per-query statistics.
 #pragma once
 
+#include <type_traits>
+
 #include "common.hpp"
 
 namespace restkv {
@@ -42,7 +44,7 @@ __device__ __forceinline__ void dma_1k(const void* base, uint32_t voff, void* ld
 
 // ---- planes -------------------------------------------------------------------
 // FP32 values as bf16 planes: x = h + m + l, h the bf16 nearest to x, m the nearest to what is left, l the rest
-// (exact: 8 + 8 + 8 bits).  A bf16 value has one plane.
+// (exact, 8 + 8 + 8 bits, where PlaneRange says so).  A bf16 value has one plane.
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
@@ -87,9 +89,30 @@ __device__ __forceinline__ Op<NP> split8(float4 a, float4 b) {
   return split8<NP>(x);
 }
 
+// Planes give products as the FP32 instruction does between values of which one side (q rows, u rows, Gram entries) lies in this
+// range: groups of eight whose largest lies in (2^-40, 2^60), or of zeros.  What the other side's l plane loses below the bf16
+// subnormals is then below 2^-73, and products of planes are normal numbers.  A value beyond the bf16 range, or an
+// infinity, leaves inf - inf in its planes (and in its neighbour's, 0 * inf in the two-term product): every product with it is NaN.
+// Whoever finds a value out of range, or such a sum, takes the FP32 instruction.
+struct PlaneRange {
+  uint32_t worst = 0u;                  // in halves: largest upper 16 bits of the groups' largest magnitudes, and of their negatives
+  __device__ __forceinline__ void take(float4 a, float4 b) {
+    float m = a.x;
+    asm("v_max3_f32 %0, |%1|, |%2|, |%0|" : "+v"(m) : "v"(a.y), "v"(a.z));
+    asm("v_max3_f32 %0, |%1|, |%2|, %0" : "+v"(m) : "v"(a.w), "v"(b.x));
+    asm("v_max3_f32 %0, |%1|, |%2|, %0" : "+v"(m) : "v"(b.y), "v"(b.z));
+    asm("v_max_f32_e64 %0, |%1|, %0" : "+v"(m) : "v"(b.w));
+    const uint32_t u = __float_as_uint(m), both = __builtin_amdgcn_perm(u, 0u - u, 0x07060302u);
+    asm("v_pk_max_u16 %0, %0, %1" : "+v"(worst) : "v"(both));
+  }
+  __device__ __forceinline__ bool out() const { return worst >= 0x5D800000u || (worst & 0xFFFFu) >= 0xD480u; }
+};
+
 // Rows of a head as the FP32 score pass takes them, an item per 32 window positions of a query head and kind (q, u):
 // the planes in operand order ([plane][d/16][lane half][32 rows][8] bf16, so that an operand register is one 1 KiB
-// run), then the rows' statistics ([32][4] f32; q: maximum, denominator; u: zz, champion, its score).
+// run), then the rows' statistics ([32][4] f32; q: maximum, denominator; u: zz, champion, its score), the last of which is
+// 1.0 for a row out of the planes' range, whose values are there in FP32: of eight the first four in the place of their
+// h plane, the others in that of m.
 constexpr int row_item(int d) { return (3 * d / 16 + 1) * 1024; }
 inline __host__ __device__ int row_items(int W) { return (W + 31) / 32; }
 
@@ -473,22 +496,42 @@ __global__ __launch_bounds__(4 * D, 4) void k_attn_combine(Prob pb, const T* __r
     }
   } else {
     // planes of q and u (see row_item)
-    for (int x = tid; x < RQ * (D / 8); x += NT) {
-      const int r = x / (D / 8), c8 = x % (D / 8), i = i0 + r;
-      if (i >= pb.W) continue;
-      const T* qp = q + (int64_t)h * pb.q_sh + (int64_t)i * pb.q_st + 8 * c8;
+    constexpr int LPR = D / 8;                             // lanes of a row
+    for (int x = tid; x < RQ * LPR; x += NT) {
+      const int r = x / LPR, c8 = x % LPR, i = i0 + r;
+      const bool there = i < pb.W;
+      const T* qp = q + (int64_t)h * pb.q_sh + (int64_t)min(i, pb.W - 1) * pb.q_st + 8 * c8;
       const f32x4_t qa = quad_of(qp), qb = quad_of(qp + 4);
-      const float qv[8] = {qa[0], qa[1], qa[2], qa[3], qb[0], qb[1], qb[2], qb[3]};
-      float uv[8];
+      const f32x4_t ua = *(const f32x4_t*)&xs[UB + r][8 * c8], ub = *(const f32x4_t*)&xs[UB + r][8 * c8 + 4];
+      auto put = [&](int which, const f32x4_t& va, const f32x4_t& vb, bool small, auto np) {
+        constexpr int N = decltype(np)::value;
+        const float4 a = make_float4(va[0], va[1], va[2], va[3]), b = make_float4(vb[0], vb[1], vb[2], vb[3]);
+        PlaneRange in;
+        in.take(a, b);
+        // (a bf16 row is its own plane, whatever it holds; the lanes of a row are neighbours)
+        const unsigned long long mine = ((1ull << LPR) - 1ull) << (l & ~(LPR - 1));
+        const bool raw = N > 1 && (__ballot(in.out() || small) & mine) != 0ull;
+        if (!there) return;
+        char* const at = item_of(i, which) + c8 * 512 + (i & 31) * 16;
+        const Op<N> o8 = split8<N>(a, b);
+        if (raw) {
+          *(float4*)at = a;
+          *(float4*)(at + (D / 16) * 1024) = b;
+        } else {
 #pragma unroll
-      for (int e = 0; e < 8; ++e) uv[e] = xs[UB + r][8 * c8 + e];
-      const Op<planes_of<T>> qo = split8<planes_of<T>>(qv);
-      const Op<3> uo = split8<3>(uv);
-      const int at = c8 * 512 + (i & 31) * 16;
+          for (int p = 0; p < N; ++p) *(uint4*)(at + p * (D / 16) * 1024) = o8.p[p];
+        }
+        if (c8 == 0) *stat(i, which, 3) = raw ? 1.f : 0.f;
+      };
+      put(0, qa, qb, false, std::integral_constant<int, planes_of<T>>{});
+      // (a row whose u.v the score pass sets against a zz so much smaller than u that values' low planes count)
+      float um = 0.f;
 #pragma unroll
-      for (int p = 0; p < planes_of<T>; ++p) *(uint4*)(item_of(i, 0) + p * (D / 16) * 1024 + at) = qo.p[p];
+      for (int e = 0; e < 4; ++e) um = fmaxf(um, fmaxf(fabsf(ua[e]), fabsf(ub[e])));
+      float zz = 0.f;
 #pragma unroll
-      for (int p = 0; p < 3; ++p) *(uint4*)(item_of(i, 1) + p * (D / 16) * 1024 + at) = uo.p[p];
+      for (int k = 0; k < NWV; ++k) zz += red[k][r][0];
+      put(1, ua, ub, fabsf(zz) < 0x1p-90f * um, std::integral_constant<int, 3>{});
     }
   }
 }

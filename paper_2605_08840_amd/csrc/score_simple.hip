@@ -3,14 +3,17 @@
 //
 // The same four stages and scratch layout as the bf16 path.  Every product of FP32 values runs on
 // v_mfma_f32_32x32x16_bf16 with both sides cut into planes: x = h + m + l, each a bf16 (h the nearest
-// to x, m the nearest to what is left, l the rest, exact: 8 + 8 + 8 bits), and x y as the six products
+// to x, m the nearest to what is left, l the rest: 8 + 8 + 8 bits), and x y as the six products
 // h h, h m, m h, m m, h l, l h with FP32 accumulation; what is dropped (m l, l m, l l) is below
 // 2^-25 |x y|, less than the rounding of one FP32 addition.  Six bf16 instructions of 32 cycles take
 // 16 K indices, eight v_mfma_f32_32x32x2_f32 of 64 cycles take the same: 2.7 times the rate.  A bf16
-// input has one plane (it is exact), so its products with FP32 values are three.  Scores are as far from 64 bits as
-// with FP32 products or nearer (8k tokens: 2.4e-7 against 2.9e-7, 2-norm; sixteen other shapes 3 to 30 % nearer).
-// 8k tokens, 32/8 heads of 128, window 32: attention pass 52 -> 38 us, value-Gram pass 54 -> 34, score pass
-// 58 -> 40; score and smoothing 179 -> 131 us.  What bounds them now: per 32 keys a wavefront has 96 to 120 MFMAs
+// input has one plane (it is exact), so its products with FP32 values are three.  Scores are nearer to 64 bits than
+// with FP32 products: 0.81 of the distance (2-norm, mean of 70 shapes; with sinks, where a few entries carry the
+// norm, 0.79 to 0.90 over 60 seeds of five shapes).
+// Planes hold values of ordinary size (PlaneRange).  Where operands are not, each kernel notices at the end of its work, by
+// sums that are not finite or by the range of q, u and Gram entries, and does that part again on the FP32 instruction.
+// 8k tokens, 32/8 heads of 128, window 32, against kernels of FP32 products: attention pass 52 -> 39 us, value-Gram pass
+// 54 -> 35, score pass 58 -> 42; score and smoothing 177 -> 132 us.  What bounds them now: per 32 keys a wavefront has 96 to 120 MFMAs
 // (3.1k to 3.8k cycles) and 200 to 350 vector instructions that cut values into planes, and both wavefronts of a
 // SIMD are in the same phase most of the time.
 //
@@ -38,6 +41,20 @@ typedef short s16x8 __attribute__((ext_vector_type(8)));
 constexpr int KB = 32;      // keys per block (one side of an MFMA)
 constexpr float LOG2E = 1.4426950408889634f;
 constexpr float RESCALE_TH = 8.0f;  // log2 units a joining logit may run ahead of the reference
+
+// the FP32 instruction, for what planes do not hold (PlaneRange): a lane has ONE K index, chosen by its half
+#define MFMA32(a, b, c) __builtin_amdgcn_mfma_f32_32x32x2f32((a), (b), (c), 0, 0, 0)
+__device__ __forceinline__ void mul4(f32x16& acc, float4 a, float4 b) {
+  acc = MFMA32(a.x, b.x, acc);
+  acc = MFMA32(a.y, b.y, acc);
+  acc = MFMA32(a.z, b.z, acc);
+  acc = MFMA32(a.w, b.w, acc);
+}
+
+// acc + registers 4 jq .. of a block times four values
+__device__ __forceinline__ float dot4(const f32x16& y, int jq, float4 x, float acc) {
+  return fmaf(y[4 * jq + 3], x.w, fmaf(y[4 * jq + 2], x.z, fmaf(y[4 * jq + 1], x.y, fmaf(y[4 * jq], x.x, acc))));
+}
 
 // Wait states between the last MFMA on a block and the first read of its result, spelled out: where
 // branches lie in between, hipcc 7.2 inserts too few on some path, and the last registers of the block
@@ -205,23 +222,27 @@ __global__ __launch_bounds__(NW * 64, NW == 2 ? 1 : 2) void k_attn_f32(Prob pb, 
   const int kbeg = s * kps, kend = min(pb.L, kbeg + kps);
   const int nblk = kend > kbeg ? (kend - kbeg + KB - 1) / KB : 0;
 
+  __shared__ int beyond[NW];            // a wavefront has found that planes do not hold a value of this split or of its rows
+  bool out;
   Op<NP> qf[D / 16];
   {
+    PlaneRange in;
     const T* qp = q + (int64_t)(g * pb.G + hl) * pb.q_sh + (int64_t)i * pb.q_st + 8 * hf;
 #pragma unroll
-    for (int a = 0; a < D / 16; ++a) qf[a] = split8<NP>(load4<VEC>(qp + 16 * a), load4<VEC>(qp + 16 * a + 4));
+    for (int a = 0; a < D / 16; ++a) {
+      const float4 x = load4<VEC>(qp + 16 * a), y = load4<VEC>(qp + 16 * a + 4);
+      qf[a] = split8<NP>(x, y);
+      in.take(x, y);
+    }
+    out = __ballot(in.out()) != 0ull;
   }
   // row and column of the 8 bytes that this lane contributes to a transposing read
   const int s16 = l & 15, vrow = 4 * hf + (s16 >> 2), vcol = 16 * ((l >> 4) & 1) + 4 * (s16 & 3);
   const float c2 = pb.scale * LOG2E;
-  float mall = -INFINITY, mref = -INFINITY, mx = -INFINITY, lsum = 0.f;
-  int nx = -1;                       // key kept out of the sums, -1: none
-  int ni = 0;                        // key of the largest logit (the one kept out, if any)
+  float mall, mref, mx, lsum;
+  int nx;                            // key kept out of the sums, -1: none
+  int ni;                            // key of the largest logit (the one kept out, if any)
   f32x16 oacc[CB];
-#pragma unroll
-  for (int cb = 0; cb < CB; ++cb)
-#pragma unroll
-    for (int j = 0; j < 16; ++j) oacc[cb][j] = 0.f;
 
   // moves the reference onto a logit that runs far ahead of it (also if there is none yet: 2^-inf = 0)
   auto rescale = [&](float to) {
@@ -239,121 +260,181 @@ __global__ __launch_bounds__(NW * 64, NW == 2 ? 1 : 2) void k_attn_f32(Prob pb, 
     const int k0 = kbeg + t * KB;
     sg.template fetch<VEC>(base + (int64_t)k0 * pb.kv_st, pb.kv_st, kend - k0);
   };
-  if (nblk > 0) {
-    fetch(kg, 0);
-    const Stage<D, NW * 64> sk = sg;
-    fetch(vg, 0);
-    sk.store(Ks);
-    sg.store(Vs);
-    __syncthreads();
-  }
-  for (int t = 0; t < nblk; ++t) {
-    const int k0 = kbeg + t * KB;
-    if (t + 1 < nblk) fetch(kg, t + 1);
-    f32x16 sacc;
+  // the split in planes, or (raw) every product on the FP32 instruction with operands straight from memory
+  auto walk = [&](auto raw) {
+    constexpr bool RAW = decltype(raw)::value;
+    mall = mref = mx = -INFINITY;
+    lsum = 0.f;
+    nx = -1;
+    ni = 0;
 #pragma unroll
-    for (int j = 0; j < 16; ++j) sacc[j] = 0.f;
-    contract<NP, NP, D / 16>([&](int) -> f32x16& { return sacc; }, [&](int a, int p) { return Ks.cols(rr, hf, a, p); }, [&](int a) { return qf[a]; });
-    __syncthreads();                   // the K planes have been read, the V planes of this block are complete
-    if (t + 1 < nblk) {
-      sg.store(Ks);
-      fetch(vg, t + 1);
+    for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+      for (int j = 0; j < 16; ++j) oacc[cb][j] = 0.f;
+    if (!RAW && nblk > 0) {
+      fetch(kg, 0);
+      const Stage<D, NW * 64> sk = sg;
+      fetch(vg, 0);
+      sk.store(Ks);
+      sg.store(Vs);
+      __syncthreads();
     }
-    settle(sacc);
-    if (k0 + KB > kend || (pb.causal && k0 + KB - 1 > pb.P)) {
+    for (int t = 0; t < nblk; ++t) {
+      const int k0 = kbeg + t * KB;
+      f32x16 sacc;
 #pragma unroll
-      for (int j = 0; j < 16; ++j) {
-        const int n = k0 + cidx(j, hf);
-        if (n >= kend || n > vis_last) sacc[j] = -INFINITY;
+      for (int j = 0; j < 16; ++j) sacc[j] = 0.f;
+      if constexpr (RAW) {
+        int r2 = r;
+        asm volatile("" : "+v"(r2));     // (formed here, not kept in registers through the walk in planes)
+        const T* qr = q + (int64_t)(g * pb.G + (valid ? r2 / pb.W : 0)) * pb.q_sh + (int64_t)(valid ? r2 % pb.W : 0) * pb.q_st;
+        const T* kr = kg + (int64_t)min(k0 + rr, kend - 1) * pb.kv_st + 4 * hf;
+#pragma unroll 4
+        for (int a = 0; a < D; a += 8) mul4(sacc, load4<VEC>(kr + a), load4<VEC>(qr + 4 * hf + a));
+      } else {
+        if (t + 1 < nblk) fetch(kg, t + 1);
+        contract<NP, NP, D / 16>([&](int) -> f32x16& { return sacc; }, [&](int a, int p) { return Ks.cols(rr, hf, a, p); }, [&](int a) { return qf[a]; });
+        __syncthreads();                 // the K planes have been read, the V planes of this block are complete
+        if (t + 1 < nblk) {
+          sg.store(Ks);
+          fetch(vg, t + 1);
+        }
       }
-    }
-    float tm = sacc[0];
-#pragma unroll
-    for (int j = 1; j < 16; ++j) tm = fmaxf(tm, sacc[j]);
-    tm = half_max(tm);
-    // The reference of the exponentials is a logit that is part of the sums; it moves when a
-    // joining logit runs RESCALE_TH ahead of it.  A key is kept out when it is the largest so far
-    // and holds more than half of the mass including its own block's (what a key that ends with
-    // more than half of the total always does), and only as long as it is the largest.
-    const bool newmax = tm > mall;
-    mall = fmaxf(mall, tm);
-    float tinc = tm;                   // largest logit of the block that joins the sums
-    if (__ballot(newmax) != 0ull) {
-      int cand = 0x7FFFFFFF;
-#pragma unroll
-      for (int j = 0; j < 16; ++j)
-        if (sacc[j] == tm) cand = min(cand, k0 + cidx(j, hf));
-      cand = half_min(cand);
-      ni = newmax ? cand : ni;
-      // (this lane's share of the sum alone outweighs most candidates)
-      bool dominant = newmax && tm > -INFINITY && lsum < 1.0002f * __builtin_amdgcn_exp2f((tm - mref) * c2);
-      if (__ballot(dominant) != 0ull) {
-        // mass without the candidate, relative to the candidate itself
-        float rest = lsum * __builtin_amdgcn_exp2f((mref - tm) * c2);    // (empty sums: 0 * 0)
-#pragma unroll
-        for (int j = 0; j < 16; ++j) rest += __builtin_amdgcn_exp2f((sacc[j] - tm) * c2);
-        rest = half_sum(rest) - 1.f;
-        if (nx >= 0) rest += __builtin_amdgcn_exp2f((mx - tm) * c2);
-        // (rest carries the rounding of the sum it was taken from: a tie may go either way)
-        dominant = dominant && rest < 1.0001f;
-      }
-      const bool joins = newmax && nx >= 0;          // the key kept out so far is not the largest any more: it joins the sums
-      if (__ballot(dominant || joins) != 0ull) {
-        const int cz = dominant ? cand : -1;
-        tinc = -INFINITY;
+      settle(sacc);
+      if (k0 + KB > kend || (pb.causal && k0 + KB - 1 > pb.P)) {
 #pragma unroll
         for (int j = 0; j < 16; ++j) {
-          sacc[j] = k0 + cidx(j, hf) == cz ? -INFINITY : sacc[j];
-          tinc = fmaxf(tinc, sacc[j]);
+          const int n = k0 + cidx(j, hf);
+          if (n >= kend || n > vis_last) sacc[j] = -INFINITY;
         }
-        tinc = half_max(tinc);
-        if (joins) tinc = fmaxf(tinc, mx);
-        rescale(tinc);
-        if (joins) {
-          const float w = __builtin_amdgcn_exp2f((mx - mref) * c2);
-          if (hf == 0) lsum += w;
-          const T* vr = vg + (int64_t)nx * pb.kv_st + 4 * hf;
+      }
+      float tm = sacc[0];
 #pragma unroll
-          for (int cb = 0; cb < CB; ++cb)
+      for (int j = 1; j < 16; ++j) tm = fmaxf(tm, sacc[j]);
+      tm = half_max(tm);
+      // The reference of the exponentials is a logit that is part of the sums; it moves when a
+      // joining logit runs RESCALE_TH ahead of it.  A key is kept out when it is the largest so far
+      // and holds more than half of the mass including its own block's (what a key that ends with
+      // more than half of the total always does), and only as long as it is the largest.
+      const bool newmax = tm > mall;
+      mall = fmaxf(mall, tm);
+      float tinc = tm;                   // largest logit of the block that joins the sums
+      if (__ballot(newmax) != 0ull) {
+        int cand = 0x7FFFFFFF;
 #pragma unroll
-            for (int jq = 0; jq < 4; ++jq) {
-              const float4 x = load4<VEC>(vr + 32 * cb + 8 * jq);
-              oacc[cb][4 * jq + 0] = fmaf(w, x.x, oacc[cb][4 * jq + 0]);
-              oacc[cb][4 * jq + 1] = fmaf(w, x.y, oacc[cb][4 * jq + 1]);
-              oacc[cb][4 * jq + 2] = fmaf(w, x.z, oacc[cb][4 * jq + 2]);
-              oacc[cb][4 * jq + 3] = fmaf(w, x.w, oacc[cb][4 * jq + 3]);
-            }
+        for (int j = 0; j < 16; ++j)
+          if (sacc[j] == tm) cand = min(cand, k0 + cidx(j, hf));
+        cand = half_min(cand);
+        ni = newmax ? cand : ni;
+        // (this lane's share of the sum alone outweighs most candidates)
+        bool dominant = newmax && tm > -INFINITY && lsum < 1.0002f * __builtin_amdgcn_exp2f((tm - mref) * c2);
+        if (__ballot(dominant) != 0ull) {
+          // mass without the candidate, relative to the candidate itself
+          float rest = lsum * __builtin_amdgcn_exp2f((mref - tm) * c2);    // (empty sums: 0 * 0)
+#pragma unroll
+          for (int j = 0; j < 16; ++j) rest += __builtin_amdgcn_exp2f((sacc[j] - tm) * c2);
+          rest = half_sum(rest) - 1.f;
+          if (nx >= 0) rest += __builtin_amdgcn_exp2f((mx - tm) * c2);
+          // (rest carries the rounding of the sum it was taken from: a tie may go either way)
+          dominant = dominant && rest < 1.0001f;
         }
-        if (dominant || joins) {
-          mx = tm;
-          nx = dominant ? cand : -1;
+        const bool joins = newmax && nx >= 0;          // the key kept out so far is not the largest any more: it joins the sums
+        if (__ballot(dominant || joins) != 0ull) {
+          const int cz = dominant ? cand : -1;
+          tinc = -INFINITY;
+#pragma unroll
+          for (int j = 0; j < 16; ++j) {
+            sacc[j] = k0 + cidx(j, hf) == cz ? -INFINITY : sacc[j];
+            tinc = fmaxf(tinc, sacc[j]);
+          }
+          tinc = half_max(tinc);
+          if (joins) tinc = fmaxf(tinc, mx);
+          rescale(tinc);
+          if (joins) {
+            const float w = __builtin_amdgcn_exp2f((mx - mref) * c2);
+            if (hf == 0) lsum += w;
+            const T* vr = vg + (int64_t)nx * pb.kv_st + 4 * hf;
+#pragma unroll
+            for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+              for (int jq = 0; jq < 4; ++jq) {
+                const float4 x = load4<VEC>(vr + 32 * cb + 8 * jq);
+                oacc[cb][4 * jq + 0] = fmaf(w, x.x, oacc[cb][4 * jq + 0]);
+                oacc[cb][4 * jq + 1] = fmaf(w, x.y, oacc[cb][4 * jq + 1]);
+                oacc[cb][4 * jq + 2] = fmaf(w, x.z, oacc[cb][4 * jq + 2]);
+                oacc[cb][4 * jq + 3] = fmaf(w, x.w, oacc[cb][4 * jq + 3]);
+              }
+          }
+          if (dominant || joins) {
+            mx = tm;
+            nx = dominant ? cand : -1;
+          }
+        }
+      }
+      if (__ballot((tinc - mref) * c2 > RESCALE_TH) != 0ull) rescale(tinc);
+      // weights relative to the reference (a row that has none yet has nothing to add).  The instruction
+      // makes 0 of weights below 2^-126: the sums hold the reference's own weight, 1, and do not notice.
+      const float nm = mref == -INFINITY ? 0.f : -mref * c2;
+#pragma unroll
+      for (int j = 0; j < 16; ++j) sacc[j] = __builtin_amdgcn_exp2f(fmaf(sacc[j], c2, nm));
+      lsum += ((sacc[0] + sacc[1]) + (sacc[2] + sacc[3])) + ((sacc[4] + sacc[5]) + (sacc[6] + sacc[7])) +
+              (((sacc[8] + sacc[9]) + (sacc[10] + sacc[11])) + ((sacc[12] + sacc[13]) + (sacc[14] + sacc[15])));
+      if constexpr (RAW) {
+#pragma unroll
+        for (int j = 0; j < 16; ++j) {
+          const int n = k0 + cidx(j, hf);
+          const T* vr = vg + (int64_t)min(n, kend - 1) * pb.kv_st + rr;
+#pragma unroll
+          for (int cb = 0; cb < CB; ++cb) {
+            const float x = to_float(vr[32 * cb]);
+            oacc[cb] = MFMA32(n < kend ? x : 0.f, sacc[j], oacc[cb]);
+          }
+          __builtin_amdgcn_sched_barrier(0);
+        }
+#pragma unroll
+        for (int cb = 0; cb < CB; ++cb) settle(oacc[cb]);
+      } else {
+#pragma unroll
+        for (int grp = 0; grp < 2; ++grp) {
+          float pe[8];
+#pragma unroll
+          for (int e = 0; e < 8; ++e) pe[e] = sacc[8 * grp + e];
+          const Op<3> pv = split8<3>(pe);
+          contract<NP, 3, CB>([&](int cb) -> f32x16& { return oacc[cb]; }, [&](int cb, int p) { return Vs.rows(grp, cb, vrow, vcol, p); },
+                              [&](int) { return pv; });
+        }
+        if (t + 1 < nblk) {
+          __syncthreads();               // the V planes have been read, the K planes of the next block are complete
+          sg.store(Vs);
         }
       }
     }
-    if (__ballot((tinc - mref) * c2 > RESCALE_TH) != 0ull) rescale(tinc);
-    // weights relative to the reference (a row that has none yet has nothing to add).  The instruction
-    // makes 0 of weights below 2^-126: the sums hold the reference's own weight, 1, and do not notice.
-    const float nm = mref == -INFINITY ? 0.f : -mref * c2;
 #pragma unroll
-    for (int j = 0; j < 16; ++j) sacc[j] = __builtin_amdgcn_exp2f(fmaf(sacc[j], c2, nm));
-    lsum += ((sacc[0] + sacc[1]) + (sacc[2] + sacc[3])) + ((sacc[4] + sacc[5]) + (sacc[6] + sacc[7])) +
-            (((sacc[8] + sacc[9]) + (sacc[10] + sacc[11])) + ((sacc[12] + sacc[13]) + (sacc[14] + sacc[15])));
+    for (int cb = 0; cb < CB; ++cb) settle(oacc[cb]);
+  };
+  walk(std::false_type{});
+  if (nblk > 0) {
+    // With queries in the planes' range, a key or value beyond it has made a sum NaN or infinite (a key whose logits are all
+    // -inf: no largest logit where there is a visible key), and values that are all so small that their low planes are
+    // lost (2^-133 each) have made sums below 2^-90 of the weights'.
+    float big = 0.f, t = lsum;
 #pragma unroll
-    for (int grp = 0; grp < 2; ++grp) {
-      float pe[8];
+    for (int cb = 0; cb < CB; ++cb)
 #pragma unroll
-      for (int e = 0; e < 8; ++e) pe[e] = sacc[8 * grp + e];
-      const Op<3> pv = split8<3>(pe);
-      contract<NP, 3, CB>([&](int cb) -> f32x16& { return oacc[cb]; }, [&](int cb, int p) { return Vs.rows(grp, cb, vrow, vcol, p); },
-                          [&](int) { return pv; });
-    }
-    if (t + 1 < nblk) {
-      __syncthreads();                 // the V planes have been read, the K planes of the next block are complete
-      sg.store(Vs);
-    }
+      for (int j = 0; j < 16; j += 2) {
+        big = fmaxf(big, fmaxf(fabsf(oacc[cb][j]), fabsf(oacc[cb][j + 1])));
+        t += oacc[cb][j] * oacc[cb][j + 1];
+      }
+    big = half_max(big);
+    out |= __ballot(!(fabsf(t) < INFINITY) || (big != 0.f && big < 0x1p-90f * lsum) ||
+                    (valid && mall == -INFINITY && kbeg <= vis_last)) != 0ull;
+    beyond[wv] = out;
+    __syncthreads();
+    int any = 0;
+#pragma unroll
+    for (int k = 0; k < NW; ++k) any |= beyond[k];
+    if (__builtin_expect(__builtin_amdgcn_readfirstlane(any), 0)) walk(std::true_type{});
   }
-#pragma unroll
-  for (int cb = 0; cb < CB; ++cb) settle(oacc[cb]);
   const float ltot = half_sum(lsum);
   if (valid) {
     const int64_t po = ((int64_t)g * pb.R + r) * S + s;
@@ -385,6 +466,7 @@ __global__ __launch_bounds__(256, 2) void k_vv_f32(Prob pb, const T* __restrict_
   constexpr int CB = D / 32, KS = D / 16, NP = planes_of<T>;
   constexpr int NB = CB * (CB + 1);                    // pieces on or above the diagonal: KS - 2 cb of row block cb
   __shared__ __attribute__((aligned(16))) uint4 Ts[NB][3][64];
+  __shared__ int beyond[4];                            // a wavefront has found that planes do not hold an entry of T
   const int h = blockIdx.y, g = h / pb.G;
   const int l = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), rr = l & 31, hf = l >> 5;
   const T* vg = v + (int64_t)g * pb.kv_sh;
@@ -400,6 +482,7 @@ __global__ __launch_bounds__(256, 2) void k_vv_f32(Prob pb, const T* __restrict_
   };
   int b = blockIdx.x * 4 + wv;
   if (b < nb) fetch(b);
+  PlaneRange seen;                                     // of the Gram entries this thread has cut into planes
   // (all loads first: one round trip)
   constexpr int NPC = (NB + 3) / 4;                    // pieces per wavefront
   const float* Mh = gram + (int64_t)h * D * D;
@@ -426,10 +509,13 @@ __global__ __launch_bounds__(256, 2) void k_vv_f32(Prob pb, const T* __restrict_
       x[e] = c > i ? 2.f * f : (c == i ? f : 0.f);
     }
     const Op<3> t = split8<3>(x);
+    seen.take(make_float4(x[0], x[1], x[2], x[3]), make_float4(x[4], x[5], x[6], x[7]));
 #pragma unroll
     for (int p = 0; p < 3; ++p) Ts[wv + 4 * j][p][l] = t.p[p];
   }
+  beyond[wv] = __ballot(seen.out()) != 0ull;
   __syncthreads();
+  bool raw = __builtin_amdgcn_readfirstlane(beyond[0] | beyond[1] | beyond[2] | beyond[3]);
   for (; b < nb; b += 4 * gridDim.x) {
     Op<NP> vo[KS];
 #pragma unroll
@@ -449,17 +535,40 @@ __global__ __launch_bounds__(256, 2) void k_vv_f32(Prob pb, const T* __restrict_
       }
       settle(y);
 #pragma unroll
-      for (int jq = 0; jq < 4; ++jq) {
-        const float4 x = vf[2 * cb + (jq >> 1)][jq & 1];
-        acc = fmaf(y[4 * jq + 0], x.x, acc);
-        acc = fmaf(y[4 * jq + 1], x.y, acc);
-        acc = fmaf(y[4 * jq + 2], x.z, acc);
-        acc = fmaf(y[4 * jq + 3], x.w, acc);
-      }
+      for (int jq = 0; jq < 4; ++jq) acc = dot4(y, jq, vf[2 * cb + (jq >> 1)][jq & 1], acc);
     }
     const int n = b * KB + rr;
+    raw |= __ballot(!(fabsf(acc) < INFINITY)) != 0ull;
     acc = half_sum(acc);
     if (b + 4 * (int)gridDim.x < nb) fetch(b + 4 * gridDim.x);
+    if (hf == 0 && n < pb.P) vv[(int64_t)h * ldv + n] = acc;
+  }
+  if (__builtin_expect(!raw, 1)) return;
+  // This wavefront's blocks once more, on the FP32 instruction with everything from memory: planes do not hold T or a value.  (A
+  // value beyond them has made a sum NaN or infinite; with T in their range one too small for them has a square below FP32.)
+#pragma unroll 1
+  for (int b = blockIdx.x * 4 + wv; b < nb; b += 4 * gridDim.x) {
+    const int n = b * KB + rr;
+    const T* vr = vg + (int64_t)min(n, pb.P - 1) * pb.kv_st + 4 * hf;
+    float acc = 0.f;
+#pragma unroll 1
+    for (int cb = 0; cb < CB; ++cb) {
+      const int i = 32 * cb + rr;
+      f32x16 y;
+#pragma unroll
+      for (int j = 0; j < 16; ++j) y[j] = 0.f;
+#pragma unroll 1
+      for (int k = 32 * cb; k < D; k += 8) {
+        const int c = k + 4 * hf;
+        const f32x4_t m = quad_of(Mh + i * D + c);
+        auto up = [&](int e) { return c + e > i ? 2.f * m[e] : (c + e == i ? m[e] : 0.f); };
+        mul4(y, make_float4(up(0), up(1), up(2), up(3)), load4<VEC>(vr + k));
+      }
+      settle(y);
+#pragma unroll
+      for (int jq = 0; jq < 4; ++jq) acc = dot4(y, jq, load4<VEC>(vr + 32 * cb + 8 * jq), acc);
+    }
+    acc = half_sum(acc);
     if (hf == 0 && n < pb.P) vv[(int64_t)h * ldv + n] = acc;
   }
 }
@@ -541,6 +650,24 @@ __global__ __launch_bounds__(NW * 64, NW == 1 ? 1 : 2) void k_score_f32(Prob pb,
   };
   auto stat = [&](int bf, int j) { return *(const float4*)&rows[bf][3 * KS * 1024 + cidx(j, hf) * 16]; };
   auto row_op = [&](int bf, int a, int p) { return *(const uint4*)&rows[bf][(p * KS + a) * 1024 + l * 16]; };
+  // row rr: in FP32 if it is out of the planes' range; four of its values, those from 8 a + 4 hf on
+  auto raw_row = [&](int bf) { return *(const float*)&rows[bf][3 * KS * 1024 + rr * 16 + 12] != 0.f; };
+  auto row_quad = [&](int bf, int a, bool raw, auto np) {
+    const char* const at = &rows[bf][(a >> 1) * 1024 + (a & 1) * 512 + rr * 16];
+    const float4 x = *(const float4*)(at + hf * KS * 1024);
+    f32x4_t s = quad_of((const bf16_t*)(at + 8 * hf));
+#pragma unroll
+    for (int p = 1; p < decltype(np)::value; ++p) s += quad_of((const bf16_t*)(at + p * KS * 1024 + 8 * hf));
+    return raw ? x : make_float4(s[0], s[1], s[2], s[3]);
+  };
+  // acc += rows x keys on the FP32 instruction: a key's row from memory
+  auto raw_product = [&](f32x16& acc, int bf, const T* key, auto np) {
+    const bool raw = raw_row(bf);
+#pragma unroll
+    for (int j = 0; j < 16; ++j) acc[j] = 0.f;
+#pragma unroll 1
+    for (int a = 0; a < D / 8; ++a) mul4(acc, row_quad(bf, a, raw, np), load4<VEC>(key - 4 * hf + 8 * a));
+  };
   // what has been copied is complete, and what was read is free, after this
   auto turn = [] {
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -553,6 +680,54 @@ __global__ __launch_bounds__(NW * 64, NW == 1 ? 1 : 2) void k_score_f32(Prob pb,
     for (int a = 0; a < KS; ++a) {
       kv[a] = split8<NP>(load4<VEC>(p + 16 * a), load4<VEC>(p + 16 * a + 4));
       if (a % 4 == 3) __builtin_amdgcn_sched_barrier(0);      // (eight loads in flight)
+    }
+  };
+  // Whether planes do not hold the operands of a product: the row (known from its item), or a key or value beyond them, which
+  // has made its sums NaN or infinite.
+  auto sums_of = [&](const f32x16& acc) {
+    float t[2] = {0.f, 0.f};
+#pragma unroll
+    for (int j = 0; j < 16; j += 2) t[(j >> 1) & 1] = fmaf(acc[j], acc[j + 1], t[(j >> 1) & 1]);
+    return t[0] + t[1];
+  };
+  auto beyond = [](float t, bool raw) { return __builtin_expect(__ballot(raw || !(fabsf(t) < INFINITY)) != 0ull, 0); };
+  // logits -> A / (1 - A).  Attention weights relative to the row's maximum: the instruction makes 0 of one below 2^-126, and where
+  // a wavefront has such a weight the library call, which scales it, takes all of them (for every
+  // weight it costs the pass 3 %).
+  auto weigh = [&](f32x16& s, int bf) {
+    float low = INFINITY;
+#pragma unroll
+    for (int j = 0; j < 16; ++j) {
+      s[j] = fmaf(s[j], c2, -stat(bf, j).x);           // maximum
+      low = fminf(low, s[j]);
+    }
+    if (__ballot(low < -126.f) != 0ull) {
+#pragma unroll
+      for (int j = 0; j < 16; ++j) {
+        s[j] = exp2f(s[j]);
+        if (j % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+      }
+    } else {
+#pragma unroll
+      for (int j = 0; j < 16; ++j) s[j] = __builtin_amdgcn_exp2f(s[j]);
+    }
+#pragma unroll
+    for (int j = 0; j < 16; ++j) s[j] = quotient(s[j], fmaf(-rec, s[j], stat(bf, j).y));      // denominator
+  };
+  // cross terms -> indicators
+  auto measure = [&](f32x16& s, const f32x16& w, int bf, float vvn) {
+#pragma unroll
+    for (int jq = 0; jq < 4; ++jq) {
+      float4 r[4];                                     // zz, champion, its score
+      float x[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        r[e] = stat(bf, 4 * jq + e);
+        x[e] = fmaxf(fmaf(-2.f, s[4 * jq + e], r[e].x) + vvn, 0.f);
+      }
+      roots(x);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) s[4 * jq + e] = n == __float_as_int(r[e].y) ? r[e].z : w[4 * jq + e] * x[e];
     }
   };
   float out[16];
@@ -573,29 +748,16 @@ __global__ __launch_bounds__(NW * 64, NW == 1 ? 1 : 2) void k_score_f32(Prob pb,
       f32x16 sacc;
 #pragma unroll
       for (int j = 0; j < 16; ++j) sacc[j] = 0.f;
+      const bool raw = raw_row(bf);
       contract<NP, NP, KS>([&](int) -> f32x16& { return sacc; }, [&](int a, int p) { return row_op(bf, a, p); }, [&](int a) { return kv[a]; });
       settle(sacc);
-      // Attention weights relative to the row's maximum.  The instruction makes 0 of one below 2^-126: where
-      // a wavefront has such a weight the library call, which scales it, takes all of them (for every
-      // weight it costs the pass 3 %).
-      float low = INFINITY;
-#pragma unroll
-      for (int j = 0; j < 16; ++j) {
-        sacc[j] = fmaf(sacc[j], c2, -stat(bf, j).x);   // maximum
-        low = fminf(low, sacc[j]);
+      const float t = sums_of(sacc);
+      weigh(sacc, bf);
+      if (beyond(t, raw)) {
+        raw_product(sacc, bf, kr, std::integral_constant<int, NP>{});
+        settle(sacc);
+        weigh(sacc, bf);
       }
-      if (__ballot(low < -126.f) != 0ull) {
-#pragma unroll
-        for (int j = 0; j < 16; ++j) {
-          sacc[j] = exp2f(sacc[j]);
-          if (j % 4 == 3) __builtin_amdgcn_sched_barrier(0);
-        }
-      } else {
-#pragma unroll
-        for (int j = 0; j < 16; ++j) sacc[j] = __builtin_amdgcn_exp2f(sacc[j]);
-      }
-#pragma unroll
-      for (int j = 0; j < 16; ++j) sacc[j] = quotient(sacc[j], fmaf(-rec, sacc[j], stat(bf, j).y));      // denominator
       wt[c] = sacc;
       turn();
       bf ^= 1;
@@ -610,26 +772,18 @@ __global__ __launch_bounds__(NW * 64, NW == 1 ? 1 : 2) void k_score_f32(Prob pb,
       f32x16 cacc;
 #pragma unroll
       for (int j = 0; j < 16; ++j) cacc[j] = 0.f;
+      const bool raw = raw_row(bf);
       contract<3, NP, KS>([&](int) -> f32x16& { return cacc; }, [&](int a, int p) { return row_op(bf, a, p); }, [&](int a) { return kv[a]; });
       settle(cacc);
-#pragma unroll
-      for (int jq = 0; jq < 4; ++jq) {
-        float4 r[4];                                   // zz, champion, its score
-        float x[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          r[e] = stat(bf, 4 * jq + e);
-          x[e] = fmaxf(fmaf(-2.f, cacc[4 * jq + e], r[e].x) + vvn, 0.f);
-        }
-        roots(x);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const int j = 4 * jq + e;
-          float val = wt[c][j] * x[e];
-          val = n == __float_as_int(r[e].y) ? r[e].z : val;
-          out[j] = pb.gmax ? fmaxf(out[j], val) : out[j] + val;
-        }
+      const float t = sums_of(cacc);
+      measure(cacc, wt[c], bf, vvn);
+      if (beyond(t, raw)) {
+        raw_product(cacc, bf, vr, std::integral_constant<int, 3>{});
+        settle(cacc);
+        measure(cacc, wt[c], bf, vvn);
       }
+#pragma unroll
+      for (int j = 0; j < 16; ++j) out[j] = pb.gmax ? fmaxf(out[j], cacc[j]) : out[j] + cacc[j];
       if (!end) {
         turn();
         bf ^= 1;

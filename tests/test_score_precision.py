@@ -237,3 +237,46 @@ def test_fp32_scores_are_as_exact_as_fp32_products(rk, layer):  # noqa: F811
         args = heads_of(w, q, k, v, gram, g)
         ref = scores64(*args)
         assert distance(got[g], ref) <= fp32_bound(w, ref, args), f"head {g}"
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("d,W", [(64, 9), (128, 40)])
+@pytest.mark.parametrize("value", [float("-inf"), -torch.finfo(torch.float32).max, -3.4e38, -1e30])
+def test_fp32_keys_outside_of_the_planes(rk, d, W, value):  # noqa: F811
+    """Keys whose logits are -inf or far below every other: weight and score zero, the rest of every row as if they were
+    not there.  -FLT_MAX and -3.4e38 round to an infinite bf16."""
+    w, q, k, v, wo = fp32_layer(4, 2, d, 777, W, 0.0)
+    q[..., 5] = q[..., 5].abs() + 0.5
+    gone = [0, 31, 300, 600]
+    k[:, gone] = 0.0
+    k[:, gone, 5] = value
+    got, gram = gpu_scores(rk, w, q, k, v, wo)
+    for g in range(2):
+        args = heads_of(w, q, k.clamp_min(-1e30), v, gram, g)
+        ref = scores64(*args)
+        assert bool((got[g][:, gone] == 0).all()) and bool((ref[:, gone] == 0).all())
+        assert distance(got[g], ref) <= fp32_bound(w, ref, args), f"head {g}"
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("d,W", [(64, 9), (128, 40)])
+@pytest.mark.parametrize("q2,k2,v2,m2", [
+    (110, -110, 0, 0),          # keys whose low planes would be subnormal
+    (-112, 112, 0, 0),          # queries likewise; keys whose products with a query's high plane are of ordinary size
+    (0, 0, -114, 118),          # values, outputs and u rows; Gram entries near the end of the range
+    (0, 0, 40, -70),            # Gram entries below the range, values inside it
+    (0, 0, 61, -100),           # values above it
+])
+def test_fp32_operands_far_from_one(rk, d, W, q2, k2, v2, m2):  # noqa: F811
+    """Powers of two that leave the logits as they are and scale the scores: as exact as with operands around one."""
+    w, q, k, v, wo = fp32_layer(4, 2, d, 777, W, 0.3)
+    p = params_for(rk, w)
+    gram = gram_of(w, wo).float()
+    buf = rk.alloc_layer_buffers(p, q.dtype, "cuda")
+    up = lambda x, e: torch.ldexp(x, torch.tensor(e // 2)).ldexp(torch.tensor(e - e // 2))        # noqa: E731
+    rk.restkv_score(p, up(q, q2).cuda(), up(k, k2).cuda(), up(v, v2).cuda(), up(gram, m2).cuda(), buf.score, buf.workspace)
+    got = buf.score[..., :w.prefix].cpu().double() * 2.0 ** (-v2 - m2 / 2)
+    for g in range(2):
+        args = heads_of(w, q, k, v, gram, g)
+        ref = scores64(*args)
+        assert distance(got[g], ref) <= fp32_bound(w, ref, args), f"head {g}"
