@@ -5,6 +5,8 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "restkv.h"
 
 namespace restkv {
@@ -141,13 +143,17 @@ __device__ __forceinline__ int head_budget(const Prob& pb, int g) {
   return min(max(pb.hb[g], pb.W + 1), pb.B);
 }
 
-// Workgroup id (x fastest) -> (KV head, part of the head's work): workgroups go round the eight XCDs by their id, so the heads are
-// taken eight at a time, the head running fastest: a head's workgroups share one XCD and find in its L2 what the others
-// have fetched and what the pass before left there, and follow each other closely in time.  Fewer than eight heads (or
-// what is left of them) run fastest too: on as few XCDs as there are.  Against the parts running fastest: select, 8
-// heads, 128k 25.2 -> 23.4 us; score + smoothing, 8k FP32 130 -> 123, 64k 329 -> 318.
+// Workgroup -> (KV head, part of the head's work).  BY8, for eight heads or more: workgroups go round the eight XCDs by their number (x
+// fastest), so the heads are taken eight at a time, the head running fastest: a head's workgroups share one XCD and find in its L2 what the others
+// have fetched and what the pass before left there, and follow each other closely in time.  What is left of the heads runs
+// fastest too.  Against the parts running fastest, 8 heads: select, 128k 24.8 -> 23.4 us, score + smoothing, 8k 62.1 -> 60.3,
+// scores from statistics + smoothing, 20k 66.1 -> 60.4, 32k 139.5 -> 136.8, most others within 1 %; 16 heads, select, 100k
+// 27.9 -> 25.3.  Fewer heads have the parts running fastest: four heads on two XCDs each gain nothing, and the divisions with which every
+// workgroup then begins cost a select 0.7 us (55k 19.2 us against 19.9).
 struct HeadPart { int g, x; };
+template <bool BY8>
 __device__ __forceinline__ HeadPart head_part(const Prob& pb) {
+  if constexpr (!BY8) return {(int)blockIdx.y, (int)blockIdx.x};
   const unsigned id = blockIdx.y * gridDim.x + blockIdx.x, parts = gridDim.x, full = (unsigned)pb.Hkv & ~7u;
   if (id < full * parts) return {(int)(id / (8u * parts) * 8u + (id & 7u)), (int)((id >> 3) % parts)};
   const unsigned left = (unsigned)pb.Hkv - full, r = id - full * parts;
@@ -155,6 +161,12 @@ __device__ __forceinline__ HeadPart head_part(const Prob& pb) {
 }
 // (two dimensions, for the ids of a launch: the threads along one of them have to stay below 2^32)
 inline dim3 head_grid(const Prob& pb, int parts) { return dim3(parts, pb.Hkv); }
+// f(BY8) with the instance for this number of heads
+template <typename F>
+inline void by_heads(const Prob& pb, F f) {
+  if (pb.Hkv >= 8) f(std::true_type{});
+  else f(std::false_type{});
+}
 
 // Order-preserving map float -> uint32 (larger float <=> larger key; -0 < +0; NaNs at the ends).  Never
 // 0, which stands for "no entry" in the searches: the one value that would be (a NaN with every bit

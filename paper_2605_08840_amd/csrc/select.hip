@@ -123,11 +123,12 @@ __global__ __launch_bounds__(NT, NT == 1024 ? 4 : 1) void k_sel_row(Prob pb, con
 // flight.  Thread t then owns positions chunk * 4096 + 16 t .. + 15: the entries above the bracket
 // are counted (one count per chunk), the entries inside it leave as a 16-bit mask per thread
 // (element e at bit 15 - e).  head_grid: parts = chunks, 256 threads.
+template <bool BY8>
 __global__ __launch_bounds__(256) void k_sel_scan(Prob pb, const float* __restrict__ fin, SelPtrs w,
                                                   int nchunks, int vec) {
   __shared__ CutSmem cs;
   __shared__ uint32_t red[4];
-  const HeadPart hp = head_part(pb);
+  const HeadPart hp = head_part<BY8>(pb);
   const int g = hp.g, ch = hp.x, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const float* row = fin + (int64_t)g * pb.ld;
   const int n0 = ch * SCH + 16 * tid;
@@ -179,6 +180,7 @@ __global__ __launch_bounds__(256) void k_sel_scan(Prob pb, const float* __restri
 //     positions of each).  Window tokens and the unused tail of a smaller per-head budget are
 //     written by the first workgroup.
 // head_grid: parts = workgroups of a head, 512 threads; workgroup x owns the chunks [x cpw, (x + 1) cpw).
+template <bool BY8>
 __global__ __launch_bounds__(512) void k_sel_emit(Prob pb, const float* __restrict__ fin, SelPtrs w,
                                                   int nchunks, int cpw, int vec, int32_t* __restrict__ idx) {
   constexpr int NT = 512, NW = NT / 64, FPT = SCAP / NT;
@@ -187,7 +189,7 @@ __global__ __launch_bounds__(512) void k_sel_emit(Prob pb, const float* __restri
   __shared__ uint32_t red[2][NW];
   __shared__ uint32_t flag;
   __shared__ int cpos[SCAP];
-  const HeadPart hp = head_part(pb);
+  const HeadPart hp = head_part<BY8>(pb);
   const int g = hp.g, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const float* row = fin + (int64_t)g * pb.ld;
   const int bg = head_budget(pb, g), k = bg - pb.W;
@@ -327,9 +329,12 @@ int launch_select(const Prob& pb, const float* fin, int32_t* idx, char* ws, hipS
   }
   const int nch = (pb.P + SCH - 1) / SCH;
   const SelPtrs w = sel_ptrs(pb, ws, nullptr);
-  RK_LAUNCH(ST_SELECT, st, k_sel_scan, head_grid(pb, nch), dim3(256), 0, st, pb, fin, w, nch, vec ? 1 : 0);
   const int cpw = (nch + EMIT_WGS - 1) / EMIT_WGS;
-  RK_LAUNCH(ST_SELECT, st, k_sel_emit, head_grid(pb, (nch + cpw - 1) / cpw), dim3(512), 0, st, pb, fin, w, nch, cpw, vec ? 1 : 0, idx);
+  by_heads(pb, [&](auto by8) {
+    constexpr bool BY8 = decltype(by8)::value;
+    RK_LAUNCH(ST_SELECT, st, k_sel_scan<BY8>, head_grid(pb, nch), dim3(256), 0, st, pb, fin, w, nch, vec ? 1 : 0);
+    RK_LAUNCH(ST_SELECT, st, k_sel_emit<BY8>, head_grid(pb, (nch + cpw - 1) / cpw), dim3(512), 0, st, pb, fin, w, nch, cpw, vec ? 1 : 0, idx);
+  });
   return hip_status();
 }
 

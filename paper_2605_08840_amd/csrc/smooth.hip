@@ -21,12 +21,13 @@ constexpr int ROW_NS = 4096;        // samples per row that the bracket kernel f
 // thr[row] = {lo, hi}: the threshold lies in (lo, hi] unless the sample misled us (then the
 // finishing kernel falls back to the exact radix search).  Also clears the row's counters.
 // head_grid: parts = W, 512 threads, ROW_NS / 512 samples per thread in registers.
+template <bool BY8>
 __global__ __launch_bounds__(512) void k_sample_bracket(Prob pb, const float* __restrict__ score,
                                                         float2* __restrict__ thr,
                                                         uint32_t* __restrict__ cnt_hi,
                                                         unsigned long long* __restrict__ sum_hi) {
   __shared__ CutSmem cs;
-  const HeadPart hp = head_part(pb);
+  const HeadPart hp = head_part<BY8>(pb);
   const int i = hp.x, g = hp.g, r = g * pb.W + i;
   const float* row = score + (int64_t)r * pb.ld;
   const int k = min(head_budget(pb, g), pb.P);
@@ -82,7 +83,7 @@ __device__ __forceinline__ float temporal_weight(const Prob& pb, int i) {
 __device__ __forceinline__ int scan_position(int wbase, int l, int k) { return wbase + 256 * (k >> 2) + 4 * l + (k & 3); }
 __host__ __device__ inline int scan_waves(int P) { return (P + EW_POS - 1) / EW_POS; }
 
-template <bool VEC>
+template <bool VEC, bool BY8>
 __global__ __launch_bounds__(256) void k_ema_scan(Prob pb, const float* __restrict__ score,
                                                   float* __restrict__ ema, const float2* __restrict__ thr,
                                                   uint32_t* __restrict__ cnt_hi,
@@ -92,7 +93,7 @@ __global__ __launch_bounds__(256) void k_ema_scan(Prob pb, const float* __restri
   // among them (short prefixes: more wavefronts, more bytes in flight); their partial weighted
   // sums meet in LDS at the end.  rs = 1: a wavefront works alone, no barrier anywhere.
   __shared__ float esum[4][EW_NE][64];
-  const HeadPart hp = head_part(pb);
+  const HeadPart hp = head_part<BY8>(pb);
   const int g = hp.g, l = threadIdx.x & 63;
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);     // (a scalar for the compiler)
   const int part = wv % rs, rpp = 64 / rs;       // this wavefront's share of a block of 64 rows
@@ -238,6 +239,7 @@ __device__ inline unsigned long long row_exact_sum(const float* __restrict__ row
 // equal values in position order).  A row whose bracket missed, or that has more than
 // CAND_CAP candidates, is searched exactly (radix select over the whole row) on the spot.
 // head_grid: parts = W, 512 threads.
+template <bool BY8>
 __global__ __launch_bounds__(512) void k_row_finish(Prob pb, const float* __restrict__ score,
                                                     const uint32_t* __restrict__ cnt_hi,
                                                     const unsigned long long* __restrict__ sum_hi,
@@ -250,7 +252,7 @@ __global__ __launch_bounds__(512) void k_row_finish(Prob pb, const float* __rest
   __shared__ uint32_t wsum[SEL_NW];
   __shared__ int cpos[CAND_CAP];                 // positions of the row's candidates
   __shared__ SelectSmem sm;                      // (exact search only)
-  const HeadPart hp = head_part(pb);
+  const HeadPart hp = head_part<BY8>(pb);
   const int i = hp.x, g = hp.g, r = g * pb.W + i;
   const int k = min(head_budget(pb, g), pb.P);
   if (k >= pb.P) {
@@ -338,13 +340,13 @@ __global__ __launch_bounds__(512) void k_row_finish(Prob pb, const float* __rest
 // the others take NT positions each and add up the weighted window queries.  Three launches (sample
 // bracket, scan, finish) are latency at these sizes: 33.5 us at 8k tokens, 8 KV heads, window 32,
 // against 8.1 here; 27.4 against 4.5 us at 1k tokens, 2 heads.  head_grid: parts = nrow + ceil(P / NT).
-template <int NT, int NPT, bool VEC>
+template <int NT, int NPT, bool VEC, bool BY8>
 __global__ __launch_bounds__(NT, NT == 1024 && NPT == 16 ? 8 : 4) void k_short_rows(Prob pb, const float* __restrict__ score,
                                                                       float* __restrict__ ema,
                                                                       unsigned long long* __restrict__ rowsum, int nrow) {
   __shared__ CutSmem cs;
   __shared__ unsigned long long isum[NT / 64];
-  const HeadPart hp = head_part(pb);
+  const HeadPart hp = head_part<BY8>(pb);
   const int g = hp.g;
   if (hp.x < nrow) {
     const int r = g * pb.W + hp.x;
@@ -427,11 +429,12 @@ __device__ inline void aws_window(const Prob& pb, unsigned long long sf, unsigne
 // loads of a window offset are independent and coalesced); every workgroup derives the head's
 // window from the index sums itself.
 constexpr int BOX_PT = 4;
+template <bool BY8>
 __global__ __launch_bounds__(256) void k_box(Prob pb, const float* __restrict__ ema,
                                              const unsigned long long* __restrict__ rowsum,
                                              float* __restrict__ fin, int32_t* __restrict__ aws_info,
                                              double* __restrict__ aws_d) {
-  const HeadPart hp = head_part(pb);
+  const HeadPart hp = head_part<BY8>(pb);
   const int g = hp.g;
   __shared__ int sh_ws, sh_gamma;
   __shared__ unsigned long long sh_sum[2][4];
@@ -547,37 +550,40 @@ int launch_smooth(const Prob& pb, const float* score, float* ema, float* fin, in
   uint16_t* cmask = (uint16_t*)(ws + lay.cmask);
   float* e = ema ? ema : (float*)(ws + lay.ema);
   const bool vec = (pb.ld & 3) == 0 && (((uintptr_t)score | (uintptr_t)e) & 15u) == 0;
-  // One launch for short prefixes.  Rows above 16384 positions take a compute unit each: two rounds of
-  // them (512 rows of 32k: 37 us) lose against three launches that stream (34 us), one (132 rows of 20k:
-  // 12 us against 31) does not.
-  if (pb.P <= 16384 || (pb.P <= ROW_REG_MAX && pb.W * pb.Hkv <= n_cu())) {
-    const int nrow = pb.adaptive ? pb.W : 0;
-    with_row_block(pb.P, [&](auto nt, auto npt) {
-      constexpr int NT = decltype(nt)::value, NPT = decltype(npt)::value;
-      const dim3 gr = head_grid(pb, nrow + (pb.P + NT - 1) / NT);
-      if (vec) RK_LAUNCH(ST_EMA, st, (k_short_rows<NT, NPT, true>), gr, dim3(NT), 0, st, pb, score, e, rowsum, nrow);
-      else RK_LAUNCH(ST_EMA, st, (k_short_rows<NT, NPT, false>), gr, dim3(NT), 0, st, pb, score, e, rowsum, nrow);
-    });
-  } else {
-    if (pb.adaptive)
-      RK_LAUNCH(ST_ROWTOPK, st, k_sample_bracket, head_grid(pb, pb.W), dim3(512), 0, st, pb, score, thr,
-                cnt_hi, sum_hi);
-    // short prefixes: 2 or 4 wavefronts per run of positions, until about a thousand wavefronts stream
-    const int64_t runs = (int64_t)scan_waves(pb.P) * pb.Hkv;
-    const int rs = runs >= 1024 ? 1 : (runs >= 512 ? 2 : 4);
-    const int ppw = 4 / rs;
-    const dim3 ge = head_grid(pb, (scan_waves(pb.P) + ppw - 1) / ppw);
-    if (vec)
-      RK_LAUNCH(ST_EMA, st, k_ema_scan<true>, ge, dim3(256), 0, st, pb, score, e, thr, cnt_hi, sum_hi, cmask, rs);
-    else
-      RK_LAUNCH(ST_EMA, st, k_ema_scan<false>, ge, dim3(256), 0, st, pb, score, e, thr, cnt_hi, sum_hi, cmask, rs);
-    if (pb.adaptive) {
-      RK_LAUNCH(ST_ROWTOPK, st, k_row_finish, head_grid(pb, pb.W), dim3(512), 0, st, pb, score, cnt_hi, sum_hi,
-                cmask, thr, rowsum);
+  by_heads(pb, [&](auto by8) {
+    constexpr bool BY8 = decltype(by8)::value;
+    // One launch for short prefixes.  Rows above 16384 positions take a compute unit each: two rounds of
+    // them (512 rows of 32k: 37 us) lose against three launches that stream (34 us), one (132 rows of 20k:
+    // 12 us against 31) does not.
+    if (pb.P <= 16384 || (pb.P <= ROW_REG_MAX && pb.W * pb.Hkv <= n_cu())) {
+      const int nrow = pb.adaptive ? pb.W : 0;
+      with_row_block(pb.P, [&](auto nt, auto npt) {
+        constexpr int NT = decltype(nt)::value, NPT = decltype(npt)::value;
+        const dim3 gr = head_grid(pb, nrow + (pb.P + NT - 1) / NT);
+        if (vec) RK_LAUNCH(ST_EMA, st, (k_short_rows<NT, NPT, true, BY8>), gr, dim3(NT), 0, st, pb, score, e, rowsum, nrow);
+        else RK_LAUNCH(ST_EMA, st, (k_short_rows<NT, NPT, false, BY8>), gr, dim3(NT), 0, st, pb, score, e, rowsum, nrow);
+      });
+    } else {
+      if (pb.adaptive)
+        RK_LAUNCH(ST_ROWTOPK, st, k_sample_bracket<BY8>, head_grid(pb, pb.W), dim3(512), 0, st, pb, score, thr,
+                  cnt_hi, sum_hi);
+      // short prefixes: 2 or 4 wavefronts per run of positions, until about a thousand wavefronts stream
+      const int64_t runs = (int64_t)scan_waves(pb.P) * pb.Hkv;
+      const int rs = runs >= 1024 ? 1 : (runs >= 512 ? 2 : 4);
+      const int ppw = 4 / rs;
+      const dim3 ge = head_grid(pb, (scan_waves(pb.P) + ppw - 1) / ppw);
+      if (vec)
+        RK_LAUNCH(ST_EMA, st, (k_ema_scan<true, BY8>), ge, dim3(256), 0, st, pb, score, e, thr, cnt_hi, sum_hi, cmask, rs);
+      else
+        RK_LAUNCH(ST_EMA, st, (k_ema_scan<false, BY8>), ge, dim3(256), 0, st, pb, score, e, thr, cnt_hi, sum_hi, cmask, rs);
+      if (pb.adaptive) {
+        RK_LAUNCH(ST_ROWTOPK, st, k_row_finish<BY8>, head_grid(pb, pb.W), dim3(512), 0, st, pb, score, cnt_hi, sum_hi,
+                  cmask, thr, rowsum);
+      }
     }
-  }
-  RK_LAUNCH(ST_BOX, st, k_box, head_grid(pb, (pb.P + 256 * BOX_PT - 1) / (256 * BOX_PT)), dim3(256), 0, st, pb, e, rowsum, fin,
-            aws_info, aws_d);
+    RK_LAUNCH(ST_BOX, st, k_box<BY8>, head_grid(pb, (pb.P + 256 * BOX_PT - 1) / (256 * BOX_PT)), dim3(256), 0, st, pb, e, rowsum, fin,
+              aws_info, aws_d);
+  });
   return hip_status();
 }
 

@@ -176,6 +176,27 @@ def test_infinite_scores_stay_infinite(rk, W, P):  # noqa: F811
     assert all(set(hi) <= set(r.tolist()) and not set(lo) & set(r.tolist()) for r in idx)
 
 
+@pytest.mark.parametrize("P", [700, 17000, 40003, 70001])     # one launch for the statistics; the streaming launches
+def test_heads_of_one_layer_as_of_two(rk, P):  # noqa: F811
+    """Eight heads and more are dealt to the workgroups eight at a time, fewer with their parts running fastest: 13 heads
+    (eight and a remainder of five) give bit for bit what layers of 7 and 6 heads give."""
+    Hkv, W = 13, 5
+    s = torch.from_numpy(np.random.default_rng(P).lognormal(size=(Hkv, W, P)).astype(np.float32))
+
+    def run(part):
+        p = rk.make_params(n_q_heads=len(part), n_kv_heads=len(part), head_dim=64, seq_len=P + W, window=W, budget=W + 300,
+                           dtype="bf16", ema_alpha=0.25, base_window=3, beta=50.0)
+        b = rk.alloc_layer_buffers(p, torch.bfloat16, "cuda")
+        b.score[..., :P].copy_(part)
+        rk.restkv_smooth(p, b.score, b.ema, b.final, b.aws_info, b.aws_d, b.workspace)
+        rk.restkv_select(p, b.final, b.idx, b.workspace)
+        torch.cuda.synchronize()
+        return [x.cpu() for x in (b.ema[:, :P], b.final[:, :P], b.aws_info, b.aws_d, b.idx)]
+
+    for whole, a, b in zip(run(s), run(s[:7]), run(s[7:])):
+        assert torch.equal(whole, torch.cat([a, b]))
+
+
 def _keys(x):
     """The order the searches work in: larger float <=> larger key, -0 < +0, NaNs at the ends."""
     b = np.ascontiguousarray(x, dtype=np.float32).view(np.uint32)
