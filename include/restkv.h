@@ -100,7 +100,11 @@ typedef struct restkv_params {
   int64_t ld_score;      /* row stride (floats) of score / ema / final (0: P; >= P)    */
 } restkv_params;
 
-/* Bytes of scratch the four calls below need for these parameters (0 if invalid). */
+/*
+ * Bytes of scratch the four calls below need for these parameters (0 if invalid).  The number differs between
+ * builds of the library: ask the one that is loaded, keep none.  It covers both score paths, so bf16 layers
+ * hold room for the FP32 one too.
+ */
 size_t restkv_workspace_bytes(const restkv_params* p);
 
 /*
@@ -258,6 +262,9 @@ int restkv_compact(const restkv_params* p, const void* k, const void* v, const i
  * arrays of n_stages >= RESTKV_N_STAGES entries) and forgets them.  Disabled by
  * default; enabling or disabling also forgets pending records.  Not thread-safe
  * against concurrent launches on other host threads beyond a mutex on the records.
+ * Stages "attn_partial" and "vv" (attention and value-Gram pass): on the bf16 matrix-core path they are one launch, which
+ * "attn_partial" counts, and "vv" reports launches only where there is no attention pass (statistics handed in) and for the
+ * value norms of the indicators without a projection.  The FP32 path launches and reports them one by one.
  */
 #define RESTKV_N_STAGES 10
 int restkv_timing_enable(int stage_mask);

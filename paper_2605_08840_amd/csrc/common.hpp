@@ -143,13 +143,13 @@ __device__ __forceinline__ int head_budget(const Prob& pb, int g) {
   return min(max(pb.hb[g], pb.W + 1), pb.B);
 }
 
-// Workgroup -> (KV head, part of the head's work).  BY8, for eight heads or more: workgroups go round the eight XCDs by their number (x
-// fastest), so the heads are taken eight at a time, the head running fastest: a head's workgroups share one XCD and find in its L2 what the others
-// have fetched and what the pass before left there, and follow each other closely in time.  What is left of the heads runs
-// fastest too.  Against the parts running fastest, 8 heads: select, 128k 24.8 -> 23.4 us, score + smoothing, 8k 62.1 -> 60.3,
-// scores from statistics + smoothing, 20k 66.1 -> 60.4, 32k 139.5 -> 136.8, most others within 1 %; 16 heads, select, 100k
-// 27.9 -> 25.3.  Fewer heads have the parts running fastest: four heads on two XCDs each gain nothing, and the divisions with which every
-// workgroup then begins cost a select 0.7 us (55k 19.2 us against 19.9).
+// Workgroup -> (KV head, part of the head's work).  BY8, for eight heads or more: workgroups go round the eight XCDs by
+// their number (x fastest), so the heads are taken eight at a time, the head running fastest: a head's workgroups share one
+// XCD and find in its L2 what the others have fetched and what the pass before left there, and follow each other closely in
+// time.  What is left of the heads runs fastest too.  Against the parts running fastest, 8 heads: select, 128k 24.8 -> 23.4
+// us, score + smoothing, 8k 62.1 -> 60.3, scores from statistics + smoothing, 20k 66.1 -> 60.4, 32k 138.5 -> 136.8, most
+// others within 1 %; 16 heads, select, 100k 27.7 -> 25.1.  Fewer heads have the parts running fastest: four heads on two XCDs
+// each gain nothing, and the divisions with which every workgroup then begins cost a select 0.8 us (55k 19.5 us against 20.3).
 struct HeadPart { int g, x; };
 template <bool BY8>
 __device__ __forceinline__ HeadPart head_part(const Prob& pb) {

@@ -863,7 +863,8 @@ __device__ __forceinline__ void attn_pass(const Prob& pb, WgAt at, AttnSmem<D>& 
 }
 
 // The two passes that need nothing of each other, one launch: workgroups [va.at, va.at + va.n) are the value-Gram pass's,
-// the others the attention pass's; the second pass's start as the first one's end (a workgroup fills a compute unit either way).
+// the others the attention pass's; the second pass's start as the first one's end.  By registers (heads of 128 202 to 248, heads
+// of 64 up to 175) a compute unit holds one workgroup; only where both passes split their tiles in heads of 64 (126) two.
 // ATTN, VV: 0 that pass is not there, 1 it is, 2 with KS2, 3 with LO.  512 threads.
 struct AttnArgs { int S, ny, kps, log2iw; float heavy; };
 struct VvArgs { int at, n, chunks, ny, ldv, tiles_per_wg; };
