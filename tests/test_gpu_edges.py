@@ -352,21 +352,22 @@ def test_gram_and_statistics_at_any_float_address(rk, dtype, d):  # noqa: F811
     assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
 
 
-@pytest.mark.parametrize("Hq,Hkv,d,L,W", [
-    (8, 8, 128, 64 * 3 + 1 + 16, 16),     # prefix of three tiles and a key: hardly more tiles than units to share
-    (32, 8, 128, 64 * 33, 64),            # 33 tiles a head, prefix ends with a tile
-    (32, 8, 128, 64 * 33 + 1, 64),        # one key in the last tile of the whole context
-    (16, 4, 128, 1500, 40),               # four KV heads, five row blocks
-    (28, 4, 128, 900, 33),                # nine row blocks: the second workgroup of a split is nearly empty, one pass after the other
-    (64, 8, 128, 1200, 64),               # two full workgroups of rows, two of heads
+@pytest.mark.parametrize("Hq,Hkv,d,L,W,side,two", [
+    (8, 8, 128, 64 * 3 + 1 + 16, 16, 1, 0),     # prefix of three tiles and a key: hardly more tiles than units to share
+    (32, 8, 128, 64 * 33, 64, 1, 1),            # 33 tiles a head, prefix ends with a tile
+    (32, 8, 128, 64 * 33 + 1, 64, 1, 1),        # one key in the last tile of the whole context
+    (16, 4, 128, 1500, 40, 1, 0),               # four KV heads, five row blocks
+    (28, 4, 128, 900, 33, 0, 0),                # nine row blocks: the second workgroup of a split is nearly empty, one pass after the other
+    (64, 8, 128, 1200, 64, 1, 0),               # two full workgroups of rows, two of heads
 ])
-def test_attention_and_value_gram_passes_share_the_chip(rk, oracle_mod, Hq, Hkv, d, L, W):  # noqa: F811
-    """The two passes in one launch, side by side or one after the other: first and last KV head against the oracle, and
-    the same bits from a workspace full of ones (no sum is read that was not written)."""
+def test_attention_and_value_gram_passes_share_the_chip(rk, oracle_mod, Hq, Hkv, d, L, W, side, two):  # noqa: F811
+    """The two passes in one launch, side by side (`side`; heavy weights in two parts: `two`) or one after the other: first
+    and last KV head against the oracle, and the same bits from a workspace full of ones (no sum is read that was not written)."""
     w = workloads.small_case(Hq=Hq, Hkv=Hkv, d=d, L=L, W=W, B=W + 20, dtype="bf16", D=2 * d, structure="sinks", seed=91)
     q, k, v = workloads.make_qkv(w)
     wo = workloads.make_wo(w)
     p = params_for(rk, w)
+    assert rk.restkv_debug_score_plan(p)[2:] == (side, two)
     gram = torch.empty((Hq, d, d), dtype=torch.float32, device="cuda")
     rk.restkv_prepare_wo(p, wo.cuda(), gram)
     buf = rk.alloc_layer_buffers(p, q.dtype, "cuda")
