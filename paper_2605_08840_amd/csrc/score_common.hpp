@@ -250,13 +250,14 @@ __global__ __launch_bounds__(4 * D, 4) void k_attn_combine(Prob pb, const T* __r
   };
 #pragma unroll
   for (int m = 0; m < MB; ++m) fetch_splits(m, part);
-  // Gram entries of this lane: column 16 wv + l % 16, the K index of step 4 a + e being 16 a + 4 (l / 16) + e;
-  // read along the row of the same number (M is symmetric), four at a time
+  // Gram entries of this lane: column 16 wv + l % 16, the K index of step 4 a + e being 16 a + 4 (l / 16) + e
   f32x4_t mreg[D / 16];
   if (gram) {
-    const float* Mh = gram + ((int64_t)h * D + 16 * wv + (l & 15)) * D + 4 * (l >> 4);
+    const float* Mh = gram + ((int64_t)h * D + 4 * (l >> 4)) * D + 16 * wv + (l & 15);
 #pragma unroll
-    for (int a = 0; a < D / 16; ++a) mreg[a] = quad_of(Mh + 16 * a);      // (the caller's array: float alignment)
+    for (int a = 0; a < D / 16; ++a)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) mreg[a][e] = Mh[(16 * a + e) * D];
   }
   for (int r = tid / SW; r < RQ; r += NT / SW) {
     const int row = h * pb.W + min(i0 + r, pb.W - 1);

@@ -151,6 +151,10 @@ __device__ __forceinline__ void dma_1k_to(const void* base, uint32_t voff, uint3
   asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(voff), "s"(base), "s"(lds_dst)
                : "memory", "m0");
 }
+// the same with a 64-bit address per lane
+__device__ __forceinline__ void dma_1k_from(const void* src, uint32_t lds_dst) {
+  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(src), "s"(lds_dst) : "memory", "m0");
+}
 // LDS byte address of a __shared__ object
 __device__ __forceinline__ uint32_t lds_addr(const void* p) {
   return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const void*)p;
@@ -233,12 +237,14 @@ __device__ __forceinline__ void wait_vm() {
 }
 
 // ------------------------------------------------------------------------------------------
-// vv[h, n] = v_n M_h v_n^T with the symmetric Gram matrix M_h, as  sum_i v_i (T v)_i  with the
-// upper triangular T = diag(M) + 2 triu(M, 1): only the 32 x 32 blocks on or above the diagonal
+// vv[h, n] = v_n M_h v_n^T with the symmetric Gram matrix M_h, as  sum_j v_j (T v)_j  with the
+// lower triangular T = (diag(M) + 2 triu(M, 1))^T: only the 32 x 32 blocks on or below the diagonal
 // are multiplied (10 of 16 for D = 128).  Y^T = T V^T runs on the MFMA with T split into bf16
 // high and low parts that stay in registers for the whole kernel; row block rb needs the k-steps
-// from 2 rb on, so a wavefront takes the row blocks pr and D/32 - 1 - pr of one head: D/16 + 2
-// k-steps whatever pr.  The value tiles arrive through a 4-deep asynchronous LDS ring and are
+// up to 2 rb + 1, so a wavefront takes the row blocks pr and D/32 - 1 - pr of one head: D/16 + 2
+// k-steps whatever pr.  (Lower, so that the lanes of a load, which are rows of T, read along a row of M: with the
+// upper triangle every lane read its own row, a cache line per lane and instruction, and a workgroup's Gram entries took 6 us;
+// scores from statistics + smoothing, 32/8 heads, 32k, 136.0 -> 133.3 us with the same in the merge.)  The value tiles arrive through a 4-deep asynchronous LDS ring and are
 // the B operand shared by all wavefronts; the partial dots of a head's wavefronts meet in LDS.
 // A tile has a matrix part (two 32-key halves of 20 MFMAs) and a vector part (the row dots);
 // wavefronts 0..3 and 4..7 run them in complementary order (see the loop), so the matrix cores
@@ -308,29 +314,28 @@ __device__ __forceinline__ void vv_pass(const Prob& pb, WgAt at, VvSmem<D, KS2>&
 
   auto body = [&](auto prc) {
     constexpr int PR = decltype(prc)::value;
-    constexpr int RB0 = PR, RB1 = CB - 1 - PR;      // RB0 <= RB1
-    constexpr int N0 = KS - 2 * RB0, N1 = KS - 2 * RB1;
+    constexpr int RB0 = CB - 1 - PR, RB1 = PR;      // RB0 >= RB1
+    constexpr int N0 = 2 * (RB0 + 1), N1 = 2 * (RB1 + 1);
     bf16x8 ahi0[N0], alo0[N0], ahi1[N1], alo1[N1];
     auto load_frag = [&](int rb, int ks, bf16x8& hi8, bf16x8& lo8) {
-      // Gram row of this lane: the rows of a block in the order in which a lane's registers of the product (rows
-      // 8 a + 4 hf + b) are the value entries that it holds as operands (16 (a / 2) + 8 hf + 4 (a % 2) + b)
-      const int i = 32 * rb + ((rr & 0x13) | (rr & 4) << 1 | (rr & 8) >> 1);
-      const float* mrow = gram + ((int64_t)h * D + i) * D + 16 * ks + 8 * hf;
-      const f32x4 x0 = quad_of(mrow), x1 = quad_of(mrow + 4);     // (the caller's array: float alignment)
+      // Column of the Gram matrix that is this lane's row of T: the rows of a block in the order in which a lane's
+      // registers of the product (rows 8 a + 4 hf + b) are the value entries that it holds as operands (16 (a / 2) + 8 hf + 4 (a % 2) + b)
+      const int j = 32 * rb + ((rr & 0x13) | (rr & 4) << 1 | (rr & 8) >> 1);
+      const float* mcol = gram + ((int64_t)h * D + 16 * ks + 8 * hf) * D + j;
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
-        const int j = 16 * ks + 8 * hf + e;
-        float f = e < 4 ? x0[e] : x1[e - 4];
-        f = j > i ? 2.f * f : (j == i ? f : 0.f);
+        const int i = 16 * ks + 8 * hf + e;
+        float f = mcol[e * D];
+        f = i < j ? 2.f * f : (i == j ? f : 0.f);
         const __bf16 hi = (__bf16)f;
         hi8[e] = hi;
         lo8[e] = (__bf16)(f - (float)hi);
       }
     };
 #pragma unroll
-    for (int a = 0; a < N0; ++a) load_frag(RB0, 2 * RB0 + a, ahi0[a], alo0[a]);
+    for (int a = 0; a < N0; ++a) load_frag(RB0, a, ahi0[a], alo0[a]);
 #pragma unroll
-    for (int a = 0; a < N1; ++a) load_frag(RB1, 2 * RB1 + a, ahi1[a], alo1[a]);
+    for (int a = 0; a < N1; ++a) load_frag(RB1, a, ahi1[a], alo1[a]);
 
     // vv of one tile of this wavefront's head: the partial dots of the head's wavefronts meet here
     auto head_sum = [&](int t) {
@@ -356,18 +361,18 @@ __device__ __forceinline__ void vv_pass(const Prob& pb, WgAt at, VvSmem<D, KS2>&
       // LDS round trip per k-step
       bf16x8 b[N0];
 #pragma unroll
-      for (int a = 0; a < N0; ++a) b[a] = as_bf16x8(*(const uint4*)&vt[Ring::off(ko + 32 * nb + rr, 2 * (2 * RB0 + a) + hf)]);
+      for (int a = 0; a < N0; ++a) b[a] = as_bf16x8(*(const uint4*)&vt[Ring::off(ko + 32 * nb + rr, 2 * a + hf)]);
 #pragma unroll
       for (int a = 0; a < 2; ++a) {
-        vq0[nb][a] = __builtin_bit_cast(uint4, b[a]);
-        vq1[nb][a] = __builtin_bit_cast(uint4, b[2 * (RB1 - RB0) + a]);
+        vq0[nb][a] = __builtin_bit_cast(uint4, b[N0 - 2 + a]);
+        vq1[nb][a] = __builtin_bit_cast(uint4, b[N1 - 2 + a]);
       }
 #pragma unroll
-      for (int ks = 2 * RB0; ks < KS; ++ks) {
-        y0[nb] = MFMA(ahi0[ks - 2 * RB0], b[ks - 2 * RB0], y0[nb]);
-        if (ks >= 2 * RB1) y1[nb] = MFMA(ahi1[ks - 2 * RB1], b[ks - 2 * RB0], y1[nb]);
-        y0[nb] = MFMA(alo0[ks - 2 * RB0], b[ks - 2 * RB0], y0[nb]);
-        if (ks >= 2 * RB1) y1[nb] = MFMA(alo1[ks - 2 * RB1], b[ks - 2 * RB0], y1[nb]);
+      for (int ks = 0; ks < N0; ++ks) {
+        y0[nb] = MFMA(ahi0[ks], b[ks], y0[nb]);
+        if (ks < N1) y1[nb] = MFMA(ahi1[ks], b[ks], y1[nb]);
+        y0[nb] = MFMA(alo0[ks], b[ks], y0[nb]);
+        if (ks < N1) y1[nb] = MFMA(alo1[ks], b[ks], y1[nb]);
       }
       __builtin_amdgcn_s_setprio(0);
     };
@@ -466,6 +471,11 @@ __device__ __forceinline__ void vv_pass(const Prob& pb, WgAt at, VvSmem<D, KS2>&
 // halves meet in LDS at the end, so that a split leaves one set of sums either way.  A wavefront
 // without rows only copies.
 //
+// Query rows and sums pass through LDS on their way in and out, so that accesses to memory run along rows: with an access of
+// every lane to its own row the rows took 1.3 us and the sums 2 to 3.6 us of a workgroup's time (score + smoothing, 32/8 heads, 8k,
+// window 32: 59.3 -> 58.0 us with the Gram entries of the other pass and of the merge read along rows; 28/4 heads of 64,
+// 20k 81.4 -> 79.6; 256 KV heads of 2112 tokens 368 -> 358).
+//
 // LO: groups of 16 keys that hold a heavy weight enter P.V a second time with what bf16 has left of their weights.
 template <int D>
 struct AttnSmem { __attribute__((aligned(1024))) uint16_t ring[7][TN * D]; };
@@ -508,17 +518,23 @@ __device__ __forceinline__ void attn_pass(const Prob& pb, WgAt at, AttnSmem<D>& 
       RingV::template issue<NW>(vg, pitch, kb, pb.L, Vs[t & 3], wv, l);
     }
   };
+  // The wavefront's query rows come through LDS, in the slots of K tiles 1, 2 and V tiles 1, 2 (half a slot each): a lane that
+  // loads its own row's operands touches a cache line per lane and instruction.
+  const int row_blk = at.y * RB + wv % RB;
+  uint16_t* const qs = ring[(wv < NW / 2 ? 1 : 4) + (wv >> 1 & 1)] + (wv & 1) * (32 * D);
+  constexpr int QI = 32 / RingK::RPI;               // copies of a wavefront's query rows
   if (ntiles > 0) {
-    issue_tile(0);
-    issue_tile(1);
-  }
-
-  bf16x8 qf[KS];
+    const uint32_t qd = lds_addr(qs);
 #pragma unroll
-  for (int ks = 0; ks < KS; ++ks) {       // an absent row re-reads row (h, 0) and is masked: no branch around the loads
-    const uint4 u = *(const uint4*)(q + (int64_t)ri.h * pb.q_sh + (int64_t)(ri.valid ? ri.i : 0) * pb.q_st + 16 * ks + 8 * hf);
-    qf[ks] = as_bf16x8(ri.valid ? u : make_uint4(0, 0, 0, 0));
+    for (int j = 0; j < QI; ++j) {                  // (an absent row: row (h, 0) once more, masked below)
+      const int r = j * RingK::RPI + l / RingK::CH;
+      const RowInfo x = row_info(pb, g, row_blk, r, log2iw);
+      dma_1k_from(q + (int64_t)x.h * pb.q_sh + (int64_t)(x.valid ? x.i : 0) * pb.q_st + 8 * RingK::swz(r, l % RingK::CH),
+                  qd + (uint32_t)j * 1024u);
+    }
+    issue_tile(0);
   }
+  bf16x8 qf[KS];
   const int vis_last = (pb.causal && ri.valid) ? pb.P + ri.i : pb.L - 1;
   const float c2 = pb.scale * LOG2E;
 
@@ -570,8 +586,9 @@ __device__ __forceinline__ void attn_pass(const Prob& pb, WgAt at, AttnSmem<D>& 
   };
 
   if (ntiles > 0 && idle) {
-    wait_vm<NG>();
+    wait_vm<0>();
     wg_barrier();
+    issue_tile(1);
     for (int t = 0; t < ntiles; ++t) {
       issue_tile(t + 2);
       wait_vm<NG>();
@@ -579,8 +596,15 @@ __device__ __forceinline__ void attn_pass(const Prob& pb, WgAt at, AttnSmem<D>& 
     }
     wait_vm<0>();
   } else if (ntiles > 0) {
-    wait_vm<NG>();           // own share of tile 0
-    wg_barrier();            // B_-1
+    wait_vm<NG>();           // the query rows
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+      const uint4 u = *(const uint4*)&qs[RingK::off(rr, 2 * ks + hf)];
+      qf[ks] = as_bf16x8(ri.valid ? u : make_uint4(0, 0, 0, 0));
+    }
+    wait_vm<0>();            // own share of tile 0
+    wg_barrier();            // B_-1: every wavefront has its query rows in registers
+    issue_tile(1);
     const bool late = wv >= NW / 2;
 
     for (int t = 0; t < ntiles; ++t) {
@@ -858,25 +882,40 @@ __device__ __forceinline__ void attn_pass(const Prob& pb, WgAt at, AttnSmem<D>& 
       o.part_ref[po] = ntiles > 0 ? mref * c2 : 0.f;
       o.part_l[po] = ltot;
     }
-    float* zp = o.part_z + po * D;
+  }
+  // The sums leave through LDS, 32 columns at a time, so that a store instruction writes whole cache lines (eight rows) and not
+  // 16 bytes of 32 rows.  The memory is the wavefront's own: where its half's sums were, or a part of the ring that nobody reads
+  // or copies to any more.
+  if constexpr (!KS2) wg_barrier();
+  float* const zb = KS2 ? (float*)&ring[0][0] + (wv % RB) * ((CB * 16 + 1) * 64) : (float*)&ring[0][0] + wv * (32 * 32 * (D / 64));
+  RowInfo zr[4];
 #pragma unroll
-    for (int cb = 0; cb < CB; ++cb)
+  for (int k = 0; k < 4; ++k) zr[k] = row_info(pb, g, row_blk, 8 * k + (l >> 3), log2iw);
 #pragma unroll
-      for (int jq = 0; jq < 4; ++jq) {
-        f32x4 x = {oacc[cb][4 * jq], oacc[cb][4 * jq + 1], oacc[cb][4 * jq + 2], oacc[cb][4 * jq + 3]};
-        *(f32x4*)(zp + 32 * cb + 8 * jq + 4 * hf) = x;
-      }
+  for (int cb = 0; cb < CB; ++cb) {
+    float* const zc = zb + (cb & (D / 64 - 1)) * (32 * 32);        // 16-byte chunk c of row r at c ^ (r % 8)
+#pragma unroll
+    for (int jq = 0; jq < 4; ++jq) {
+      const f32x4 x = {oacc[cb][4 * jq], oacc[cb][4 * jq + 1], oacc[cb][4 * jq + 2], oacc[cb][4 * jq + 3]};
+      *(f32x4*)(zc + 32 * rr + 4 * ((2 * jq + hf) ^ (rr & 7))) = x;
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const int r = 8 * k + (l >> 3);
+      const f32x4 x = *(const f32x4*)(zc + 32 * r + 4 * ((l & 7) ^ (r & 7)));
+      if (zr[k].valid) *(f32x4*)(o.part_z + ((int64_t)zr[k].row * S + s) * D + 32 * cb + 4 * (l & 7)) = x;
+    }
   }
 }
 
 // The two passes that need nothing of each other, one launch: workgroups [va.at, va.at + va.n) are the value-Gram pass's,
-// the others the attention pass's; the second pass's start as the first one's end.  By registers (heads of 128 202 to 248, heads
-// of 64 up to 175) a compute unit holds one workgroup; only where both passes split their tiles in heads of 64 (126) two.
+// the others the attention pass's; the second pass's start as the first one's end.  By registers (heads of 128 205 to 251, heads
+// of 64 up to 167) a compute unit holds one workgroup; only where both passes split their tiles in heads of 64 (127: the bound) two.
 // ATTN, VV: 0 that pass is not there, 1 it is, 2 with KS2, 3 with LO.  512 threads.
 struct AttnArgs { int S, ny, kps, log2iw; float heavy; };
 struct VvArgs { int at, n, chunks, ny, ldv, tiles_per_wg; };
 template <int D, int ATTN, int VV>
-__global__ __launch_bounds__(512) void k_attn_vv(Prob pb, const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
+__global__ __launch_bounds__(512, D == 64 && ATTN == 2 && VV != 1 ? 4 : 2) void k_attn_vv(Prob pb, const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
                                                  const uint16_t* __restrict__ v, const float* __restrict__ gram,
                                                  ScorePtrs o, AttnArgs aa, VvArgs va) {
   __shared__ union { AttnSmem<ATTN ? D : 64> a; VvSmem<D, VV == 2> v; } sm;
