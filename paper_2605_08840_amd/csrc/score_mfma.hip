@@ -67,6 +67,38 @@ __device__ __forceinline__ int xhalf_min(int x) {
 }
 __device__ __forceinline__ float bf16_to_f(uint16_t b) { return __uint_as_float(((uint32_t)b) << 16); }
 
+// Bit string of a comparison: bits = 16 bits + (x == t), one bit for each x in order.  And x[] = v where register number X + i is n.  In
+// groups of four for the distance between a compare and the instruction that reads its outcome (see shift_in_gt_2x2).
+__device__ __forceinline__ void shift_in_eq4(uint32_t& bits, float x0, float x1, float x2, float x3, float t) {
+  unsigned long long c0, c1, c2;
+  asm("v_cmp_eq_f32_e64 %1, %4, %8\n\t"
+      "v_cmp_eq_f32_e64 %2, %5, %8\n\t"
+      "v_cmp_eq_f32_e64 %3, %6, %8\n\t"
+      "v_cmp_eq_f32_e32 vcc, %7, %8\n\t"
+      "v_addc_co_u32_e64 %0, %1, %0, %0, %1\n\t"
+      "v_addc_co_u32_e64 %0, %2, %0, %0, %2\n\t"
+      "v_addc_co_u32_e64 %0, %3, %0, %0, %3\n\t"
+      "v_addc_co_u32_e32 %0, vcc, %0, %0, vcc"
+      : "+v"(bits), "=&s"(c0), "=&s"(c1), "=&s"(c2)
+      : "v"(x0), "v"(x1), "v"(x2), "v"(x3), "v"(t)
+      : "vcc");
+}
+template <int X>
+__device__ __forceinline__ void set_where4(float& x0, float& x1, float& x2, float& x3, int n, float v) {
+  unsigned long long c0, c1, c2;
+  asm("v_cmp_eq_u32_e64 %4, %8, %7\n\t"
+      "v_cmp_eq_u32_e64 %5, %9, %7\n\t"
+      "v_cmp_eq_u32_e64 %6, %10, %7\n\t"
+      "v_cmp_eq_u32_e32 vcc, %11, %7\n\t"
+      "v_cndmask_b32_e64 %0, %0, %12, %4\n\t"
+      "v_cndmask_b32_e64 %1, %1, %12, %5\n\t"
+      "v_cndmask_b32_e64 %2, %2, %12, %6\n\t"
+      "v_cndmask_b32_e32 %3, %3, %12, vcc"
+      : "+v"(x0), "+v"(x1), "+v"(x2), "+v"(x3), "=&s"(c0), "=&s"(c1), "=&s"(c2)
+      : "v"(n), "n"(X), "n"(X + 1), "n"(X + 2), "n"(X + 3), "v"(v)
+      : "vcc");
+}
+
 // key (or value-column) index of register j of a 32x32 block for this lane half
 __device__ __forceinline__ constexpr int cidx(int j, int hf) { return 8 * (j >> 2) + 4 * hf + (j & 3); }
 
@@ -238,7 +270,7 @@ __device__ __forceinline__ void wait_vm() {
 
 // ------------------------------------------------------------------------------------------
 // vv[h, n] = v_n M_h v_n^T with the symmetric Gram matrix M_h, as  sum_j v_j (T v)_j  with the
-// lower triangular T = (diag(M) + 2 triu(M, 1))^T: only the 32 x 32 blocks on or below the diagonal
+// lower triangular T = (diag(M) + 2 triu(M, 1))^T, of which half is kept: only the 32 x 32 blocks on or below the diagonal
 // are multiplied (10 of 16 for D = 128).  Y^T = T V^T runs on the MFMA with T split into bf16
 // high and low parts that stay in registers for the whole kernel; row block rb needs the k-steps
 // up to 2 rb + 1, so a wavefront takes the row blocks pr and D/32 - 1 - pr of one head: D/16 + 2
@@ -322,15 +354,17 @@ __device__ __forceinline__ void vv_pass(const Prob& pb, WgAt at, VvSmem<D, KS2>&
       // registers of the product (rows 8 a + 4 hf + b) are the value entries that it holds as operands (16 (a / 2) + 8 hf + 4 (a % 2) + b)
       const int j = 32 * rb + ((rr & 0x13) | (rr & 4) << 1 | (rr & 8) >> 1);
       const float* mcol = gram + ((int64_t)h * D + 16 * ks + 8 * hf) * D + j;
+      float x[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) x[e] = mcol[e * D];
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
         const int i = 16 * ks + 8 * hf + e;
-        float f = mcol[e * D];
-        f = i < j ? 2.f * f : (i == j ? f : 0.f);
-        const __bf16 hi = (__bf16)f;
-        hi8[e] = hi;
-        lo8[e] = (__bf16)(f - (float)hi);
+        if (ks >= 2 * rb) x[e] = i < j ? x[e] : (i == j ? 0.5f * x[e] : 0.f);    // (else: left of the diagonal block)
       }
+      const Op<2> o = split8<2>(x);
+      hi8 = as_bf16x8(o.p[0]);
+      lo8 = as_bf16x8(o.p[1]);
     };
 #pragma unroll
     for (int a = 0; a < N0; ++a) load_frag(RB0, a, ahi0[a], alo0[a]);
@@ -345,7 +379,7 @@ __device__ __forceinline__ void vv_pass(const Prob& pb, WgAt at, VvSmem<D, KS2>&
           float sum = 0.f;
 #pragma unroll
           for (int m2 = 0; m2 < WPH; ++m2) sum += part[(t - t0) & 1][hw][m2][KS2 ? ko + (l & 31) : l];
-          vv[(int64_t)h * ldv + n] = sum;
+          vv[(int64_t)h * ldv + n] = 2.f * sum;
         }
       }
     };
@@ -553,35 +587,53 @@ __device__ __forceinline__ void attn_pass(const Prob& pb, WgAt at, AttnSmem<D>& 
   const int s16 = l & 15;
   const int vrow = 4 * hf + (s16 >> 2), vcol = 16 * ((l >> 4) & 1) + 4 * (s16 & 3);
 
-  // P.V of one tile: O^T[c, row] += V^T P^T.  The transposing reads of the next 16-key group are
-  // issued before the MFMAs of the current one, so the matrix cores do not wait one LDS round
-  // trip per MFMA.
-  auto accumulate = [&](const uint16_t* vt) {
-    auto fetch = [&](int grp, bf16x8 (&av)[CB]) {       // grp = 2 mb + kg2
-      const int r0 = ko + 16 * grp + vrow;
+  // Operand i of P.V (O^T[c, row] += V^T P^T: 16-key group i / CB, columns 32 (i % CB) ..), of Q.K (k-step i / NMB, keys
+  // 32 (i % NMB) ..).
+  // One address per lane and tile: the permutation is an XOR of address bits that the row's pitch leaves alone (rows 8, 16, 32
+  // apart share it), so the chunks of a k-step or column block are an XOR with a constant away.
+  typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
+  typedef __attribute__((address_space(3))) const bf16x8 lds_bf16x8;
+  const uint32_t v_lane = vs_base + 2u * (uint32_t)(RingV::off(ko + vrow, vcol >> 3) + (vcol & 7));
+  const uint32_t k_lane = ks_base + 2u * (uint32_t)RingK::off(ko + rr, hf);
+  auto v_tile = [&](int t) { return v_lane + (uint32_t)(t & 3) * (TN * D * 2); };
+  auto k_tile = [&](int t) { return k_lane + (uint32_t)(t % 3) * (TN * D * 2); };
+  auto read_v = [&](uint32_t vt, int i) {
+    const uint32_t at = (vt ^ ((uint32_t)(i % CB) << 6)) + (uint32_t)(i / CB) * (16 * D * 2);
+    const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)at);
+    const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(at + 8 * D * 2));
+    union { s16x8 s; bf16x8 b; } a;
+    a.s = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+    return a.b;
+  };
+  auto read_k = [&](uint32_t kt, int i) {
+    return *(lds_bf16x8*)((kt ^ ((uint32_t)(i / NMB) << 5)) + (uint32_t)(i % NMB) * (32 * D * 2));
+  };
+  constexpr int NPV = 2 * NMB * CB, NQK = NMB * KS;
+  // The products of a step are one stream with RD operands read ahead (a product is 32 cycles, an LDS round trip four or five): left
+  // to itself the compiler asks for an operand right before its product.  Score + smoothing, 32/8 heads, 128k 590 -> 583 us, 32k
+  // clustered 209 -> 203; the latter 201 with the search of a key to keep out in groups of four compares.
+  constexpr int RD = NPV < 6 ? NPV : 6;
+  bf16x8 op[RD];
+  // remainders of heavy weights (LO), with operands of their own: few groups have them
+  auto second_parts = [&](uint32_t vt) {
 #pragma unroll
-      for (int cb = 0; cb < CB; ++cb) {
-        const int col = 32 * cb + vcol;
-        const uint16_t* base = vt + RingV::off(r0, col >> 3) + (col & 7);   // rows r0 and r0+8 share the XOR key
-        const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-            (__attribute__((address_space(3))) s16x4*)(base));
-        const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-            (__attribute__((address_space(3))) s16x4*)(base + 8 * D));
-        union { s16x8 s; bf16x8 b; } a;
-        a.s = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-        av[cb] = a.b;
-      }
-    };
-    bf16x8 av[2][CB];
-    fetch(0, av[0]);
+    for (int grp = 0; grp < 2 * NMB; ++grp)
+      if (two >> grp & 1u)                               // (uniform)
 #pragma unroll
-    for (int grp = 0; grp < 2 * NMB; ++grp) {
-      if (grp + 1 < 2 * NMB) fetch(grp + 1, av[(grp + 1) & 1]);
+        for (int cb = 0; cb < CB; ++cb) oacc[cb] = MFMA(read_v(vt, grp * CB + cb), pr[grp >> 1][grp & 1], oacc[cb]);
+  };
+  // P.V of a tile; next(i): operand i of what follows (nothing after the last tile)
+  auto accumulate = [&](uint32_t vt, auto next) {
+    if (LO && two) second_parts(vt);
 #pragma unroll
-      for (int cb = 0; cb < CB; ++cb) oacc[cb] = MFMA(av[grp & 1][cb], pv[grp >> 1][grp & 1], oacc[cb]);
-      if (LO && (two >> grp & 1u))                        // (uniform)
+    for (int i = 0; i < RD; ++i) op[i] = read_v(vt, i);
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int cb = 0; cb < CB; ++cb) oacc[cb] = MFMA(av[grp & 1][cb], pr[grp >> 1][grp & 1], oacc[cb]);
+    for (int i = 0; i < NPV; ++i) {
+      oacc[i % CB] = MFMA(op[i % RD], pv[i / (2 * CB)][i / CB & 1], oacc[i % CB]);
+      if (i + RD < NPV) op[i % RD] = read_v(vt, i + RD);
+      else op[i % RD] = next(i + RD - NPV, op[i % RD]);
+      __builtin_amdgcn_sched_barrier(0);
     }
   };
 
@@ -606,32 +658,28 @@ __device__ __forceinline__ void attn_pass(const Prob& pb, WgAt at, AttnSmem<D>& 
     wg_barrier();            // B_-1: every wavefront has its query rows in registers
     issue_tile(1);
     const bool late = wv >= NW / 2;
+    constexpr int S0 = NPV % RD;         // place of the first operand of Q.K
+#pragma unroll
+    for (int i = 0; i < RD; ++i) op[(S0 + i) % RD] = read_k(k_tile(0), i);
 
     for (int t = 0; t < ntiles; ++t) {
       const int kb = kbeg + t * TN;
       issue_tile(t + 2);     // into the K slot of tile t-1 and the V slot of tile t-2, both last read before B_t-1
       __builtin_amdgcn_s_setprio(0);
       // ---- matrix half: P.V of the previous tile, logits S^T[key, row] = K Q^T of this one ----
-      if (t > 0) accumulate(Vs[(t - 1) & 3]);
-      const uint16_t* kt = Ks[t % 3];
+      const uint32_t kt = k_tile(t);
+      if (t > 0) accumulate(v_tile(t - 1), [&](int i, bf16x8) { return read_k(kt, i); });
       f32x16 sacc[NMB];
 #pragma unroll
       for (int mb = 0; mb < NMB; ++mb)
 #pragma unroll
         for (int j = 0; j < 16; ++j) sacc[mb][j] = 0.f;
-      // operand reads in batches of eight ahead of their MFMAs (one LDS round trip per batch)
+      __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int k0 = 0; k0 < KS; k0 += 4) {
-        bf16x8 a[4][NMB];
-#pragma unroll
-        for (int ks = 0; ks < 4; ++ks)
-#pragma unroll
-          for (int mb = 0; mb < NMB; ++mb)
-            a[ks][mb] = as_bf16x8(*(const uint4*)&kt[RingK::off(ko + 32 * mb + rr, 2 * (k0 + ks) + hf)]);
-#pragma unroll
-        for (int ks = 0; ks < 4; ++ks)
-#pragma unroll
-          for (int mb = 0; mb < NMB; ++mb) sacc[mb] = MFMA(a[ks][mb], qf[k0 + ks], sacc[mb]);
+      for (int i = 0; i < NQK; ++i) {
+        sacc[i % NMB] = MFMA(op[(S0 + i) % RD], qf[i / NMB], sacc[i % NMB]);
+        if (i + RD < NQK) op[(S0 + i) % RD] = read_k(kt, i + RD);
+        __builtin_amdgcn_sched_barrier(0);
       }
       __builtin_amdgcn_s_setprio(2);
       if (late) {            // B_t of the late wavefronts: between the halves
@@ -641,13 +689,12 @@ __device__ __forceinline__ void attn_pass(const Prob& pb, WgAt at, AttnSmem<D>& 
       // ---- vector half ----
       const bool tile_mask = (kb + TN > kend) || (pb.causal && kb + TN - 1 > pb.P);
       if (tile_mask) {
+        const int lim = min(kend - 1, vis_last) - (kb + ko + 4 * hf);
 #pragma unroll
         for (int mb = 0; mb < NMB; ++mb)
 #pragma unroll
-          for (int j = 0; j < 16; ++j) {
-            const int n = kb + ko + 32 * mb + cidx(j, hf);
-            if (n >= kend || n > vis_last) sacc[mb][j] = -INFINITY;
-          }
+          for (int j = 0; j < 16; ++j)
+            if (32 * mb + cidx(j, 0) > lim) sacc[mb][j] = -INFINITY;
       }
       // (only one wavefront of the SIMD is in its vector half: independent chains, not one long one)
       auto tile_max = [&] {
@@ -696,21 +743,30 @@ __device__ __forceinline__ void attn_pass(const Prob& pb, WgAt at, AttnSmem<D>& 
         float tinc = tm;                 // largest logit of the tile that joins the sums
         int cand = INT_MAX;
         if (__ballot(dominant) != 0ull) {
-          if (dominant) {
-#pragma unroll
-            for (int mb = 0; mb < NMB; ++mb)
-#pragma unroll
-              for (int j = 0; j < 16; ++j)
-                if (sacc[mb][j] == tm) cand = min(cand, kb + ko + 32 * mb + cidx(j, hf));
-          }
-          cand = xhalf_min(cand);
-          // the new kept-out key leaves the tile: its weight below is exp2(-inf) = 0
-          const int cz = dominant ? cand : -1;
+          // first register of the lane that holds the maximum (-1: none), and the key of it
+          uint32_t eq = 0;
 #pragma unroll
           for (int mb = 0; mb < NMB; ++mb)
 #pragma unroll
-            for (int j = 0; j < 16; ++j)
-              sacc[mb][j] = (kb + ko + 32 * mb + cidx(j, hf)) == cz ? -INFINITY : sacc[mb][j];
+            for (int j = 0; j < 16; j += 4) shift_in_eq4(eq, sacc[mb][j], sacc[mb][j + 1], sacc[mb][j + 2], sacc[mb][j + 3], tm);
+          const int cj = eq ? __builtin_clz(eq) - (32 - 16 * NMB) : -1;
+          const int mine = cj >= 0 && dominant ? kb + ko + 4 * hf + 2 * (cj & ~3) + (cj & 3) : INT_MAX;
+          cand = xhalf_min(mine);
+          // the new kept-out key leaves the tile: its weight below is exp2(-inf) = 0
+          const int cz = dominant && mine == cand ? cj : -1;
+          const float none = -INFINITY;
+          auto leave = [&](auto x) {
+            constexpr int X = decltype(x)::value, MB = X >> 4, J = X & 15;
+            float x0 = sacc[MB][J], x1 = sacc[MB][J + 1], x2 = sacc[MB][J + 2], x3 = sacc[MB][J + 3];
+            set_where4<X>(x0, x1, x2, x3, cz, none);
+            sacc[MB][J] = x0; sacc[MB][J + 1] = x1; sacc[MB][J + 2] = x2; sacc[MB][J + 3] = x3;
+          };
+          leave(std::integral_constant<int, 0>()); leave(std::integral_constant<int, 4>());
+          leave(std::integral_constant<int, 8>()); leave(std::integral_constant<int, 12>());
+          if constexpr (NMB > 1) {
+            leave(std::integral_constant<int, 16>()); leave(std::integral_constant<int, 20>());
+            leave(std::integral_constant<int, 24>()); leave(std::integral_constant<int, 28>());
+          }
           tinc = tile_max();
         }
         // Where nothing of the tile joins (one visible key, and it is kept out) the reference
@@ -729,10 +785,11 @@ __device__ __forceinline__ void attn_pass(const Prob& pb, WgAt at, AttnSmem<D>& 
         if (tref != mref) {
           const float f = __builtin_amdgcn_exp2f((mref - tref) * c2);   // first tile: 2^-inf = 0
           lsum *= f;
+          if (t > 0)                   // (the first tile finds empty sums)
 #pragma unroll
-          for (int cb = 0; cb < CB; ++cb)
+            for (int cb = 0; cb < CB; ++cb)
 #pragma unroll
-            for (int j = 0; j < 16; ++j) oacc[cb][j] *= f;
+              for (int j = 0; j < 16; ++j) oacc[cb][j] *= f;
           mref = tref;
         }
         if (dominant) {
@@ -800,7 +857,7 @@ __device__ __forceinline__ void attn_pass(const Prob& pb, WgAt at, AttnSmem<D>& 
         wg_barrier();
       }
     }
-    accumulate(Vs[(ntiles - 1) & 3]);   // its slot is not a target of the copies still in flight
+    accumulate(v_tile(ntiles - 1), [](int, bf16x8 x) { return x; });   // its slot is not a target of the copies still in flight
     // (wait states before the first read of the sums, spelled out: the last products may lie behind a branch, after which the
     // compiler inserts too few)
     if (LO)
