@@ -252,6 +252,16 @@ int restkv_compact(const restkv_params* p, const void* k, const void* v, const i
                    void* k_out, void* v_out, restkv_stream_t stream);
 
 /*
+ * The four calls of a layer as one: restkv_score, restkv_smooth, restkv_select, restkv_compact with the same arguments and
+ * the same results, bit for bit.  For short layers the smoothing over positions, the selection and the gather are one
+ * launch (its time is stage "select"; "box" and "compact" then have none).  Every argument of every stage is checked
+ * before anything is enqueued; ema, aws_info and aws_d may be NULL.
+ */
+int restkv_evict(const restkv_params* p, const void* q, const void* k, const void* v, const float* gram,
+                 float* score, float* ema, float* final_score, int32_t* aws_info, double* aws_d, int32_t* idx,
+                 void* k_out, void* v_out, void* workspace, size_t workspace_bytes, restkv_stream_t stream);
+
+/*
  * Profiling aid (not part of the method): every kernel launch of a selected stage
  * is bracketed by two HIP events on the caller's stream.  stage_mask: bit s selects
  * stage s (see restkv_stage_name), -1 selects all, 0 turns timing off.  A bracket

@@ -76,6 +76,8 @@ def lib() -> ctypes.CDLL:
         L.restkv_select_static_capacity.restype = sz
         L.restkv_select_static_capacity.argtypes = []
         L.restkv_compact.argtypes = [P, vp, vp, vp, vp, vp, vp]
+        L.restkv_evict.argtypes = [P] + [vp] * 13 + [sz, vp]
+        L.restkv_evict.restype = ctypes.c_int
         L.restkv_strerror.restype = ctypes.c_char_p
         L.restkv_strerror.argtypes = [ctypes.c_int]
         L.restkv_timing_read.argtypes = [vp, vp, ctypes.c_int]
@@ -280,13 +282,9 @@ def alloc_layer_buffers(p: RestkvParams, dtype: torch.dtype, device="cuda") -> L
 
 
 def evict_layer(p: RestkvParams, q, k, v, gram, buf: LayerBuffers, stream=None, fused=False):
-    """The calls of one layer, back to back on one stream (no host synchronisation); with
-    fused=True the score and the smoothing run as the one fused call."""
-    if fused:
-        restkv_score_smooth(p, q, k, v, gram, buf.score, buf.ema, buf.final, buf.aws_info, buf.aws_d,
-                            buf.workspace, stream)
-    else:
-        restkv_score(p, q, k, v, gram, buf.score, buf.workspace, stream)
-        restkv_smooth(p, buf.score, buf.ema, buf.final, buf.aws_info, buf.aws_d, buf.workspace, stream)
-    restkv_select(p, buf.final, buf.idx, buf.workspace, stream)
-    restkv_compact(p, k, v, buf.idx, buf.k_out, buf.v_out, stream)
+    """The stages of one layer as one call on one stream (no host synchronisation).  ``fused`` changes
+    nothing: score and smoothing have the same results, as two calls or as one."""
+    wp, wn = _ws(buf.workspace)
+    _chk(lib().restkv_evict(ctypes.byref(p), _ptr(q), _ptr(k), _ptr(v), _ptr(gram), _ptr(buf.score), _ptr(buf.ema),
+                            _ptr(buf.final), _ptr(buf.aws_info), _ptr(buf.aws_d), _ptr(buf.idx), _ptr(buf.k_out),
+                            _ptr(buf.v_out), wp, wn, _stream(stream)), "restkv_evict")

@@ -262,6 +262,31 @@ int restkv_compact(const restkv_params* p, const void* k, const void* v, const i
   return launch_compact(pb, k, v, idx, k_out, v_out, (hipStream_t)stream);
 }
 
+int restkv_evict(const restkv_params* p, const void* q, const void* k, const void* v, const float* gram, float* score,
+                 float* ema, float* final_score, int32_t* aws_info, double* aws_d, int32_t* idx, void* k_out, void* v_out,
+                 void* workspace, size_t workspace_bytes, restkv_stream_t stream) {
+  Prob pb;
+  int rc = resolve(p, &pb);
+  if (rc) return rc;
+  if (!q || !k || !v || !score || !final_score || !idx || !k_out || !v_out) return RESTKV_EINVAL;
+  // (all sizes first, so that nothing is enqueued when a later stage would fail; the stages use the workspace one after the other)
+  const SmoothWs lay = smooth_ws(pb);
+  rc = check_ws(workspace, workspace_bytes, std::max(std::max(score_ws(pb).bytes, lay.bytes), select_ws_bytes(pb)));
+  if (rc) return rc;
+  rc = restkv_score(p, q, k, v, gram, score, workspace, workspace_bytes, stream);
+  if (rc) return rc;
+  if (short_rows(pb) && finish_eligible(pb, k, v, k_out, v_out)) {
+    unsigned long long* rowsum = (unsigned long long*)((char*)workspace + lay.rowsum);
+    float* e = ema ? ema : (float*)((char*)workspace + lay.ema);
+    launch_short_rows(pb, score, e, rowsum, (hipStream_t)stream);
+    return launch_finish(pb, e, rowsum, final_score, aws_info, aws_d, idx, k, v, k_out, v_out, (hipStream_t)stream);
+  }
+  rc = restkv_smooth(p, score, ema, final_score, aws_info, aws_d, workspace, workspace_bytes, stream);
+  if (!rc) rc = restkv_select(p, final_score, idx, workspace, workspace_bytes, stream);
+  if (!rc) rc = restkv_compact(p, k, v, idx, k_out, v_out, stream);
+  return rc;
+}
+
 const char* restkv_strerror(int code) {
   switch (code) {
     case RESTKV_OK: return "ok";

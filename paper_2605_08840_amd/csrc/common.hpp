@@ -67,6 +67,14 @@ int launch_score_mfma(const Prob& pb, const void* q, const void* k, const void* 
 int score_plan(const Prob& pb, int32_t* plan);     // see restkv_debug_score_plan
 int launch_smooth(const Prob& pb, const float* score, float* ema, float* fin, int32_t* aws_info,
                   double* aws_d, char* ws, const SmoothWs& lay, hipStream_t st);
+// the statistics of a short prefix in one launch: whether it takes this one, and the launch
+bool short_rows(const Prob& pb);
+void launch_short_rows(const Prob& pb, const float* score, float* e, unsigned long long* rowsum, hipStream_t st);
+// box mean, selection and gather of a short layer in one launch, after launch_short_rows
+constexpr int FINISH_MAX = 16384;
+bool finish_eligible(const Prob& pb, const void* k, const void* v, const void* k_out, const void* v_out);
+int launch_finish(const Prob& pb, const float* ema, const unsigned long long* rowsum, float* fin, int32_t* aws_info,
+                  double* aws_d, int32_t* idx, const void* k, const void* v, void* k_out, void* v_out, hipStream_t st);
 size_t select_ws_bytes(const Prob& pb);
 int launch_select(const Prob& pb, const float* fin, int32_t* idx, char* ws, hipStream_t st);
 // the same with the library's own static scratch (RESTKV_EWORKSPACE beyond its capacity)

@@ -9,6 +9,7 @@
 #include <type_traits>
 
 #include "rowselect.hpp"
+#include "window.hpp"
 
 namespace restkv {
 
@@ -406,24 +407,6 @@ __global__ __launch_bounds__(NT, NT == 1024 && NPT == 16 ? 8 : 4) void k_short_r
   if (n < pb.P) ema[(int64_t)g * pb.ld + n] = e;
 }
 
-// Window size and shift from the drift statistic (device function so that every block of
-// the box kernel derives the same integers without a host round trip).
-// (front and rear index sums come in already added up)
-__device__ inline void aws_window(const Prob& pb, unsigned long long sf, unsigned long long sr, int g,
-                                  int& w_s, int& gamma, double& d_front, double& d_rear) {
-  w_s = pb.base_k; gamma = 0; d_front = 0.0; d_rear = 0.0;
-  if (!pb.adaptive) return;
-  const int nf = pb.W / 2;
-  const double bt = (double)min(head_budget(pb, g), pb.P);
-  d_front = (double)sf / (bt * (double)nf);
-  d_rear = (double)sr / (bt * (double)(pb.W - nf));
-  const double x = d_front - d_rear;
-  const double beta = (double)pb.beta;
-  w_s = pb.base_k + 2 * (int)floor(fabs(x) / beta);
-  const int f = (int)floor(x / beta);
-  gamma = x > 0.0 ? f : f + 1;
-}
-
 // final[g,n] = (1/W_s) sum_{j=gamma-half}^{gamma+half} ema[g,n+j], zero outside [0,P).
 // head_grid: parts = ceil(P / (256 BOX_PT)), 256 threads; a thread owns BOX_PT positions 256 apart (the
 // loads of a window offset are independent and coalesced); every workgroup derives the head's
@@ -436,35 +419,10 @@ __global__ __launch_bounds__(256) void k_box(Prob pb, const float* __restrict__ 
                                              double* __restrict__ aws_d) {
   const HeadPart hp = head_part<BY8>(pb);
   const int g = hp.g;
-  __shared__ int sh_ws, sh_gamma;
-  __shared__ unsigned long long sh_sum[2][4];
+  __shared__ AwsSmem aw;
   __shared__ float tile[2 * 256 * BOX_PT];           // span + reach of the window (when it fits)
-  // the W index sums of the head: all loads in flight at once, wavefront sums, then thread 0
-  {
-    unsigned long long sf = 0, sr = 0;
-    if (pb.adaptive)
-      for (int i = threadIdx.x; i < pb.W; i += 256) {
-        const unsigned long long s = rowsum[g * pb.W + i];
-        if (i < pb.W / 2) sf += s; else sr += s;
-      }
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) { sf += __shfl_xor(sf, o, 64); sr += __shfl_xor(sr, o, 64); }
-    if ((threadIdx.x & 63) == 0) { sh_sum[0][threadIdx.x >> 6] = sf; sh_sum[1][threadIdx.x >> 6] = sr; }
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    int w_s0, gamma0;
-    double df, dr;
-    aws_window(pb, sh_sum[0][0] + sh_sum[0][1] + sh_sum[0][2] + sh_sum[0][3],
-               sh_sum[1][0] + sh_sum[1][1] + sh_sum[1][2] + sh_sum[1][3], g, w_s0, gamma0, df, dr);
-    sh_ws = w_s0; sh_gamma = gamma0;
-    if (hp.x == 0) {
-      if (aws_info) { aws_info[2 * g] = w_s0; aws_info[2 * g + 1] = gamma0; }
-      if (aws_d) { aws_d[2 * g] = df; aws_d[2 * g + 1] = dr; }
-    }
-  }
-  __syncthreads();
-  const int w_s = sh_ws, gamma = sh_gamma;
+  int w_s, gamma;
+  head_window<256>(pb, g, rowsum, hp.x == 0, aws_info, aws_d, aw, w_s, gamma);
   const int n0 = hp.x * (256 * BOX_PT) + threadIdx.x;
   const float* e = ema + (int64_t)g * pb.ld;
   const int half = w_s / 2;
@@ -541,6 +499,25 @@ __global__ __launch_bounds__(256) void k_box(Prob pb, const float* __restrict__ 
 
 }  // namespace
 
+// One launch for short prefixes.  Rows above 16384 positions take a compute unit each: two rounds of
+// them (512 rows of 32k: 37 us) lose against three launches that stream (34 us), one (132 rows of 20k:
+// 12 us against 31) does not.
+bool short_rows(const Prob& pb) { return pb.P <= 16384 || (pb.P <= ROW_REG_MAX && pb.W * pb.Hkv <= n_cu()); }
+
+void launch_short_rows(const Prob& pb, const float* score, float* e, unsigned long long* rowsum, hipStream_t st) {
+  const bool vec = (pb.ld & 3) == 0 && (((uintptr_t)score | (uintptr_t)e) & 15u) == 0;
+  by_heads(pb, [&](auto by8) {
+    constexpr bool BY8 = decltype(by8)::value;
+    const int nrow = pb.adaptive ? pb.W : 0;
+    with_row_block(pb.P, [&](auto nt, auto npt) {
+      constexpr int NT = decltype(nt)::value, NPT = decltype(npt)::value;
+      const dim3 gr = head_grid(pb, nrow + (pb.P + NT - 1) / NT);
+      if (vec) RK_LAUNCH(ST_EMA, st, (k_short_rows<NT, NPT, true, BY8>), gr, dim3(NT), 0, st, pb, score, e, rowsum, nrow);
+      else RK_LAUNCH(ST_EMA, st, (k_short_rows<NT, NPT, false, BY8>), gr, dim3(NT), 0, st, pb, score, e, rowsum, nrow);
+    });
+  });
+}
+
 int launch_smooth(const Prob& pb, const float* score, float* ema, float* fin, int32_t* aws_info,
                   double* aws_d, char* ws, const SmoothWs& lay, hipStream_t st) {
   unsigned long long* rowsum = (unsigned long long*)(ws + lay.rowsum);
@@ -552,17 +529,8 @@ int launch_smooth(const Prob& pb, const float* score, float* ema, float* fin, in
   const bool vec = (pb.ld & 3) == 0 && (((uintptr_t)score | (uintptr_t)e) & 15u) == 0;
   by_heads(pb, [&](auto by8) {
     constexpr bool BY8 = decltype(by8)::value;
-    // One launch for short prefixes.  Rows above 16384 positions take a compute unit each: two rounds of
-    // them (512 rows of 32k: 37 us) lose against three launches that stream (34 us), one (132 rows of 20k:
-    // 12 us against 31) does not.
-    if (pb.P <= 16384 || (pb.P <= ROW_REG_MAX && pb.W * pb.Hkv <= n_cu())) {
-      const int nrow = pb.adaptive ? pb.W : 0;
-      with_row_block(pb.P, [&](auto nt, auto npt) {
-        constexpr int NT = decltype(nt)::value, NPT = decltype(npt)::value;
-        const dim3 gr = head_grid(pb, nrow + (pb.P + NT - 1) / NT);
-        if (vec) RK_LAUNCH(ST_EMA, st, (k_short_rows<NT, NPT, true, BY8>), gr, dim3(NT), 0, st, pb, score, e, rowsum, nrow);
-        else RK_LAUNCH(ST_EMA, st, (k_short_rows<NT, NPT, false, BY8>), gr, dim3(NT), 0, st, pb, score, e, rowsum, nrow);
-      });
+    if (short_rows(pb)) {
+      launch_short_rows(pb, score, e, rowsum, st);
     } else {
       if (pb.adaptive)
         RK_LAUNCH(ST_ROWTOPK, st, k_sample_bracket<BY8>, head_grid(pb, pb.W), dim3(512), 0, st, pb, score, thr,

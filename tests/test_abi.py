@@ -125,3 +125,20 @@ def test_binding_has_no_cpu_fallback(rk, monkeypatch):
     monkeypatch.setattr(b, "LIB_PATH", "/nonexistent/librestkv.so")
     with pytest.raises(ImportError):
         b.lib()
+
+
+def test_evict_checks_every_stage_before_it_enqueues(rk):
+    L = rk.lib()
+    p = good(rk)
+    one = ctypes.c_void_p(256)            # never dereferenced on the host
+    ws_n = rk.restkv_workspace_bytes(p)
+
+    def call(p, at=None, ws=one, n=ws_n):
+        # q, k, v, gram, score, ema, final, aws_info, aws_d, idx, k_out, v_out
+        ptrs = [None if j == at else one for j in range(12)]
+        return L.restkv_evict(ctypes.byref(p), *ptrs, ws, n, None)
+
+    for at in (0, 1, 2, 4, 6, 9, 10, 11):
+        assert call(p, at) == -1, at
+    assert call(p, ws=None) == -3 and call(p, n=ws_n - 256) == -3 and call(p, ws=ctypes.c_void_p(264)) == -3
+    assert call(good(rk, budget=32)) == -1 and call(good(rk, head_dim=96)) == -2
