@@ -204,16 +204,22 @@ struct Stage {
 // keys are in LDS (48 KiB for D = 128, two workgroups per compute unit); the next block's loads are in
 // flight while a block is worked on, its K planes are written when the logits have been formed, its V
 // planes when the values have been added up: two barriers per block of 96 MFMAs per wavefront.
-// grid (S, ceil(R / (32 NW)), Hkv), 64 NW threads.
+// Workgroups: S splits x ceil(R / (32 NW)) row blocks x KV heads, 64 NW threads.
+template <int D, int NP, int NW>
+struct AttnSmem {
+  __attribute__((aligned(16))) ColTile<D, NP> Ks;
+  __attribute__((aligned(16))) RowTile<D, NP> Vs;
+  int beyond[NW];                       // a wavefront has found that planes do not hold a value of this split or of its rows
+};
 template <typename T, int D, int NW, bool VEC>
-__global__ __launch_bounds__(NW * 64, NW == 2 ? 1 : 2) void k_attn_f32(Prob pb, const T* __restrict__ q, const T* __restrict__ k,
-                                                         const T* __restrict__ v, int S, int kps, ScorePtrs o) {
+__device__ __forceinline__ void attn_pass(const Prob& pb, int s, int yb, int g, AttnSmem<D, planes_of<T>, NW>& sm, const T* __restrict__ q,
+                                          const T* __restrict__ k, const T* __restrict__ v, int S, int kps, const ScorePtrs& o) {
   constexpr int CB = D / 32, NP = planes_of<T>;
-  __shared__ __attribute__((aligned(16))) ColTile<D, NP> Ks;
-  __shared__ __attribute__((aligned(16))) RowTile<D, NP> Vs;
-  const int s = blockIdx.x, g = blockIdx.z;
+  auto& Ks = sm.Ks;
+  auto& Vs = sm.Vs;
+  auto& beyond = sm.beyond;
   const int l = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), rr = l & 31, hf = l >> 5;
-  const int r = (blockIdx.y * NW + wv) * 32 + rr;       // row inside the KV head
+  const int r = (yb * NW + wv) * 32 + rr;               // row inside the KV head
   const bool valid = r < pb.R;
   const int hl = valid ? r / pb.W : 0, i = valid ? r % pb.W : 0;
   const int vis_last = (pb.causal && valid) ? pb.P + i : pb.L - 1;
@@ -222,7 +228,6 @@ __global__ __launch_bounds__(NW * 64, NW == 2 ? 1 : 2) void k_attn_f32(Prob pb, 
   const int kbeg = s * kps, kend = min(pb.L, kbeg + kps);
   const int nblk = kend > kbeg ? (kend - kbeg + KB - 1) / KB : 0;
 
-  __shared__ int beyond[NW];            // a wavefront has found that planes do not hold a value of this split or of its rows
   bool out;
   Op<NP> qf[D / 16];
   {
@@ -459,15 +464,20 @@ __global__ __launch_bounds__(NW * 64, NW == 2 ? 1 : 2) void k_attn_f32(Prob pb, 
 // (M is symmetric), so that 32x16 pieces below the diagonal are skipped.  The planes of T of the
 // workgroup's head stay in LDS in operand order (one 1 KiB run per piece and plane); a wavefront takes
 // 32 keys at a time, on the N side.  K indices are taken in the order of a C block's registers: the
-// values a lane holds as operands are also the factors of its row dots.  grid (chunks, Hq), 256 threads.
-template <typename T, int D, bool VEC>
-__global__ __launch_bounds__(256, 2) void k_vv_f32(Prob pb, const T* __restrict__ v, const float* __restrict__ gram,
-                                                   float* __restrict__ vv, int ldv) {
-  constexpr int CB = D / 32, KS = D / 16, NP = planes_of<T>;
-  constexpr int NB = CB * (CB + 1);                    // pieces on or above the diagonal: KS - 2 cb of row block cb
-  __shared__ __attribute__((aligned(16))) uint4 Ts[NB][3][64];
-  __shared__ int beyond[4];                            // a wavefront has found that planes do not hold an entry of T
-  const int h = blockIdx.y, g = h / pb.G;
+// values a lane holds as operands are also the factors of its row dots.  Workgroups: chunks x query heads, 64 NW threads.
+template <int D, int NW>
+struct VvSmem {
+  static constexpr int NB = D / 32 * (D / 32 + 1);     // pieces on or above the diagonal: KS - 2 cb of row block cb
+  __attribute__((aligned(16))) uint4 Ts[NB][3][64];
+  int beyond[NW];                                      // a wavefront has found that planes do not hold an entry of T
+};
+template <typename T, int D, int NW, bool VEC>
+__device__ __forceinline__ void vv_pass(const Prob& pb, int chunk, int chunks, int h, VvSmem<D, NW>& sm, const T* __restrict__ v,
+                                        const float* __restrict__ gram, float* __restrict__ vv, int ldv) {
+  constexpr int CB = D / 32, KS = D / 16, NP = planes_of<T>, NB = VvSmem<D, NW>::NB;
+  auto& Ts = sm.Ts;
+  auto& beyond = sm.beyond;
+  const int g = h / pb.G, stride = NW * chunks;
   const int l = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), rr = l & 31, hf = l >> 5;
   const T* vg = v + (int64_t)g * pb.kv_sh;
   const int nb = (pb.P + KB - 1) / KB;
@@ -480,16 +490,16 @@ __global__ __launch_bounds__(256, 2) void k_vv_f32(Prob pb, const T* __restrict_
       vf[a][1] = load4<VEC>(vr + 16 * a + 8);
     }
   };
-  int b = blockIdx.x * 4 + wv;
+  int b = chunk * NW + wv;
   if (b < nb) fetch(b);
   PlaneRange seen;                                     // of the Gram entries this thread has cut into planes
   // (all loads first: one round trip)
-  constexpr int NPC = (NB + 3) / 4;                    // pieces per wavefront
+  constexpr int NPC = (NB + NW - 1) / NW;                   // pieces per wavefront
   const float* Mh = gram + (int64_t)h * D * D;
   f32x4_t m[NPC][2];
 #pragma unroll
   for (int j = 0; j < NPC; ++j) {
-    int cb = 0, a = min(wv + 4 * j, NB - 1);           // piece: row block cb, step 2 cb + a
+    int cb = 0, a = min(wv + NW * j, NB - 1);           // piece: row block cb, step 2 cb + a
     while (a >= KS - 2 * cb) { a -= KS - 2 * cb; ++cb; }
     const float* p = Mh + (32 * cb + rr) * D + 16 * (2 * cb + a) + 4 * hf;
     m[j][0] = quad_of(p);
@@ -497,8 +507,8 @@ __global__ __launch_bounds__(256, 2) void k_vv_f32(Prob pb, const T* __restrict_
   }
 #pragma unroll
   for (int j = 0; j < NPC; ++j) {
-    if (wv + 4 * j >= NB) break;
-    int cb = 0, a = wv + 4 * j;
+    if (wv + NW * j >= NB) break;
+    int cb = 0, a = wv + NW * j;
     while (a >= KS - 2 * cb) { a -= KS - 2 * cb; ++cb; }
     const int i = 32 * cb + rr, j0 = 16 * (2 * cb + a) + 4 * hf;
     float x[8];
@@ -511,12 +521,15 @@ __global__ __launch_bounds__(256, 2) void k_vv_f32(Prob pb, const T* __restrict_
     const Op<3> t = split8<3>(x);
     seen.take(make_float4(x[0], x[1], x[2], x[3]), make_float4(x[4], x[5], x[6], x[7]));
 #pragma unroll
-    for (int p = 0; p < 3; ++p) Ts[wv + 4 * j][p][l] = t.p[p];
+    for (int p = 0; p < 3; ++p) Ts[wv + NW * j][p][l] = t.p[p];
   }
   beyond[wv] = __ballot(seen.out()) != 0ull;
   __syncthreads();
-  bool raw = __builtin_amdgcn_readfirstlane(beyond[0] | beyond[1] | beyond[2] | beyond[3]);
-  for (; b < nb; b += 4 * gridDim.x) {
+  int any = 0;
+#pragma unroll
+  for (int j = 0; j < NW; ++j) any |= beyond[j];
+  bool raw = __builtin_amdgcn_readfirstlane(any);
+  for (; b < nb; b += stride) {
     Op<NP> vo[KS];
 #pragma unroll
     for (int a = 0; a < KS; ++a) vo[a] = split8<NP>(vf[a][0], vf[a][1]);
@@ -540,14 +553,14 @@ __global__ __launch_bounds__(256, 2) void k_vv_f32(Prob pb, const T* __restrict_
     const int n = b * KB + rr;
     raw |= __ballot(!(fabsf(acc) < INFINITY)) != 0ull;
     acc = half_sum(acc);
-    if (b + 4 * (int)gridDim.x < nb) fetch(b + 4 * gridDim.x);
+    if (b + stride < nb) fetch(b + stride);
     if (hf == 0 && n < pb.P) vv[(int64_t)h * ldv + n] = acc;
   }
   if (__builtin_expect(!raw, 1)) return;
   // This wavefront's blocks once more, on the FP32 instruction with everything from memory: planes do not hold T or a value.  (A
   // value beyond them has made a sum NaN or infinite; with T in their range one too small for them has a square below FP32.)
 #pragma unroll 1
-  for (int b = blockIdx.x * 4 + wv; b < nb; b += 4 * gridDim.x) {
+  for (int b = chunk * NW + wv; b < nb; b += stride) {
     const int n = b * KB + rr;
     const T* vr = vg + (int64_t)min(n, pb.P - 1) * pb.kv_st + 4 * hf;
     float acc = 0.f;
@@ -570,6 +583,37 @@ __global__ __launch_bounds__(256, 2) void k_vv_f32(Prob pb, const T* __restrict_
     }
     acc = half_sum(acc);
     if (hf == 0 && n < pb.P) vv[(int64_t)h * ldv + n] = acc;
+  }
+}
+
+// The two passes that need nothing of each other, one launch: the first workgroups are the attention pass's (split fastest,
+// then row block, then head), the others the value-Gram pass's (chunk fastest).  Either one is five to forty microseconds of
+// workgroups of few blocks, and its start and end hide behind the other's.  Score + smoothing, 32/8 heads of 128, window 32: 8k tokens 131 ->
+// 128 us, 1.5k 77.6 -> 72.5; 28/4 heads, 5k 130 -> 115; 4/2 heads, 16k 88 -> 77; heads of 64, 8/8, 12k 75 -> 67; four heads of 64, 1k, whole
+// path 41.7 -> 37.0.  (With the value-Gram pass first 4/2 heads, 16k 91.)  Where the launch is not taken (see run): 16/4 heads of 128,
+// window 16, 16k 126 us in two launches, 137 in one; 8/8 heads, window 32, 8k 75.7 and 77.4, 16k 116 and 118; 28/4, window 8, 8k 133 and 131, 16k 190 and 195.
+//
+// ATTN, VV: whether that pass is there; alone it has a grid of its own dimensions, (S, gy, Hkv) or (chunks, Hq).  64 NW threads.
+struct AttnArgs { int S, gy, kps; };
+struct VvArgs { int at, chunks, ldv; };               // workgroups from `at` on
+template <typename T, int D, int NW, bool VEC, bool ATTN, bool VV>
+__global__ __launch_bounds__(NW * 64, NW == 2 ? 1 : 2) void k_attn_vv_f32(Prob pb, const T* __restrict__ q, const T* __restrict__ k,
+                                                                          const T* __restrict__ v, const float* __restrict__ gram,
+                                                                          ScorePtrs o, AttnArgs aa, VvArgs va) {
+  __shared__ union { AttnSmem<ATTN ? D : 32, planes_of<T>, NW> a; VvSmem<VV ? D : 32, NW> v; } sm;
+  if constexpr (!VV) {
+    attn_pass<T, D, NW, VEC>(pb, blockIdx.x, blockIdx.y, blockIdx.z, sm.a, q, k, v, aa.S, aa.kps, o);
+  } else if constexpr (!ATTN) {
+    vv_pass<T, D, NW, VEC>(pb, blockIdx.x, va.chunks, blockIdx.y, sm.v, v, gram, o.vv, va.ldv);
+  } else {
+    const int id = blockIdx.x;
+    if (id < va.at) {
+      const int y = id / aa.S;
+      attn_pass<T, D, NW, VEC>(pb, id - y * aa.S, y % aa.gy, y / aa.gy, sm.a, q, k, v, aa.S, aa.kps, o);
+    } else {
+      const int x = id - va.at, h = x / va.chunks;
+      vv_pass<T, D, NW, VEC>(pb, x - h * va.chunks, va.chunks, h, sm.v, v, gram, o.vv, va.ldv);
+    }
   }
 }
 
@@ -821,21 +865,33 @@ int run(const Prob& pb, const void* q, const void* k, const void* v, const float
   if (pb.ext_lse) {
     S = 1;                                         // the caller's attention output and log-sum-exp stand in for the pass: one "split"
     part_z = pb.ext_out;
-  } else {
-    if (nw == 4)
-      RK_LAUNCH(ST_ATTN, st, (k_attn_f32<T, D, 4, VEC>), dim3(S, gy, pb.Hkv), dim3(256), 0, st, pb, qq, kk, vp, S, kps, w);
-    else
-      RK_LAUNCH(ST_ATTN, st, (k_attn_f32<T, D, 2, VEC>), dim3(S, gy, pb.Hkv), dim3(128), 0, st, pb, qq, kk, vp, S, kps, w);
   }
+  const int nb = (pb.P + KB - 1) / KB;             // blocks of keys
+  const AttnArgs aa = {S, gy, kps};
+  const int na = S * gy * pb.Hkv;                  // workgroups of the attention pass
+  // Together, unless two wavefronts hold all rows of a head of 128 and have their splits on every compute unit: with 350 registers
+  // each they are one to a SIMD, where the value-Gram pass wants two.
+  const bool joint = gram && !pb.ext_lse && (D == 64 || nw == 4 || 2 * na <= cu);
+  auto attn_vv = [&](auto nwc, auto attn, auto vvp, const dim3& gr, const VvArgs& va) {
+    constexpr int NW = decltype(nwc)::value;
+    constexpr bool ATTN = decltype(attn)::value, VV = decltype(vvp)::value;
+    RK_LAUNCH(ATTN ? ST_ATTN : ST_VV, st, (k_attn_vv_f32<T, D, NW, VEC, ATTN, VV>), gr, dim3(64 * NW), 0, st, pb, qq, kk, vp, gram, w,
+              aa, va);
+  };
+  auto chunks_of = [&](int nwv) { return std::min((2 * cu + pb.Hq - 1) / pb.Hq, (nb + nwv - 1) / nwv); };
+  auto attn = [&](auto nwc) {
+    const int chunks = chunks_of(decltype(nwc)::value);
+    if (joint) attn_vv(nwc, std::true_type{}, std::true_type{}, dim3(na + chunks * pb.Hq), VvArgs{na, chunks, lay.ldv});
+    else attn_vv(nwc, std::true_type{}, std::false_type{}, dim3(S, gy, pb.Hkv), VvArgs{});
+  };
+  const std::integral_constant<int, 4> four;
+  if (!pb.ext_lse) {
+    if (nw == 4) attn(four);
+    else attn(std::integral_constant<int, 2>{});
+  }
+  if (gram && !joint) attn_vv(four, std::false_type{}, std::true_type{}, dim3(chunks_of(4), pb.Hq), VvArgs{0, chunks_of(4), lay.ldv});
+  if (!gram) RK_LAUNCH(ST_VV, st, (k_vnorm2_f32<T, D>), dim3((pb.P + 255) / 256, pb.Hkv), dim3(256), 0, st, pb, vp, w.vv, lay.ldv);
   launch_combine<T, D, 2>(pb, vp, S, gram, w, part_z, qq, 0, 0, st);
-  const int nb = (pb.P + KB - 1) / KB;               // blocks of keys
-  if (gram) {
-    int chunks = (2 * cu + pb.Hq - 1) / pb.Hq;
-    chunks = std::min(chunks, (nb + 3) / 4);
-    RK_LAUNCH(ST_VV, st, (k_vv_f32<T, D, VEC>), dim3(chunks, pb.Hq), dim3(256), 0, st, pb, vp, gram, w.vv, lay.ldv);
-  } else {
-    RK_LAUNCH(ST_VV, st, (k_vnorm2_f32<T, D>), dim3((pb.P + 255) / 256, pb.Hkv), dim3(256), 0, st, pb, vp, w.vv, lay.ldv);
-  }
   // one wavefront per workgroup while that leaves compute units idle, else four that share the staged rows
   const int gw = (pb.W + 31) / 32;
   if ((int64_t)nb * gw * pb.Hkv <= 2 * cu)
