@@ -666,15 +666,23 @@ __device__ __forceinline__ void roots(float (&x)[4]) {
 // (both at once are 192 registers, and two wavefronts per SIMD have 256 each).  The planes of a head's
 // q and u rows pass through double-buffered LDS, shared by the workgroup's wavefronts, the next rows' loads in
 // flight while a head is worked on.  grid (ceil(P / (32 NW)), ceil(W / 32), Hkv), 64 NW threads.
-template <typename T, int D, int NW, bool VEC>
-__global__ __launch_bounds__(NW * 64, NW == 1 ? 1 : 2) void k_score_f32(Prob pb, const T* __restrict__ q, const T* __restrict__ k,
+//
+// HS: the wavefronts of a workgroup share 32 keys and divide the heads of the group; each has the planes of the K and V rows in
+// registers and an LDS buffer of its own for its heads' rows, and their sums meet in LDS at the end.  One wavefront per 32 keys
+// that walks all heads is a serial chain: per head 96 products on one accumulator and 600 vector instructions, at one
+// instruction per six cycles for a wavefront that has a SIMD to itself.  Score + smoothing, one wavefront walking the heads and HS:
+// 32/8 heads of 128, window 32, 1k tokens 60.3 -> 48.2 us; 28/4, 2k 90.7 -> 66.5; 64/8, 1k 98.1 -> 70.4; 4/2, 4k 51.0 -> 46.7; 4/1 heads
+// of 128, 2k, whole path 56.0 -> 44.5; 4/2 heads of 64, 1k, whole path 35.8 -> 34.5.  grid (ceil(P / 32), ceil(W / 32), Hkv).
+template <typename T, int D, int NW, bool VEC, bool HS>
+__global__ __launch_bounds__(NW * 64, NW == 1 || HS ? 1 : 2) void k_score_f32(Prob pb, const T* __restrict__ q, const T* __restrict__ k,
                                                           const T* __restrict__ v, ScorePtrs o, int ldv,
                                                           float* __restrict__ score) {
   constexpr int KS = D / 16, NP = planes_of<T>, HC = 2;
-  __shared__ __attribute__((aligned(1024))) char rows[2][row_item(D)];
+  constexpr int PL = 3 * KS * 1024;          // planes of an item
+  __shared__ __attribute__((aligned(1024))) char rows[HS ? NW : 2][row_item(D) + (HS ? 1024 : 0)];
   const int g = blockIdx.z, i0 = blockIdx.y * 32;
   const int l = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), rr = l & 31, hf = l >> 5;
-  const int n = (blockIdx.x * NW + wv) * KB + rr, nc = min(n, pb.P - 1);
+  const int n = (HS ? blockIdx.x : blockIdx.x * NW + wv) * KB + rr, nc = min(n, pb.P - 1);
   const T* kr = k + (int64_t)g * pb.kv_sh + (int64_t)nc * pb.kv_st + 8 * hf;
   const T* vr = v + (int64_t)g * pb.kv_sh + (int64_t)nc * pb.kv_st + 8 * hf;
   const float c2 = pb.scale * LOG2E;
@@ -684,20 +692,22 @@ __global__ __launch_bounds__(NW * 64, NW == 1 ? 1 : 2) void k_score_f32(Prob pb,
   // Item (head, which) on its way to LDS: q rows with the statistics of their weights (maximum, denominator), or
   // u rows with zz, the champion's key and its score.
   const char* const items = (const char*)o.op + (int64_t)(g * pb.G * gridDim.y + blockIdx.y) * 2 * row_item(D);
+  auto planes = [&](int bf) { return &rows[HS ? wv : bf][0]; };      // (HS: one buffer for the planes, two for the statistics)
+  auto stats = [&](int bf) { return planes(bf) + PL + (HS ? bf * 1024 : 0); };
   auto copy_item = [&](int hl, int which, int bf) {
     const int np = which ? 3 : NP;
     const char* src = items + ((int64_t)hl * gridDim.y * 2 + which) * row_item(D);
     // (a row past the window's end becomes a copy of the last one)
     const int row = min(rr, pb.W - 1 - i0);
-    for (int x = wv; x < np * KS; x += NW) dma_1k(src + x * 1024, 16u * (uint32_t)(32 * hf + row), &rows[bf][x * 1024]);
-    if (wv == NW - 1) dma_1k(src + 3 * KS * 1024, 16u * (uint32_t)row, &rows[bf][3 * KS * 1024]);
+    for (int x = HS ? 0 : wv; x < np * KS; x += HS ? 1 : NW) dma_1k(src + x * 1024, 16u * (uint32_t)(32 * hf + row), planes(bf) + x * 1024);
+    if (HS || wv == NW - 1) dma_1k(src + PL, 16u * (uint32_t)row, stats(bf));
   };
-  auto stat = [&](int bf, int j) { return *(const float4*)&rows[bf][3 * KS * 1024 + cidx(j, hf) * 16]; };
-  auto row_op = [&](int bf, int a, int p) { return *(const uint4*)&rows[bf][(p * KS + a) * 1024 + l * 16]; };
+  auto stat = [&](int bf, int j) { return *(const float4*)(stats(bf) + cidx(j, hf) * 16); };
+  auto row_op = [&](int bf, int a, int p) { return *(const uint4*)(planes(bf) + (p * KS + a) * 1024 + l * 16); };
   // row rr: in FP32 if it is out of the planes' range; four of its values, those from 8 a + 4 hf on
-  auto raw_row = [&](int bf) { return *(const float*)&rows[bf][3 * KS * 1024 + rr * 16 + 12] != 0.f; };
+  auto raw_row = [&](int bf) { return *(const float*)(stats(bf) + rr * 16 + 12) != 0.f; };
   auto row_quad = [&](int bf, int a, bool raw, auto np) {
-    const char* const at = &rows[bf][(a >> 1) * 1024 + (a & 1) * 512 + rr * 16];
+    const char* const at = planes(bf) + (a >> 1) * 1024 + (a & 1) * 512 + rr * 16;
     const float4 x = *(const float4*)(at + hf * KS * 1024);
     f32x4_t s = quad_of((const bf16_t*)(at + 8 * hf));
 #pragma unroll
@@ -718,8 +728,28 @@ __global__ __launch_bounds__(NW * 64, NW == 1 ? 1 : 2) void k_score_f32(Prob pb,
     __syncthreads();
   };
   Op<NP> kv[KS];                  // planes of this lane's K row, then of its V row
+  // One wavefront in a workgroup has registers for both rows: asked for at once and before the first turn, they are one round trip.
+  constexpr bool BOTH = NW == 1 || HS;
+  Op<NP> kk[BOTH ? KS : 1], vo[BOTH ? KS : 1];
+  if constexpr (BOTH) {
+    float4 x[2 * KS], y[2 * KS];
+#pragma unroll
+    for (int a = 0; a < KS; ++a) {
+      x[2 * a] = load4<VEC>(kr + 16 * a); x[2 * a + 1] = load4<VEC>(kr + 16 * a + 4);
+      y[2 * a] = load4<VEC>(vr + 16 * a); y[2 * a + 1] = load4<VEC>(vr + 16 * a + 4);
+    }
+    if (!HS || wv < pb.G) copy_item(HS ? wv : 0, 0, 0);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int a = 0; a < KS; ++a) {
+      kk[a] = split8<NP>(x[2 * a], x[2 * a + 1]);
+      vo[a] = split8<NP>(y[2 * a], y[2 * a + 1]);
+    }
+  }
   auto load_kv = [&](const T* p) {
-    asm volatile("" : "+v"(p));   // (both rows' planes would be taken out of the loop over the chunks, and spill)
+    int o = 0;                    // (both rows' planes would be taken out of the loop over the chunks, and spill)
+    asm volatile("" : "+v"(o));
+    p += o;
 #pragma unroll
     for (int a = 0; a < KS; ++a) {
       kv[a] = split8<NP>(load4<VEC>(p + 16 * a), load4<VEC>(p + 16 * a + 4));
@@ -777,13 +807,66 @@ __global__ __launch_bounds__(NW * 64, NW == 1 ? 1 : 2) void k_score_f32(Prob pb,
   float out[16];
 #pragma unroll
   for (int j = 0; j < 16; ++j) out[j] = 0.f;
-  // (a lane's rows come in before the turns: their round trip runs beside the copies')
-  copy_item(0, 0, 0);
+  if constexpr (HS) {
+    // this wavefront's heads; nothing is shared until the end
+    auto landed = [] { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); };
+    for (int h = wv; h < pb.G; h += NW) {
+      const float vvn = o.vv[(int64_t)(g * pb.G + h) * ldv + nc];
+      f32x16 wt, cacc;
+#pragma unroll
+      for (int j = 0; j < 16; ++j) { wt[j] = 0.f; cacc[j] = 0.f; }
+      landed();
+      bool raw = raw_row(0);
+      contract<NP, NP, KS>([&](int) -> f32x16& { return wt; }, [&](int a, int p) { return row_op(0, a, p); }, [&](int a) { return kk[a]; });
+      settle(wt);
+      if (beyond(sums_of(wt), raw)) {
+        raw_product(wt, 0, kr, std::integral_constant<int, NP>{});
+        settle(wt);
+      }
+      copy_item(h, 1, 1);                              // (the q planes have been read; their statistics stay)
+      weigh(wt, 0);
+      landed();
+      raw = raw_row(1);
+      contract<3, NP, KS>([&](int) -> f32x16& { return cacc; }, [&](int a, int p) { return row_op(1, a, p); }, [&](int a) { return vo[a]; });
+      settle(cacc);
+      if (beyond(sums_of(cacc), raw)) {
+        raw_product(cacc, 1, vr, std::integral_constant<int, 3>{});
+        settle(cacc);
+      }
+      if (h + NW < pb.G) copy_item(h + NW, 0, 0);
+      measure(cacc, wt, 1, vvn);
+#pragma unroll
+      for (int j = 0; j < 16; ++j) out[j] = pb.gmax ? fmaxf(out[j], cacc[j]) : out[j] + cacc[j];
+    }
+    // the heads of the group meet, in the order of the wavefronts, which take a quarter of the rows each
+    float* const sums = (float*)&rows[0][0];
+    __syncthreads();                                   // every wavefront is done with its buffer
+#pragma unroll
+    for (int j = 0; j < 16; ++j) sums[(wv * 16 + j) * 64 + l] = out[j];
+    __syncthreads();
+    const float invG = pb.gmax ? 1.f : 1.0f / (float)pb.G;
+#pragma unroll
+    for (int jj = 0; jj < 16 / NW; ++jj) {
+      const int j = wv * (16 / NW) + jj, i = i0 + 8 * (j >> 2) + 4 * hf + (j & 3);
+      float x = sums[j * 64 + l];
+#pragma unroll
+      for (int k = 1; k < NW; ++k) {
+        const float y = sums[(k * 16 + j) * 64 + l];
+        x = pb.gmax ? fmaxf(x, y) : x + y;
+      }
+      if (n < pb.P && i < pb.W) score[((int64_t)g * pb.W + i) * pb.ld + n] = x * invG;
+    }
+    return;
+  }
+  if constexpr (!BOTH) copy_item(0, 0, 0);
   turn();
   int bf = 0;                     // buffer of the current rows; the other one was last read before the last barrier
   for (int h0 = 0; h0 < pb.G; h0 += HC) {
     f32x16 wt[HC];                // logits, then A / (1 - A), of the heads of this chunk
-    load_kv(kr);
+    float vvn[HC];
+#pragma unroll
+    for (int c = 0; c < HC; ++c) vvn[c] = o.vv[(int64_t)(g * pb.G + min(h0 + c, pb.G - 1)) * ldv + nc];
+    if constexpr (!BOTH) load_kv(kr);
 #pragma unroll
     for (int c = 0; c < HC; ++c) {
       if (h0 + c >= pb.G) break;                       // (uniform)
@@ -793,7 +876,7 @@ __global__ __launch_bounds__(NW * 64, NW == 1 ? 1 : 2) void k_score_f32(Prob pb,
 #pragma unroll
       for (int j = 0; j < 16; ++j) sacc[j] = 0.f;
       const bool raw = raw_row(bf);
-      contract<NP, NP, KS>([&](int) -> f32x16& { return sacc; }, [&](int a, int p) { return row_op(bf, a, p); }, [&](int a) { return kv[a]; });
+      contract<NP, NP, KS>([&](int) -> f32x16& { return sacc; }, [&](int a, int p) { return row_op(bf, a, p); }, [&](int a) { return BOTH ? kk[BOTH ? a : 0] : kv[a]; });
       settle(sacc);
       const float t = sums_of(sacc);
       weigh(sacc, bf);
@@ -806,25 +889,24 @@ __global__ __launch_bounds__(NW * 64, NW == 1 ? 1 : 2) void k_score_f32(Prob pb,
       turn();
       bf ^= 1;
     }
-    load_kv(vr);
+    if constexpr (!BOTH) load_kv(vr);
 #pragma unroll
     for (int c = 0; c < HC; ++c) {
       if (h0 + c >= pb.G) break;
       const bool last = c == HC - 1 || h0 + c + 1 == pb.G, end = h0 + c + 1 == pb.G;
-      const float vvn = o.vv[(int64_t)(g * pb.G + h0 + c) * ldv + nc];
       if (!last) copy_item(h0 + c + 1, 1, bf ^ 1); else if (!end) copy_item(h0 + HC, 0, bf ^ 1);
       f32x16 cacc;
 #pragma unroll
       for (int j = 0; j < 16; ++j) cacc[j] = 0.f;
       const bool raw = raw_row(bf);
-      contract<3, NP, KS>([&](int) -> f32x16& { return cacc; }, [&](int a, int p) { return row_op(bf, a, p); }, [&](int a) { return kv[a]; });
+      contract<3, NP, KS>([&](int) -> f32x16& { return cacc; }, [&](int a, int p) { return row_op(bf, a, p); }, [&](int a) { return BOTH ? vo[BOTH ? a : 0] : kv[a]; });
       settle(cacc);
       const float t = sums_of(cacc);
-      measure(cacc, wt[c], bf, vvn);
+      measure(cacc, wt[c], bf, vvn[c]);
       if (beyond(t, raw)) {
         raw_product(cacc, bf, vr, std::integral_constant<int, 3>{});
         settle(cacc);
-        measure(cacc, wt[c], bf, vvn);
+        measure(cacc, wt[c], bf, vvn[c]);
       }
 #pragma unroll
       for (int j = 0; j < 16; ++j) out[j] = pb.gmax ? fmaxf(out[j], cacc[j]) : out[j] + cacc[j];
@@ -892,13 +974,27 @@ int run(const Prob& pb, const void* q, const void* k, const void* v, const float
   if (gram && !joint) attn_vv(four, std::false_type{}, std::true_type{}, dim3(chunks_of(4), pb.Hq), VvArgs{0, chunks_of(4), lay.ldv});
   if (!gram) RK_LAUNCH(ST_VV, st, (k_vnorm2_f32<T, D>), dim3((pb.P + 255) / 256, pb.Hkv), dim3(256), 0, st, pb, vp, w.vv, lay.ldv);
   launch_combine<T, D, 2>(pb, vp, S, gram, w, part_z, qq, 0, 0, st);
-  // one wavefront per workgroup while that leaves compute units idle, else four that share the staged rows
+  // The heads of a group on up to four wavefronts while a workgroup of them for every 32 keys and positions fits the chip at once (D =
+  // 128: one to a compute unit by registers and LDS, two rounds still pay; D = 64: two), else four wavefronts of 32 keys that share the
+  // staged rows.  Score + smoothing, both sides of the limits: heads of 128, 500 workgroups, 28/4 heads 96 us against 104, 4/2 heads 57.2 /
+  // 59.9, 1000 workgroups, 32/8 heads 110 / 94; heads of 64, 750 workgroups, 28/4 heads 68.9 / 77.5, 32/8 57.2 / 59.8, 1000 workgroups,
+  // 16/4 heads 58.3 / 57.2, 32/8 61.6 / 61.3.  A group of one head has one wavefront while that leaves compute units idle.
   const int gw = (pb.W + 31) / 32;
-  if ((int64_t)nb * gw * pb.Hkv <= 2 * cu)
-    RK_LAUNCH(ST_SCORE, st, (k_score_f32<T, D, 1, VEC>), dim3(nb, gw, pb.Hkv), dim3(64), 0, st, pb, qq, kk, vp, w, lay.ldv, score);
-  else
-    RK_LAUNCH(ST_SCORE, st, (k_score_f32<T, D, 4, VEC>), dim3((nb + 3) / 4, gw, pb.Hkv), dim3(256), 0, st, pb, qq, kk, vp, w, lay.ldv,
-              score);
+  const int64_t nwg = (int64_t)nb * gw * pb.Hkv;
+  auto score_pass = [&](auto nwc, auto hs) {
+    constexpr int NW = decltype(nwc)::value;
+    constexpr bool HS = decltype(hs)::value;
+    RK_LAUNCH(ST_SCORE, st, (k_score_f32<T, D, NW, VEC, HS>), dim3(HS ? nb : (nb + NW - 1) / NW, gw, pb.Hkv), dim3(64 * NW), 0, st, pb, qq, kk,
+              vp, w, lay.ldv, score);
+  };
+  if (pb.G >= 2 && nwg <= (D == 64 ? 3 : 2) * cu) {
+    if (pb.G == 2) score_pass(std::integral_constant<int, 2>{}, std::true_type{});
+    else score_pass(four, std::true_type{});
+  } else if (nwg <= 2 * cu) {
+    score_pass(std::integral_constant<int, 1>{}, std::false_type{});
+  } else {
+    score_pass(four, std::false_type{});
+  }
   return hip_status();
 }
 

@@ -280,3 +280,24 @@ def test_fp32_operands_far_from_one(rk, d, W, q2, k2, v2, m2):  # noqa: F811
         args = heads_of(w, q, k, v, gram, g)
         ref = scores64(*args)
         assert distance(got[g], ref) <= fp32_bound(w, ref, args), f"head {g}"
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("Hq,Hkv,d,P", [
+    (12, 4, 128, 4096), (12, 4, 128, 4097),       # 512 workgroups: the last size at which the heads of a group have wavefronts of their own
+    (8, 4, 64, 6144), (8, 4, 64, 6145),           # the same for heads of 64, two wavefronts
+    (20, 4, 64, 6144), (20, 4, 64, 6145),         # five heads on four wavefronts
+])
+def test_fp32_heads_side_by_side_and_one_after_the_other(rk, Hq, Hkv, d, P):  # noqa: F811
+    """Either side of the rule, with keys that planes do not hold."""
+    w, q, k, v, wo = fp32_layer(Hq, Hkv, d, P + 3, 3, 0.3)
+    q[..., 5] = q[..., 5].abs() + 0.5
+    gone = [0, 31, 300, P - 1]
+    k[:, gone] = 0.0
+    k[:, gone, 5] = float("-inf")
+    got, gram = gpu_scores(rk, w, q, k, v, wo)
+    for g in (0, Hkv - 1):
+        args = heads_of(w, q, k.clamp_min(-1e30), v, gram, g)
+        ref = scores64(*args)
+        assert bool((got[g][:, gone] == 0).all())
+        assert distance(got[g], ref) <= fp32_bound(w, ref, args), f"head {g}"
