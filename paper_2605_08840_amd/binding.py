@@ -282,8 +282,13 @@ def alloc_layer_buffers(p: RestkvParams, dtype: torch.dtype, device="cuda") -> L
 
 
 def evict_layer(p: RestkvParams, q, k, v, gram, buf: LayerBuffers, stream=None, fused=False):
-    """The stages of one layer as one call on one stream (no host synchronisation).  ``fused`` changes
-    nothing: score and smoothing have the same results, as two calls or as one."""
+    """The stages of one layer on one stream (no host synchronisation): one call, or with fused=True the fused call
+    of score and smoothing (restkv_score_smooth), then selection and gather."""
+    if fused:
+        restkv_score_smooth(p, q, k, v, gram, buf.score, buf.ema, buf.final, buf.aws_info, buf.aws_d, buf.workspace, stream)
+        restkv_select(p, buf.final, buf.idx, buf.workspace, stream)
+        restkv_compact(p, k, v, buf.idx, buf.k_out, buf.v_out, stream)
+        return
     wp, wn = _ws(buf.workspace)
     _chk(lib().restkv_evict(ctypes.byref(p), _ptr(q), _ptr(k), _ptr(v), _ptr(gram), _ptr(buf.score), _ptr(buf.ema),
                             _ptr(buf.final), _ptr(buf.aws_info), _ptr(buf.aws_d), _ptr(buf.idx), _ptr(buf.k_out),

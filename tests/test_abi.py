@@ -5,6 +5,7 @@ import os
 import re
 
 import pytest
+import torch
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
@@ -142,3 +143,22 @@ def test_evict_checks_every_stage_before_it_enqueues(rk):
         assert call(p, at) == -1, at
     assert call(p, ws=None) == -3 and call(p, n=ws_n - 256) == -3 and call(p, ws=ctypes.c_void_p(264)) == -3
     assert call(good(rk, budget=32)) == -1 and call(good(rk, head_dim=96)) == -2
+
+
+@pytest.mark.parametrize("fused,calls", [(False, ["restkv_evict"]),
+                                         (True, ["restkv_score_smooth", "restkv_select", "restkv_compact"])])
+def test_fused_switch_of_a_layer_reaches_the_fused_call(rk, monkeypatch, fused, calls):
+    import types
+
+    import paper_2605_08840_amd.binding as b
+    p, seen = good(rk), []
+    buf = rk.alloc_layer_buffers(p, torch.float32, "cpu")
+
+    class Recorder:
+        def __getattr__(self, name):
+            return lambda *args: seen.append(name) or 0
+
+    monkeypatch.setattr(b, "_lib", Recorder())
+    q, k, v, gram = torch.empty(4, 32, 64), torch.empty(2, 1024, 64), torch.empty(2, 1024, 64), torch.empty(4, 64, 64)
+    rk.evict_layer(p, q, k, v, gram, buf, stream=types.SimpleNamespace(cuda_stream=0), fused=fused)
+    assert seen == calls
