@@ -23,21 +23,23 @@ PEAK_FP32 = 157.3e12         # vector FP32, FLOP/s
 PEAK_HBM = 8.0e12            # HBM3E, B/s
 
 
-def stage_work(w, stage: str):
+def stage_work(w, stage: str, seen):
     """Algorithmic work of one layer pass of each stage as (flops, bytes): the flops of its
     contractions (the logits recomputed by the scoring pass are not counted) and the bytes it
     must move to and from HBM once (inputs read once, outputs written once; split partials and
-    other scratch of the implementation are not counted)."""
+    other scratch of the implementation are not counted).  seen: the stages that had launches.  The
+    work of a stage without any is in the launch that counts under another name: value-Gram pass
+    under "attn_partial", box mean and gather of a short layer under "select"."""
     Hq, Hkv, d, L, W, P, B = w.n_q_heads, w.n_kv_heads, w.head_dim, w.seq_len, w.window, w.prefix, w.budget
     esz = 4 if w.dtype == "f32" else 2
     if stage == "attn_partial":      # q K^T and A V over all L keys; K and V read once
         flops, nbytes = 2 * (2.0 * Hq * W * L * d), 2.0 * Hkv * L * d * esz + Hq * W * d * (esz + 4.0)
-        if w.dtype != "f32":         # bf16: V M_h for every query head in the same launch, vv written
+        if "vv" not in seen:         # V M_h for every query head in the same launch, vv written
             flops, nbytes = flops + 2.0 * Hq * P * d * d, nbytes + 4.0 * Hq * P
         return flops, nbytes
     if stage == "score":             # cross term u V^T; K, V prefix and vv read, raw score written
         return 2.0 * Hq * W * P * d, 2.0 * Hkv * P * d * esz + 4.0 * Hq * P + 4.0 * Hkv * W * P
-    if stage == "vv":                # V M_h for every query head (float32 layers: a launch of its own)
+    if stage == "vv":                # V M_h for every query head (float32 layers, where it is a launch of its own)
         return 2.0 * Hq * P * d * d, 1.0 * Hkv * P * d * esz + 4.0 * Hq * P
     if stage == "ema":               # one read of the raw score, EMA written
         return 0.0, 4.0 * Hkv * W * P + 4.0 * Hkv * P
@@ -45,20 +47,23 @@ def stage_work(w, stage: str):
         return 0.0, 0.0
     if stage == "box":
         return 0.0, 8.0 * Hkv * P
+    gather = 2.0 * 2.0 * Hkv * B * d * esz      # read and write of the kept K and V rows
+    if stage == "select" and "box" not in seen:      # EMA read, final scores and list written, rows gathered
+        return 0.0, 8.0 * Hkv * P + 4.0 * Hkv * B + gather
     if stage == "select":
         return 0.0, 4.0 * Hkv * P + 4.0 * Hkv * B
-    if stage == "compact":           # read and write of the kept K and V rows
-        return 0.0, 2.0 * 2.0 * Hkv * B * d * esz
+    if stage == "compact":
+        return 0.0, gather
     return 0.0, 0.0
 
 
-def stage_read_write(w, stage: str):
+def stage_read_write(w, stage: str, seen):
     """The algorithmic bytes of stage_work split into (read, written), or None for the stages
     without a streaming share."""
     Hq, Hkv, d, L, W, P, B = w.n_q_heads, w.n_kv_heads, w.head_dim, w.seq_len, w.window, w.prefix, w.budget
     esz = 4 if w.dtype == "f32" else 2
     if stage == "attn_partial":
-        return 2.0 * Hkv * L * d * esz + Hq * W * d * esz, 4.0 * Hq * W * d + (0.0 if w.dtype == "f32" else 4.0 * Hq * P)
+        return 2.0 * Hkv * L * d * esz + Hq * W * d * esz, 4.0 * Hq * W * d + (0.0 if "vv" in seen else 4.0 * Hq * P)
     if stage == "score":
         return 2.0 * Hkv * P * d * esz + 4.0 * Hq * P, 4.0 * Hkv * W * P
     if stage == "vv":
@@ -91,9 +96,22 @@ def stream_reference(rk, read_bytes, write_bytes, reps=10):
     return ts[len(ts) // 2]
 
 
-# kernel behind each timed stage whose HBM traffic was measured with rocprofv3 --pmc
-STAGE_KERNEL = {"attn_partial": "k_attn_vv", "score": "k_score_pipe", "ema": "k_ema_scan",
-                "compact": "k_compact", "box": "k_box"}
+def stage_kernel(w, stage: str, seen):
+    """Kernel behind a timed stage (the stage's name where it is several); seen as in stage_work."""
+    if stage in ("attn_partial", "score", "vv"):
+        bf16 = {"attn_partial": "k_attn_vv", "score": "k_score_pipe"}
+        return {"score": "k_score_f32"}.get(stage, "k_attn_vv_f32") if w.dtype == "f32" else bf16.get(stage, stage)
+    if stage == "ema":
+        return "k_ema_scan" if "row_topk" in seen else "k_short_rows"
+    if stage == "select":
+        return "select" if "box" in seen else "k_finish"
+    return {"compact": "k_compact", "box": "k_box"}.get(stage, stage)
+
+
+def score_stages(seen):
+    """Stages of restkv_score, or None where one of them had no launch."""
+    names = ["attn_partial", "attn_combine", "score"]
+    return names + (["vv"] if "vv" in seen else []) if all(n in seen for n in names) else None
 
 
 def measured_traffic(workload: str, kern):
@@ -229,13 +247,14 @@ def main():
         step()
     torch.cuda.synchronize()
     # One more untimed step with every kernel bracketed by HIP events shows which stage dominates.
-    dom = None
+    dom, seen = None, set()
     if not args.no_kernel_events:
         rk.restkv_timing_enable(True)
         step()
         torch.cuda.synchronize()
         probe = rk.restkv_timing_read()
-        dom = max((s for s in probe if s != "gram" and stage_work(w, s) != (0.0, 0.0)), key=lambda s: probe[s][0])
+        seen = {s for s, (_, n) in probe.items() if n}
+        dom = max((s for s in probe if s != "gram" and stage_work(w, s, seen) != (0.0, 0.0)), key=lambda s: probe[s][0])
 
     # Timed region: exactly `steps` steps.  Only the dominant stage keeps its events (two per
     # layer); bracketing every kernel of a layer costs about a tenth of the step time.
@@ -262,7 +281,7 @@ def main():
     peak_mfma = PEAK_FP32 if w.dtype == "f32" else PEAK_MFMA_BF16
 
     def price(name, ms, n):
-        flops, nbytes = stage_work(w, name)
+        flops, nbytes = stage_work(w, name, seen)
         t = ms / passes                              # ms of this stage per layer pass
         t_mfma, t_hbm = flops / peak_mfma, nbytes / PEAK_HBM
         bound = "mfma" if t_mfma > t_hbm else "hbm"
@@ -275,12 +294,13 @@ def main():
         s = price(dom, *timed[dom])                  # durations from the timed region itself
         unit = "TFLOP/s" if s["bound"] == "mfma" else "GB/s"
         div = 1e12 if s["bound"] == "mfma" else 1e9
-        roof = {"kernel": STAGE_KERNEL.get(dom, dom), "stage": dom, "bound": s["bound"],
+        kern = stage_kernel(w, dom, seen)
+        roof = {"kernel": kern, "stage": dom, "bound": s["bound"],
                 "achieved": s["achieved"] / div, "peak": s["peak"] / div,
-                "unit": unit, "frac": s["achieved"] / s["peak"], "traffic": measured_traffic(w.name, STAGE_KERNEL.get(dom)),
+                "unit": unit, "frac": s["achieved"] / s["peak"], "traffic": measured_traffic(w.name, kern),
                 "avg_ms": s["ms"] / s["launches"]}
         # the same byte mix through a plain streaming kernel on this part, measured now
-        rw = stage_read_write(w, dom)
+        rw = stage_read_write(w, dom, seen)
         if s["bound"] == "hbm" and rw and not args.no_stream_ref:
             us = stream_reference(rk, *rw)
             roof["stream_ref"] = {"read_bytes": rw[0], "write_bytes": rw[1], "us": us,
@@ -400,11 +420,11 @@ def main():
     rk.restkv_timing_enable(False)
 
     # restkv_score as a whole against the matrix-core peak on ALGORITHMIC flops (three window
-    # contractions and V M_h), beside what the kernels execute (logit recompute, two-term u and
+    # contractions and V M_h), beside what the bf16 kernels execute (logit recompute, two-term u and
     # Gram operands) and the HBM bytes the counters saw against K + V once + the raw score once.
     score_call = None
-    call_stages = ["attn_partial", "attn_combine", "score"] + (["vv"] if w.dtype == "f32" else [])
-    if all(n in per for n in call_stages):
+    call_stages = score_stages(per)
+    if call_stages:
         Wn, Ln, Pn = w.window, w.seq_len, w.prefix
         unit = 2.0 * Hq * Wn * Ln * d
         f_alg = 3.0 * unit + 2.0 * Hq * Ln * d * d
@@ -415,7 +435,7 @@ def main():
         tr = [measured_traffic(w.name, n) for n in ("k_attn_vv", "k_attn_combine", "k_score_pipe")]
         traffic = sum(tr) if all(x is not None for x in tr) else None
         score_call = {"ms_per_layer": ms_call, "f_alg": f_alg, "frac_mfma_alg": f_alg / (ms_call * 1e-3) / peak_mfma,
-                      "executed_over_alg": f_exec / f_alg, "algorithmic_bytes": b_alg,
+                      "executed_over_alg": f_exec / f_alg if w.dtype == "bf16" else None, "algorithmic_bytes": b_alg,
                       "traffic_over_alg": (traffic / b_alg) if traffic else None}
 
     cpu = None

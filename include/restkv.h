@@ -272,9 +272,10 @@ int restkv_evict(const restkv_params* p, const void* q, const void* k, const voi
  * arrays of n_stages >= RESTKV_N_STAGES entries) and forgets them.  Disabled by
  * default; enabling or disabling also forgets pending records.  Not thread-safe
  * against concurrent launches on other host threads beyond a mutex on the records.
- * Stages "attn_partial" and "vv" (attention and value-Gram pass): on the bf16 matrix-core path they are one launch, which
- * "attn_partial" counts, and "vv" reports launches only where there is no attention pass (statistics handed in) and for the
- * value norms of the indicators without a projection.  The FP32 path launches and reports them one by one.
+ * Stages "attn_partial" and "vv" (attention and value-Gram pass): on the bf16 matrix-core path, and on most layers of the
+ * FP32 path, they are one launch, which "attn_partial" counts.  "vv" reports launches where there is no attention pass
+ * (statistics handed in), for the value norms of the indicators without a projection, and on FP32 layers where few rows per KV
+ * head keep two wavefronts per workgroup and their key splits fill the compute units (heads of 128).
  */
 #define RESTKV_N_STAGES 10
 int restkv_timing_enable(int stage_mask);

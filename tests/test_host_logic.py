@@ -123,3 +123,28 @@ def test_bench_reports_counters_of_the_present_kernels_only(tmp_path, monkeypatc
         assert bench.measured_traffic("x", "k_box") == want
         assert bench.measured_traffic("x", "k_none") is None
     assert bench.measured_traffic("y", "k_box") is None and bench.measured_traffic("x", None) is None
+
+
+def test_bench_prices_a_launch_with_the_work_of_the_stages_in_it():
+    """A stage without launches has its work in another one's launch: the totals over the stages stay the same, and the
+    score call is priced from the stages that ran."""
+    import bench
+    import workloads
+    score = ["attn_partial", "attn_combine", "score"]
+    for name, apart, joint in (("tiny", score + ["vv"], score), ("drift_128k", None, score)):
+        w = workloads.WORKLOADS[name]
+        tail = ["ema", "row_topk", "box", "select", "compact"]
+        short = ["ema", "select"]
+        total = lambda seen: [sum(x) for x in zip(*(bench.stage_work(w, s, seen) for s in seen))]        # noqa: E731
+        if apart:
+            a, b = total(apart), total(joint)
+            assert a[0] == b[0] and a[1] - b[1] == 1.0 * w.n_kv_heads * w.prefix * w.head_dim * 4      # V is read once
+            assert bench.score_stages(apart + tail) == apart
+        assert bench.score_stages(joint + tail) == bench.score_stages(joint + short) == joint
+        assert bench.score_stages(["attn_partial", "score"]) is None
+        staged, one = (dict(zip(seen, (bench.stage_work(w, s, seen) for s in seen))) for seen in (joint + tail, joint + short))
+        final_once_more = 4.0 * w.n_kv_heads * w.prefix                      # read back by a selection of its own
+        assert one["select"][1] == staged["box"][1] + staged["select"][1] + staged["compact"][1] - final_once_more
+        assert bench.stage_read_write(w, "attn_partial", joint)[1] == 4.0 * w.n_q_heads * (w.window * w.head_dim + w.prefix)
+    w = workloads.WORKLOADS["tiny"]
+    assert [bench.stage_kernel(w, s, score + short) for s in score[:1] + short] == ["k_attn_vv_f32", "k_short_rows", "k_finish"]
