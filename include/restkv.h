@@ -309,6 +309,13 @@ int restkv_debug_force_fp32(int on);
  */
 int restkv_debug_score_plan(const restkv_params* p, int32_t* plan);
 
+/*
+ * Debug aid: how restkv_score with Gram matrices launches the passes of a float32 layer (RESTKV_EUNSUPPORTED for other
+ * inputs).  plan: HOST array of 4: number of key splits, 1 if the value-Gram pass is in the attention pass's launch,
+ * wavefronts of a workgroup of the score pass, 1 if these divide the heads of the group (else the keys).
+ */
+int restkv_debug_fp32_plan(const restkv_params* p, int32_t* plan);
+
 /* Static description of an error code. */
 const char* restkv_strerror(int code);
 

@@ -88,6 +88,8 @@ def lib() -> ctypes.CDLL:
         L.restkv_debug_force_fp32.restype = ctypes.c_int
         L.restkv_debug_score_plan.argtypes = [P, vp]
         L.restkv_debug_score_plan.restype = ctypes.c_int
+        L.restkv_debug_fp32_plan.argtypes = [P, vp]
+        L.restkv_debug_fp32_plan.restype = ctypes.c_int
         L.restkv_stream_reference.argtypes = [vp, sz, vp, sz, vp]
         L.restkv_stream_reference.restype = ctypes.c_int
         for f in ("restkv_timing_enable", "restkv_timing_read", "restkv_prepare_wo", "restkv_score", "restkv_smooth", "restkv_select",
@@ -238,6 +240,13 @@ def restkv_debug_score_plan(p):
     """(key splits, 64-key tiles of a split, side by side, heavy weights in two parts) of the attention pass on the bf16 matrix-core path."""
     plan = (ctypes.c_int32 * 4)()
     _chk(lib().restkv_debug_score_plan(ctypes.byref(p), plan), "restkv_debug_score_plan")
+    return tuple(plan)
+
+
+def restkv_debug_fp32_plan(p):
+    """(key splits, value-Gram pass in the attention launch, wavefronts of a score workgroup, these divide the heads) of a float32 layer."""
+    plan = (ctypes.c_int32 * 4)()
+    _chk(lib().restkv_debug_fp32_plan(ctypes.byref(p), plan), "restkv_debug_fp32_plan")
     return tuple(plan)
 
 

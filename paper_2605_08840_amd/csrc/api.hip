@@ -313,4 +313,12 @@ int restkv_debug_score_plan(const restkv_params* p, int32_t* plan) {
   return score_plan(pb, plan);
 }
 
+int restkv_debug_fp32_plan(const restkv_params* p, int32_t* plan) {
+  Prob pb;
+  int rc = resolve(p, &pb);
+  if (rc) return rc;
+  if (!plan) return RESTKV_EINVAL;
+  return fp32_plan(pb, plan);
+}
+
 }  // extern "C"

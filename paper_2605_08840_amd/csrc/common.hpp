@@ -65,6 +65,7 @@ bool mfma_eligible(const Prob& pb, const void* q, const void* k, const void* v);
 int launch_score_mfma(const Prob& pb, const void* q, const void* k, const void* v, const float* gram,
                       float* score, char* ws, const ScoreWs& lay, hipStream_t st);
 int score_plan(const Prob& pb, int32_t* plan);     // see restkv_debug_score_plan
+int fp32_plan(const Prob& pb, int32_t* plan);      // see restkv_debug_fp32_plan
 int launch_smooth(const Prob& pb, const float* score, float* ema, float* fin, int32_t* aws_info,
                   double* aws_d, char* ws, const SmoothWs& lay, hipStream_t st);
 // the statistics of a short prefix in one launch: whether it takes this one, and the launch

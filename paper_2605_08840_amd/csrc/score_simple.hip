@@ -926,6 +926,44 @@ __global__ __launch_bounds__(NW * 64, NW == 1 || HS ? 1 : 2) void k_score_f32(Pr
   }
 }
 
+// How the passes of a layer are launched.
+struct Plan {
+  int nw, gy, S, kps;       // attention pass: wavefronts of a workgroup, row blocks, key splits, keys of a split
+  int na;                   // its workgroups
+  bool joint;               // the value-Gram pass is in its launch
+  int nb, gw;               // blocks of keys, and of window positions, of the score pass
+  int snw;                  // wavefronts of a workgroup of the score pass
+  bool hs;                  // they divide the heads of the group
+};
+Plan plan_f32(const Prob& pb, int s_max, bool gram) {
+  Plan x;
+  const int cu = n_cu();
+  // four wavefronts of 32 rows per workgroup where there are rows for them; splits until about two
+  // workgroups per compute unit, at least one block of keys each
+  x.nw = pb.R > 64 ? 4 : 2;
+  x.gy = (pb.R + 32 * x.nw - 1) / (32 * x.nw);
+  int S = (2 * cu + pb.Hkv * x.gy - 1) / (pb.Hkv * x.gy);
+  S = std::max(1, std::min(std::min(S, s_max), (pb.L + KB - 1) / KB));
+  x.kps = ((pb.L + S - 1) / S + KB - 1) / KB * KB;
+  // (one "split": the caller's attention output and log-sum-exp stand in for the pass)
+  x.S = pb.ext_lse ? 1 : (pb.L + x.kps - 1) / x.kps;
+  x.na = x.S * x.gy * pb.Hkv;
+  // Together, unless two wavefronts hold all rows of a head of 128 and have their splits on every compute unit: with 350 registers
+  // each they are one to a SIMD, where the value-Gram pass wants two.
+  x.joint = gram && !pb.ext_lse && (pb.d == 64 || x.nw == 4 || 2 * x.na <= cu);
+  // The heads of a group on up to four wavefronts while a workgroup of them for every 32 keys and positions fits the chip at once (D =
+  // 128: one to a compute unit by registers and LDS, two rounds still pay; D = 64: two), else four wavefronts of 32 keys that share the
+  // staged rows.  Score + smoothing, both sides of the limits: heads of 128, 500 workgroups, 28/4 heads 96 us against 104, 4/2 heads 57.2 /
+  // 59.9, 1000 workgroups, 32/8 heads 110 / 94; heads of 64, 750 workgroups, 28/4 heads 68.9 / 77.5, 32/8 57.2 / 59.8, 1000 workgroups,
+  // 16/4 heads 58.3 / 57.2, 32/8 61.6 / 61.3.  A group of one head has one wavefront while that leaves compute units idle.
+  x.nb = (pb.P + KB - 1) / KB;
+  x.gw = (pb.W + 31) / 32;
+  const int64_t nwg = (int64_t)x.nb * x.gw * pb.Hkv;
+  x.hs = pb.G >= 2 && nwg <= (pb.d == 64 ? 3 : 2) * cu;
+  x.snw = x.hs ? (pb.G == 2 ? 2 : 4) : nwg <= 2 * cu ? 1 : 4;
+  return x;
+}
+
 template <typename T, int D, bool VEC>
 int run(const Prob& pb, const void* q, const void* k, const void* v, const float* gram,
         float* score, char* ws, const ScoreWs& lay, hipStream_t st) {
@@ -933,27 +971,12 @@ int run(const Prob& pb, const void* q, const void* k, const void* v, const float
   const T* kk = (const T*)k;
   const T* vp = (const T*)v;
   const ScorePtrs w = score_ptrs(ws, lay);
-  const int cu = n_cu();
-  // four wavefronts of 32 rows per workgroup where there are rows for them; splits until about two
-  // workgroups per compute unit, at least one block of keys each
-  const int nw = pb.R > 64 ? 4 : 2;
-  const int gy = (pb.R + 32 * nw - 1) / (32 * nw);
-  int S = (2 * cu + pb.Hkv * gy - 1) / (pb.Hkv * gy);
-  S = std::max(1, std::min(std::min(S, lay.S_max), (pb.L + KB - 1) / KB));
-  const int kps = ((pb.L + S - 1) / S + KB - 1) / KB * KB;
-  S = (pb.L + kps - 1) / kps;
   if (pb.ind != 0) gram = nullptr;                 // no projection: vv becomes the squared norm of the value row
-  const float* part_z = w.part_z;
-  if (pb.ext_lse) {
-    S = 1;                                         // the caller's attention output and log-sum-exp stand in for the pass: one "split"
-    part_z = pb.ext_out;
-  }
-  const int nb = (pb.P + KB - 1) / KB;             // blocks of keys
-  const AttnArgs aa = {S, gy, kps};
-  const int na = S * gy * pb.Hkv;                  // workgroups of the attention pass
-  // Together, unless two wavefronts hold all rows of a head of 128 and have their splits on every compute unit: with 350 registers
-  // each they are one to a SIMD, where the value-Gram pass wants two.
-  const bool joint = gram && !pb.ext_lse && (D == 64 || nw == 4 || 2 * na <= cu);
+  const Plan pl = plan_f32(pb, lay.S_max, gram != nullptr);
+  const int cu = n_cu(), S = pl.S, na = pl.na, nb = pl.nb;
+  const bool joint = pl.joint;
+  const float* part_z = pb.ext_lse ? pb.ext_out : w.part_z;
+  const AttnArgs aa = {S, pl.gy, pl.kps};
   auto attn_vv = [&](auto nwc, auto attn, auto vvp, const dim3& gr, const VvArgs& va) {
     constexpr int NW = decltype(nwc)::value;
     constexpr bool ATTN = decltype(attn)::value, VV = decltype(vvp)::value;
@@ -964,37 +987,26 @@ int run(const Prob& pb, const void* q, const void* k, const void* v, const float
   auto attn = [&](auto nwc) {
     const int chunks = chunks_of(decltype(nwc)::value);
     if (joint) attn_vv(nwc, std::true_type{}, std::true_type{}, dim3(na + chunks * pb.Hq), VvArgs{na, chunks, lay.ldv});
-    else attn_vv(nwc, std::true_type{}, std::false_type{}, dim3(S, gy, pb.Hkv), VvArgs{});
+    else attn_vv(nwc, std::true_type{}, std::false_type{}, dim3(S, pl.gy, pb.Hkv), VvArgs{});
   };
   const std::integral_constant<int, 4> four;
   if (!pb.ext_lse) {
-    if (nw == 4) attn(four);
+    if (pl.nw == 4) attn(four);
     else attn(std::integral_constant<int, 2>{});
   }
   if (gram && !joint) attn_vv(four, std::false_type{}, std::true_type{}, dim3(chunks_of(4), pb.Hq), VvArgs{0, chunks_of(4), lay.ldv});
   if (!gram) RK_LAUNCH(ST_VV, st, (k_vnorm2_f32<T, D>), dim3((pb.P + 255) / 256, pb.Hkv), dim3(256), 0, st, pb, vp, w.vv, lay.ldv);
   launch_combine<T, D, 2>(pb, vp, S, gram, w, part_z, qq, 0, 0, st);
-  // The heads of a group on up to four wavefronts while a workgroup of them for every 32 keys and positions fits the chip at once (D =
-  // 128: one to a compute unit by registers and LDS, two rounds still pay; D = 64: two), else four wavefronts of 32 keys that share the
-  // staged rows.  Score + smoothing, both sides of the limits: heads of 128, 500 workgroups, 28/4 heads 96 us against 104, 4/2 heads 57.2 /
-  // 59.9, 1000 workgroups, 32/8 heads 110 / 94; heads of 64, 750 workgroups, 28/4 heads 68.9 / 77.5, 32/8 57.2 / 59.8, 1000 workgroups,
-  // 16/4 heads 58.3 / 57.2, 32/8 61.6 / 61.3.  A group of one head has one wavefront while that leaves compute units idle.
-  const int gw = (pb.W + 31) / 32;
-  const int64_t nwg = (int64_t)nb * gw * pb.Hkv;
   auto score_pass = [&](auto nwc, auto hs) {
     constexpr int NW = decltype(nwc)::value;
     constexpr bool HS = decltype(hs)::value;
-    RK_LAUNCH(ST_SCORE, st, (k_score_f32<T, D, NW, VEC, HS>), dim3(HS ? nb : (nb + NW - 1) / NW, gw, pb.Hkv), dim3(64 * NW), 0, st, pb, qq, kk,
+    RK_LAUNCH(ST_SCORE, st, (k_score_f32<T, D, NW, VEC, HS>), dim3(HS ? nb : (nb + NW - 1) / NW, pl.gw, pb.Hkv), dim3(64 * NW), 0, st, pb, qq, kk,
               vp, w, lay.ldv, score);
   };
-  if (pb.G >= 2 && nwg <= (D == 64 ? 3 : 2) * cu) {
-    if (pb.G == 2) score_pass(std::integral_constant<int, 2>{}, std::true_type{});
-    else score_pass(four, std::true_type{});
-  } else if (nwg <= 2 * cu) {
-    score_pass(std::integral_constant<int, 1>{}, std::false_type{});
-  } else {
-    score_pass(four, std::false_type{});
-  }
+  if (pl.hs && pl.snw == 2) score_pass(std::integral_constant<int, 2>{}, std::true_type{});
+  else if (pl.hs) score_pass(four, std::true_type{});
+  else if (pl.snw == 1) score_pass(std::integral_constant<int, 1>{}, std::false_type{});
+  else score_pass(four, std::false_type{});
   return hip_status();
 }
 
@@ -1008,6 +1020,16 @@ int pick(const Prob& pb, const void* q, const void* k, const void* v, const floa
 }
 
 }  // namespace
+
+int fp32_plan(const Prob& pb, int32_t* plan) {
+  if (pb.dtype != RESTKV_F32) return RESTKV_EUNSUPPORTED;
+  const Plan x = plan_f32(pb, score_ws(pb).S_max, pb.ind == 0);
+  plan[0] = x.S;
+  plan[1] = x.joint;
+  plan[2] = x.snw;
+  plan[3] = x.hs;
+  return RESTKV_OK;
+}
 
 int launch_score_simple(const Prob& pb, const void* q, const void* k, const void* v,
                         const float* gram, float* score, char* ws, const ScoreWs& lay,

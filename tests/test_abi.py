@@ -120,6 +120,22 @@ def test_score_plan_covers_the_context_and_both_launch_orders(rk):
     assert rk.lib().restkv_debug_score_plan(ctypes.byref(good(rk)), None) == -1
 
 
+@pytest.mark.parametrize("heads,d,L,W,plan", [
+    ((4, 2), 64, 1024, 32, (32, 1, 2, 1)),             # the toy layer
+    ((8, 2), 128, 16384, 16, (64, 1, 4, 0)),           # two wavefronts hold a head's rows: splits on half of the compute units ...
+    ((16, 4), 128, 16384, 16, (64, 0, 4, 0)),          # ... and on all of them: two launches
+    ((16, 4), 64, 16384, 16, (64, 1, 4, 0)),
+    ((28, 4), 128, 4096, 32, (64, 1, 4, 1)), ((28, 4), 128, 4129, 32, (44, 1, 4, 0)),
+    ((8, 8), 128, 2000, 16, (63, 0, 1, 0)),            # a group of one head
+])
+def test_fp32_plan_on_either_side_of_its_rules(rk, heads, d, L, W, plan):
+    p = good(rk, n_q_heads=heads[0], n_kv_heads=heads[1], head_dim=d, seq_len=L, window=W, budget=W + 64)
+    assert rk.restkv_debug_fp32_plan(p) == plan
+    with pytest.raises(rk.RestkvError):
+        rk.restkv_debug_fp32_plan(good(rk, dtype="bf16"))
+    assert rk.lib().restkv_debug_fp32_plan(ctypes.byref(p), None) == -1
+
+
 def test_binding_has_no_cpu_fallback(rk, monkeypatch):
     import paper_2605_08840_amd.binding as b
     monkeypatch.setattr(b, "_lib", None)

@@ -11,8 +11,8 @@ from gpu_util import params_for
 from test_gpu_parity import rk  # noqa: F401
 
 
-def scores64(q, k, v, gram, W, weights=None, dot=None):
-    """Indicator of one KV head (mean over its query heads) [W, P] in float64; q [G,W,d], k, v [L,d], gram [G,d,d].  The key
+def scores64(q, k, v, gram, W, weights=None, dot=None, gmax=False):
+    """Indicator of one KV head (mean over its query heads, or the largest) [W, P] in float64; q [G,W,d], k, v [L,d], gram [G,d,d].  The key
     with a row's largest weight in leave-one-out form.  weights: what becomes of the weights of A V [G,W,L], relative to
     their row's largest; dot(a, b): the products a b^T."""
     q, k, v, gram = q.double(), k.double(), v.double(), gram.double()
@@ -41,8 +41,8 @@ def scores64(q, k, v, gram, W, weights=None, dot=None):
         loo = (p.gather(1, top) / den)[:, 0] * (dot(y, gram[h]) * y).sum(-1).clamp_min(0.0).sqrt()
         rows = (top[:, 0] < P).nonzero()[:, 0]
         ind[rows, top[rows, 0]] = loo[rows]
-        out += ind
-    return out / G
+        out = torch.maximum(out, ind) if gmax else out + ind
+    return out if gmax else out / G
 
 
 def distance(a, b):
@@ -54,8 +54,8 @@ def heads_of(w, q, k, v, gram, g):
     return q[g * G:(g + 1) * G], k[g], v[g], gram[g * G:(g + 1) * G], w.window
 
 
-def gpu_scores(rk, w, q, k, v, wo):  # noqa: F811
-    p = params_for(rk, w)
+def gpu_scores(rk, w, q, k, v, wo, **over):  # noqa: F811
+    p = params_for(rk, w, **over)
     gram = torch.empty((w.n_q_heads, w.head_dim, w.head_dim), dtype=torch.float32, device="cuda")
     rk.restkv_prepare_wo(p, wo.cuda(), gram)
     buf = rk.alloc_layer_buffers(p, q.dtype, "cuda")
@@ -211,10 +211,10 @@ def fp32_layer(Hq, Hkv, d, L, W, strength):
     return w, q, k, v, workloads.make_wo(w)
 
 
-def fp32_bound(w, ref, args):
+def fp32_bound(w, ref, args, **kw):
     """Twice what products in float32 alone give (torch's, on the CPU), and 3e-7, five roundings of 2^-24, for the exponential, the quotient, the
     root and the sums outside of the products."""
-    return 2.0 * distance(scores64(*args, dot=lambda a, b: (a.float() @ b.float().T).double()), ref) + 3e-7
+    return 2.0 * distance(scores64(*args, dot=lambda a, b: (a.float() @ b.float().T).double(), **kw), ref) + 3e-7
 
 
 @pytest.mark.parametrize("layer", FP32_LAYERS)
@@ -283,21 +283,25 @@ def test_fp32_operands_far_from_one(rk, d, W, q2, k2, v2, m2):  # noqa: F811
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("Hq,Hkv,d,P", [
-    (12, 4, 128, 4096), (12, 4, 128, 4097),       # 512 workgroups: the last size at which the heads of a group have wavefronts of their own
-    (8, 4, 64, 6144), (8, 4, 64, 6145),           # the same for heads of 64, two wavefronts
-    (20, 4, 64, 6144), (20, 4, 64, 6145),         # five heads on four wavefronts
+@pytest.mark.parametrize("Hq,Hkv,d,P,form,gmax", [
+    (12, 4, 128, 4096, (4, 1), False), (12, 4, 128, 4097, (4, 0), False),       # 512 workgroups: the last size at which the heads of a group have wavefronts of their own
+    (8, 4, 64, 6144, (2, 1), False), (8, 4, 64, 6145, (4, 0), False),           # the same for heads of 64, two wavefronts
+    (20, 4, 64, 6144, (4, 1), False), (20, 4, 64, 6145, (4, 0), False),         # five heads on four wavefronts
+    (8, 4, 64, 1000, (2, 1), True), (20, 4, 64, 1000, (4, 1), True),            # the group's largest: the wavefronts' results meet by maximum
+    (4, 4, 128, 4096, (1, 0), False),                                           # one head: one wavefront
 ])
-def test_fp32_heads_side_by_side_and_one_after_the_other(rk, Hq, Hkv, d, P):  # noqa: F811
-    """Either side of the rule, with keys that planes do not hold."""
+def test_fp32_heads_side_by_side_and_one_after_the_other(rk, Hq, Hkv, d, P, form, gmax):  # noqa: F811
+    """Either side of the rule, with keys that planes do not hold.  form: wavefronts of a workgroup, whether they divide the heads."""
     w, q, k, v, wo = fp32_layer(Hq, Hkv, d, P + 3, 3, 0.3)
+    over = dict(variant=rk.RESTKV_GROUP_MAX) if gmax else {}
+    assert rk.restkv_debug_fp32_plan(params_for(rk, w, **over))[2:] == form
     q[..., 5] = q[..., 5].abs() + 0.5
     gone = [0, 31, 300, P - 1]
     k[:, gone] = 0.0
     k[:, gone, 5] = float("-inf")
-    got, gram = gpu_scores(rk, w, q, k, v, wo)
+    got, gram = gpu_scores(rk, w, q, k, v, wo, **over)
     for g in (0, Hkv - 1):
         args = heads_of(w, q, k.clamp_min(-1e30), v, gram, g)
-        ref = scores64(*args)
+        ref = scores64(*args, gmax=gmax)
         assert bool((got[g][:, gone] == 0).all())
-        assert distance(got[g], ref) <= fp32_bound(w, ref, args), f"head {g}"
+        assert distance(got[g], ref) <= fp32_bound(w, ref, args, gmax=gmax), f"head {g}"
