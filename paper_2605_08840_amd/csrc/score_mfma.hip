@@ -553,18 +553,23 @@ __device__ __forceinline__ void attn_pass(const Prob& pb, WgAt at, AttnSmem<D>& 
     }
   };
   // The wavefront's query rows come through LDS, in the slots of K tiles 1, 2 and V tiles 1, 2 (half a slot each): a lane that
-  // loads its own row's operands touches a cache line per lane and instruction.
+  // loads its own row's operands touches a cache line per lane and instruction.  (Copies for wavefronts without rows too held up
+  // the first tile: 8/8 heads of 128 without the other pass, window 16, 3.8k tokens 8.0 us against 8.4; heads of 64, 12k, with it 17.7
+  // against 18.4.  Tile 1 of K on its way before the rows are read, V tile 1 in the slot that is free then: the second wait in
+  // the loop costs 32k clustered 91.7 against 91.1, 256 KV heads of 2112 tokens 150.4 against 148.8.)
   const int row_blk = at.y * RB + wv % RB;
   uint16_t* const qs = ring[(wv < NW / 2 ? 1 : 4) + (wv >> 1 & 1)] + (wv & 1) * (32 * D);
   constexpr int QI = 32 / RingK::RPI;               // copies of a wavefront's query rows
   if (ntiles > 0) {
     const uint32_t qd = lds_addr(qs);
+    if (!idle) {
 #pragma unroll
-    for (int j = 0; j < QI; ++j) {                  // (an absent row: row (h, 0) once more, masked below)
-      const int r = j * RingK::RPI + l / RingK::CH;
-      const RowInfo x = row_info(pb, g, row_blk, r, log2iw);
-      dma_1k_from(q + (int64_t)x.h * pb.q_sh + (int64_t)(x.valid ? x.i : 0) * pb.q_st + 8 * RingK::swz(r, l % RingK::CH),
-                  qd + (uint32_t)j * 1024u);
+      for (int j = 0; j < QI; ++j) {                // (an absent row: row (h, 0) once more, masked below)
+        const int r = j * RingK::RPI + l / RingK::CH;
+        const RowInfo x = row_info(pb, g, row_blk, r, log2iw);
+        dma_1k_from(q + (int64_t)x.h * pb.q_sh + (int64_t)(x.valid ? x.i : 0) * pb.q_st + 8 * RingK::swz(r, l % RingK::CH),
+                    qd + (uint32_t)j * 1024u);
+      }
     }
     issue_tile(0);
   }

@@ -359,6 +359,10 @@ def test_gram_and_statistics_at_any_float_address(rk, dtype, d):  # noqa: F811
     (16, 4, 128, 1500, 40, 1, 0),               # four KV heads, five row blocks
     (28, 4, 128, 900, 33, 0, 0),                # nine row blocks: the second workgroup of a split is nearly empty, one pass after the other
     (64, 8, 128, 1200, 64, 1, 0),               # two full workgroups of rows, two of heads
+    (8, 8, 64, 2300, 16, 0, 0),                 # splits of two tiles, half a row block
+    (64, 8, 64, 1900, 33, 0, 0),                # ... and row blocks for all wavefronts
+    (64, 8, 128, 2300, 64, 1, 0),               # three tiles, no second parts
+    (8, 8, 128, 2300, 5, 1, 1),                 # three tiles, one wavefront with rows
 ])
 def test_attention_and_value_gram_passes_share_the_chip(rk, oracle_mod, Hq, Hkv, d, L, W, side, two):  # noqa: F811
     """The two passes in one launch, side by side (`side`; heavy weights in two parts: `two`) or one after the other: first
