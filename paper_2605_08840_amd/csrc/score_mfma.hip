@@ -616,25 +616,23 @@ __device__ __forceinline__ void attn_pass(const Prob& pb, WgAt at, AttnSmem<D>& 
   constexpr int NPV = 2 * NMB * CB, NQK = NMB * KS;
   // The products of a step are one stream with RD operands read ahead (a product is 32 cycles, an LDS round trip four or five): left
   // to itself the compiler asks for an operand right before its product.  Score + smoothing, 32/8 heads, 128k 590 -> 583 us, 32k
-  // clustered 209 -> 203; the latter 201 with the search of a key to keep out in groups of four compares.
-  constexpr int RD = NPV < 6 ? NPV : 6;
+  // clustered 209 -> 203; the latter 201 with the search of a key to keep out in groups of four compares.  (LO: five, with six a
+  // register goes to scratch.)
+  constexpr int RD = NPV < 6 ? NPV : LO ? 5 : 6;
   bf16x8 op[RD];
-  // remainders of heavy weights (LO), with operands of their own: few groups have them
-  auto second_parts = [&](uint32_t vt) {
-#pragma unroll
-    for (int grp = 0; grp < 2 * NMB; ++grp)
-      if (two >> grp & 1u)                               // (uniform)
-#pragma unroll
-        for (int cb = 0; cb < CB; ++cb) oacc[cb] = MFMA(read_v(vt, grp * CB + cb), pr[grp >> 1][grp & 1], oacc[cb]);
-  };
-  // P.V of a tile; next(i): operand i of what follows (nothing after the last tile)
+  // P.V of a tile; next(i): operand i of what follows (nothing after the last tile).  LO: remainders of heavy weights go in
+  // ahead of their group's products, with the operands that these have asked for (with reads of their own ahead of the stream, this launch,
+  // clustered, window 64: 16/4 heads of 128, 4k 25.7 us against 24.1, 32/8, 8k 40.6 against 38.0; 8/8, window 16, 4k 14.0 / 13.4).
   auto accumulate = [&](uint32_t vt, auto next) {
-    if (LO && two) second_parts(vt);
 #pragma unroll
     for (int i = 0; i < RD; ++i) op[i] = read_v(vt, i);
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int i = 0; i < NPV; ++i) {
+      if (LO && i % CB == 0 && (two >> i / CB & 1u)) {     // (uniform)
+#pragma unroll
+        for (int cb = 0; cb < CB; ++cb) oacc[cb] = MFMA(op[(i + cb) % RD], pr[i / (2 * CB)][i / CB & 1], oacc[cb]);
+      }
       oacc[i % CB] = MFMA(op[i % RD], pv[i / (2 * CB)][i / CB & 1], oacc[i % CB]);
       if (i + RD < NPV) op[i % RD] = read_v(vt, i + RD);
       else op[i % RD] = next(i + RD - NPV, op[i % RD]);
@@ -863,11 +861,6 @@ __device__ __forceinline__ void attn_pass(const Prob& pb, WgAt at, AttnSmem<D>& 
       }
     }
     accumulate(v_tile(ntiles - 1), [](int, bf16x8 x) { return x; });   // its slot is not a target of the copies still in flight
-    // (wait states before the first read of the sums, spelled out: the last products may lie behind a branch, after which the
-    // compiler inserts too few)
-    if (LO)
-#pragma unroll
-      for (int cb = 0; cb < CB; ++cb) asm volatile("s_nop 15\n\ts_nop 3" : "+v"(oacc[cb]));
     wait_vm<0>();            // no copy may land in LDS after the workgroup has gone
   }
   float ltot = xhalf_sum(lsum);
