@@ -250,14 +250,24 @@ __global__ __launch_bounds__(4 * D, 4) void k_attn_combine(Prob pb, const T* __r
   };
 #pragma unroll
   for (int m = 0; m < MB; ++m) fetch_splits(m, part);
-  // Gram entries of this lane: column 16 wv + l % 16, the K index of step 4 a + e being 16 a + 4 (l / 16) + e
+  // Gram entries of this lane: column 16 wv + l % 16, the K index of step 4 a + e being 16 a + 4 (l / 16) + e.  Heads of 128 read
+  // them along rows of M (8/8 heads, 3.8k tokens 7.8 -> 7.3 us for the merge), heads of 64, a quarter of the entries, from the
+  // row of the same number (M is symmetric), four at a time (32/8 heads, two layers of 3.5k, statistics in: 5.5 us against 5.7.  bf16
+  // alone: in the FP32 path the same, 5.0 against 5.6, moves the code of the merge for heads of 128, which then takes 11.8 us for
+  // 11.1 at 8k with not an instruction changed).
   f32x4_t mreg[D / 16];
   if (gram) {
-    const float* Mh = gram + ((int64_t)h * D + 4 * (l >> 4)) * D + 16 * wv + (l & 15);
+    if constexpr (D == 64 && USE_OP == 1) {
+      const float* Mh = gram + ((int64_t)h * D + 16 * wv + (l & 15)) * D + 4 * (l >> 4);
 #pragma unroll
-    for (int a = 0; a < D / 16; ++a)
+      for (int a = 0; a < D / 16; ++a) mreg[a] = quad_of(Mh + 16 * a);
+    } else {
+      const float* Mh = gram + ((int64_t)h * D + 4 * (l >> 4)) * D + 16 * wv + (l & 15);
 #pragma unroll
-      for (int e = 0; e < 4; ++e) mreg[a][e] = Mh[(16 * a + e) * D];
+      for (int a = 0; a < D / 16; ++a)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) mreg[a][e] = Mh[(16 * a + e) * D];
+    }
   }
   for (int r = tid / SW; r < RQ; r += NT / SW) {
     const int row = h * pb.W + min(i0 + r, pb.W - 1);
