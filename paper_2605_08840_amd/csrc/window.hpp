@@ -25,8 +25,8 @@ __device__ inline void aws_window(const Prob& pb, unsigned long long sf, unsigne
 }
 
 struct AwsSmem {
+  alignas(16) unsigned long long sum[2][16];
   int w_s, gamma;
-  unsigned long long sum[2][16];
 };
 // Window of head g from the index sums of its W queries, for every thread of the block: all loads in flight at once, wavefront
 // sums, then thread 0, which also writes them out where `leave` says so.  Two barriers.
