@@ -838,7 +838,7 @@ __global__ __launch_bounds__(NW * 64, NW == 1 || HS ? 1 : 2) void k_score_f32(Pr
 #pragma unroll
       for (int j = 0; j < 16; ++j) out[j] = pb.gmax ? fmaxf(out[j], cacc[j]) : out[j] + cacc[j];
     }
-    // the heads of the group meet, in the order of the wavefronts, which take a quarter of the rows each
+    // the heads of the group meet, in the order of the wavefronts, which take 1 / NW of the rows each
     float* const sums = (float*)&rows[0][0];
     __syncthreads();                                   // every wavefront is done with its buffer
 #pragma unroll

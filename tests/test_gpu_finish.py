@@ -89,3 +89,29 @@ def test_evict_matches_its_stages(P, W, kept, heads, boxes, more):
     for name in ("score", "ema", "final", "aws_info", "aws_d", "idx", "k_out", "v_out"):
         x, y = getattr(a, name), getattr(b, name)
         assert torch.equal(x.view(torch.uint8), y.view(torch.uint8)), name
+
+
+@pytest.mark.parametrize("P,boxes", [(2047, 0), (16385, 1)])
+def test_evict_without_the_optional_outputs(P, boxes):
+    """ema, aws_info and aws_d absent: the smoothed scores stay in the workspace, the other outputs are the same bits."""
+    p = rk.make_params(n_q_heads=4, n_kv_heads=2, head_dim=64, seq_len=P + 16, window=16, budget=300, dtype="bf16", beta=100.0)
+    q, k, v, gram = _layer(p, P)
+    a, b = rk.alloc_layer_buffers(p, k.dtype), rk.alloc_layer_buffers(p, k.dtype)
+    rk.restkv_score(p, q, k, v, gram, a.score, a.workspace)
+    rk.restkv_smooth(p, a.score, a.ema, a.final, a.aws_info, a.aws_d, a.workspace)
+    rk.restkv_select(p, a.final, a.idx, a.workspace)
+    rk.restkv_compact(p, k, v, a.idx, a.k_out, a.v_out)
+    kept = [x.fill_(-7) for x in (b.ema, b.aws_info, b.aws_d)]
+    want = [x.clone() for x in kept]
+    b.ema = b.aws_info = b.aws_d = None
+    rk.restkv_timing_enable(True)
+    try:
+        rk.evict_layer(p, q, k, v, gram, b)
+        launches = rk.restkv_timing_read()["box"][1]
+    finally:
+        rk.restkv_timing_enable(False)
+    torch.cuda.synchronize()
+    assert launches == boxes
+    for name in ("score", "final", "idx", "k_out", "v_out"):
+        assert torch.equal(getattr(a, name).view(torch.uint8), getattr(b, name).view(torch.uint8)), name
+    assert all(torch.equal(x, y) for x, y in zip(kept, want))

@@ -182,8 +182,8 @@ def _carved_buffers(rk, p, dtype):
 @pytest.mark.parametrize("seed", range(12))
 def test_random_shapes_write_nothing_outside_their_buffers(rk, seed):
     """Every output buffer and the workspace sit between guard zones in one pool: after the whole
-    path (every third case through the fused call, with a prefix beyond the one-launch kernels) no guard
-    byte has changed."""
+    path (every third case through the fused call, with a prefix beyond the one-launch kernels; the others as one call and
+    once more as four) no guard byte has changed."""
     r = np.random.default_rng(80000 + seed)
     fused = seed % 3 == 0
     G = int(r.choice([1, 2, 3, 4, 8, 16]))
@@ -202,8 +202,19 @@ def test_random_shapes_write_nothing_outside_their_buffers(rk, seed):
     gram = torch.empty((w.n_q_heads, d, d), dtype=torch.float32, device="cuda")
     rk.restkv_prepare_wo(p, wo, gram)
     buf, pool, guards = _carved_buffers(rk, p, q.dtype)
+
+    def intact(how):
+        torch.cuda.synchronize()
+        for a, b in guards:
+            assert bool((pool[a:b] == 0xA5).all()), f"guard bytes [{a}, {b}) changed: {w} {how}"
+        assert int(buf.idx.min()) >= 0 and int(buf.idx.max()) < L
+
     rk.evict_layer(p, q, k, v, gram, buf, fused=fused)
-    torch.cuda.synchronize()
-    for a, b in guards:
-        assert bool((pool[a:b] == 0xA5).all()), f"guard bytes [{a}, {b}) changed: {w} fused={fused}"
-    assert int(buf.idx.min()) >= 0 and int(buf.idx.max()) < L
+    intact("fused" if fused else "one call")
+    if not fused:                                # short layers: box mean, selection and gather in launches of their own
+        buf.idx.fill_(-7)
+        rk.restkv_score(p, q, k, v, gram, buf.score, buf.workspace)
+        rk.restkv_smooth(p, buf.score, buf.ema, buf.final, buf.aws_info, buf.aws_d, buf.workspace)
+        rk.restkv_select(p, buf.final, buf.idx, buf.workspace)
+        rk.restkv_compact(p, k, v, buf.idx, buf.k_out, buf.v_out)
+        intact("four calls")
